@@ -533,8 +533,8 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     uint8_t* marks = (uint8_t*)(ws + w.cover);
     const int grid = (int)std::min<int64_t>((total_bytes + 255) / 256, 16384);
     hipLaunchKernelGGL(cover_clear_kernel, dim3(grid), dim3(256), 0, stream, marks, total_bytes);
-    hipLaunchKernelGGL(special_mark_kernel, dim3(grid), dim3(256), 0, stream, bytes, offsets, batch, total_bytes,
-                       table->d_specials, marks);
+    hipLaunchKernelGGL(special_mark_kernel, dim3((unsigned)((total_bytes + kMarkBlock - 1) / kMarkBlock)), dim3(256), 0,
+                       stream, bytes, offsets, batch, total_bytes, table->d_specials, marks);
     cover = marks;
   }
   const int64_t* piece_begin = nullptr;

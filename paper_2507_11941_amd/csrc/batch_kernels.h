@@ -300,6 +300,34 @@ __global__ __launch_bounds__(256) void cut_search_kernel(const uint8_t* bytes, c
   if (valid && sub == 0) piece_begin[g] = start;
 }
 
+// Where the piece that starts in slot g ends: at the next piece of its string, or at the string's end.  The slots it
+// runs over are void; piece_len tells each how many slots back its piece starts (negative), so that the packing kernel
+// can give it a share of the copying.  (A void first slot, of a string that cannot be encoded, holds 0.)  In text the
+// next slot nearly always holds a piece; after it, eight slots are asked at a time: a 64 KiB run has 73 void slots.
+__device__ inline int64_t piece_end(const int64_t* offsets, int s, uint32_t g, const int32_t* slot_base,
+                                    const int64_t* piece_begin, int32_t* piece_len) {
+  const int end = slot_base[s + 1];
+  int h = (int)g + 1;
+  if (h < end) {
+    const int64_t next = piece_begin[h];
+    if (next >= 0) return next;
+  }
+  while (h < end) {
+    int64_t next[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) next[u] = piece_begin[min(h + u, end - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (h + u < end) {
+        if (next[u] >= 0) return next[u];
+        piece_len[h + u] = (int32_t)g - (h + u);
+      }
+    }
+    h += 8;
+  }
+  return offsets[s + 1];
+}
+
 // One thread per slot: piece lengths, and the histogram of (tier, length bucket) keys.
 __global__ __launch_bounds__(256) void piece_hist_kernel(const int64_t* offsets, TierPlan plan, Control* c,
                                                          const int32_t* slot_base, const int32_t* slot_string,
@@ -311,18 +339,15 @@ __global__ __launch_bounds__(256) void piece_hist_kernel(const int64_t* offsets,
   const uint32_t n_slots = c->n_slots;
   for (uint32_t g = blockIdx.x * 256 + threadIdx.x; g < n_slots; g += gridDim.x * 256) {
     const int64_t start = piece_begin[g];
+    const int s = slot_string[g];
     int32_t len = 0;
     int key = -1;
     if (start >= 0) {
-      const int s = slot_string[g];
-      int64_t next = offsets[s + 1];
-      for (int h = (int)g + 1; h < slot_base[s + 1]; ++h)
-        if (piece_begin[h] >= 0) { next = piece_begin[h]; break; }
-      len = (int32_t)(next - start);
+      len = (int32_t)(piece_end(offsets, s, g, slot_base, piece_begin, piece_len) - start);
       key = bin_key(len, plan);
       if (key >= 0) atomicAdd(&hist[key], 1u);
     }
-    piece_len[g] = len;
+    if (start >= 0 || slot_base[s] == (int32_t)g) piece_len[g] = len;   // (other void slots: the piece's own thread)
     if (key < 0) counts[g] = 0;                        // void slot, or too long for the launched variants
   }
   __syncthreads();
@@ -421,16 +446,13 @@ __global__ __launch_bounds__(1024) void piece_list_small_kernel(const int64_t* o
     start[j] = -1;
     if (g < n_slots) {
       start[j] = piece_begin[g];
+      const int s = slot_string[g];
       if (start[j] >= 0) {
-        const int s = slot_string[g];
-        int64_t next = offsets[s + 1];
-        for (int h = (int)g + 1; h < slot_base[s + 1]; ++h)
-          if (piece_begin[h] >= 0) { next = piece_begin[h]; break; }
-        len[j] = (int32_t)(next - start[j]);
+        len[j] = (int32_t)(piece_end(offsets, s, g, slot_base, piece_begin, piece_len) - start[j]);
         key[j] = bin_key(len[j], plan);
         if (key[j] >= 0) rank[j] = atomicAdd(&hist[key[j]], 1u);
       }
-      piece_len[g] = len[j];
+      if (start[j] >= 0 || slot_base[s] == (int32_t)g) piece_len[g] = len[j];
       if (key[j] < 0) counts[g] = 0;                   // void slot, or too long for the launched variants
     }
   }
@@ -692,15 +714,20 @@ __global__ __launch_bounds__(256) void special_mark_kernel(const uint8_t* bytes,
 }
 
 // Copy every piece's ids to their place in the dense output.  A piece has a few hundred ids, so what limits
-// this kernel is how many loads are in flight: a wave takes two pieces at a time, reads the next two descriptors
-// while it copies, and issues four rows of loads per piece before the first store.
+// this kernel is how many loads are in flight: a wave takes two slots at a time, reads the next two descriptors
+// while it copies, and issues four rows of loads per slot -- and, where the ids are a vocabulary's, their look-ups --
+// before the first store.  A slot copies at most kPackShare ids; what a longer piece has beyond them is copied by the
+// void slots it runs over, kPackShare each: a piece over m slots has at most (m - 1) * piece target + 1024 bytes.
+// 256 pieces of 64 KiB, 41,000 ids each: 121 us with one wave a piece, about 20 us so (whole call 443 -> 346 us).
+constexpr int kPackShare = 1024;
 struct PackItem {
+  uint32_t g;
   int k;
   int64_t src, dst;
 };
 __device__ inline PackItem pack_item(uint32_t g, uint32_t n_slots, const int64_t* piece_begin, const int32_t* counts,
                                      const int64_t* slot_out) {
-  PackItem it{0, 0, 0};
+  PackItem it{g, 0, 0, 0};
   if (g < n_slots) {
     it.k = counts[g];
     it.src = piece_begin[g];
@@ -708,13 +735,28 @@ __device__ inline PackItem pack_item(uint32_t g, uint32_t n_slots, const int64_t
   }
   return it;
 }
+// A void slot turned into its share of the piece that runs over it, and a piece cut to its own share.
+__device__ inline void pack_share(PackItem& it, const int64_t* piece_begin, const int32_t* piece_len,
+                                  const int32_t* counts, const int64_t* slot_out) {
+  if (it.src < 0) {                                    // (per wave: uniform)
+    const int back = piece_len[it.g];
+    if (back < 0) {
+      const uint32_t owner = it.g + (uint32_t)back;
+      const int skip = -back * kPackShare;
+      it.k = counts[owner] - skip;
+      it.src = piece_begin[owner] + skip;
+      it.dst = slot_out[owner] + skip;
+    }
+  }
+  it.k = min(it.k, kPackShare);
+}
 __global__ __launch_bounds__(256) void piece_pack_kernel(const int32_t* tmp_ids, const Control* c,
-                                                         const int64_t* piece_begin, const int32_t* counts,
-                                                         const int64_t* slot_out, int32_t* out_ids,
-                                                         const int32_t* id_map) {
+                                                         const int64_t* piece_begin, const int32_t* piece_len,
+                                                         const int32_t* counts, const int64_t* slot_out,
+                                                         int32_t* out_ids, const int32_t* id_map) {
   const uint32_t n_slots = c->n_slots;
   const int lane = threadIdx.x & 63;
-  const uint32_t stride = gridDim.x * 4;               // pieces one round of the grid takes: wave w takes w and w + stride
+  const uint32_t stride = gridDim.x * 4;               // slots one round of the grid takes: wave w takes w and w + stride
   uint32_t g = blockIdx.x * 4 + (threadIdx.x >> 6);
   PackItem a = pack_item(g, n_slots, piece_begin, counts, slot_out);
   PackItem b = pack_item(g + stride, n_slots, piece_begin, counts, slot_out);
@@ -722,6 +764,8 @@ __global__ __launch_bounds__(256) void piece_pack_kernel(const int32_t* tmp_ids,
     const uint32_t g_next = g + 2 * stride;
     const PackItem a_next = pack_item(g_next, n_slots, piece_begin, counts, slot_out);
     const PackItem b_next = pack_item(g_next + stride, n_slots, piece_begin, counts, slot_out);
+    pack_share(a, piece_begin, piece_len, counts, slot_out);
+    pack_share(b, piece_begin, piece_len, counts, slot_out);
     const int longest = max(a.k, b.k);                 // (per wave: uniform)
     for (int i0 = 0; i0 < longest; i0 += 256) {
       int32_t va[4], vb[4];
@@ -731,11 +775,18 @@ __global__ __launch_bounds__(256) void piece_pack_kernel(const int32_t* tmp_ids,
         va[u] = i < a.k ? tmp_ids[a.src + i] : 0;
         vb[u] = i < b.k ? tmp_ids[b.src + i] : 0;
       }
+      if (id_map) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          va[u] = id_map[va[u]];                       // (token 0 exists in every table)
+          vb[u] = id_map[vb[u]];
+        }
+      }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int i = i0 + 64 * u + lane;
-        if (i < a.k) out_ids[a.dst + i] = vocabulary_id(id_map, va[u]);
-        if (i < b.k) out_ids[b.dst + i] = vocabulary_id(id_map, vb[u]);
+        if (i < a.k) out_ids[a.dst + i] = va[u];
+        if (i < b.k) out_ids[b.dst + i] = vb[u];
       }
     }
     g = g_next;

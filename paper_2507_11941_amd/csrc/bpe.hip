@@ -665,8 +665,8 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
                          slot_string, slot_out, out_offsets);
     }
     const int grid = (int)std::min<int64_t>((w.max_slots + 7) / 8, 32768);   // two pieces per wave and round
-    hipLaunchKernelGGL(piece_pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, ctrl, piece_begin, counts,
-                       slot_out, out_ids, table->d_id_map);
+    hipLaunchKernelGGL(piece_pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, ctrl, piece_begin, piece_len,
+                       counts, slot_out, out_ids, table->d_id_map);
   }
   return hipGetLastError() == hipSuccess ? BPE_OK : BPE_EHIP;
 }

@@ -602,11 +602,6 @@ struct SpecialSet {
   uint8_t text[kMaxSpecials][kMaxSpecialBytes];
 };
 
-__global__ __launch_bounds__(256) void cover_clear_kernel(uint8_t* cover, int64_t total_bytes) {
-  const int64_t words = (total_bytes + 3) / 4;         // the buffer is padded to whole words
-  for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < words; i += gridDim.x * 256ll) ((uint32_t*)cover)[i] = 0u;
-}
-
 // The last string with offsets[s] <= at (for at below the first offset: string 0), found by a whole wave: every
 // round asks 64 strings at once, so 65,536 strings take three round trips instead of sixteen.  All lanes take part
 // and get the result; `at` is uniform.
@@ -625,36 +620,44 @@ __device__ inline int wave_string_at(const int64_t* offsets, int batch, int64_t 
   return lo;
 }
 
-// A workgroup marks kMarkBlock consecutive bytes.  What bounds it is the text itself (one pass over it, 16 bytes a
-// lane), as long as the bytes that merely look like the start of a special stay cheap: every byte asks an LDS bit
-// set, a hit compares its first four bytes, from the copy of the text in LDS, with those of the set's texts, and the
-// string that holds a full match is searched only among the strings of the workgroup's own stretch, which two of its
-// waves look up once.  One chunk a thread: with four, a wave works off four times the hits one after the other
-// (2.5 MB of conversations: 30 us instead of 13).  54 MB with a special at every 600th
-// byte: 80 us; with a search over the whole batch for every byte that starts a special, one byte a thread: 368 us.
-constexpr int kMarkBlock = 256 * 16;
-constexpr int kMarkWords = (kMarkBlock + kMaxSpecialBytes) / 4;
+// A workgroup writes the marks of kMarkBlock consecutive bytes, each once and 16 bytes a lane: it collects them in LDS,
+// for which it also looks at the kMaxSpecialBytes positions before its stretch, where an occurrence that reaches into
+// it can start.  What bounds it is the text and the marks themselves, as long as a byte that starts a special, or looks
+// like it, waits for no memory: every byte asks an LDS bit set, a hit is compared with the set's texts four bytes at a
+// time, all from LDS, and the string that holds a full match is searched only among the strings of the workgroup's own
+// stretch, which two of its waves look up once and whose ends come to LDS.  One chunk a
+// thread: with four, a wave works off four times the hits one after the other (2.5 MB of conversations: 30 us instead
+// of 13).  54 MB with a special at every 600th byte: about 70 us; with the marks cleared by a kernel before and written
+// byte by byte, strings searched in memory: 90 us; one byte a thread with a search over the whole batch: 379 us.
+constexpr int kMarkText = 256 * 16;                    // bytes whose occurrences a workgroup looks for
+constexpr int kMarkBlock = kMarkText - kMaxSpecialBytes;
+constexpr int kMarkWords = (kMarkText + kMaxSpecialBytes) / 4;
+constexpr int kMarkStrings = 255;                      // string ends kept in LDS; more (short strings) stay in memory
 __global__ __launch_bounds__(256) void special_mark_kernel(const uint8_t* bytes, const int64_t* offsets, int batch,
                                                            int64_t total_bytes, const SpecialSet* set,
                                                            uint8_t* cover) {
+  static_assert(kMarkBlock % 16 == 0 && kMaxSpecialBytes % 16 == 0, "chunks of 16 bytes");
   __shared__ __align__(16) uint32_t text[kMarkWords + 4];
-  __shared__ uint32_t first_byte[8], prefix[kMaxSpecials], prefix_mask[kMaxSpecials];
+  __shared__ __align__(16) uint32_t marks[kMarkBlock / 4];
+  __shared__ uint32_t special[kMaxSpecials * kMaxSpecialBytes / 4];
+  __shared__ uint32_t first_byte[8];
   __shared__ int32_t length[kMaxSpecials];
+  __shared__ int32_t string_begin[kMarkStrings + 1];
   __shared__ int first_string, last_string;
   const int tid = threadIdx.x;
   const int n_specials = set->n;
-  const int64_t base = (int64_t)blockIdx.x * kMarkBlock;
+  const int64_t base = (int64_t)blockIdx.x * kMarkBlock;         // the first byte that this workgroup marks ...
+  const int64_t start = base - kMaxSpecialBytes;                 // ... and the first that it looks at
+  const int64_t end = min(base + kMarkBlock, total_bytes);
   if (tid < 8) first_byte[tid] = set->first_byte[tid];
-  if (tid < n_specials) {
-    const int len = set->len[tid];
-    length[tid] = len;
-    prefix[tid] = *(const uint32_t*)set->text[tid];    // (unused bytes of a text are zero)
-    prefix_mask[tid] = len >= 4 ? 0xFFFFFFFFu : (1u << (8 * len)) - 1u;
-  }
-  // 16 bytes of the text from position p on, zeros past its end.  Wide loads need the pointer's alignment; without
-  // it, and at the end of the text, bytes are read one by one.
+  if (tid < n_specials) length[tid] = set->len[tid];
+  for (int i = tid; i < n_specials * (kMaxSpecialBytes / 4); i += 256)
+    special[i] = ((const uint32_t*)set->text)[i];      // (unused bytes of a text are zero)
+  // 16 bytes of the text from position p on, zeros before its beginning and past its end.  Wide loads need the
+  // pointer's alignment; without it, and at the end of the text, bytes are read one by one.
   const bool aligned = ((uintptr_t)bytes & 15u) == 0;
   auto chunk_at = [&](int64_t p) {
+    if (p < 0) return make_uint4(0, 0, 0, 0);          // (a whole chunk: `start` is a multiple of 16)
     if (aligned && p + 16 <= total_bytes) return *(const uint4*)(bytes + p);
     uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -662,20 +665,27 @@ __global__ __launch_bounds__(256) void special_mark_kernel(const uint8_t* bytes,
       if (p + j < total_bytes) w[j >> 2] |= (uint32_t)bytes[p + j] << (8 * (j & 3));
     return make_uint4(w[0], w[1], w[2], w[3]);
   };
-  const uint4 mine = chunk_at(base + 16 * tid);
+  const uint4 mine = chunk_at(start + 16 * tid);
   *(uint4*)&text[4 * tid] = mine;
-  if (tid < kMaxSpecialBytes / 16) *(uint4*)&text[kMarkBlock / 4 + 4 * tid] = chunk_at(base + kMarkBlock + 16 * tid);
+  if (tid < kMaxSpecialBytes / 16) *(uint4*)&text[kMarkText / 4 + 4 * tid] = chunk_at(start + kMarkText + 16 * tid);
   if (tid == 0) text[kMarkWords] = 0;
+  if (tid < kMarkBlock / 16) *(uint4*)&marks[4 * tid] = make_uint4(0, 0, 0, 0);
   if (tid >= 128 && tid < 192) {
-    const int s = wave_string_at(offsets, batch, base);
+    const int s = wave_string_at(offsets, batch, max(start, (int64_t)0));
     if (tid == 128) first_string = s;
   } else if (tid >= 192) {
-    const int s = wave_string_at(offsets, batch, min(base + kMarkBlock, total_bytes) - 1);
+    const int s = wave_string_at(offsets, batch, end - 1);
     if (tid == 192) last_string = s;
   }
   __syncthreads();
+  const int s0 = first_string, s1 = last_string;
+  const bool ends_here = s1 - s0 < kMarkStrings;       // uniform
+  // (positions relative to `start`, clamped far outside the stretch: only comparisons and short rooms are asked)
+  if (ends_here && tid <= s1 - s0 + 1)
+    string_begin[tid] = (int32_t)min(max(offsets[s0 + tid] - start, (int64_t)-(1 << 28)), (int64_t)1 << 28);
+  __syncthreads();
   const uint32_t own[4] = {mine.x, mine.y, mine.z, mine.w};
-  const int64_t left = total_bytes - base - 16 * tid;  // bytes of the text from my first one on
+  const int64_t left = total_bytes - start - 16 * tid; // bytes of the text from my first one on
   uint32_t hits = 0;                                   // bit j: my byte j could start a special
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
@@ -683,34 +693,55 @@ __global__ __launch_bounds__(256) void special_mark_kernel(const uint8_t* bytes,
     hits |= ((first_byte[b >> 5] >> (b & 31u)) & 1u) << j;
   }
   if (left < 16) hits &= left > 0 ? (1u << (int)left) - 1u : 0u;
+  if (start + 16 * tid < 0) hits = 0;
   while (hits) {
     const int at = 16 * tid + __builtin_ctz(hits);     // in the workgroup's text
     hits &= hits - 1u;
-    const int64_t p = base + at;
-    const uint32_t head = __builtin_amdgcn_alignbit(text[(at >> 2) + 1], text[at >> 2], 8u * (at & 3));
+    const int64_t p = start + at;
+    // byte differences between word w of special i and the text from `at` on, as far as the special goes
+    auto differs = [&](int i, int w, int len) {
+      const uint32_t here = __builtin_amdgcn_alignbit(text[(at >> 2) + w + 1], text[(at >> 2) + w], 8u * (at & 3));
+      const uint32_t word = here ^ special[i * (kMaxSpecialBytes / 4) + w];
+      return len - 4 * w >= 4 ? word : word & ((1u << (8 * (len - 4 * w))) - 1u);
+    };
     int64_t room = -1;                                 // bytes from p to the end of its string, once they are asked for
     int best = -1, best_len = 0;
     for (int i = 0; i < n_specials; ++i) {
       const int len = length[i];
-      if (((head ^ prefix[i]) & prefix_mask[i]) || len <= best_len || p + len > total_bytes) continue;
-      int j = 4;
-      while (j < len && ((const uint8_t*)text)[at + j] == set->text[i][j]) ++j;
-      if (j < len) continue;
-      if (room < 0) {
-        int lo = first_string, hi = last_string;       // the string that holds p: last s with offsets[s] <= p
-        while (lo < hi) {
-          const int mid = lo + ((hi - lo + 1) >> 1);
-          if (offsets[mid] <= p) lo = mid; else hi = mid - 1;
+      if (len <= best_len || p + len > total_bytes) continue;
+      int w = 0;
+      while (4 * w < len && !differs(i, w, len)) ++w;
+      if (4 * w < len) continue;
+      if (room < 0) {                                  // the string that holds p: last s with offsets[s] <= p
+        if (ends_here) {
+          int lo = 0, hi = s1 - s0;
+          while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (string_begin[mid] <= at) lo = mid; else hi = mid - 1;
+          }
+          room = max(string_begin[lo + 1] - at, 0);
+        } else {
+          int lo = s0, hi = s1;
+          while (lo < hi) {
+            const int mid = lo + ((hi - lo + 1) >> 1);
+            if (offsets[mid] <= p) lo = mid; else hi = mid - 1;
+          }
+          room = max(offsets[lo + 1] - p, (int64_t)0);
         }
-        room = max(offsets[lo + 1] - p, (int64_t)0);
       }
       if (len <= room) { best = i; best_len = len; }
     }
     if (best >= 0) {
-      cover[p] = (uint8_t)(kCoverFirst | (uint32_t)best);
-      for (int j = 1; j < best_len; ++j) cover[p + j] = (uint8_t)kCoverRest;
+      const int to = at - kMaxSpecialBytes;            // in the workgroup's marks
+      for (int j = 0; j < best_len; ++j)
+        if ((uint32_t)(to + j) < (uint32_t)kMarkBlock)
+          ((uint8_t*)marks)[to + j] = (uint8_t)(j == 0 ? kCoverFirst | (uint32_t)best : kCoverRest);
     }
   }
+  __syncthreads();
+  // (whole chunks: the marks' buffer is padded beyond the text)
+  if (tid < kMarkBlock / 16 && base + 16 * tid < total_bytes)
+    *(uint4*)(cover + base + 16 * tid) = *(const uint4*)&marks[4 * tid];
 }
 
 // Copy every piece's ids to their place in the dense output.  A piece has a few hundred ids, so what limits

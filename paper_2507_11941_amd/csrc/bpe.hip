@@ -188,7 +188,7 @@ WorkspaceLayout layout_for(int32_t batch, int64_t total_bytes, int32_t max_len) 
   w.fallback = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
   w.counts = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
   w.tmp_ids = at; at += align_up((size_t)total_bytes * sizeof(int32_t));
-  w.cover = at; at += align_up((size_t)total_bytes + 4);      // special-token marks, one per byte
+  w.cover = at; at += align_up((size_t)total_bytes + 4);      // special-token marks, one per byte, whole chunks of 16
   w.slot_base = w.slot_string = w.piece_begin = w.piece_len = w.slot_out = w.tile_sum = 0;
   if (w.split) {
     w.slot_base = at; at += align_up(((size_t)batch + 1) * sizeof(int32_t));
@@ -531,8 +531,6 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const uint8_t* cover = nullptr;                        // special tokens: mark their occurrences first
   if (table->d_specials && batch > 0 && total_bytes > 0) {
     uint8_t* marks = (uint8_t*)(ws + w.cover);
-    const int grid = (int)std::min<int64_t>((total_bytes + 255) / 256, 16384);
-    hipLaunchKernelGGL(cover_clear_kernel, dim3(grid), dim3(256), 0, stream, marks, total_bytes);
     hipLaunchKernelGGL(special_mark_kernel, dim3((unsigned)((total_bytes + kMarkBlock - 1) / kMarkBlock)), dim3(256), 0,
                        stream, bytes, offsets, batch, total_bytes, table->d_specials, marks);
     cover = marks;

@@ -1,4 +1,4 @@
-"""Special tokens at the edges of the marking kernel's 16-byte chunks and 4 KiB stretches, with strings that end inside
+"""Special tokens at the edges of the marking kernel's 16-byte chunks and 4,032-byte stretches, with strings that end inside
 an occurrence, for aligned and unaligned input pointers: GPU path against the oracle."""
 import random
 
@@ -15,7 +15,7 @@ SPECIALS = {b"<|endoftext|>": 70001, b"<|endoftext|>2": 70002, b"[S]": 70003, b"
 
 
 @pytest.mark.parametrize("shift", [0, 1, 15])
-@pytest.mark.parametrize("total", [1, 15, 16, 17, 4096, 16384, 16385, 49159])
+@pytest.mark.parametrize("total", [1, 15, 16, 17, 4032, 4033, 4096, 16384, 16385, 49159])
 def test_marks_at_block_edges(total, shift):
     import torch
 
@@ -24,7 +24,8 @@ def test_marks_at_block_edges(total, shift):
     rng = random.Random(total * 16 + shift)
     rows = [(97, 98), (256, 60), (124, 62), (101, 110), (113, 113)]
     text = bytearray(rng.choice(b"ab<|>[enq ") for _ in range(total))
-    for edge in range(0, total + 1, 4096):                       # occurrences that touch, cross and end at the edges
+    # occurrences that touch, cross and end at the edges
+    for edge in (*range(0, total + 1, 4096), *range(4032, total + 1, 4032)):
         word = rng.choice(list(SPECIALS))
         at = edge - rng.randint(0, len(word))
         if 0 <= at and at + len(word) <= total:

@@ -95,28 +95,52 @@ __global__ __launch_bounds__(1024) void bin_kernel(const int64_t* offsets, int b
   }
 }
 
-// out_offsets[i] = sum of counts[0..i), out_offsets[batch] = total.  One workgroup walks the batch.
-__global__ __launch_bounds__(1024) void offsets_scan_kernel(const int32_t* counts, int batch,
+// out_offsets[i] = sum of counts[0..i), out_offsets[batch] = total.  A workgroup owns a stretch of strings (whole
+// tiles of 1024; the host picks one tile, and more once that would be over kOffsetsGrid workgroups).  It sums the
+// counts before its stretch itself, sixteen strings' loads in flight per thread -- they come from L2, 4 bytes per
+// string -- so no workgroup waits for another.  What bounds it is those loads' latency: with one workgroup walking
+// the whole batch, a tile cost 1.5 us one after the other (20,011 strings: 30 us).
+constexpr int kOffsetsGrid = 256;
+__global__ __launch_bounds__(1024) void offsets_scan_kernel(const int32_t* counts, int batch, int stretch,
                                                             int64_t* out_offsets) {
   __shared__ int64_t wave_sum[16];
   __shared__ int64_t carry_s;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) { carry_s = 0; out_offsets[0] = 0; }
+  const int first = (int)min((int64_t)blockIdx.x * stretch, (int64_t)batch);
+  const int last = (int)min((int64_t)first + stretch, (int64_t)batch);
+  int64_t before = 0;                                  // tokens of all strings before the stretch
+  const int4* const quads = (const int4*)counts;       // (`first` is a multiple of 1024, or nothing is left to do)
+  const int n_quads = first / 4;
+  for (int q = tid; q < n_quads; q += 4 * 1024) {      // the loads are unconditional (index clamped), the test comes after
+    int4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = quads[min(q + u * 1024, n_quads - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (q + u * 1024 < n_quads) before += ((int64_t)v[u].x + v[u].y) + ((int64_t)v[u].z + v[u].w);
+  }
+  for (int step = 32; step >= 1; step >>= 1) before += __shfl_xor(before, step, 64);
+  if (lane == 0) wave_sum[wave] = before;
+  if (blockIdx.x == 0 && tid == 0) out_offsets[0] = 0;
   __syncthreads();
-  for (int base = 0; base < batch; base += 1024) {
+  int64_t carry = 0;                                   // (the same in all threads)
+  for (int w = 0; w < 16; ++w) carry += wave_sum[w];
+  __syncthreads();
+  for (int base = first; base < last; base += 1024) {
     const int i = base + tid;
-    int64_t v = i < batch ? (int64_t)counts[i] : 0;
+    int64_t v = i < last ? (int64_t)counts[i] : 0;
     for (int step = 1; step < 64; step <<= 1) {
       int64_t o = __shfl_up(v, step, 64);
       if (lane >= step) v += o;
     }
     if (lane == 63) wave_sum[wave] = v;
     __syncthreads();
-    int64_t before = carry_s;
-    for (int w = 0; w < wave; ++w) before += wave_sum[w];
-    if (i < batch) out_offsets[i + 1] = before + v;
+    int64_t at = carry;
+    for (int w = 0; w < wave; ++w) at += wave_sum[w];
+    if (i < last) out_offsets[i + 1] = at + v;
+    if (tid == 1023) carry_s = at + v;
     __syncthreads();
-    if (tid == 1023) carry_s = before + v;
+    carry = carry_s;
     __syncthreads();
   }
 }
@@ -149,14 +173,28 @@ __global__ __launch_bounds__(256) void scan_pack_kernel(const int32_t* tmp_ids, 
   for (int i = threadIdx.x; i < k; i += 256) out_ids[dst + i] = vocabulary_id(id_map, tmp_ids[src + i]);
 }
 
-// One workgroup per string: copy its ids from the per-string staging area to the dense output.
+// One wave per string: copy its ids from the per-string staging area to the dense output, four rows of 64 loads in
+// flight.  (Rows of a data set have a few dozen ids: a workgroup per string leaves three of its four waves idle.)
 __global__ __launch_bounds__(256) void pack_kernel(const int32_t* tmp_ids, const int64_t* offsets,
                                                    const int64_t* out_offsets, int batch, int32_t* out_ids,
                                                    const int32_t* id_map) {
-  for (int s = blockIdx.x; s < batch; s += gridDim.x) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t s = blockIdx.x * 4ll + (threadIdx.x >> 6); s < batch; s += gridDim.x * 4ll) {
     const int64_t src = offsets[s], dst = out_offsets[s];
     const int k = (int)(out_offsets[s + 1] - dst);
-    for (int i = threadIdx.x; i < k; i += blockDim.x) out_ids[dst + i] = vocabulary_id(id_map, tmp_ids[src + i]);
+    for (int i0 = 0; i0 < k; i0 += 256) {
+      int32_t v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 64 * u + lane;
+        v[u] = i < k ? tmp_ids[src + i] : 0;           // (token 0 exists in every table)
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 64 * u + lane;
+        if (i < k) out_ids[dst + i] = vocabulary_id(id_map, v[u]);
+      }
+    }
   }
 }
 

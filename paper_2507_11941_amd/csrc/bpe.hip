@@ -644,9 +644,12 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     hipLaunchKernelGGL(scan_pack_kernel, dim3(batch), dim3(256), 0, stream, tmp_ids, offsets, counts, batch,
                        out_offsets, out_ids, table->d_id_map);
   } else if (!w.split) {
-    hipLaunchKernelGGL(offsets_scan_kernel, dim3(1), dim3(1024), 0, stream, counts, batch, out_offsets);
+    const int64_t tiles = std::max<int64_t>(((int64_t)batch + 1023) / 1024, 1);
+    const int64_t tiles_each = (tiles + kOffsetsGrid - 1) / kOffsetsGrid;     // (beyond 262,144 strings)
+    hipLaunchKernelGGL(offsets_scan_kernel, dim3((unsigned)((tiles + tiles_each - 1) / tiles_each)), dim3(1024), 0,
+                       stream, counts, batch, (int)(tiles_each * 1024), out_offsets);
     if (batch > 0) {
-      const int grid = batch < 65536 ? batch : 65536;
+      const int grid = (int)std::min<int64_t>(((int64_t)batch + 3) / 4, 65536);
       hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, offsets, out_offsets, batch, out_ids,
                          table->d_id_map);
     }

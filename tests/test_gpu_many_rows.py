@@ -1,0 +1,47 @@
+"""Batches of more short strings than are resident at once: the work list is made and the offsets are summed by stretches
+of strings.  Sizes around a workgroup's 1,024 strings, where a stretch outgrows them (131,072 strings for the list,
+262,144 for the offsets), with empty strings, strings at the limit and one beyond max_len (unspecified output: here it yields no tokens)."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import assert_same_encoding
+
+pytestmark = pytest.mark.gpu
+
+ROWS = [(97, 98), (256, 99), (32, 97), (98, 98)]
+
+
+@pytest.mark.parametrize("vocab", [False, True])
+@pytest.mark.parametrize("batch", [4097, 5120, 8193, 131073, 262145, 300001])
+def test_many_rows(batch, vocab):
+    import torch
+
+    import paper_2507_11941_amd as bpe
+
+    rng = np.random.default_rng(batch)
+    lens = rng.integers(0, 25, size=batch)
+    some = rng.permutation(batch)[:60]
+    lens[some] = np.repeat([1024, 1023, 257, 256, 255, 65], 10)
+    lens[some[0]], lens[0], lens[-1] = 1500, 300, 1024
+    offsets = np.zeros(batch + 1, dtype=np.int64)
+    np.cumsum(lens, out=offsets[1:])
+    data = rng.choice(np.frombuffer(b"aabbc  x", dtype=np.uint8), size=int(offsets[-1]))
+    if vocab:
+        names = rng.permutation(256 + len(ROWS)).astype(np.int32)
+        args = names[:256], names[np.array(ROWS)], names[256:]
+        table, orc = bpe.build_table_vocab(*args), oracle.Table(args[1], byte_ids=args[0], merged_ids=args[2])
+    else:
+        table, orc = bpe.build_table(ROWS), oracle.Table(ROWS)
+    dev = torch.device("cuda:0")
+    for max_len in (1024, 1500):                       # one list for all strings; pieces
+        ids, out_off = bpe.encode_batch(table, torch.from_numpy(data).to(dev), torch.from_numpy(offsets).to(dev), max_len)
+        out_off = out_off.cpu().numpy()
+        ids = ids[: int(out_off[-1])].cpu().numpy()
+        want_ids, want_off = orc.encode_batch(data, offsets, tier=oracle.HEAP, nthreads=8)
+        if max_len == 1024:
+            at, end = want_off[some[0]], want_off[some[0] + 1]
+            want_ids = np.delete(want_ids, np.s_[at:end])
+            want_off = want_off - (np.arange(batch + 1) > some[0]) * (end - at)
+        assert_same_encoding(ids, out_off, want_ids, want_off, f"{batch} strings, max_len {max_len}")
+    table.free()

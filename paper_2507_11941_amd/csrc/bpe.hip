@@ -548,8 +548,15 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     if (direct) {
       list = nullptr;
     } else if (!w.split) {
-      hipLaunchKernelGGL(bin_kernel, dim3(1), dim3(1024), 0, stream, offsets, batch, plan, ctrl, list,
-                         (ItemDesc*)(ws + w.list_desc), counts);
+      // (the stretches' histograms, 256 bytes per 1,024 strings at most, borrow the fallback list, 4 bytes a string,
+      // which is written only once the work list is made)
+      uint32_t* part = (uint32_t*)(ws + w.fallback);
+      const int wanted = (int)std::min<int64_t>(((int64_t)batch + 1023) / 1024, kBinGrid);
+      const int stretch = (int)(((int64_t)batch + wanted - 1) / wanted);
+      const int grid = (int)(((int64_t)batch + stretch - 1) / stretch);
+      hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, plan, part, counts);
+      hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, plan, ctrl, part,
+                         list, (ItemDesc*)(ws + w.list_desc));
     } else {
       int32_t* sb = (int32_t*)(ws + w.slot_base);
       int32_t* ss = (int32_t*)(ws + w.slot_string);

@@ -56,46 +56,84 @@ struct ItemDesc {
   int32_t item;                                      // string index, or slot index when strings are split
 };
 
-// The work list of a batch whose strings are not split: string indices, longest length bucket first.  (Such a batch has
-// one tier: its strings fit the first variant, or the batch would be split.)  Workgroup b owns the strings
-// [b stretch, (b + 1) stretch).  bin_count_kernel leaves each stretch's histogram of the length buckets in `part`
-// (kLenBuckets words per workgroup); bin_scatter_kernel adds up everybody's, which is at most kBinGrid rows of 256
-// bytes, so it knows where each bucket begins and where its own part of it does, and needs no atomics on memory.
-// What bounds them is latency, a chain of a few loads each: one workgroup that walks the batch twice took 1.3 us per
-// 1,024 strings (20,011 strings: 27 us).
+// The work list of a batch whose strings are not split and that has more of them than are resident at once: groups of
+// neighbouring strings, longest length bucket first.  (Such a batch has one tier.)  An item costs its wave some ten
+// microseconds of round trips whatever its length, so short strings go together: 20,011 strings of up to 400 bytes
+// were 105 us one by one and are 45.  Every 64 strings are divided by one wave, first come first served: a group
+// takes strings until the next one would end more than `room` bytes after its beginning.  (With groups of all strings
+// that start in one window of the text, which need no walk, items were a third smaller.)
+//
+// Workgroup b owns the strings [b stretch, (b + 1) stretch), whole tiles of 1,024.  bin_count_kernel leaves each
+// stretch's histogram of the length buckets in `part` (kLenBuckets words per workgroup); bin_scatter_kernel adds up
+// everybody's, which is at most kBinGrid rows of 256 bytes, so it knows where each bucket begins and where its own part
+// of it does, and needs no atomics on memory.  What bounds them is latency, a chain of a few loads each: one workgroup
+// that walks the batch twice took 1.3 us per 1,024 strings (20,011 strings: 27 us).
 constexpr int kBinGrid = 128;
-__device__ inline int string_bin(const int64_t* offsets, int s, const TierPlan& plan, int64_t& begin, int32_t& len) {
-  begin = offsets[s];
-  const int64_t n = offsets[s + 1] - begin;
-  len = (int32_t)n;
-  return (n < 0 || n > 0x7FFFFFFF) ? -1 : bin_key((int)n, plan);
+constexpr int kGroupLen = 0xFFF;                       // a group's ItemDesc::len: its length in bytes (kGroupLen: not
+constexpr int kGroupShift = 12;                        //   encodable), its strings from bit kGroupShift on, and
+constexpr int kGroupMask = 0x7F;                       //   kGroupApart once its strings have been encoded one by one,
+constexpr int kGroupApart = 1 << 30;                   //   each to its own place
+// The group that string s = tile + threadIdx.x heads; members = 0 if it heads none.  Whole waves take part.
+struct StringGroup {
+  int64_t begin;
+  int members, len;
+};
+__device__ inline StringGroup string_group(const int64_t* offsets, int64_t tile, int batch, int room) {
+  const int lane = threadIdx.x & 63;
+  const int64_t first = tile + (threadIdx.x & ~63u);   // the wave's first string ...
+  const int n = (int)min((int64_t)batch - first, (int64_t)64);           // ... and how many it has (0 or less: none)
+  StringGroup g{0, 0, kGroupLen};
+  if (n <= 0) return g;                                // uniform
+  const int64_t base = offsets[first];
+  int64_t end = 0;
+  if (lane < n) {
+    g.begin = offsets[first + lane];
+    end = offsets[first + lane + 1];
+  }
+  // relative to the wave's first byte, clamped: beyond 2^28 nothing fits a group anyway
+  const int from = (int)min(max(g.begin - base, (int64_t)-1), (int64_t)1 << 28);
+  const int to = (int)min(max(end - base, (int64_t)-1), (int64_t)1 << 28);
+  const bool bad = from < 0 || to < from;              // (offsets that decrease: such a string stays alone)
+  const uint64_t bad_lanes = __ballot(lane >= n || bad);
+  uint64_t heads = 0;
+  for (int at = 0; at < n;) {                          // uniform; `at` grows every round
+    heads |= 1ull << at;
+    const uint64_t later = at < 63 ? ~0ull << (at + 1) : 0ull;
+    uint64_t stop = (__ballot(to > __builtin_amdgcn_readlane(from, at) + room) | bad_lanes) & later;
+    if ((bad_lanes >> at) & 1ull) stop = later;
+    at = stop ? __builtin_ctzll(stop) : 64;
+  }
+  if ((heads >> lane) & 1ull) {
+    const uint64_t later = lane < 63 ? heads & (~0ull << (lane + 1)) : 0ull;
+    g.members = (later ? __builtin_ctzll(later) : n) - lane;
+  }
+  const int group_end = __shfl(to, max(lane + g.members - 1, 0), 64);
+  if (g.members && !bad && group_end - from <= 1024) g.len = group_end - from;
+  return g;
 }
-__global__ __launch_bounds__(1024) void bin_count_kernel(const int64_t* offsets, int batch, int stretch, TierPlan plan,
-                                                         uint32_t* part, int32_t* counts) {
+__global__ __launch_bounds__(1024) void bin_count_kernel(const int64_t* offsets, int batch, int64_t stretch, int room,
+                                                         TierPlan plan, uint32_t* part) {
   __shared__ uint32_t hist[kLenBuckets];
   const int t = threadIdx.x;
-  const int first = blockIdx.x * stretch, last = first + min(stretch, batch - first);
+  const int64_t first = blockIdx.x * stretch, last = min(first + stretch, (int64_t)batch);
   if (t < kLenBuckets) hist[t] = 0;
   __syncthreads();
-  for (int s = first + t; s < last; s += 1024) {
-    int64_t begin;
-    int32_t len;
-    const int key = string_bin(offsets, s, plan, begin, len);
-    if (key >= 0) atomicAdd(&hist[key], 1u);
-    else counts[s] = 0;                                // never encoded: contributes no tokens
+  for (int64_t tile = first; tile < last; tile += 1024) {
+    const StringGroup g = string_group(offsets, tile, batch, room);
+    if (g.members) atomicAdd(&hist[bin_key(min(g.len, 1024), plan)], 1u);
   }
   __syncthreads();
   if (t < kLenBuckets) part[blockIdx.x * kLenBuckets + t] = hist[t];
 }
 // Also resets the work-queue heads.
-__global__ __launch_bounds__(1024) void bin_scatter_kernel(const int64_t* offsets, int batch, int stretch,
-                                                           TierPlan plan, Control* c, const uint32_t* part,
-                                                           int32_t* list, ItemDesc* desc) {
+__global__ __launch_bounds__(1024) void bin_scatter_kernel(const int64_t* offsets, int batch, int64_t stretch,
+                                                           int room, TierPlan plan, Control* c,
+                                                           const uint32_t* part, ItemDesc* desc) {
   static_assert(kLenBuckets == 64, "a lane per length bucket");
   __shared__ uint32_t sum_all[16][kLenBuckets], sum_before[16][kLenBuckets];
   __shared__ uint32_t cursor[kLenBuckets];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  uint32_t all = 0, before = 0;                        // of bucket `lane`: strings, and those of earlier stretches
+  uint32_t all = 0, before = 0;                        // of bucket `lane`: groups, and those of earlier stretches
   for (int b = wave; b < (int)gridDim.x; b += 16) {
     const uint32_t n = part[b * kLenBuckets + lane];
     all += n;
@@ -121,15 +159,12 @@ __global__ __launch_bounds__(1024) void bin_scatter_kernel(const int64_t* offset
     }
   }
   __syncthreads();
-  const int first = blockIdx.x * stretch, last = first + min(stretch, batch - first);
-  for (int s = first + t; s < last; s += 1024) {
-    int64_t begin;
-    int32_t len;
-    const int key = string_bin(offsets, s, plan, begin, len);
-    if (key < 0) continue;
-    const uint32_t pos = atomicAdd(&cursor[key], 1u);
-    list[pos] = s;
-    desc[pos] = ItemDesc{begin, len, s};
+  const int64_t first = blockIdx.x * stretch, last = min(first + stretch, (int64_t)batch);
+  for (int64_t tile = first; tile < last; tile += 1024) {
+    const StringGroup g = string_group(offsets, tile, batch, room);
+    if (g.members)
+      desc[atomicAdd(&cursor[bin_key(min(g.len, 1024), plan)], 1u)] =
+          ItemDesc{g.begin, g.len | (g.members << kGroupShift), (int)(tile + t)};
   }
 }
 
@@ -211,26 +246,33 @@ __global__ __launch_bounds__(256) void scan_pack_kernel(const int32_t* tmp_ids, 
   for (int i = threadIdx.x; i < k; i += 256) out_ids[dst + i] = vocabulary_id(id_map, tmp_ids[src + i]);
 }
 
-// One wave per string: copy its ids from the per-string staging area to the dense output, four rows of 64 loads in
-// flight.  (Rows of a data set have a few dozen ids: a workgroup per string leaves three of its four waves idle.)
+// One wave per group of strings: copy its ids from the staging area to the dense output, four rows of 64 loads in
+// flight.  (A group's ids lie together on both sides, unless its strings were encoded one by one.)
 __global__ __launch_bounds__(256) void pack_kernel(const int32_t* tmp_ids, const int64_t* offsets,
-                                                   const int64_t* out_offsets, int batch, int32_t* out_ids,
-                                                   const int32_t* id_map) {
+                                                   const int64_t* out_offsets, const Control* c, const ItemDesc* desc,
+                                                   int32_t* out_ids, const int32_t* id_map) {
   const int lane = threadIdx.x & 63;
-  for (int64_t s = blockIdx.x * 4ll + (threadIdx.x >> 6); s < batch; s += gridDim.x * 4ll) {
-    const int64_t src = offsets[s], dst = out_offsets[s];
-    const int k = (int)(out_offsets[s + 1] - dst);
-    for (int i0 = 0; i0 < k; i0 += 256) {
-      int32_t v[4];
+  const uint32_t n_groups = c->tier_base[1];
+  for (uint32_t g = blockIdx.x * 4 + (threadIdx.x >> 6); g < n_groups; g += gridDim.x * 4) {
+    const ItemDesc d = desc[g];
+    const int members = (d.len >> kGroupShift) & kGroupMask;
+    const int each = (d.len & kGroupApart) ? 1 : members;
+    for (int m = 0; m < members; m += each) {          // (uniform)
+      const int s = d.item + m;
+      const int64_t src = offsets[s], dst = out_offsets[s];
+      const int k = (int)(out_offsets[s + each] - dst);
+      for (int i0 = 0; i0 < k; i0 += 256) {
+        int32_t v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + 64 * u + lane;
-        v[u] = i < k ? tmp_ids[src + i] : 0;           // (token 0 exists in every table)
-      }
+        for (int u = 0; u < 4; ++u) {
+          const int i = i0 + 64 * u + lane;
+          v[u] = i < k ? tmp_ids[src + i] : 0;         // (token 0 exists in every table)
+        }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + 64 * u + lane;
-        if (i < k) out_ids[dst + i] = vocabulary_id(id_map, v[u]);
+        for (int u = 0; u < 4; ++u) {
+          const int i = i0 + 64 * u + lane;
+          if (i < k) out_ids[dst + i] = vocabulary_id(id_map, v[u]);
+        }
       }
     }
   }
@@ -325,9 +367,9 @@ __global__ __launch_bounds__(1024) void slot_layout_kernel(const int64_t* offset
   }
 }
 
-// Eight lanes per slot, eight slots per wave: where does the slot's piece start?  The candidates are the 128
+// Sixteen lanes per slot, four slots per wave: where does the slot's piece start?  The candidates are the 128
 // positions q = t, t-1, ..., t-127 below the slot's nominal start t (a cut "before q" lies between bytes q-1 and
-// q); the largest one with a cut wins.  A group looks at eight candidates per round -- in text the first round
+// q); the largest one with a cut wins.  A group looks at sixteen candidates per round -- in text the first round
 // nearly always finds one -- and the wave goes on while any of its groups is still looking.
 constexpr int kCutSlotsPerWave = 4;
 __global__ __launch_bounds__(256) void cut_search_kernel(const uint8_t* bytes, const int64_t* offsets,

@@ -92,12 +92,13 @@ Variant (&g_variants)[kMaxTiers] = g_variant_families[0];   // sizes and capacit
 
 // Items of up to 1 KiB go to the lane-per-segment kernel first; the one-wave variant above then takes those that
 // kernel passes on (items with a segment of more than 32 bytes).  [family][0]: passes them on through the
-// fallback list; [family][1]: encodes them itself (the launch without a work list).
-template <bool SPC, bool INL>
+// fallback list; [family][1]: encodes them itself (the launch without a work list); [family][2]: items are groups of
+// whole strings.
+template <bool SPC, bool INL, bool GRP>
 void launch_lanes(const EncodeParams& p, int grid, hipStream_t stream) {
-  encode_lanes_kernel<SPC, INL><<<dim3(grid), dim3(64), lanes_lds_bytes<INL>(), stream>>>(p);
+  encode_lanes_kernel<SPC, INL, GRP><<<dim3(grid), dim3(64), lanes_lds_bytes<INL>(), stream>>>(p);
 }
-template <bool SPC, bool INL>
+template <bool SPC, bool INL, bool GRP>
 Variant make_lanes_variant() {
   Variant v;
   v.waves = 1;
@@ -106,13 +107,15 @@ Variant make_lanes_variant() {
   v.limits = false;
   v.capacity = kLaneItemBytes;
   v.lds = lanes_lds_bytes<INL>();
-  v.fn = (const void*)&encode_lanes_kernel<SPC, INL>;
-  v.launch = &launch_lanes<SPC, INL>;
+  v.fn = (const void*)&encode_lanes_kernel<SPC, INL, GRP>;
+  v.launch = &launch_lanes<SPC, INL, GRP>;
   return v;
 }
-Variant g_lanes_variants[2][2] = {
-    {make_lanes_variant<false, false>(), make_lanes_variant<false, true>()},
-    {make_lanes_variant<true, false>(), make_lanes_variant<true, true>()},
+Variant g_lanes_variants[2][3] = {
+    {make_lanes_variant<false, false, false>(), make_lanes_variant<false, true, false>(),
+     make_lanes_variant<false, false, true>()},
+    {make_lanes_variant<true, false, false>(), make_lanes_variant<true, true, false>(),
+     make_lanes_variant<true, false, true>()},
 };
 std::once_flag g_variants_once;
 int g_variants_status = BPE_OK;
@@ -551,12 +554,18 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
       // (the stretches' histograms, 256 bytes per 1,024 strings at most, borrow the fallback list, 4 bytes a string,
       // which is written only once the work list is made)
       uint32_t* part = (uint32_t*)(ws + w.fallback);
-      const int wanted = (int)std::min<int64_t>(((int64_t)batch + 1023) / 1024, kBinGrid);
-      const int stretch = (int)(((int64_t)batch + wanted - 1) / wanted);
+      const int64_t tiles = ((int64_t)batch + 1023) / 1024;
+      const int64_t stretch = (tiles + kBinGrid - 1) / kBinGrid * 1024;
       const int grid = (int)(((int64_t)batch + stretch - 1) / stretch);
-      hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, plan, part, counts);
-      hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, plan, ctrl, part,
-                         list, (ItemDesc*)(ws + w.list_desc));
+      // Neighbouring strings within `room` bytes are one work item: an item's capacity, but so little in small batches
+      // that three quarters of the resident workgroups get an item before any gets two (a group stays half a string
+      // below its room on average).
+      const int64_t mean = total_bytes / batch;
+      const int room = (int)std::min<int64_t>(total_bytes / std::max(1, lanes[2].max_grid * 3 / 4) + mean / 2, kLaneItemBytes);
+      hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, plan,
+                         part);
+      hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, plan,
+                         ctrl, part, (ItemDesc*)(ws + w.list_desc));
     } else {
       int32_t* sb = (int32_t*)(ws + w.slot_base);
       int32_t* ss = (int32_t*)(ws + w.slot_string);
@@ -632,7 +641,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
       if (t == 0) {
         // one lane per segment; what it cannot take (a segment of more than 32 bytes) it encodes itself when
         // there is no work list, and else leaves on the fallback list for the wave-per-item variant
-        const Variant& lv = lanes[direct ? 1 : 0];
+        const Variant& lv = lanes[direct ? 1 : w.split ? 0 : 2];
         lv.launch(p, lv.max_grid < n_items_max ? lv.max_grid : n_items_max, stream);
         if (direct) continue;
         EncodeParams rest = p;
@@ -656,9 +665,9 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     hipLaunchKernelGGL(offsets_scan_kernel, dim3((unsigned)((tiles + tiles_each - 1) / tiles_each)), dim3(1024), 0,
                        stream, counts, batch, (int)(tiles_each * 1024), out_offsets);
     if (batch > 0) {
-      const int grid = (int)std::min<int64_t>(((int64_t)batch + 3) / 4, 65536);
-      hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, offsets, out_offsets, batch, out_ids,
-                         table->d_id_map);
+      const int grid = (int)std::min<int64_t>(((int64_t)batch + 3) / 4, 8192);      // (there are fewer groups than strings)
+      hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, offsets, out_offsets, ctrl,
+                         (const ItemDesc*)(ws + w.list_desc), out_ids, table->d_id_map);
     }
   } else {
     int64_t* tile_sum = (int64_t*)(ws + w.tile_sum);

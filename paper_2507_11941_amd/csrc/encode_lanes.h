@@ -62,9 +62,11 @@ __device__ inline uint32_t mbcnt64(uint64_t mask) {                     // set b
 
 // Encodes item s -- n bytes from `begin` on (both uniform) -- if all its segments fit a lane; returns false (and
 // has written nothing to global memory) if one does not.  lds: this wave's LaneLds words (kFlags filled in by the
-// kernel).
-template <bool SPECIAL>
-__device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, int64_t begin, int n, uint32_t* lds) {
+// kernel).  GROUPS: the item is the `members` strings from s on, which lie one after the other in those bytes: a
+// string's last byte ends a segment like any cut does, and each string gets its own count.
+template <bool SPECIAL, bool GROUPS>
+__device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, int64_t begin, int n, int members,
+                                                  uint32_t* lds) {
   const int lane = (int)threadIdx.x & 63;
   const DeviceTable& tab = p.table;
   uint32_t* const T = lds + LaneLds::kT;
@@ -74,7 +76,11 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
   uint32_t* const hist = lds + LaneLds::kHist;
 
   if (n <= 0 || n > kLaneItemBytes) {                  // uniform; too long only if max_len was wrong
-    if (lane == 63) p.counts[s] = 0;
+    if constexpr (GROUPS) {
+      for (int i = lane; i < members; i += 64) p.counts[s + i] = 0;
+    } else {
+      if (lane == 63) p.counts[s] = 0;
+    }
     return true;
   }
   const int rows = (n + 63) >> 6;                      // uniform
@@ -96,6 +102,16 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
       }
     }
     b[kLaneRows] = mk[kLaneRows] = 0;
+    // the last bytes of the item's strings, a bit each, in the words that the tokens take afterwards
+    if constexpr (GROUPS) {
+      if (lane < 2 * kLaneRows) T[lane] = 0;
+      __syncthreads();
+      for (int i = lane; i < members; i += 64) {
+        const int64_t at = p.offsets[s + i + 1] - begin - 1;             // (an empty string's is its predecessor's)
+        if (at >= 0 && at < n) atomicOr(&T[at >> 5], 1u << (at & 31));
+      }
+      __syncthreads();
+    }
     uint32_t raw[kLaneRows];
     uint32_t word[kLaneRows];
 #pragma unroll
@@ -120,8 +136,11 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
           if (mk[j]) word[j] = (mk[j] & kCoverFirst) ? p.special_base + (mk[j] & kCoverIndex) : kTokNone;
           if (mk[j] | nm) raw[j] = kCut;
         }
+        if constexpr (GROUPS)
+          if ((T[2 * j + (lane >> 5)] >> (lane & 31)) & 1u) raw[j] = kCut;
       }
     }
+    if constexpr (GROUPS) __syncthreads();
     uint64_t carry = 1;                                // the item's first byte starts a segment
 #pragma unroll
     for (int j = 0; j < kLaneRows; ++j) {
@@ -307,10 +326,30 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
         const uint32_t tok = T[64 * j + lane];         // (positions from n on hold "no token")
         const uint64_t live_row = __ballot(tok != kTokNone);
         if (tok != kTokNone) dst[total + mbcnt64(live_row)] = (int32_t)(tok & kTokIdMask);
+        // (the pair values are no longer needed: their words keep, per row, the ballot and the tokens before it)
+        if constexpr (GROUPS) {
+          if (lane == 0) {
+            *(uint64_t*)(V + 2 * j) = live_row;
+            V[2 * kLaneRows + j] = total;
+          }
+        }
         total += (uint32_t)__builtin_popcountll(live_row);
       }
     }
-    if (lane == 63) p.counts[s] = (int32_t)total;
+    if constexpr (GROUPS) {
+      __syncthreads();
+      auto tokens_before = [&](int64_t at) {           // tokens of the item that start before its byte `at`
+        if (at <= 0) return 0;
+        if (at >= n) return (int)total;
+        const int j = (int)at >> 6;
+        return (int)V[2 * kLaneRows + j] +
+               (int)__builtin_popcountll(*(const uint64_t*)(V + 2 * j) & ((1ull << (at & 63)) - 1ull));
+      };
+      for (int i = lane; i < members; i += 64)
+        p.counts[s + i] = max(tokens_before(p.offsets[s + i + 1] - begin) - tokens_before(p.offsets[s + i] - begin), 0);
+    } else {
+      if (lane == 63) p.counts[s] = (int32_t)total;
+    }
     __syncthreads();                                   // LDS is reused by the next item
   }
   return true;
@@ -319,7 +358,9 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
 // Persistent one-wave workgroups over the items of tier 0.  An item with a segment that no lane can take goes to
 // the wave-per-item encoder: in this kernel when INLINE (the launch that has no work list and no
 // kernel after it to pick such items up), else through p.fallback_list.
-template <bool SPECIAL, bool INLINE>
+// GROUPS: the items are groups of strings (see bin_scatter_kernel); the strings of a group that cannot be taken go to
+// p.fallback_list one by one, and the group's descriptor is marked for the packing kernel.
+template <bool SPECIAL, bool INLINE, bool GROUPS>
 __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
   extern __shared__ uint32_t smem[];
   uint32_t* const arrays = smem;                       // this wave's LaneLds
@@ -330,7 +371,10 @@ __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
   // are two rounds of 2,560 -- the same two item times, with fewer waves sharing each SIMD.
   const uint32_t rounds = (count + gridDim.x - 1) / gridDim.x;
   const uint32_t g = rounds ? (count + rounds - 1) / rounds : 1u;
-  const uint32_t per_claim = min(count / g >= 32u ? 2u * kLaneChunk : kLaneChunk, max(1u, count / g));
+  // (Two or three rounds are dealt out whole: with count / g, which is one less unless g divides the count, all
+  // workgroups come back for a claim at the same moment -- 20,011 strings in some 6,000 groups, 50 us or 110.)
+  const uint32_t per_claim = rounds < kLaneChunk ? max(1u, rounds)
+                                                 : min(count / g >= 32u ? 2u * kLaneChunk : kLaneChunk, count / g);
   if (blockIdx.x >= g || (uint64_t)blockIdx.x * per_claim >= count) return;   // uniform: nothing for this workgroup
   // the capability bits of the 256 byte tokens, packed 16 bytes to a word
   if (threadIdx.x < 16) arrays[LaneLds::kFlags + threadIdx.x] = 0;
@@ -367,13 +411,15 @@ __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
       }
     }
   };
-  auto encode_chunk = [&](uint32_t here, const ItemDesc& cur) __attribute__((always_inline)) {
+  auto encode_chunk = [&](uint64_t at, uint32_t here, const ItemDesc& cur) __attribute__((always_inline)) {
     for (uint32_t i = 0; i < here; ++i) {
       const int s = __builtin_amdgcn_readlane(cur.item, (int)i);
       const int n = __builtin_amdgcn_readlane(cur.len, (int)i);
       const int64_t begin = ((int64_t)__builtin_amdgcn_readlane((int)(cur.begin >> 32), (int)i) << 32) |
                             (uint32_t)__builtin_amdgcn_readlane((int)cur.begin, (int)i);
-      const bool done = encode_item_lanes<SPECIAL>(p, s, begin, n, arrays);
+      const int members = GROUPS ? (n >> kGroupShift) & kGroupMask : 1;
+      const bool done =
+          encode_item_lanes<SPECIAL, GROUPS>(p, s, begin, GROUPS ? n & kGroupLen : n, members, arrays);
       if (!done) {                                     // uniform
         if constexpr (INLINE) {
           __syncthreads();
@@ -387,6 +433,10 @@ __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
           sh.byte_word = byte_word;
           encode_string_segmented<1, 16, true, SPECIAL>(p, s, other, other + kLaneItemBytes,
                                                         other + 2 * kLaneItemBytes, sh);
+        } else if constexpr (GROUPS) {
+          const uint32_t slot = uniform(atomicAdd(p.fallback_count, threadIdx.x == 0 ? (uint32_t)members : 0u));
+          for (int m = lane; m < members; m += 64) p.fallback_list[slot + m] = s + m;
+          if (lane == 0) ((ItemDesc*)p.list_desc)[first + at + i].len = n | kGroupApart;
         } else {
           // every lane takes part in the atomic (lane 0 adds 1): no lane-dependent branch at the loop's edge
           const uint32_t slot = uniform(atomicAdd(p.fallback_count, threadIdx.x == 0 ? 1u : 0u));
@@ -408,7 +458,7 @@ __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
   ItemDesc cur;
   load_chunk(first_item, here, cur);
   for (;;) {
-    encode_chunk(here, cur);
+    encode_chunk(first_item, here, cur);
     if (own_items >= count) break;                     // uniform: the grid's own chunks cover the list
     // (lane 0 adds 1; every lane takes part, so that no lane-dependent branch sits at the loop's edge)
     const uint32_t claimed = atomicAdd(p.queue_head + p.tier, threadIdx.x == 0 ? 1u : 0u);

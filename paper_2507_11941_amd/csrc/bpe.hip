@@ -656,7 +656,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     }
     if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
   }
-  if (!w.split && batch > 0 && batch <= 4096) {
+  if (direct && batch > 0 && batch <= 4096) {            // (groups' ids do not lie string by string)
     hipLaunchKernelGGL(scan_pack_kernel, dim3(batch), dim3(256), 0, stream, tmp_ids, offsets, counts, batch,
                        out_offsets, out_ids, table->d_id_map);
   } else if (!w.split) {

@@ -14,7 +14,7 @@ ROWS = [(97, 98), (256, 99), (32, 97), (98, 98)]
 
 
 @pytest.mark.parametrize("ids", ["own", "vocab", "specials"])
-@pytest.mark.parametrize("batch, mean", [(4097, 12), (5120, 200), (8193, 500), (20011, 100), (131073, 2), (262145, 12),
+@pytest.mark.parametrize("batch, mean", [(1793, 200), (4096, 30), (4097, 12), (5120, 200), (8193, 500), (20011, 100), (131073, 2), (262145, 12),
                                          (300001, 1)])
 def test_many_rows(batch, mean, ids):
     import torch

@@ -547,9 +547,13 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const Variant* family = g_variant_families[cover ? 1 : 0];
   const Variant* lanes = g_lanes_variants[cover ? 1 : 0];
   const bool direct = !w.split && plan.n_tiers == 1 && batch <= lanes[1].max_grid;
+  const bool singles = !w.split && !direct && batch <= kSinglesMax;    // one item a string; above, groups of strings
   if (batch > 0) {
     if (direct) {
       list = nullptr;
+    } else if (singles) {
+      hipLaunchKernelGGL(bin_kernel, dim3(1), dim3(1024), 0, stream, offsets, batch, plan, ctrl, list,
+                         (ItemDesc*)(ws + w.list_desc), counts);
     } else if (!w.split) {
       // (the stretches' histograms, 256 bytes per 1,024 strings at most, borrow the fallback list, 4 bytes a string,
       // which is written only once the work list is made)
@@ -641,7 +645,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
       if (t == 0) {
         // one lane per segment; what it cannot take (a segment of more than 32 bytes) it encodes itself when
         // there is no work list, and else leaves on the fallback list for the wave-per-item variant
-        const Variant& lv = lanes[direct ? 1 : w.split ? 0 : 2];
+        const Variant& lv = lanes[direct ? 1 : w.split || singles ? 0 : 2];
         lv.launch(p, lv.max_grid < n_items_max ? lv.max_grid : n_items_max, stream);
         if (direct) continue;
         EncodeParams rest = p;
@@ -656,7 +660,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     }
     if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
   }
-  if (direct && batch > 0 && batch <= 4096) {            // (groups' ids do not lie string by string)
+  if (!w.split && batch > 0 && batch <= kSinglesMax) {   // (groups' ids do not lie string by string)
     hipLaunchKernelGGL(scan_pack_kernel, dim3(batch), dim3(256), 0, stream, tmp_ids, offsets, counts, batch,
                        out_offsets, out_ids, table->d_id_map);
   } else if (!w.split) {

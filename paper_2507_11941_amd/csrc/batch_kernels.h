@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "string_groups.h"
 #include "table_format.h"
 
 namespace bpe {
@@ -112,48 +113,6 @@ __global__ __launch_bounds__(1024) void bin_kernel(const int64_t* offsets, int b
 // of it does, and needs no atomics on memory.  What bounds them is latency, a chain of a few loads each: one workgroup
 // that walks the batch twice took 1.3 us per 1,024 strings (20,011 strings: 27 us).
 constexpr int kBinGrid = 128;
-constexpr int kGroupLen = 0xFFF;                       // a group's ItemDesc::len: its length in bytes (kGroupLen: not
-constexpr int kGroupShift = 12;                        //   encodable), its strings from bit kGroupShift on, and
-constexpr int kGroupMask = 0x7F;                       //   kGroupApart once its strings have been encoded one by one,
-constexpr int kGroupApart = 1 << 30;                   //   each to its own place
-// The group that string s = tile + threadIdx.x heads; members = 0 if it heads none.  Whole waves take part.
-struct StringGroup {
-  int64_t begin;
-  int members, len;
-};
-__device__ inline StringGroup string_group(const int64_t* offsets, int64_t tile, int batch, int room) {
-  const int lane = threadIdx.x & 63;
-  const int64_t first = tile + (threadIdx.x & ~63u);   // the wave's first string ...
-  const int n = (int)min((int64_t)batch - first, (int64_t)64);           // ... and how many it has (0 or less: none)
-  StringGroup g{0, 0, kGroupLen};
-  if (n <= 0) return g;                                // uniform
-  const int64_t base = offsets[first];
-  int64_t end = 0;
-  if (lane < n) {
-    g.begin = offsets[first + lane];
-    end = offsets[first + lane + 1];
-  }
-  // relative to the wave's first byte, clamped: beyond 2^28 nothing fits a group anyway
-  const int from = (int)min(max(g.begin - base, (int64_t)-1), (int64_t)1 << 28);
-  const int to = (int)min(max(end - base, (int64_t)-1), (int64_t)1 << 28);
-  const bool bad = from < 0 || to < from;              // (offsets that decrease: such a string stays alone)
-  const uint64_t bad_lanes = __ballot(lane >= n || bad);
-  uint64_t heads = 0;
-  for (int at = 0; at < n;) {                          // uniform; `at` grows every round
-    heads |= 1ull << at;
-    const uint64_t later = at < 63 ? ~0ull << (at + 1) : 0ull;
-    uint64_t stop = (__ballot(to > __builtin_amdgcn_readlane(from, at) + room) | bad_lanes) & later;
-    if ((bad_lanes >> at) & 1ull) stop = later;
-    at = stop ? __builtin_ctzll(stop) : 64;
-  }
-  if ((heads >> lane) & 1ull) {
-    const uint64_t later = lane < 63 ? heads & (~0ull << (lane + 1)) : 0ull;
-    g.members = (later ? __builtin_ctzll(later) : n) - lane;
-  }
-  const int group_end = __shfl(to, max(lane + g.members - 1, 0), 64);
-  if (g.members && !bad && group_end - from <= 1024) g.len = group_end - from;
-  return g;
-}
 __global__ __launch_bounds__(1024) void bin_count_kernel(const int64_t* offsets, int batch, int64_t stretch, int room,
                                                          TierPlan plan, uint32_t* part) {
   __shared__ uint32_t hist[kLenBuckets];
@@ -163,7 +122,7 @@ __global__ __launch_bounds__(1024) void bin_count_kernel(const int64_t* offsets,
   __syncthreads();
   for (int64_t tile = first; tile < last; tile += 1024) {
     const StringGroup g = string_group(offsets, tile, batch, room);
-    if (g.members) atomicAdd(&hist[bin_key(min(g.len, 1024), plan)], 1u);
+    if (g.members) atomicAdd(&hist[bin_key(min(g.len, kGroupBytes), plan)], 1u);
   }
   __syncthreads();
   if (t < kLenBuckets) part[blockIdx.x * kLenBuckets + t] = hist[t];
@@ -206,7 +165,7 @@ __global__ __launch_bounds__(1024) void bin_scatter_kernel(const int64_t* offset
   for (int64_t tile = first; tile < last; tile += 1024) {
     const StringGroup g = string_group(offsets, tile, batch, room);
     if (g.members)
-      desc[atomicAdd(&cursor[bin_key(min(g.len, 1024), plan)], 1u)] =
+      desc[atomicAdd(&cursor[bin_key(min(g.len, kGroupBytes), plan)], 1u)] =
           ItemDesc{g.begin, g.len | (g.members << kGroupShift), (int)(tile + t)};
   }
 }

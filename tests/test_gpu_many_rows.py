@@ -53,3 +53,31 @@ def test_many_rows(batch, mean, ids):
             want_off = want_off - (np.arange(batch + 1) > some[0]) * (end - at)
         assert_same_encoding(got, out_off, want_ids, want_off, f"{batch} strings, max_len {max_len}")
     table.free()
+
+
+def test_one_very_long_string_leaves_its_neighbours():
+    """A string of 2^28 bytes among short ones, with max_len said to be 1,024: its own output is unspecified (here: no
+    tokens), the strings that share its wave in the listing kernels are encoded all the same."""
+    import torch
+
+    import paper_2507_11941_amd as bpe
+
+    rng = np.random.default_rng(28)
+    lens = rng.integers(0, 60, size=5000)
+    long_one, huge = 70, 1 << 28
+    offsets = np.cumsum([0, *lens], dtype=np.int64)
+    data = rng.choice(np.frombuffer(b"aabbc  x", dtype=np.uint8), size=int(offsets[-1]))
+    dev = torch.device("cuda:0")
+    at = int(offsets[long_one])
+    text = torch.full((len(data) + huge,), 98, dtype=torch.uint8, device=dev)
+    text[:at] = torch.from_numpy(data[:at]).to(dev)
+    text[at + huge:] = torch.from_numpy(data[at:]).to(dev)
+    with_long = np.concatenate([offsets[:long_one + 1], offsets[long_one:] + huge])
+    table, orc = bpe.build_table(ROWS), oracle.Table(ROWS)
+    got, out_off = bpe.encode_batch(table, text, torch.from_numpy(with_long).to(dev), 1024)
+    out_off = out_off.cpu().numpy()
+    got = got[: int(out_off[-1])].cpu().numpy()
+    assert out_off[long_one + 1] == out_off[long_one]
+    want_ids, want_off = orc.encode_batch(data, offsets, tier=oracle.HEAP, nthreads=8)
+    assert_same_encoding(got, np.delete(out_off, long_one), want_ids, want_off, "around the long string")
+    table.free()

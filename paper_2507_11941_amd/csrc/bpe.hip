@@ -527,12 +527,17 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   int32_t* counts = (int32_t*)(ws + w.counts);
   int32_t* tmp_ids = (int32_t*)(ws + w.tmp_ids);
 
+  if (batch == 0) {                                      // whatever max_len says: nothing to list, encode or pack
+    hipLaunchKernelGGL(offsets_scan_kernel, dim3(1), dim3(1024), 0, stream, counts, 0, 1024, out_offsets);
+    return hipGetLastError() == hipSuccess ? BPE_OK : BPE_EHIP;
+  }
+
   TierPlan plan;
   plan.n_tiers = n_tiers_for(max_len);
   for (int t = 0; t < kMaxTiers; ++t) plan.cap[t] = g_variants[t].capacity;
 
   const uint8_t* cover = nullptr;                        // special tokens: mark their occurrences first
-  if (table->d_specials && batch > 0 && total_bytes > 0) {
+  if (table->d_specials && total_bytes > 0) {
     uint8_t* marks = (uint8_t*)(ws + w.cover);
     hipLaunchKernelGGL(special_mark_kernel, dim3((unsigned)((total_bytes + kMarkBlock - 1) / kMarkBlock)), dim3(256), 0,
                        stream, bytes, offsets, batch, total_bytes, table->d_specials, marks);
@@ -548,131 +553,127 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const Variant* lanes = g_lanes_variants[cover ? 1 : 0];
   const bool direct = !w.split && plan.n_tiers == 1 && batch <= lanes[1].max_grid;
   const bool singles = !w.split && !direct && batch <= kSinglesMax;    // one item a string; above, groups of strings
-  if (batch > 0) {
-    if (direct) {
-      list = nullptr;
-    } else if (singles) {
-      hipLaunchKernelGGL(bin_kernel, dim3(1), dim3(1024), 0, stream, offsets, batch, plan, ctrl, list,
-                         (ItemDesc*)(ws + w.list_desc), counts);
-    } else if (!w.split) {
-      // (the stretches' histograms, 256 bytes per 1,024 strings at most, borrow the fallback list, 4 bytes a string,
-      // which is written only once the work list is made)
-      uint32_t* part = (uint32_t*)(ws + w.fallback);
-      const int64_t tiles = ((int64_t)batch + 1023) / 1024;
-      const int64_t stretch = (tiles + kBinGrid - 1) / kBinGrid * 1024;
-      const int grid = (int)(((int64_t)batch + stretch - 1) / stretch);
-      // Neighbouring strings within `room` bytes are one work item: an item's capacity, but so little in small batches
-      // that three quarters of the resident workgroups get an item before any gets two (a group stays half a string
-      // below its room on average).
-      const int64_t mean = total_bytes / batch;
-      const int room = (int)std::min<int64_t>(total_bytes / std::max(1, lanes[2].max_grid * 3 / 4) + mean / 2, kLaneItemBytes);
-      hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, plan,
-                         part);
-      hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, plan,
-                         ctrl, part, (ItemDesc*)(ws + w.list_desc));
+  if (direct) {
+    list = nullptr;
+  } else if (singles) {
+    hipLaunchKernelGGL(bin_kernel, dim3(1), dim3(1024), 0, stream, offsets, batch, plan, ctrl, list,
+                       (ItemDesc*)(ws + w.list_desc), counts);
+  } else if (!w.split) {
+    // (the stretches' histograms, 256 bytes per 1,024 strings at most, borrow the fallback list, 4 bytes a string,
+    // which is written only once the work list is made)
+    uint32_t* part = (uint32_t*)(ws + w.fallback);
+    const int64_t tiles = ((int64_t)batch + 1023) / 1024;
+    const int64_t stretch = (tiles + kBinGrid - 1) / kBinGrid * 1024;
+    const int grid = (int)(((int64_t)batch + stretch - 1) / stretch);
+    // Neighbouring strings within `room` bytes are one work item: an item's capacity, but so little in small batches
+    // that three quarters of the resident workgroups get an item before any gets two (a group stays half a string
+    // below its room on average).
+    const int64_t mean = total_bytes / batch;
+    const int room = (int)std::min<int64_t>(total_bytes / std::max(1, lanes[2].max_grid * 3 / 4) + mean / 2, kLaneItemBytes);
+    hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, plan,
+                       part);
+    hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, plan,
+                       ctrl, part, (ItemDesc*)(ws + w.list_desc));
+  } else {
+    int32_t* sb = (int32_t*)(ws + w.slot_base);
+    int32_t* ss = (int32_t*)(ws + w.slot_string);
+    int64_t* pb = (int64_t*)(ws + w.piece_begin);
+    int32_t* pl = (int32_t*)(ws + w.piece_len);
+    const uint32_t* byte_pair =
+        (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes) + 256;
+    const int per_slot_grid = (int)std::min<int64_t>((w.max_slots + 255) / 256, 256);   // (each workgroup ends with a few global atomics)
+    hipLaunchKernelGGL(slot_layout_kernel, dim3((unsigned)((batch + 1023) / 1024)), dim3(1024), 0, stream, offsets, batch, kPieceTarget,
+                       BPE_MAX_STRING_BYTES, ctrl, sb, ss);
+    hipLaunchKernelGGL(cut_search_kernel, dim3((unsigned)((w.max_slots + 4 * kCutSlotsPerWave - 1) / (4 * kCutSlotsPerWave))), dim3(256), 0, stream, bytes,
+                       offsets, byte_pair, kPieceTarget, BPE_MAX_STRING_BYTES, ctrl, sb, ss, pb, cover);
+    if (w.max_slots <= kSmallSlots) {
+      hipLaunchKernelGGL(piece_list_small_kernel, dim3(1), dim3(1024), 0, stream, offsets, plan, ctrl, sb, ss, pb, pl,
+                         counts, list, (ItemDesc*)(ws + w.list_desc));
     } else {
-      int32_t* sb = (int32_t*)(ws + w.slot_base);
-      int32_t* ss = (int32_t*)(ws + w.slot_string);
-      int64_t* pb = (int64_t*)(ws + w.piece_begin);
-      int32_t* pl = (int32_t*)(ws + w.piece_len);
-      const uint32_t* byte_pair =
-          (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes) + 256;
-      const int per_slot_grid = (int)std::min<int64_t>((w.max_slots + 255) / 256, 256);   // (each workgroup ends with a few global atomics)
-      hipLaunchKernelGGL(slot_layout_kernel, dim3((unsigned)((batch + 1023) / 1024)), dim3(1024), 0, stream, offsets, batch, kPieceTarget,
-                         BPE_MAX_STRING_BYTES, ctrl, sb, ss);
-      hipLaunchKernelGGL(cut_search_kernel, dim3((unsigned)((w.max_slots + 4 * kCutSlotsPerWave - 1) / (4 * kCutSlotsPerWave))), dim3(256), 0, stream, bytes,
-                         offsets, byte_pair, kPieceTarget, BPE_MAX_STRING_BYTES, ctrl, sb, ss, pb, cover);
-      if (w.max_slots <= kSmallSlots) {
-        hipLaunchKernelGGL(piece_list_small_kernel, dim3(1), dim3(1024), 0, stream, offsets, plan, ctrl, sb, ss, pb, pl,
-                           counts, list, (ItemDesc*)(ws + w.list_desc));
-      } else {
-        hipLaunchKernelGGL(piece_hist_kernel, dim3(per_slot_grid), dim3(256), 0, stream, offsets, plan, ctrl, sb, ss,
-                           pb, pl, counts);
-        hipLaunchKernelGGL(piece_scan_kernel, dim3(1), dim3(256), 0, stream, ctrl, plan.n_tiers);
-        hipLaunchKernelGGL(piece_scatter_kernel, dim3((unsigned)((w.max_slots + 256 * kScatterPer - 1) / (256 * kScatterPer))), dim3(256), 0, stream, plan,
-                           ctrl, pb, pl, list, (ItemDesc*)(ws + w.list_desc));
-      }
-      piece_begin = pb;
-      piece_len = pl;
-      slot_base = sb;
-      slot_string = ss;
+      hipLaunchKernelGGL(piece_hist_kernel, dim3(per_slot_grid), dim3(256), 0, stream, offsets, plan, ctrl, sb, ss,
+                         pb, pl, counts);
+      hipLaunchKernelGGL(piece_scan_kernel, dim3(1), dim3(256), 0, stream, ctrl, plan.n_tiers);
+      hipLaunchKernelGGL(piece_scatter_kernel, dim3((unsigned)((w.max_slots + 256 * kScatterPer - 1) / (256 * kScatterPer))), dim3(256), 0, stream, plan,
+                         ctrl, pb, pl, list, (ItemDesc*)(ws + w.list_desc));
     }
-
-    EncodeParams p;
-    p.table.buckets = (const uint4*)table->d_mem;
-    p.table.byte_word = (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes);
-    p.table.byte_pair = p.table.byte_word + 256;
-    p.table.log2_buckets = table->log2_buckets;
-    p.bytes = bytes;
-    p.offsets = offsets;
-    p.piece_begin = piece_begin;
-    p.piece_len = piece_len;
-    p.list = list;
-    p.list_desc = list ? (const void*)(ws + w.list_desc) : nullptr;
-    p.tier_base = ctrl->tier_base;
-    p.queue_head = ctrl->queue_head;
-    p.tmp_ids = tmp_ids;
-    p.counts = counts;
-    p.direct_count = (uint32_t)batch;
-    p.cover = cover;
-    p.special_base = 256u + (uint32_t)table->n_merges;
-    p.total_bytes = total_bytes;
-    p.fallback_count = &ctrl->fallback_range[1];
-    p.fallback_list = (int32_t*)(ws + w.fallback);
-    // Warming L2 pays once the batch probes the table more often than it has lines: ~1 probe per input byte.
-    const size_t table_bytes = table->bucket_bytes + (256 + 65536) * sizeof(uint32_t);
-    p.prefetch_lines = (size_t)total_bytes >= table_bytes / 4 ? (uint32_t)(table_bytes / 128) : 0u;
-
-    int prof_slot = -1;
-    if (g_profiling) {                                   // the event pairs exist already: nothing is created here
-      std::lock_guard<std::mutex> lock(g_prof_mutex);
-      if (g_profiling && g_prof.used < g_prof.created) {
-        prof_slot = g_prof.used++;
-        if (hipEventRecord(g_prof.begin[prof_slot], stream) != hipSuccess) return BPE_EHIP;
-      }
-    }
-    size_t staged_at = w.staged;
-    for (int t = 0; t < plan.n_tiers; ++t) {
-      const Variant& v = family[t];
-      int grid = v.max_grid < n_items_max ? v.max_grid : n_items_max;
-      p.tier = t;
-      p.staged = nullptr;
-      if (v.staged) {
-        if (grid > kMaxStagedGrid) grid = kMaxStagedGrid;
-        p.staged = (uint32_t*)(ws + staged_at);
-        staged_at += align_up(staged_slab_bytes(v) * kMaxStagedGrid);
-      }
-      if (t == 0) {
-        // one lane per segment; what it cannot take (a segment of more than 32 bytes) it encodes itself when
-        // there is no work list, and else leaves on the fallback list for the wave-per-item variant
-        const Variant& lv = lanes[direct ? 1 : w.split || singles ? 0 : 2];
-        lv.launch(p, lv.max_grid < n_items_max ? lv.max_grid : n_items_max, stream);
-        if (direct) continue;
-        EncodeParams rest = p;
-        rest.list = p.fallback_list;
-        rest.tier_base = ctrl->fallback_range;
-        rest.queue_head = &ctrl->fallback_queue;
-        rest.prefetch_lines = 0;
-        v.launch(rest, grid, stream);
-        continue;
-      }
-      v.launch(p, grid, stream);
-    }
-    if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
+    piece_begin = pb;
+    piece_len = pl;
+    slot_base = sb;
+    slot_string = ss;
   }
-  if (!w.split && batch > 0 && batch <= kSinglesMax) {   // (groups' ids do not lie string by string)
+
+  EncodeParams p;
+  p.table.buckets = (const uint4*)table->d_mem;
+  p.table.byte_word = (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes);
+  p.table.byte_pair = p.table.byte_word + 256;
+  p.table.log2_buckets = table->log2_buckets;
+  p.bytes = bytes;
+  p.offsets = offsets;
+  p.piece_begin = piece_begin;
+  p.piece_len = piece_len;
+  p.list = list;
+  p.list_desc = list ? (const void*)(ws + w.list_desc) : nullptr;
+  p.tier_base = ctrl->tier_base;
+  p.queue_head = ctrl->queue_head;
+  p.tmp_ids = tmp_ids;
+  p.counts = counts;
+  p.direct_count = (uint32_t)batch;
+  p.cover = cover;
+  p.special_base = 256u + (uint32_t)table->n_merges;
+  p.total_bytes = total_bytes;
+  p.fallback_count = &ctrl->fallback_range[1];
+  p.fallback_list = (int32_t*)(ws + w.fallback);
+  // Warming L2 pays once the batch probes the table more often than it has lines: ~1 probe per input byte.
+  const size_t table_bytes = table->bucket_bytes + (256 + 65536) * sizeof(uint32_t);
+  p.prefetch_lines = (size_t)total_bytes >= table_bytes / 4 ? (uint32_t)(table_bytes / 128) : 0u;
+
+  int prof_slot = -1;
+  if (g_profiling) {                                   // the event pairs exist already: nothing is created here
+    std::lock_guard<std::mutex> lock(g_prof_mutex);
+    if (g_profiling && g_prof.used < g_prof.created) {
+      prof_slot = g_prof.used++;
+      if (hipEventRecord(g_prof.begin[prof_slot], stream) != hipSuccess) return BPE_EHIP;
+    }
+  }
+  size_t staged_at = w.staged;
+  for (int t = 0; t < plan.n_tiers; ++t) {
+    const Variant& v = family[t];
+    int grid = v.max_grid < n_items_max ? v.max_grid : n_items_max;
+    p.tier = t;
+    p.staged = nullptr;
+    if (v.staged) {
+      if (grid > kMaxStagedGrid) grid = kMaxStagedGrid;
+      p.staged = (uint32_t*)(ws + staged_at);
+      staged_at += align_up(staged_slab_bytes(v) * kMaxStagedGrid);
+    }
+    if (t == 0) {
+      // one lane per segment; what it cannot take (a segment of more than 32 bytes) it encodes itself when
+      // there is no work list, and else leaves on the fallback list for the wave-per-item variant
+      const Variant& lv = lanes[direct ? 1 : w.split || singles ? 0 : 2];
+      lv.launch(p, lv.max_grid < n_items_max ? lv.max_grid : n_items_max, stream);
+      if (direct) continue;
+      EncodeParams rest = p;
+      rest.list = p.fallback_list;
+      rest.tier_base = ctrl->fallback_range;
+      rest.queue_head = &ctrl->fallback_queue;
+      rest.prefetch_lines = 0;
+      v.launch(rest, grid, stream);
+      continue;
+    }
+    v.launch(p, grid, stream);
+  }
+  if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
+  if (!w.split && batch <= kSinglesMax) {                // (groups' ids do not lie string by string)
     hipLaunchKernelGGL(scan_pack_kernel, dim3(batch), dim3(256), 0, stream, tmp_ids, offsets, counts, batch,
                        out_offsets, out_ids, table->d_id_map);
   } else if (!w.split) {
-    const int64_t tiles = std::max<int64_t>(((int64_t)batch + 1023) / 1024, 1);
+    const int64_t tiles = ((int64_t)batch + 1023) / 1024;
     const int64_t tiles_each = (tiles + kOffsetsGrid - 1) / kOffsetsGrid;     // (beyond 262,144 strings)
     hipLaunchKernelGGL(offsets_scan_kernel, dim3((unsigned)((tiles + tiles_each - 1) / tiles_each)), dim3(1024), 0,
                        stream, counts, batch, (int)(tiles_each * 1024), out_offsets);
-    if (batch > 0) {
-      const int grid = (int)std::min<int64_t>(((int64_t)batch + 3) / 4, 8192);      // (there are fewer groups than strings)
-      hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, offsets, out_offsets, ctrl,
-                         (const ItemDesc*)(ws + w.list_desc), out_ids, table->d_id_map);
-    }
+    const int grid = (int)std::min<int64_t>(((int64_t)batch + 3) / 4, 8192);        // (there are fewer groups than strings)
+    hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, offsets, out_offsets, ctrl,
+                       (const ItemDesc*)(ws + w.list_desc), out_ids, table->d_id_map);
   } else {
     int64_t* tile_sum = (int64_t*)(ws + w.tile_sum);
     int64_t* slot_out = (int64_t*)(ws + w.slot_out);

@@ -663,7 +663,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     v.launch(p, grid, stream);
   }
   if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
-  if (!w.split && batch <= kSinglesMax) {                // (groups' ids do not lie string by string)
+  if (direct || singles) {                               // (groups' ids do not lie string by string)
     hipLaunchKernelGGL(scan_pack_kernel, dim3(batch), dim3(256), 0, stream, tmp_ids, offsets, counts, batch,
                        out_offsets, out_ids, table->d_id_map);
   } else if (!w.split) {

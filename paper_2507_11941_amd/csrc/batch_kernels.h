@@ -249,7 +249,9 @@ __global__ __launch_bounds__(256) void scan_pack_kernel(const int32_t* tmp_ids, 
 }
 
 // One wave per group of strings: copy its ids from the staging area to the dense output, four rows of 64 loads in
-// flight.  (A group's ids lie together on both sides, unless its strings were encoded one by one.)
+// flight.  A group's ids lie together on both sides; those of a group marked kGroupApart lie string by string in the
+// staging area, so lane m keeps what lies between string m's two places and each id looks its string up among them:
+// string by string would be a chain of loads each, and such a group may have 64.
 __global__ __launch_bounds__(256) void pack_kernel(const int32_t* tmp_ids, const int64_t* offsets,
                                                    const int64_t* out_offsets, const Control* c, const ItemDesc* desc,
                                                    int32_t* out_ids, const int32_t* id_map) {
@@ -258,23 +260,33 @@ __global__ __launch_bounds__(256) void pack_kernel(const int32_t* tmp_ids, const
   for (uint32_t g = blockIdx.x * 4 + (threadIdx.x >> 6); g < n_groups; g += gridDim.x * 4) {
     const ItemDesc d = desc[g];
     const int members = (d.len >> kGroupShift) & kGroupMask;
-    const int each = (d.len & kGroupApart) ? 1 : members;
-    for (int m = 0; m < members; m += each) {          // (uniform)
-      const int s = d.item + m;
-      const int64_t src = offsets[s], dst = out_offsets[s];
-      const int k = (int)(out_offsets[s + each] - dst);
-      for (int i0 = 0; i0 < k; i0 += 256) {
-        int32_t v[4];
+    const bool apart = (d.len & kGroupApart) != 0;     // (per wave: uniform)
+    const int64_t src = d.begin, dst = out_offsets[d.item];
+    const int k = (int)(out_offsets[d.item + members] - dst);
+    int first = 0x7FFFFFFF, lack = 0;                  // string `lane`: its first id in the group, and how far from
+    if (apart && lane < members) {                     //   that place in the staging area it lies
+      first = (int)(out_offsets[d.item + lane] - dst);
+      lack = (int)(offsets[d.item + lane] - src) - first;
+    }
+    for (int i0 = 0; i0 < k; i0 += 256) {
+      int32_t v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = i0 + 64 * u + lane;
-          v[u] = i < k ? tmp_ids[src + i] : 0;         // (token 0 exists in every table)
-        }
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 64 * u + lane;
+        int64_t from = src + i;
+        if (apart) {
+          int m = 0;                                   // the last string whose first id is i or before it
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = i0 + 64 * u + lane;
-          if (i < k) out_ids[dst + i] = vocabulary_id(id_map, v[u]);
+          for (int step = 32; step >= 1; step >>= 1)
+            if (__shfl(first, m + step, 64) <= i) m += step;
+          from += __shfl(lack, m, 64);
         }
+        v[u] = i < k ? tmp_ids[from] : 0;              // (token 0 exists in every table)
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 64 * u + lane;
+        if (i < k) out_ids[dst + i] = vocabulary_id(id_map, v[u]);
       }
     }
   }

@@ -60,12 +60,16 @@ __device__ inline uint32_t mbcnt64(uint64_t mask) {                     // set b
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Encodes item s -- n bytes from `begin` on (both uniform) -- if all its segments fit a lane; returns false (and
-// has written nothing to global memory) if one does not.  lds: this wave's LaneLds words (kFlags filled in by the
-// kernel).  GROUPS: the item is the `members` strings from s on, which lie one after the other in those bytes: a
-// string's last byte ends a segment like any cut does, and each string gets its own count.
+// Encodes item s -- n bytes from `begin` on (both uniform) -- if all its segments fit a lane; returns 1 (and
+// has written nothing to global memory) if one does not, else 0.  lds: this wave's LaneLds words (kFlags filled in by
+// the kernel).  GROUPS: the item is the `members` strings from s on, at most 64, which lie one after the other in those
+// bytes: a string's last byte ends a segment like any cut does, and each string gets its own count.  The result has a
+// bit for every string with a segment that fits no lane; the others are encoded all the same, and if there is such a
+// string, each one's ids lie at its own place in tmp_ids instead of one after the other.  (100,000 rows of up to 60 bytes,
+// one in twenty with such a segment: 183 us.  With the whole group given away, five rows in six went to the
+// wave-per-item encoder: 1,029 us; with each row an item of its own 728.)
 template <bool SPECIAL, bool GROUPS>
-__device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, int64_t begin, int n, int members,
+__device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int s, int64_t begin, int n, int members,
                                                   uint32_t* lds) {
   const int lane = (int)threadIdx.x & 63;
   const DeviceTable& tab = p.table;
@@ -81,9 +85,18 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
     } else {
       if (lane == 63) p.counts[s] = 0;
     }
-    return true;
+    return 0;
   }
   const int rows = (n + 63) >> 6;                      // uniform
+  auto mark_string_ends = [&](uint32_t* bits) {        // (groups only) bit `at`: the item's byte `at` is a string's last
+    if (lane < 2 * kLaneRows) bits[lane] = 0;
+    __syncthreads();
+    if (lane < members) {
+      const int64_t at = p.offsets[s + lane + 1] - begin - 1;            // (an empty string's is its predecessor's)
+      if (at >= 0 && at < n) atomicOr(&bits[at >> 5], 1u << (at & 31));
+    }
+    __syncthreads();
+  };
   __builtin_amdgcn_s_setprio(3);                       // (the load phase too is a chain of round trips, and the
                                                        // sooner its loads go out the better)
 
@@ -103,15 +116,7 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
     }
     b[kLaneRows] = mk[kLaneRows] = 0;
     // the last bytes of the item's strings, a bit each, in the words that the tokens take afterwards
-    if constexpr (GROUPS) {
-      if (lane < 2 * kLaneRows) T[lane] = 0;
-      __syncthreads();
-      for (int i = lane; i < members; i += 64) {
-        const int64_t at = p.offsets[s + i + 1] - begin - 1;             // (an empty string's is its predecessor's)
-        if (at >= 0 && at < n) atomicOr(&T[at >> 5], 1u << (at & 31));
-      }
-      __syncthreads();
-    }
+    if constexpr (GROUPS) mark_string_ends(T);
     uint32_t raw[kLaneRows];
     uint32_t word[kLaneRows];
 #pragma unroll
@@ -164,9 +169,11 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
 
   __builtin_amdgcn_s_setprio(0);
   // ---- list, sorted: longest segments first (counting sort over the 31 possible lengths) ----
+  uint64_t left = 0;                                   // strings that are not encoded here (uniform)
   {
     constexpr int kRounds = kLaneItemBytes / 2 / 64;   // at most 512 segments of two bytes
-    uint32_t entry[kRounds], place[kRounds];
+    uint32_t entry[kRounds], place[kRounds];           // (entry: 0 for none)
+    const uint32_t n_listed = n_segments;
     bool too_long = false;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
@@ -185,7 +192,48 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
         }
       }
     }
-    if (__ballot(too_long)) return false;              // a segment no lane can take (nothing has left LDS)
+    if (__ballot(too_long)) {                          // uniform: a segment no lane can take (nothing has left LDS)
+      if constexpr (!GROUPS) return 1;
+      // The strings that hold one: lane m asks for string m.  Their tokens are taken away and their segments dropped;
+      // the others' are listed anew.
+      int from = n, to = n;                            // where string `lane` begins and ends in the item
+      if (lane < members) {
+        from = (int)min(max(p.offsets[s + lane] - begin, (int64_t)0), (int64_t)n);
+        to = (int)min(max(p.offsets[s + lane + 1] - begin, (int64_t)0), (int64_t)n);
+      }
+      n_segments = 0;
+      if (lane < 32) hist[lane] = 0;
+#pragma unroll
+      for (int r = 0; r < kRounds; ++r) {
+        if ((uint32_t)(64 * r) < n_listed) {           // uniform
+          const uint32_t first = entry[r] & 1023u;
+          const uint32_t window = __builtin_amdgcn_alignbit(ends[(first >> 5) + 1], ends[first >> 5], first & 31u);
+          uint64_t owners = __ballot(64u * r + (uint32_t)lane < n_listed && window == 0);
+          for (; owners; owners &= owners - 1ull) {    // uniform
+            const int at = (int)__builtin_amdgcn_readlane((int)first, (int)__builtin_ctzll(owners));
+            left |= __ballot(from <= at && at < to);
+          }
+        }
+      }
+      for (uint64_t m = left; m; m &= m - 1ull) {      // uniform
+        const int a = __builtin_amdgcn_readlane(from, (int)__builtin_ctzll(m));
+        const int b = __builtin_amdgcn_readlane(to, (int)__builtin_ctzll(m));
+        for (int i = a + lane; i < b; i += 64) T[i] = kTokNone;
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+          const int first = (int)(entry[r] & 1023u);
+          if (first >= a && first < b) entry[r] = 0;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < kRounds; ++r) {
+        if ((uint32_t)(64 * r) < n_listed) {           // uniform
+          n_segments += (uint32_t)__builtin_popcountll(__ballot(entry[r] != 0));
+          if (entry[r]) place[r] = atomicAdd(&hist[31u - (entry[r] >> 10)], 1u);
+        }
+      }
+    }
     __syncthreads();
     {
       const uint32_t mine = lane < 32 ? hist[lane] : 0u;
@@ -196,8 +244,8 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-      if ((uint32_t)(64 * r) < n_segments) {           // uniform
-        if (64u * r + (uint32_t)lane < n_segments)
+      if ((uint32_t)(64 * r) < n_listed) {             // uniform
+        if (GROUPS ? entry[r] != 0 : 64u * r + (uint32_t)lane < n_listed)
           seg[hist[31u - (entry[r] >> 10)] + place[r]] = (uint16_t)entry[r];
       }
     }
@@ -320,20 +368,45 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
   {
     int32_t* const dst = p.tmp_ids + begin;
     uint32_t total = 0;                                // uniform
-#pragma unroll
-    for (int j = 0; j < kLaneRows; ++j) {
-      if (j < rows) {                                  // uniform
-        const uint32_t tok = T[64 * j + lane];         // (positions from n on hold "no token")
+    // (groups: the pair values are no longer needed; their words keep, per row, the ballot and the tokens before it)
+    auto keep_row = [&](int j, uint64_t live_row) {
+      if (lane == 0) {
+        *(uint64_t*)(V + 2 * j) = live_row;
+        V[2 * kLaneRows + j] = total;
+      }
+    };
+    if (GROUPS && left) {                              // uniform: strings at their own places
+      mark_string_ends(ends);
+      uint32_t lack = 0;   // what the place of the row's first token lacks to its string's own (uniform)
+#pragma unroll 1
+      for (int j = 0; j < rows; ++j) {
+        const uint32_t tok = T[64 * j + lane];
         const uint64_t live_row = __ballot(tok != kTokNone);
-        if (tok != kTokNone) dst[total + mbcnt64(live_row)] = (int32_t)(tok & kTokIdMask);
-        // (the pair values are no longer needed: their words keep, per row, the ballot and the tokens before it)
-        if constexpr (GROUPS) {
-          if (lane == 0) {
-            *(uint64_t*)(V + 2 * j) = live_row;
-            V[2 * kLaneRows + j] = total;
-          }
+        auto tokens_upto = [&](uint32_t pos) {         // tokens before the row's position pos (at most 64)
+          return total + (uint32_t)__builtin_popcountll(pos < 64u ? live_row & ((1ull << pos) - 1ull) : live_row);
+        };
+        const uint64_t last_row = *(const uint64_t*)(ends + 2 * j);      // last bytes of strings ...
+        const uint64_t before = last_row & ((1ull << lane) - 1ull);      // ... and those before my position
+        const uint32_t start = before ? 64u - (uint32_t)__builtin_clzll(before) : 0u;
+        const uint32_t at = total + mbcnt64(live_row) + (before ? 64u * j + start - tokens_upto(start) : lack);
+        if (tok != kTokNone) dst[at] = (int32_t)(tok & kTokIdMask);
+        keep_row(j, live_row);
+        if (last_row) {                                // uniform
+          const uint32_t next_start = 64u - (uint32_t)__builtin_clzll(last_row);
+          lack = 64u * j + next_start - tokens_upto(next_start);
         }
         total += (uint32_t)__builtin_popcountll(live_row);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < kLaneRows; ++j) {
+        if (j < rows) {                                // uniform
+          const uint32_t tok = T[64 * j + lane];       // (positions from n on hold "no token")
+          const uint64_t live_row = __ballot(tok != kTokNone);
+          if (tok != kTokNone) dst[total + mbcnt64(live_row)] = (int32_t)(tok & kTokIdMask);
+          if constexpr (GROUPS) keep_row(j, live_row);
+          total += (uint32_t)__builtin_popcountll(live_row);
+        }
       }
     }
     if constexpr (GROUPS) {
@@ -345,21 +418,22 @@ __device__ __forceinline__ bool encode_item_lanes(const EncodeParams& p, int s, 
         return (int)V[2 * kLaneRows + j] +
                (int)__builtin_popcountll(*(const uint64_t*)(V + 2 * j) & ((1ull << (at & 63)) - 1ull));
       };
-      for (int i = lane; i < members; i += 64)
-        p.counts[s + i] = max(tokens_before(p.offsets[s + i + 1] - begin) - tokens_before(p.offsets[s + i] - begin), 0);
+      if (lane < members)
+        p.counts[s + lane] =
+            max(tokens_before(p.offsets[s + lane + 1] - begin) - tokens_before(p.offsets[s + lane] - begin), 0);
     } else {
       if (lane == 63) p.counts[s] = (int32_t)total;
     }
     __syncthreads();                                   // LDS is reused by the next item
   }
-  return true;
+  return left;
 }
 
 // Persistent one-wave workgroups over the items of tier 0.  An item with a segment that no lane can take goes to
 // the wave-per-item encoder: in this kernel when INLINE (the launch that has no work list and no
 // kernel after it to pick such items up), else through p.fallback_list.
 // GROUPS: the items are groups of strings (see bin_scatter_kernel); the strings of a group that cannot be taken go to
-// p.fallback_list one by one, and the group's descriptor is marked for the packing kernel.
+// p.fallback_list, and the group's descriptor is marked for the packing kernel.
 template <bool SPECIAL, bool INLINE, bool GROUPS>
 __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
   extern __shared__ uint32_t smem[];
@@ -418,9 +492,9 @@ __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
       const int64_t begin = ((int64_t)__builtin_amdgcn_readlane((int)(cur.begin >> 32), (int)i) << 32) |
                             (uint32_t)__builtin_amdgcn_readlane((int)cur.begin, (int)i);
       const int members = GROUPS ? (n >> kGroupShift) & kGroupMask : 1;
-      const bool done =
+      const uint64_t left =
           encode_item_lanes<SPECIAL, GROUPS>(p, s, begin, GROUPS ? n & kGroupLen : n, members, arrays);
-      if (!done) {                                     // uniform
+      if (left) {                                      // uniform
         if constexpr (INLINE) {
           __syncthreads();
           BlockShared<1> sh;
@@ -434,8 +508,9 @@ __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
           encode_string_segmented<1, 16, true, SPECIAL>(p, s, other, other + kLaneItemBytes,
                                                         other + 2 * kLaneItemBytes, sh);
         } else if constexpr (GROUPS) {
-          const uint32_t slot = uniform(atomicAdd(p.fallback_count, threadIdx.x == 0 ? (uint32_t)members : 0u));
-          for (int m = lane; m < members; m += 64) p.fallback_list[slot + m] = s + m;
+          const uint32_t slot = uniform(
+              atomicAdd(p.fallback_count, threadIdx.x == 0 ? (uint32_t)__builtin_popcountll(left) : 0u));
+          if ((left >> lane) & 1ull) p.fallback_list[slot + mbcnt64(left)] = s + lane;
           if (lane == 0) ((ItemDesc*)p.list_desc)[first + at + i].len = n | kGroupApart;
         } else {
           // every lane takes part in the atomic (lane 0 adds 1): no lane-dependent branch at the loop's edge

@@ -8,8 +8,8 @@ namespace bpe {
 constexpr int kGroupBytes = 1024;                      // capacity of a work item
 constexpr int kGroupLen = 0xFFF;                       // a group's ItemDesc::len: its length in bytes (kGroupLen: not
 constexpr int kGroupShift = 12;                        //   encodable), its strings from bit kGroupShift on, and
-constexpr int kGroupMask = 0x7F;                       //   kGroupApart once its strings have been encoded one by one,
-constexpr int kGroupApart = 1 << 30;                   //   each to its own place
+constexpr int kGroupMask = 0x7F;                       //   kGroupApart once one of its strings had to be passed on: then
+constexpr int kGroupApart = 1 << 30;                   //   each string's ids lie at its own place in the staging area
 // The group that string s = tile + threadIdx.x heads; members = 0 if it heads none.  Whole waves take part.
 struct StringGroup {
   int64_t begin;

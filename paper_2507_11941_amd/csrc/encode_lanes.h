@@ -91,7 +91,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
   auto mark_string_ends = [&](uint32_t* bits) {        // (groups only) bit `at`: the item's byte `at` is a string's last
     if (lane < 2 * kLaneRows) bits[lane] = 0;
     __syncthreads();
-    if (lane < members) {
+    if (lane < members - 1) {                          // (the last one's last byte is the item's)
       const int64_t at = p.offsets[s + lane + 1] - begin - 1;            // (an empty string's is its predecessor's)
       if (at >= 0 && at < n) atomicOr(&bits[at >> 5], 1u << (at & 31));
     }
@@ -409,7 +409,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         }
       }
     }
-    if constexpr (GROUPS) {
+    if (GROUPS && members > 1) {                       // uniform
       __syncthreads();
       auto tokens_before = [&](int64_t at) {           // tokens of the item that start before its byte `at`
         if (at <= 0) return 0;

@@ -61,8 +61,9 @@ struct ItemDesc {
 // 256 keys, then the scatter of string indices into the work list (class-major, longest bucket first).
 // Also resets the work-queue heads.  A second pass over the offsets is cheaper than a second launch.  For batches of up
 // to kSinglesMax strings, one item each: all of them are resident within a round or so, and the launches that groups
-// need cost more than they save (2,000 strings of up to 400 bytes: 27 us, in groups 47; from 4,097 on groups win,
-// 45 us against 85 at 60 bytes).
+// need cost more than they save (2,000 strings of up to 400 bytes: 30 us, in groups 40; 4,096 of 60, of up to 400 and of
+// 1,000 bytes: 40, 39 and 57 us, in groups 42, 41 and 61).  Beyond, where an item a string needs a second round, groups
+// win (6,000 of 100, 250 and 1,000 bytes: 61, 66 and 88 us, in groups 40, 45 and 82).
 constexpr int kSinglesMax = 4096;
 __global__ __launch_bounds__(1024) void bin_kernel(const int64_t* offsets, int batch, TierPlan plan, Control* c,
                                                    int32_t* list, ItemDesc* desc, int32_t* counts) {
@@ -103,15 +104,15 @@ __global__ __launch_bounds__(1024) void bin_kernel(const int64_t* offsets, int b
 // The work list of a batch whose strings are not split and that has more of them than are resident at once: groups of
 // neighbouring strings, longest length bucket first.  (Such a batch has one tier.)  An item costs its wave some ten
 // microseconds of round trips whatever its length, so short strings go together: 20,011 strings of up to 400 bytes
-// were 105 us one by one and are 45.  Every 64 strings are divided by one wave, first come first served: a group
+// were 105 us one by one and are 48.  Every 64 strings are divided by one wave, first come first served: a group
 // takes strings until the next one would end more than `room` bytes after its beginning.  (With groups of all strings
 // that start in one window of the text, which need no walk, items were a third smaller.)
 //
 // Workgroup b owns the strings [b stretch, (b + 1) stretch), whole tiles of 1,024.  bin_count_kernel leaves each
 // stretch's histogram of the length buckets in `part` (kLenBuckets words per workgroup); bin_scatter_kernel adds up
 // everybody's, which is at most kBinGrid rows of 256 bytes, so it knows where each bucket begins and where its own part
-// of it does, and needs no atomics on memory.  What bounds them is latency, a chain of a few loads each: one workgroup
-// that walks the batch twice took 1.3 us per 1,024 strings (20,011 strings: 27 us).
+// of it does, and needs no atomics on memory.  What bounds them is latency, a chain of a few loads each (20,011 strings:
+// 4.4 and 5.0 us); one workgroup that walks the batch twice took 1.3 us per 1,024 strings (27 us).
 constexpr int kBinGrid = 128;
 __global__ __launch_bounds__(1024) void bin_count_kernel(const int64_t* offsets, int batch, int64_t stretch, int room,
                                                          TierPlan plan, uint32_t* part) {
@@ -251,7 +252,8 @@ __global__ __launch_bounds__(256) void scan_pack_kernel(const int32_t* tmp_ids, 
 // One wave per group of strings: copy its ids from the staging area to the dense output, four rows of 64 loads in
 // flight.  A group's ids lie together on both sides; those of a group marked kGroupApart lie string by string in the
 // staging area, so lane m keeps what lies between string m's two places and each id looks its string up among them:
-// string by string would be a chain of loads each, and such a group may have 64.
+// string by string would be a chain of loads each, and such a group may have 64.  What bounds it is the loads' latency:
+// 20,011 rows of up to 400 bytes 4.8 us; 100,000 of up to 60 bytes, nearly all groups with a marked string, 6.9 us.
 __global__ __launch_bounds__(256) void pack_kernel(const int32_t* tmp_ids, const int64_t* offsets,
                                                    const int64_t* out_offsets, const Control* c, const ItemDesc* desc,
                                                    int32_t* out_ids, const int32_t* id_map) {
@@ -881,7 +883,7 @@ __global__ __launch_bounds__(256) void special_mark_kernel(const uint8_t* bytes,
 // while it copies, and issues four rows of loads per slot -- and, where the ids are a vocabulary's, their look-ups --
 // before the first store.  A slot copies at most kPackShare ids; what a longer piece has beyond them is copied by the
 // void slots it runs over, kPackShare each: a piece over m slots has at most (m - 1) * piece target + 1024 bytes.
-// 256 pieces of 64 KiB, 41,000 ids each: 121 us with one wave a piece, about 20 us so (whole call 443 -> 346 us).
+// 256 pieces of 64 KiB, 41,000 ids each: 121 us with one wave a piece, 18 us so (whole call 443 -> 346 us).
 constexpr int kPackShare = 1024;
 struct PackItem {
   uint32_t g;

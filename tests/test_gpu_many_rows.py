@@ -1,7 +1,8 @@
-"""Batches of more short strings than are resident at once: neighbours are encoded as one work item, and the offsets are
-summed by stretches of strings.  Sizes around a workgroup's 1,024 strings, where a stretch outgrows them (131,072 strings
-for the list, 262,144 for the offsets); runs of empty strings, strings at the limit, strings with a segment that sends
-their group to the other encoder, and one beyond max_len (unspecified output: here it yields no tokens)."""
+"""Batches of more short strings than are resident at once: up to 4,096 strings one work item each, above that neighbours
+are one item and the offsets are summed by stretches of strings.  Sizes on both sides of that line, around a workgroup's
+1,024 strings and where a stretch outgrows them (131,072 strings for the list, 262,144 for the offsets); runs of empty
+strings, strings at the limit, strings without a cut that go to the other encoder, and one beyond max_len (unspecified
+output: with one list for all strings it yields no tokens)."""
 import numpy as np
 import pytest
 

@@ -50,6 +50,11 @@ __device__ inline int bin_key(int len, const TierPlan& plan) {
   return -1;                                         // longer than any launched variant: skipped
 }
 
+// The key of a group of strings or pieces (tier 0).
+__device__ inline int group_key(int len) {
+  return min((kGroupBytes - min(len, kGroupBytes)) * kLenBuckets / kGroupBytes, kLenBuckets - 1);
+}
+
 // What a work item is, stored beside its place in the work list: all that an encode kernel needs to start on it.
 struct ItemDesc {
   int64_t begin;                                     // first byte of the item in `bytes`
@@ -97,7 +102,7 @@ __global__ __launch_bounds__(1024) void bin_kernel(const int64_t* offsets, int b
     if (key < 0) continue;
     const uint32_t pos = (scan[key] - hist[key]) + atomicAdd(&cursor[key], 1u);
     list[pos] = s;
-    desc[pos] = ItemDesc{offsets[s], (int32_t)len, s};
+    desc[pos] = ItemDesc{offsets[s], (int32_t)len | 1 << kGroupShift, s};
   }
 }
 
@@ -115,7 +120,7 @@ __global__ __launch_bounds__(1024) void bin_kernel(const int64_t* offsets, int b
 // 4.4 and 5.0 us); one workgroup that walks the batch twice took 1.3 us per 1,024 strings (27 us).
 constexpr int kBinGrid = 128;
 __global__ __launch_bounds__(1024) void bin_count_kernel(const int64_t* offsets, int batch, int64_t stretch, int room,
-                                                         TierPlan plan, uint32_t* part) {
+                                                         uint32_t* part) {
   __shared__ uint32_t hist[kLenBuckets];
   const int t = threadIdx.x;
   const int64_t first = blockIdx.x * stretch, last = min(first + stretch, (int64_t)batch);
@@ -123,14 +128,14 @@ __global__ __launch_bounds__(1024) void bin_count_kernel(const int64_t* offsets,
   __syncthreads();
   for (int64_t tile = first; tile < last; tile += 1024) {
     const StringGroup g = string_group(offsets, tile, batch, room);
-    if (g.members) atomicAdd(&hist[bin_key(min(g.len, kGroupBytes), plan)], 1u);
+    if (g.members) atomicAdd(&hist[group_key(g.len)], 1u);
   }
   __syncthreads();
   if (t < kLenBuckets) part[blockIdx.x * kLenBuckets + t] = hist[t];
 }
 // Also resets the work-queue heads.
 __global__ __launch_bounds__(1024) void bin_scatter_kernel(const int64_t* offsets, int batch, int64_t stretch,
-                                                           int room, TierPlan plan, Control* c,
+                                                           int room, Control* c,
                                                            const uint32_t* part, ItemDesc* desc) {
   static_assert(kLenBuckets == 64, "a lane per length bucket");
   __shared__ uint32_t sum_all[16][kLenBuckets], sum_before[16][kLenBuckets];
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(1024) void bin_scatter_kernel(const int64_t* offset
   for (int64_t tile = first; tile < last; tile += 1024) {
     const StringGroup g = string_group(offsets, tile, batch, room);
     if (g.members)
-      desc[atomicAdd(&cursor[bin_key(min(g.len, kGroupBytes), plan)], 1u)] =
+      desc[atomicAdd(&cursor[group_key(g.len)], 1u)] =
           ItemDesc{g.begin, g.len | (g.members << kGroupShift), (int)(tile + t)};
   }
 }
@@ -462,27 +467,46 @@ __device__ inline int64_t piece_end(const int64_t* offsets, int s, uint32_t g, c
   return offsets[s + 1];
 }
 
-// One thread per slot: piece lengths, and the histogram of (tier, length bucket) keys.
-__global__ __launch_bounds__(256) void piece_hist_kernel(const int64_t* offsets, TierPlan plan, Control* c,
+// What a slot's piece is to the work list.  Pieces that one wave can take (tier 0) go together while they lie within
+// `room` bytes, like short strings do, whichever strings they are of; a longer one is an item of its own.  Whole waves
+// take part.
+struct PieceItem {
+  int key;                                             // -1: no item begins here
+  int32_t len;                                         // as in ItemDesc
+};
+__device__ inline PieceItem piece_item(int64_t start, int32_t len, int64_t wave_first, uint32_t n_slots, const TierPlan& plan,
+                                       int room) {
+  const int n = (int)min((int64_t)n_slots - wave_first, (int64_t)64);
+  const int key = start >= 0 ? bin_key(len, plan) : -1;
+  const bool single = key >= 0 && key < kLenBuckets;
+  const StringGroup g = group_members(start, start + len, !single, n, room);
+  if (!single) return PieceItem{key, len};
+  return PieceItem{g.members ? group_key(g.len) : -1, g.len | (g.members << kGroupShift)};
+}
+
+// One thread per slot: piece lengths, and the histogram of (tier, length bucket) keys of the items.
+__global__ __launch_bounds__(256) void piece_hist_kernel(const int64_t* offsets, TierPlan plan, int room, Control* c,
                                                          const int32_t* slot_base, const int32_t* slot_string,
                                                          const int64_t* piece_begin, int32_t* piece_len,
-                                                         int32_t* counts) {
+                                                         int32_t* counts, int32_t* group_ids) {
   __shared__ uint32_t hist[kBinKeys];
   hist[threadIdx.x] = 0;                               // 256 threads, 256 keys
   __syncthreads();
   const uint32_t n_slots = c->n_slots;
-  for (uint32_t g = blockIdx.x * 256 + threadIdx.x; g < n_slots; g += gridDim.x * 256) {
-    const int64_t start = piece_begin[g];
-    const int s = slot_string[g];
+  for (uint32_t first = blockIdx.x * 256; first < n_slots; first += gridDim.x * 256) {                // uniform
+    const uint32_t g = first + threadIdx.x;
+    int64_t start = -1;
     int32_t len = 0;
-    int key = -1;
-    if (start >= 0) {
-      len = (int32_t)(piece_end(offsets, s, g, slot_base, piece_begin, piece_len) - start);
-      key = bin_key(len, plan);
-      if (key >= 0) atomicAdd(&hist[key], 1u);
+    if (g < n_slots) {
+      start = piece_begin[g];
+      const int s = slot_string[g];
+      if (start >= 0) len = (int32_t)(piece_end(offsets, s, g, slot_base, piece_begin, piece_len) - start);
+      if (start >= 0 || slot_base[s] == (int32_t)g) piece_len[g] = len;   // (other void slots: the piece's own thread)
+      if (start < 0 || bin_key(len, plan) < 0) counts[g] = 0;             // void slot, or too long for the launched variants
+      group_ids[g] = -1;
     }
-    if (start >= 0 || slot_base[s] == (int32_t)g) piece_len[g] = len;   // (other void slots: the piece's own thread)
-    if (key < 0) counts[g] = 0;                        // void slot, or too long for the launched variants
+    const PieceItem item = piece_item(start, len, g & ~63u, n_slots, plan, room);
+    if (item.key >= 0) atomicAdd(&hist[item.key], 1u);
   }
   __syncthreads();
   if (hist[threadIdx.x]) atomicAdd(&c->hist[threadIdx.x], hist[threadIdx.x]);
@@ -510,7 +534,7 @@ __global__ __launch_bounds__(256) void piece_scan_kernel(Control* c, int n_tiers
 // key's range of the list with one global atomic.  Those atomics land on a handful of addresses and are served
 // one after the other, so a workgroup takes kScatterPer slots per thread: fewer workgroups, fewer atomics.
 constexpr int kScatterPer = 4;
-__global__ __launch_bounds__(256) void piece_scatter_kernel(TierPlan plan, Control* c, const int64_t* piece_begin,
+__global__ __launch_bounds__(256) void piece_scatter_kernel(TierPlan plan, int room, Control* c, const int64_t* piece_begin,
                                                             const int32_t* piece_len, int32_t* list, ItemDesc* desc) {
   __shared__ uint32_t local[kBinKeys];                 // 256 threads, 256 keys
   local[threadIdx.x] = 0;
@@ -534,10 +558,10 @@ __global__ __launch_bounds__(256) void piece_scatter_kernel(TierPlan plan, Contr
   }
 #pragma unroll
   for (int j = 0; j < kScatterPer; ++j) {
-    if (begin[j] >= 0) {
-      key[j] = bin_key(len[j], plan);
-      if (key[j] >= 0) rank[j] = atomicAdd(&local[key[j]], 1u);
-    }
+    const PieceItem item = piece_item(begin[j], len[j], ((blockIdx.x * kScatterPer + j) * 256 + threadIdx.x) & ~63u, n_slots, plan, room);
+    key[j] = item.key;
+    len[j] = item.len;
+    if (key[j] >= 0) rank[j] = atomicAdd(&local[key[j]], 1u);
   }
   __syncthreads();
   const uint32_t mine = local[threadIdx.x];
@@ -557,10 +581,11 @@ __global__ __launch_bounds__(256) void piece_scatter_kernel(TierPlan plan, Contr
 // piece_hist_kernel, piece_scan_kernel and piece_scatter_kernel in one workgroup, for batches of at most
 // kSmallSlots slots (a launch costs more than the work of a small batch).  Thread t takes slots t, t + 1024, ...
 constexpr int kSmallSlots = 4096;
-__global__ __launch_bounds__(1024) void piece_list_small_kernel(const int64_t* offsets, TierPlan plan, Control* c,
+__global__ __launch_bounds__(1024) void piece_list_small_kernel(const int64_t* offsets, TierPlan plan, int room, Control* c,
                                                                 const int32_t* slot_base, const int32_t* slot_string,
                                                                 const int64_t* piece_begin, int32_t* piece_len,
-                                                                int32_t* counts, int32_t* list, ItemDesc* desc) {
+                                                                int32_t* counts, int32_t* group_ids, int32_t* list,
+                                                                ItemDesc* desc) {
   __shared__ uint32_t hist[kBinKeys], scan[kBinKeys];
   const int t = threadIdx.x;
   if (t < kBinKeys) hist[t] = 0;
@@ -583,12 +608,15 @@ __global__ __launch_bounds__(1024) void piece_list_small_kernel(const int64_t* o
       const int s = slot_string[g];
       if (start[j] >= 0) {
         len[j] = (int32_t)(piece_end(offsets, s, g, slot_base, piece_begin, piece_len) - start[j]);
-        key[j] = bin_key(len[j], plan);
-        if (key[j] >= 0) rank[j] = atomicAdd(&hist[key[j]], 1u);
       }
       if (start[j] >= 0 || slot_base[s] == (int32_t)g) piece_len[g] = len[j];
-      if (key[j] < 0) counts[g] = 0;                   // void slot, or too long for the launched variants
+      if (start[j] < 0 || bin_key(len[j], plan) < 0) counts[g] = 0;       // void slot, or too long for the launched variants
+      group_ids[g] = -1;
     }
+    const PieceItem item = piece_item(start[j], len[j], g & ~63u, n_slots, plan, room);
+    key[j] = item.key;
+    len[j] = item.len;
+    if (key[j] >= 0) rank[j] = atomicAdd(&hist[key[j]], 1u);
   }
   __syncthreads();
   if (t < kBinKeys) scan[t] = hist[t];
@@ -887,20 +915,22 @@ __global__ __launch_bounds__(256) void special_mark_kernel(const uint8_t* bytes,
 constexpr int kPackShare = 1024;
 struct PackItem {
   uint32_t g;
-  int k;
+  int k, group;                                        // the piece's own ids, and group_ids
   int64_t src, dst;
 };
 __device__ inline PackItem pack_item(uint32_t g, uint32_t n_slots, const int64_t* piece_begin, const int32_t* counts,
-                                     const int64_t* slot_out) {
-  PackItem it{g, 0, 0, 0};
+                                     const int32_t* group_ids, const int64_t* slot_out) {
+  PackItem it{g, 0, -1, 0, 0};
   if (g < n_slots) {
     it.k = counts[g];
+    it.group = group_ids[g];
     it.src = piece_begin[g];
     it.dst = slot_out[g];
   }
   return it;
 }
-// A void slot turned into its share of the piece that runs over it, and a piece cut to its own share.
+// A void slot turned into its share of the piece that runs over it, and a piece cut to its own share -- or grown to its
+// item, whose ids lie together (2 Ki at most).
 __device__ inline void pack_share(PackItem& it, const int64_t* piece_begin, const int32_t* piece_len,
                                   const int32_t* counts, const int64_t* slot_out) {
   if (it.src < 0) {                                    // (per wave: uniform)
@@ -913,22 +943,23 @@ __device__ inline void pack_share(PackItem& it, const int64_t* piece_begin, cons
       it.dst = slot_out[owner] + skip;
     }
   }
-  it.k = min(it.k, kPackShare);
+  it.k = it.group >= 0 ? it.group : min(it.k, kPackShare);
 }
 __global__ __launch_bounds__(256) void piece_pack_kernel(const int32_t* tmp_ids, const Control* c,
                                                          const int64_t* piece_begin, const int32_t* piece_len,
-                                                         const int32_t* counts, const int64_t* slot_out,
-                                                         int32_t* out_ids, const int32_t* id_map) {
+                                                         const int32_t* counts, const int32_t* group_ids,
+                                                         const int64_t* slot_out, int32_t* out_ids,
+                                                         const int32_t* id_map) {
   const uint32_t n_slots = c->n_slots;
   const int lane = threadIdx.x & 63;
   const uint32_t stride = gridDim.x * 4;               // slots one round of the grid takes: wave w takes w and w + stride
   uint32_t g = blockIdx.x * 4 + (threadIdx.x >> 6);
-  PackItem a = pack_item(g, n_slots, piece_begin, counts, slot_out);
-  PackItem b = pack_item(g + stride, n_slots, piece_begin, counts, slot_out);
+  PackItem a = pack_item(g, n_slots, piece_begin, counts, group_ids, slot_out);
+  PackItem b = pack_item(g + stride, n_slots, piece_begin, counts, group_ids, slot_out);
   while (g < n_slots) {
     const uint32_t g_next = g + 2 * stride;
-    const PackItem a_next = pack_item(g_next, n_slots, piece_begin, counts, slot_out);
-    const PackItem b_next = pack_item(g_next + stride, n_slots, piece_begin, counts, slot_out);
+    const PackItem a_next = pack_item(g_next, n_slots, piece_begin, counts, group_ids, slot_out);
+    const PackItem b_next = pack_item(g_next + stride, n_slots, piece_begin, counts, group_ids, slot_out);
     pack_share(a, piece_begin, piece_len, counts, slot_out);
     pack_share(b, piece_begin, piece_len, counts, slot_out);
     const int longest = max(a.k, b.k);                 // (per wave: uniform)

@@ -16,6 +16,7 @@
 #include "encode_lanes.h"
 #include "encode_segmented.h"
 #include "table_format.h"
+#include "word_table.h"
 
 using namespace bpe;
 
@@ -26,6 +27,8 @@ struct bpe_table {
   void* d_mem = nullptr;          // buckets, then the 256 byte token words, then the 256 x 256 byte-pair values,
                                   // then (tables over a vocabulary only) the id of every token, int32[256 + rows]
   size_t bucket_bytes = 0;
+  void* d_words = nullptr;        // bit set of the cuts, uint32[2048], then the word table: buckets, keys
+  int log2_word_buckets = 0;
   const int32_t* d_id_map = nullptr;   // null: byte b is id b, row r creates id 256 + r.  Inside d_mem, or
                                        // d_special_mem once special tokens are set
   std::vector<int32_t> id_map_host;    // the vocabulary ids of the 256 + rows tokens (empty: the default)
@@ -90,32 +93,33 @@ Variant g_variant_families[2][kMaxTiers] = {
 };
 Variant (&g_variants)[kMaxTiers] = g_variant_families[0];   // sizes and capacities are those of either family
 
-// Items of up to 1 KiB go to the lane-per-segment kernel first; the one-wave variant above then takes those that
-// kernel passes on (items with a segment of more than 32 bytes).  [family][0]: passes them on through the
-// fallback list; [family][1]: encodes them itself (the launch without a work list); [family][2]: items are groups of
-// whole strings.
-template <bool SPC, bool INL, bool GRP>
+// Items of tier 0 go to the lane-per-segment kernel first; the one-wave variant above then takes those strings and
+// pieces that this kernel passes on (they have a segment of more than 32 bytes).  [family][shape]: with kDirect item i is
+// string i, and the kernel encodes those itself (the launch without a work list); else the items are groups of strings or
+// pieces, of up to 1 KiB (kSmall) or 2 KiB (kLarge).
+enum { kDirect, kSmall, kLarge, kLaneShapes };
+template <class L, bool SPC, bool INL>
 void launch_lanes(const EncodeParams& p, int grid, hipStream_t stream) {
-  encode_lanes_kernel<SPC, INL, GRP><<<dim3(grid), dim3(64), lanes_lds_bytes<INL>(), stream>>>(p);
+  encode_lanes_kernel<L, SPC, INL><<<dim3(grid), dim3(64 * L::kWaves), L::kLdsBytes, stream>>>(p);
 }
-template <bool SPC, bool INL, bool GRP>
+template <class L, bool SPC, bool INL>
 Variant make_lanes_variant() {
   Variant v;
-  v.waves = 1;
+  v.waves = L::kWaves;
   v.depth = 16;
   v.staged = false;
   v.limits = false;
-  v.capacity = kLaneItemBytes;
-  v.lds = lanes_lds_bytes<INL>();
-  v.fn = (const void*)&encode_lanes_kernel<SPC, INL, GRP>;
-  v.launch = &launch_lanes<SPC, INL, GRP>;
+  v.capacity = L::kBytes;
+  v.lds = L::kLdsBytes;
+  v.fn = (const void*)&encode_lanes_kernel<L, SPC, INL>;
+  v.launch = &launch_lanes<L, SPC, INL>;
   return v;
 }
-Variant g_lanes_variants[2][3] = {
-    {make_lanes_variant<false, false, false>(), make_lanes_variant<false, true, false>(),
-     make_lanes_variant<false, false, true>()},
-    {make_lanes_variant<true, false, false>(), make_lanes_variant<true, true, false>(),
-     make_lanes_variant<true, false, true>()},
+Variant g_lanes_variants[2][kLaneShapes] = {
+    {make_lanes_variant<InlineItems, false, true>(), make_lanes_variant<SmallItems, false, false>(),
+     make_lanes_variant<LargeItems, false, false>()},
+    {make_lanes_variant<InlineItems, true, true>(), make_lanes_variant<SmallItems, true, false>(),
+     make_lanes_variant<LargeItems, true, false>()},
 };
 std::once_flag g_variants_once;
 int g_variants_status = BPE_OK;
@@ -175,7 +179,7 @@ struct WorkspaceLayout {
   int64_t max_slots;                 // upper bound on the number of work items (strings or piece slots)
   int n_tiles;                       // scan tiles over the slots
   size_t control, list, list_desc, fallback, counts, tmp_ids, cover, staged;
-  size_t slot_base, slot_string, piece_begin, piece_len, slot_out, tile_sum;   // split only
+  size_t slot_base, slot_string, piece_begin, piece_len, group_ids, slot_out, tile_sum;   // split only
   size_t total;
 };
 
@@ -192,12 +196,13 @@ WorkspaceLayout layout_for(int32_t batch, int64_t total_bytes, int32_t max_len) 
   w.counts = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
   w.tmp_ids = at; at += align_up((size_t)total_bytes * sizeof(int32_t));
   w.cover = at; at += align_up((size_t)total_bytes + 4);      // special-token marks, one per byte, whole chunks of 16
-  w.slot_base = w.slot_string = w.piece_begin = w.piece_len = w.slot_out = w.tile_sum = 0;
+  w.slot_base = w.slot_string = w.piece_begin = w.piece_len = w.group_ids = w.slot_out = w.tile_sum = 0;
   if (w.split) {
     w.slot_base = at; at += align_up(((size_t)batch + 1) * sizeof(int32_t));
     w.slot_string = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
     w.piece_begin = at; at += align_up((size_t)w.max_slots * sizeof(int64_t));
     w.piece_len = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
+    w.group_ids = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
     w.slot_out = at; at += align_up((size_t)w.max_slots * sizeof(int64_t));
     w.tile_sum = at; at += align_up((size_t)(w.n_tiles + 1) * sizeof(int64_t));
   }
@@ -328,13 +333,52 @@ int build_image(const int32_t* merges, int32_t n_merges, std::vector<uint32_t>& 
   return BPE_OK;
 }
 
+// Row of the pair (a, b) in a finished image, or a value above all rows.
+uint32_t image_rank(const std::vector<uint32_t>& host, int log2_buckets, uint32_t a, uint32_t b) {
+  const Placement pl = place_pair(a, b, log2_buckets);
+  const uint32_t* const home = host.data() + (size_t)pl.bucket * kSlotsPerBucket * 2;
+  const uint32_t reach = home[3] == 0xFFFFFFFFu ? 0u : bucket_reach(home[0], home[2]);
+  for (uint32_t d = 0; d <= reach; ++d) {
+    const uint32_t* const bucket = host.data() + (size_t)(pl.bucket ^ d) * kSlotsPerBucket * 2;
+    for (int k = 0; k < kSlotsPerBucket; ++k)
+      if (bucket[2 * k + 1] == slot_tag(pl.fingerprint, d)) return bucket[2 * k] >> kRankShift;
+  }
+  return kNoRank;
+}
+
+// The bit set of the cuts and the word table, as they lie in device memory: [cuts: 2048][buckets][keys].
+int build_word_memory(const int32_t* merges, int32_t n_merges, const std::vector<uint32_t>& host, int log2_buckets,
+                      std::vector<uint32_t>& memory, int& log2_word_buckets) {
+  try {
+    WordImage words;
+    build_words(merges, n_merges,
+                [&](uint32_t a, uint32_t b) { return image_rank(host, log2_buckets, a, b); }, words);
+    memory.assign(2048, 0);
+    memory.reserve(2048 + words.buckets.size() + words.keys.size());
+    const uint32_t* const byte_pair = host.data() + host.size() - 65536;
+    for (uint32_t a = 0; a < 256; ++a)
+      for (uint32_t b = 0; b < 256; ++b)
+        if (byte_pair[a << 8 | b] == kCut) memory[(b << 8 | a) >> 5] |= 1u << (a & 31u);
+    memory.insert(memory.end(), words.buckets.begin(), words.buckets.end());
+    memory.insert(memory.end(), words.keys.begin(), words.keys.end());
+    log2_word_buckets = words.log2_buckets;
+  } catch (const std::bad_alloc&) {
+    return BPE_ENOMEM;
+  }
+  return BPE_OK;
+}
+
 // merges: rows in the library's own numbering (byte b = b, row r creates 256 + r); id_map: null, or the
 // vocabulary id of each of the 256 + n_merges tokens, which the packing kernels then write instead.
 int build_table(const int32_t* merges, int32_t n_merges, const int32_t* id_map, bpe_table** out,
                 int32_t* bad_row) {
   std::vector<uint32_t> host;
   int log2_buckets = 0;
-  const int status = build_image(merges, n_merges, host, log2_buckets, bad_row);
+  int status = build_image(merges, n_merges, host, log2_buckets, bad_row);
+  if (status != BPE_OK) return status;
+  std::vector<uint32_t> words;
+  int log2_word_buckets = 0;
+  status = build_word_memory(merges, n_merges, host, log2_buckets, words, log2_word_buckets);
   if (status != BPE_OK) return status;
   bpe_table* t = new (std::nothrow) bpe_table();
   if (!t) return BPE_ENOMEM;
@@ -343,9 +387,15 @@ int build_table(const int32_t* merges, int32_t n_merges, const int32_t* id_map, 
   t->bucket_bytes = (host.size() - 256 - 65536) * sizeof(uint32_t);
   if (hipGetDevice(&t->device) != hipSuccess) { delete t; return BPE_EHIP; }
   const size_t map_words = id_map ? (size_t)n_merges + 256 : 0;
+  t->log2_word_buckets = log2_word_buckets;
   hipError_t e = hipMalloc(&t->d_mem, (host.size() + map_words) * sizeof(uint32_t));
+  if (e == hipSuccess) {
+    e = hipMalloc(&t->d_words, words.size() * sizeof(uint32_t));
+    if (e != hipSuccess) (void)hipFree(t->d_mem);
+  }
   if (e != hipSuccess) { delete t; return e == hipErrorOutOfMemory ? BPE_ENOMEM : BPE_EHIP; }
-  bool ok = hipMemcpy(t->d_mem, host.data(), host.size() * sizeof(uint32_t), hipMemcpyHostToDevice) == hipSuccess;
+  bool ok = hipMemcpy(t->d_mem, host.data(), host.size() * sizeof(uint32_t), hipMemcpyHostToDevice) == hipSuccess &&
+            hipMemcpy(t->d_words, words.data(), words.size() * sizeof(uint32_t), hipMemcpyHostToDevice) == hipSuccess;
   if (ok && id_map) {
     int32_t* d_map = (int32_t*)((uint32_t*)t->d_mem + host.size());
     ok = hipMemcpy(d_map, id_map, map_words * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
@@ -357,6 +407,7 @@ int build_table(const int32_t* merges, int32_t n_merges, const int32_t* id_map, 
     }
   }
   if (!ok) {
+    (void)hipFree(t->d_words);
     (void)hipFree(t->d_mem);
     delete t;
     return BPE_EHIP;
@@ -500,6 +551,7 @@ int bpe_table_set_specials(bpe_table* table, const uint8_t* text, const int32_t*
 void bpe_free_table(bpe_table* table) {
   if (!table) return;
   if (table->d_special_mem) (void)hipFree(table->d_special_mem);
+  if (table->d_words) (void)hipFree(table->d_words);
   if (table->d_mem) (void)hipFree(table->d_mem);
   delete table;
 }
@@ -547,12 +599,22 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const int32_t* piece_len = nullptr;
   const int32_t* slot_base = nullptr;
   const int32_t* slot_string = nullptr;
+  int32_t* group_ids = nullptr;
   const int n_items_max = (int)w.max_slots;              // grid bound for the encode kernels
   // A batch that one variant's resident grid covers needs no work list: workgroup i encodes string i.
   const Variant* family = g_variant_families[cover ? 1 : 0];
   const Variant* lanes = g_lanes_variants[cover ? 1 : 0];
-  const bool direct = !w.split && plan.n_tiers == 1 && batch <= lanes[1].max_grid;
+  const bool direct = !w.split && plan.n_tiers == 1 && batch <= lanes[kDirect].max_grid * lanes[kDirect].waves;
   const bool singles = !w.split && !direct && batch <= kSinglesMax;    // one item a string; above, groups of strings
+  // The work list's items.  As long as every string or piece gets a wave of its own, that is what it is; beyond,
+  // neighbours within `room` bytes are one item: all that the kernel takes, but so little in small batches that three
+  // quarters of the resident waves get an item before any gets two (a group stays half a member below its room on average).
+  const int64_t small_waves = (int64_t)lanes[kSmall].max_grid * lanes[kSmall].waves;
+  const bool small_items = singles || w.max_slots <= small_waves;
+  const Variant& listed = lanes[small_items ? kSmall : kLarge];
+  const int room = small_items ? -1
+                               : (int)std::min<int64_t>(total_bytes / std::max(1, listed.max_grid * listed.waves * 3 / 4) +
+                                                            total_bytes / w.max_slots / 2, listed.capacity);
   if (direct) {
     list = nullptr;
   } else if (singles) {
@@ -565,20 +627,14 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     const int64_t tiles = ((int64_t)batch + 1023) / 1024;
     const int64_t stretch = (tiles + kBinGrid - 1) / kBinGrid * 1024;
     const int grid = (int)(((int64_t)batch + stretch - 1) / stretch);
-    // Neighbouring strings within `room` bytes are one work item: an item's capacity, but so little in small batches
-    // that three quarters of the resident workgroups get an item before any gets two (a group stays half a string
-    // below its room on average).
-    const int64_t mean = total_bytes / batch;
-    const int room = (int)std::min<int64_t>(total_bytes / std::max(1, lanes[2].max_grid * 3 / 4) + mean / 2, kLaneItemBytes);
-    hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, plan,
-                       part);
-    hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, plan,
-                       ctrl, part, (ItemDesc*)(ws + w.list_desc));
+    hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, part);
+    hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, ctrl, part, (ItemDesc*)(ws + w.list_desc));
   } else {
     int32_t* sb = (int32_t*)(ws + w.slot_base);
     int32_t* ss = (int32_t*)(ws + w.slot_string);
     int64_t* pb = (int64_t*)(ws + w.piece_begin);
     int32_t* pl = (int32_t*)(ws + w.piece_len);
+    int32_t* gi = (int32_t*)(ws + w.group_ids);
     const uint32_t* byte_pair =
         (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes) + 256;
     const int per_slot_grid = (int)std::min<int64_t>((w.max_slots + 255) / 256, 256);   // (each workgroup ends with a few global atomics)
@@ -587,19 +643,20 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     hipLaunchKernelGGL(cut_search_kernel, dim3((unsigned)((w.max_slots + 4 * kCutSlotsPerWave - 1) / (4 * kCutSlotsPerWave))), dim3(256), 0, stream, bytes,
                        offsets, byte_pair, kPieceTarget, BPE_MAX_STRING_BYTES, ctrl, sb, ss, pb, cover);
     if (w.max_slots <= kSmallSlots) {
-      hipLaunchKernelGGL(piece_list_small_kernel, dim3(1), dim3(1024), 0, stream, offsets, plan, ctrl, sb, ss, pb, pl,
-                         counts, list, (ItemDesc*)(ws + w.list_desc));
+      hipLaunchKernelGGL(piece_list_small_kernel, dim3(1), dim3(1024), 0, stream, offsets, plan, room, ctrl, sb, ss, pb, pl,
+                         counts, gi, list, (ItemDesc*)(ws + w.list_desc));
     } else {
-      hipLaunchKernelGGL(piece_hist_kernel, dim3(per_slot_grid), dim3(256), 0, stream, offsets, plan, ctrl, sb, ss,
-                         pb, pl, counts);
+      hipLaunchKernelGGL(piece_hist_kernel, dim3(per_slot_grid), dim3(256), 0, stream, offsets, plan, room, ctrl, sb, ss,
+                         pb, pl, counts, gi);
       hipLaunchKernelGGL(piece_scan_kernel, dim3(1), dim3(256), 0, stream, ctrl, plan.n_tiers);
       hipLaunchKernelGGL(piece_scatter_kernel, dim3((unsigned)((w.max_slots + 256 * kScatterPer - 1) / (256 * kScatterPer))), dim3(256), 0, stream, plan,
-                         ctrl, pb, pl, list, (ItemDesc*)(ws + w.list_desc));
+                         room, ctrl, pb, pl, list, (ItemDesc*)(ws + w.list_desc));
     }
     piece_begin = pb;
     piece_len = pl;
     slot_base = sb;
     slot_string = ss;
+    group_ids = gi;
   }
 
   EncodeParams p;
@@ -607,12 +664,18 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.table.byte_word = (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes);
   p.table.byte_pair = p.table.byte_word + 256;
   p.table.log2_buckets = table->log2_buckets;
+  p.table.cuts = (const uint32_t*)table->d_words;
+  p.table.word_buckets = (const uint4*)(p.table.cuts + 2048);
+  p.table.word_keys = p.table.word_buckets + ((size_t)1 << table->log2_word_buckets);
+  p.table.log2_word_buckets = table->log2_word_buckets;
   p.bytes = bytes;
   p.offsets = offsets;
   p.piece_begin = piece_begin;
   p.piece_len = piece_len;
   p.list = list;
   p.list_desc = list ? (const void*)(ws + w.list_desc) : nullptr;
+  p.member_begin = w.split ? piece_begin : offsets;
+  p.group_ids = group_ids;
   p.tier_base = ctrl->tier_base;
   p.queue_head = ctrl->queue_head;
   p.tmp_ids = tmp_ids;
@@ -649,8 +712,8 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     if (t == 0) {
       // one lane per segment; what it cannot take (a segment of more than 32 bytes) it encodes itself when
       // there is no work list, and else leaves on the fallback list for the wave-per-item variant
-      const Variant& lv = lanes[direct ? 1 : w.split || singles ? 0 : 2];
-      lv.launch(p, lv.max_grid < n_items_max ? lv.max_grid : n_items_max, stream);
+      const Variant& lv = direct ? lanes[kDirect] : listed;
+      lv.launch(p, std::min(lv.max_grid, n_items_max), stream);
       if (direct) continue;
       EncodeParams rest = p;
       rest.list = p.fallback_list;
@@ -688,7 +751,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     }
     const int grid = (int)std::min<int64_t>((w.max_slots + 7) / 8, 32768);   // two pieces per wave and round
     hipLaunchKernelGGL(piece_pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, ctrl, piece_begin, piece_len,
-                       counts, slot_out, out_ids, table->d_id_map);
+                       counts, group_ids, slot_out, out_ids, table->d_id_map);
   }
   return hipGetLastError() == hipSuccess ? BPE_OK : BPE_EHIP;
 }

@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "table_format.h"
+#include "word_table.h"
 
 namespace bpe {
 
@@ -44,6 +45,10 @@ struct DeviceTable {
   const uint32_t* byte_word;  // [256] token word (id | capability bits) of each byte
   const uint32_t* byte_pair;  // [256*256] value of the pair (byte a, byte b) at a*256 + b, kNoRank if none
   int log2_buckets;
+  const uint32_t* cuts;       // bit a + 256 b: no merge ever joins byte a with the byte b after it (byte_pair says so too)
+  const uint4* word_buckets;  // whole segments that are one token (word_table.h)
+  const uint4* word_keys;
+  int log2_word_buckets;
 };
 
 struct EncodeParams {
@@ -57,6 +62,9 @@ struct EncodeParams {
   uint32_t* queue_head;       // [tiers] next unclaimed item of each tier
   int32_t* tmp_ids;           // ids of an item are written at tmp_ids[first byte of the item ...]
   int32_t* counts;            // token count of each item
+  const int64_t* member_begin;// lane-per-segment kernel: first byte of each string or piece; an item is several in a row
+  int32_t* group_ids;         // pieces: how many ids the packing kernel copies from a piece's first byte on: those of all its
+                              //   item, none for the item's other pieces, -1: its own
   const void* list_desc;      // ItemDesc of every entry of `list` (begin, length, item), in the same order
   uint32_t* staged;           // HBM staging for the variant whose strings exceed LDS (else null)
   uint32_t prefetch_lines;    // 128-byte lines of table memory to pull into L2 at kernel start (0 = none)

@@ -1,86 +1,212 @@
-// One lane per segment: the encoder for work items of up to 1 KiB whose segments are short.
+// One lane per segment: the encoder for work items of up to 2 KiB whose segments are short.
 //
 // A string falls apart at its cuts -- byte bigrams that lie at no merge junction, see table_format.h -- into
 // segments that Algorithm 1 processes without any interaction; with word-like text a segment is a word of a
-// few bytes.  Inside so short a stretch there is nothing for 64 lanes to share, so here every lane takes a
-// whole segment and runs Algorithm 1 on it literally: find the lowest-rank pair (left-most on ties), replace
-// it by its merged token, look up the two pairs the new token forms (section 4.2's steps, one lane wide), until
-// no pair of the segment is in the table.  The wave as a whole still works on one item (section 4.3: one block
-// per string), and a lane that finishes its segment takes the item's next one, longer segments first, so the
-// lanes stay busy whatever the mix of segment lengths.
+// few bytes.  Most of them are one token of the vocabulary and are looked up as a whole (word_table.h).  In the others
+// there is nothing for 64 lanes to share, so every lane takes a whole segment and runs Algorithm 1 on it literally: find
+// the lowest-rank pair (left-most on ties), replace it by its merged token, look up the two pairs the new token forms
+// (section 4.2's steps, one lane wide), until no pair of the segment is in the table.  The wave as a whole still works
+// on one item (section 4.3: one block per string), and a lane that finishes its segment takes the item's next one,
+// longer segments first, so the lanes stay busy whatever the mix of segment lengths.
 //
-//   load     position-parallel, one row of 64 consecutive bytes at a time: lane t holds byte 64 j + t of row j
-//            (coalesced byte loads, conflict-free LDS traffic), looks its pair with the next byte up in the direct
-//            byte-pair table, and a ballot of "this pair is a cut" is the row's piece of the segment-end bitmap.
-//   list     the segments with at least two bytes (first position and length), from the same ballots, then sorted
-//            by length, longest first: a counting sort with one LDS counter per length.  Handing the long
-//            segments out first is what keeps the lanes level at the end of an item (a third fewer trips of the
-//            merge loop than in text order).
+//   cuts     lane t holds bytes 16 t ... 16 t + 15 of the item (one wide load), asks a bit set of all byte bigrams in LDS
+//            where they are cut, and leaves the segments' first positions as a bitmap, then as a list.
+//   words    segment-parallel, 64 at a time and four such batches in flight: the segment's bytes are its key; two
+//            dependent table reads say which token it is, if it is one.
+//   list     the other segments, sorted by length, longest first: a counting sort with one LDS counter per length.
+//            Handing the long segments out first is what keeps the lanes level at the end.  Only these segments get a
+//            place in the arrays of tokens and pair values (the "arena"), in the list's order.
 //   merge    segment-parallel, as above; a lane keeps its segment's liveness as a 32-bit mask, so a segment
 //            may have at most 32 bytes.  A string with a longer segment is not encoded here: the kernel hands
 //            it to the wave-per-item encoder of encode_segmented.h, which has no such limit.  (An item is one
 //            string, a piece of one, or a group of short ones; of a group only such strings are handed on.)
-//   emit     row by row again: a ballot of the surviving tokens gives every lane its place in the output
-//            (section 4.3's compaction, as a prefix count over the ballots), and the ids go out in order.
+//   emit     segment-parallel: a prefix sum of the segments' token counts gives every one its place in the output
+//            (section 4.3's compaction).
+//
+// words to emit run over as many segments at a time as the arena and the lists hold: in text, all of the item's.
+//
+// What bounds it is instruction issue: some 1,700 vector and 900 scalar instructions per KiB of text, of which the merge
+// loop is two fifths, on three or four waves a SIMD.  With every segment going through the merges, one item of 1 KiB a wave
+// (14.9 trips of the loop per KiB instead of 6.3), the 65,536 documents of the throughput workload took 1,480 us in this
+// kernel; they take 1,060.
 #pragma once
 #include "encode_segmented.h"
 
 namespace bpe {
 
-constexpr int kLaneItemBytes = 1024;            // capacity of a work item
-constexpr int kLaneRows = kLaneItemBytes / 64;
 constexpr int kLaneSegmentMax = 32;             // positions a lane's liveness mask covers
-constexpr uint32_t kLaneChunk = 4;              // work items a workgroup claims at a time (1: 3.4 ms on the
+constexpr int kLaneBatches = 3;                 // batches of 64 segments whose look-ups are in flight together
+constexpr uint32_t kLaneChunk = 4;              // work items a wave claims at a time (1: 3.4 ms on the
                                                 // 270,000 pieces of the throughput workload, 2: 2.2, 4: 2.1, 8: 2.1);
-                                                // twice as many when the list holds 32 or more items per workgroup
+                                                // twice as many when the list holds 32 or more items per wave
 
 // Pair values as the lanes keep them: the table's value (rank in bits 12..31, the two operand-capability flags
-// in bits 10 and 11) with the bits below cleared, so that a position can ride in them through the minimum.
+// in bits 10 and 11) with the pair's position in its segment in the bits below, so that the lowest value says where it is.
 constexpr uint32_t kLaneNoPair = 0xFFFFFFFFu;
+constexpr uint32_t kLaneNoTag = 0xF8000000u;    // no slot's tag: fingerprints have 27 bits, an empty slot is all ones
+constexpr uint32_t kLaneNowhere = 0xFFFFFFFFu;  // no position
 constexpr uint32_t kLaneInvalid = 0xFFFFE000u;  // values from here on are no pair (ranks stay below 0xFFFFE)
 
-__device__ inline uint32_t lane_value(uint32_t v) { return v & ~((1u << 10) - 1u); }
+__device__ inline uint32_t lane_value(uint32_t v, uint32_t position) { return (v & ~((1u << 10) - 1u)) | position; }
 __device__ inline uint32_t lane_merged_word(uint32_t lv) {
   static_assert(kFlagLeft == 1u << 10 && kFlagRight == 1u << 11 && (kFlagLeft << 20) == kTokCanLeft &&
                 (kFlagRight << 20) == kTokCanRight, "flag positions");
   return (256u + (lv >> kRankShift)) | ((lv & (kFlagLeft | kFlagRight)) << 20);
 }
 
-// Per-wave LDS, in 32-bit words.  (9.3 KB: sixteen workgroups per CU, four waves per SIMD.)
-struct LaneLds {
-  static constexpr int kFlags = 0;                                      // 2 bits per byte value: can be a left / right operand
-  static constexpr int kT = kFlags + 16;                                // token word of every position
-  static constexpr int kV = kT + kLaneItemBytes;                        // pair value of every position; a scan may
-  static constexpr int kEnds = kV + kLaneItemBytes;                     //   read up to 31 words on (masked out)
-  static constexpr int kSeg = kEnds + kLaneItemBytes / 32 + 4;          // bit p of kEnds: position p ends its segment
-  static constexpr int kHist = kSeg + kLaneItemBytes / 4;               // kSeg: uint16 first position | (length - 1) << 10
-  static constexpr int kWords = kHist + 32;                             // kHist: segments of each length, then list bases
+// What becomes of a segment: its token's number, or one of these.
+constexpr uint32_t kRecJob = 1u << 30;          // | its first position in the arena, where its tokens are
+constexpr uint32_t kRecNone = 1u << 31;         // no token
+
+// LDS of a workgroup, in 32-bit words: read-only, shared by its waves.
+struct LaneShared {
+  static constexpr int kCuts = 0;                                       // bit a + 256 b: bytes a, b have a cut between them
+  static constexpr int kByteWord = kCuts + 2048;                        // token word of every byte
+  static constexpr int kMasks = kByteWord + 256;                        // [16][4] first l bytes of a key
+  static constexpr int kWords = kMasks + 64;
 };
+// Shape of a workgroup, and the LDS of one of its waves.  WAVES: they take items of their own; BYTES: an item's capacity;
+// LIST: segments listed at a time; JOBS: those of them that need merges; ARENA: the bytes of those, in fours.  What bounds
+// the number of waves is LDS.  Twice as long an item takes less than half as many trips of the merge loop for each of its
+// bytes (5.4 instead of 12.2 per KiB: the longest chain of merges is 10 long in either), which is why a large batch does
+// with 12 waves a CU; a small one wants each piece of text to have a wave, and 16 of them.
+template <int BYTES, int WAVES, int LIST, int JOBS, int ARENA, int AT_LEAST>
+struct LaneShape {
+  static constexpr int kBytes = BYTES, kWaves = WAVES, kListed = LIST, kMostJobs = JOBS, kArena = ARENA;
+  static constexpr int kText = 0;                                       // the item's bytes; a key's words reach beyond them
+  static constexpr int kRec = kText;                                    // once they are in the arena: what becomes of a segment
+  static constexpr int kStrings = kText + BYTES / 4 + 8;                // (groups) bit p: a string starts at p
+  static constexpr int kList = kStrings + BYTES / 32;                   // uint16 first position of a segment
+  static constexpr int kJobs = kList + LIST / 2 + 2;                    // uint16 arena position | (length - 1) << 11
+  static constexpr int kHist = kJobs + JOBS / 2;                        // jobs of each length, then list bases
+  static constexpr int kSorted = kHist + 32;                            // the jobs, sorted
+  static constexpr int kT = (kSorted + JOBS + 3) / 4 * 4;               // token word of every arena position
+  static constexpr int kV = kT + ARENA;                                 // pair value
+  static constexpr int kIdle = kV + ARENA;                              // what a lane without a segment reads and writes
+  static constexpr int kEnd = kIdle + 4;
+  // before the arena is used:
+  static constexpr int kStarts = kV;                                    // bit p: a segment starts at p, or the item ends
+  static constexpr int kFound = kV;                                     // what becomes of a segment
+  static constexpr int kFirstJobs = kT;                                 // the jobs in the text's order
+  static constexpr int kWords = ((kEnd > AT_LEAST ? kEnd : AT_LEAST) + 3) / 4 * 4;
+  static constexpr size_t kLdsBytes = lds_blocks(sizeof(uint32_t) * (LaneShared::kWords + WAVES * kWords));
+  static_assert(kText % 4 == 0 && ARENA % 4 == 0, "wide loads and stores");
+  static_assert(ARENA <= 2048 && BYTES <= 2048 && BYTES % 1024 == 0 && LIST % 64 == 0 && LIST <= 512 && JOBS % 64 == 0,
+                "fields of the packed words; a lane per word of the bitmap");
+  static_assert(JOBS <= ARENA && LIST <= ARENA && BYTES / 32 + 4 <= ARENA && LIST <= BYTES / 4 + 8, "what shares a place fits it");
+  static_assert(kLdsBytes <= 160 * 1024, "one workgroup a CU");
+};
+using LargeItems = LaneShape<kGroupBytes, 12, 448, 256, 992, 0>;
+using SmallItems = LaneShape<kMemberBytes, 16, 256, 128, 704, 0>;
+constexpr int kOtherWords = 3 * 1024 + 24;      // the arrays of the one-wave encoder that takes a string over
+using InlineItems = LaneShape<kMemberBytes, 12, 256, 128, 704, kOtherWords>;
 
 __device__ inline uint32_t mbcnt64(uint64_t mask) {                     // set bits of mask below my lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
+// Orders a wave's own LDS traffic (which the hardware executes in order) for the compiler.
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// A look-up in the merge table on its way: two start at the end of every trip of the merge loop.
+struct LaneProbe {
+  uint4 q;                                             // the home bucket: two slots of {value, tag}
+  uint32_t bucket, tag;                                // kLaneNoTag: no look-up
+};
+__device__ inline void lane_probe_start(const DeviceTable& t, uint32_t xw, uint32_t yw, LaneProbe& f) {
+  static_assert(kTokCanLeft == 1u << 30 && kTokCanRight == 1u << 31, "one bit beside the other");
+  f.tag = kLaneNoTag;
+  if ((int32_t)((xw << 1) & yw) < 0) {                 // the left token can be a left operand, the right one a right one
+    const Placement pl = place_pair(xw & kTokIdMask, yw & kTokIdMask, t.log2_buckets);
+    f.bucket = pl.bucket;
+    f.tag = slot_tag(pl.fingerprint, 0);
+    f.q = t.buckets[pl.bucket];
+  }
+}
+// Both values, kNoRank where there is no such row.  The wait is spelled out: where the first use of a load lies in a
+// branch, the compiler waits at the register's next write, and that is where the next trip starts its loads -- each then
+// waited for the one before it.
+__device__ inline void lane_probe_finish(const DeviceTable& t, const LaneProbe& a, const LaneProbe& b, uint32_t& ra, uint32_t& rb) {
+  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
+  ra = match_bucket(a.q, a.tag);
+  rb = match_bucket(b.q, b.tag);
+  // a pair that is not in its full home bucket may have been displaced, as far as the bucket's spare bits say
+  uint32_t left_a = ra == kNoRank && a.q.w != kNoRank && a.tag != kLaneNoTag ? bucket_reach(a.q.x, a.q.z) : 0u;
+  uint32_t left_b = rb == kNoRank && b.q.w != kNoRank && b.tag != kLaneNoTag ? bucket_reach(b.q.x, b.q.z) : 0u;
+  uint32_t d = 1;
+  while (__ballot((left_a | left_b) != 0)) {           // one read a lane and trip
+    if (left_a | left_b) {
+      const bool first = left_a != 0;
+      const uint32_t tag = (first ? a.tag : b.tag) | (d << kTagDisplacementShift);
+      const uint32_t found = match_bucket(t.buckets[(first ? a.bucket : b.bucket) ^ d], tag);
+      const bool over = found != kNoRank || d >= (first ? left_a : left_b);
+      if (first) ra = found; else rb = found;
+      if (over && first) left_a = 0;
+      if (over && !first) left_b = 0;
+      d = over ? 1u : d + 1u;
+    }
+  }
+}
+
+// Bytes at ... at + 15 of the `room` bytes from src on, whatever their alignment; 0 <= at < room, and what lies beyond
+// them reads as anything.  `before`: bytes that may be read before src as well.
+__device__ inline uint4 load_16_bytes(const uint8_t* src, int at, int64_t before, int64_t room) {
+  uint4 v = make_uint4(0, 0, 0, 0);
+  const int last = (int)min(room, (int64_t)1 << 30) - 16;                // (uniform)
+  if (before + last < 0) {                             // uniform: fewer than 16 bytes in all
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll 1
+    for (int j = 0; j < (int)room; ++j) {
+      const uint32_t b = src[j];
+      const int to = j - at;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (to >> 2 == i) w[i] |= b << (8 * (to & 3));
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  const int from = min(at, last);
+  __builtin_memcpy(&v, src + (int64_t)from, 16);
+  const uint32_t skip = (uint32_t)(at - from);         // 0 but at the end
+  if (__ballot(skip != 0)) {
+    if (skip & 8u) { v.x = v.z; v.y = v.w; }
+    if (skip & 4u) { v.x = v.y; v.y = v.z; v.z = v.w; }
+    const uint32_t bits = 8u * (skip & 3u);
+    v.x = __builtin_amdgcn_alignbit(v.y, v.x, bits);
+    v.y = __builtin_amdgcn_alignbit(v.z, v.y, bits);
+    v.z = __builtin_amdgcn_alignbit(v.w, v.z, bits);
+    v.w >>= bits;
+  }
+  return v;
+}
 
 // Encodes item s -- n bytes from `begin` on (both uniform) -- if all its segments fit a lane; returns 1 (and
-// has written nothing to global memory) if one does not, else 0.  lds: this wave's LaneLds words (kFlags filled in by
-// the kernel).  GROUPS: the item is the `members` strings from s on, at most 64, which lie one after the other in those
-// bytes: a string's last byte ends a segment like any cut does, and each string gets its own count.  The result has a
+// has written nothing to global memory) if one does not, else 0.  lds: this wave's words of the shape L; shared: the
+// workgroup's LaneShared.  GROUPS: the item is the `members` strings from s on, at most 64, which lie one after the other
+// in those bytes: a string's first byte starts a segment, and each string gets its own count.  The result has a
 // bit for every string with a segment that fits no lane; the others are encoded all the same, and if there is such a
 // string, each one's ids lie at its own place in tmp_ids instead of one after the other.  (100,000 rows of up to 60 bytes,
 // one in twenty with such a segment: 183 us.  With the whole group given away, five rows in six went to the
 // wave-per-item encoder: 1,029 us; with each row an item of its own 728.)
-template <bool SPECIAL, bool GROUPS>
+template <class L, bool SPECIAL, bool GROUPS>
 __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int s, int64_t begin, int n, int members,
-                                                  uint32_t* lds) {
+                                                      uint32_t* lds, const uint32_t* shared) {
   const int lane = (int)threadIdx.x & 63;
   const DeviceTable& tab = p.table;
-  uint32_t* const T = lds + LaneLds::kT;
-  uint32_t* const V = lds + LaneLds::kV;
-  uint32_t* const ends = lds + LaneLds::kEnds;
-  uint16_t* const seg = (uint16_t*)(lds + LaneLds::kSeg);
-  uint32_t* const hist = lds + LaneLds::kHist;
+  uint32_t* const text = lds + L::kText;
+  uint32_t* const starts = lds + L::kStarts;
+  uint32_t* const strings = lds + L::kStrings;
+  uint16_t* const list = (uint16_t*)(lds + L::kList);
+  uint16_t* const jobs = (uint16_t*)(lds + L::kJobs);
+  uint32_t* const hist = lds + L::kHist;
+  uint32_t* const T = lds + L::kT;
+  uint32_t* const V = lds + L::kV;
+  uint32_t* const rec = lds + L::kRec;
+  uint32_t* const sorted = lds + L::kSorted;
 
-  if (n <= 0 || n > kLaneItemBytes) {                  // uniform; too long only if max_len was wrong
+  if (n <= 0 || n > L::kBytes) {                  // uniform; too long only if max_len was wrong
     if constexpr (GROUPS) {
       for (int i = lane; i < members; i += 64) p.counts[s + i] = 0;
     } else {
@@ -88,386 +214,560 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     }
     return 0;
   }
-  const int rows = (n + 63) >> 6;                      // uniform
-  auto mark_string_ends = [&](uint32_t* bits) {        // (groups only) bit `at`: the item's byte `at` is a string's last
-    if (lane < 2 * kLaneRows) bits[lane] = 0;
-    __syncthreads();
-    if (lane < members - 1) {                          // (the last one's last byte is the item's)
-      const int64_t at = p.offsets[s + lane + 1] - begin - 1;            // (an empty string's is its predecessor's)
-      if (at >= 0 && at < n) atomicOr(&bits[at >> 5], 1u << (at & 31));
-    }
-    __syncthreads();
-  };
   __builtin_amdgcn_s_setprio(3);                       // (the load phase too is a chain of round trips, and the
                                                        // sooner its loads go out the better)
 
-  // ---- load: byte-level pre-tokenisation (section 4.1), the initial pair values, segment ends and starts ----
-  uint32_t n_segments = 0;                             // segments with a pair to look at (uniform)
-  {
-    const uint8_t* src = p.bytes + begin + lane;
-    uint32_t b[kLaneRows + 1], mk[kLaneRows + 1];
+  // ---- cuts: where the segments start ----
+  constexpr int kPasses = L::kBytes / 1024;       // a wave holds 1 KiB at a time
+  uint4 q[kPasses], marks[kPasses];
 #pragma unroll
-    for (int j = 0; j < kLaneRows; ++j) {
-      b[j] = 0;
-      mk[j] = 0;
-      if (j < rows && 64 * j + lane < n) {
-        b[j] = src[64 * j];
-        if constexpr (SPECIAL) mk[j] = p.cover[begin + lane + 64 * j];
-      }
+  for (int pass = 0; pass < kPasses; ++pass) {
+    const int at = 1024 * pass + 16 * lane;
+    q[pass] = marks[pass] = make_uint4(0, 0, 0, 0);
+    if (at < n) {
+      q[pass] = load_16_bytes(p.bytes + begin, at, begin, p.total_bytes - begin);
+      if constexpr (SPECIAL) marks[pass] = load_16_bytes(p.cover + begin, at, begin, p.total_bytes - begin);
     }
-    b[kLaneRows] = mk[kLaneRows] = 0;
-    // the last bytes of the item's strings, a bit each, in the words that the tokens take afterwards
-    if constexpr (GROUPS) mark_string_ends(T);
-    uint32_t raw[kLaneRows];
-    uint32_t word[kLaneRows];
-#pragma unroll
-    for (int j = 0; j < kLaneRows; ++j) {
-      raw[j] = kCut;
-      word[j] = kTokNone;
-      if (j < rows) {                                  // uniform
-        // the byte after mine: the next lane's of this row, or for the last lane the first of the next row
-        uint32_t nb = wave_shift_down(b[j], 0u);
-        const uint32_t wrap = (uint32_t)__builtin_amdgcn_readlane((int)b[j + 1], 0);
-        nb = lane == 63 ? wrap : nb;
-        const bool has_pair = 64 * j + lane + 1 < n;
-        if (has_pair) raw[j] = tab.byte_pair[(b[j] << 8) | nb];          // (the item's last byte ends a segment)
-        // token word of a byte: its value and the two capability bits (bits 30 and 31) from the packed table
-        word[j] = b[j] | (((lds[LaneLds::kFlags + (b[j] >> 4)] >> (2u * (b[j] & 15u))) & 3u) << 30);
-        if constexpr (SPECIAL) {
-          // an occurrence of a special token is one token on its first byte and nothing on the others; no
-          // pair involves it, so there is a cut on both sides of every marked byte
-          uint32_t nm = wave_shift_down(mk[j], 0u);
-          const uint32_t wrap_m = (uint32_t)__builtin_amdgcn_readlane((int)mk[j + 1], 0);
-          nm = lane == 63 ? wrap_m : nm;
-          if (mk[j]) word[j] = (mk[j] & kCoverFirst) ? p.special_base + (mk[j] & kCoverIndex) : kTokNone;
-          if (mk[j] | nm) raw[j] = kCut;
-        }
-        if constexpr (GROUPS)
-          if ((T[2 * j + (lane >> 5)] >> (lane & 31)) & 1u) raw[j] = kCut;
-      }
-    }
-    if constexpr (GROUPS) __syncthreads();
-    uint64_t carry = 1;                                // the item's first byte starts a segment
-#pragma unroll
-    for (int j = 0; j < kLaneRows; ++j) {
-      if (j < rows) {                                  // uniform
-        const int pos = 64 * j + lane;
-        const uint64_t end_row = __ballot(raw[j] == kCut);               // positions >= n - 1 included
-        T[pos] = pos < n ? word[j] : kTokNone;
-        V[pos] = lane_value(raw[j]);
-        if (lane == 0) *(uint64_t*)(ends + 2 * j) = end_row;
-        // segments that start in this row and hold a pair: after an end, and not an end themselves
-        const uint64_t start_row = ((end_row << 1) | carry) & ~end_row;
-        carry = end_row >> 63;
-        if ((start_row >> lane) & 1ull) seg[n_segments + mbcnt64(start_row)] = (uint16_t)pos;
-        n_segments += (uint32_t)__builtin_popcountll(start_row);
-      }
-    }
-    if (lane < 4) ends[2 * rows + lane] = 0xFFFFFFFFu;                   // a window never runs past the item
-    if (lane < 32) hist[lane] = 0;
   }
-  __syncthreads();                                     // one wave: orders the LDS traffic of the phases
-
-  __builtin_amdgcn_s_setprio(0);
-  // ---- list, sorted: longest segments first (counting sort over the 31 possible lengths) ----
-  uint64_t left = 0;                                   // strings that are not encoded here (uniform)
+  int from = n, to = n;                                // (groups) where string `lane` begins and ends in the item
+  if constexpr (GROUPS) {
+    if (lane < members) from = (int)min(max(p.member_begin[s + lane] - begin, (int64_t)0), (int64_t)n);
+    to = (int)lane_read((uint32_t)from, min(lane + 1, 63));
+    if (lane + 1 >= members) to = n;
+    if (lane < L::kBytes / 32) strings[lane] = 0;
+    wave_sync();
+    if (from < n) atomicOr(&strings[from >> 5], 1u << (from & 31));
+    wave_sync();
+  }
+  bool any_marked = false;                             // (special tokens) uniform
   {
-    constexpr int kRounds = kLaneItemBytes / 2 / 64;   // at most 512 segments of two bytes
-    uint32_t entry[kRounds], place[kRounds];           // (entry: 0 for none)
-    const uint32_t n_listed = n_segments;
-    bool too_long = false;
+    uint32_t cut_before = 1, marked_before = 0;        // of the pass's first byte (uniform); the item starts a segment
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-      entry[r] = 0;
-      place[r] = 0;
-      if ((uint32_t)(64 * r) < n_segments) {           // uniform
-        const uint32_t i = 64u * r + (uint32_t)lane;
-        if (i < n_segments) {
-          const uint32_t first = seg[i];
-          // the segment ends at the first set bit of the ends bitmap from `first` on
-          const uint32_t window = __builtin_amdgcn_alignbit(ends[(first >> 5) + 1], ends[first >> 5], first & 31u);
-          too_long |= window == 0;
-          const uint32_t len = window ? (uint32_t)__builtin_ctz(window) + 1u : 2u;      // 2..32
-          entry[r] = first | ((len - 1u) << 10);
-          place[r] = atomicAdd(&hist[32u - len], 1u);  // my place among the segments of my length
+    for (int pass = 0; pass < kPasses; ++pass) {
+      if (1024 * pass < n) {                           // uniform
+        const int at = 1024 * pass + 16 * lane;
+        const uint4 v = q[pass];
+        *(uint4*)(text + 256 * pass + 4 * lane) = v;
+        uint32_t after = wave_shift_down(v.x, 0u);     // the bytes after mine
+        if (pass + 1 < kPasses) {
+          const uint32_t wrap = (uint32_t)__builtin_amdgcn_readlane((int)q[pass + 1 < kPasses ? pass + 1 : pass].x, 0);
+          after = lane == 63 ? wrap : after;
         }
+        const uint32_t w[5] = {v.x, v.y, v.z, v.w, after};
+        uint32_t ends = 0;                             // bit j: a cut after my byte j
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          // bytes j and j + 1 in the low 16 bits, what lies above them is not looked at
+          const uint32_t pair = (j & 3) == 3 ? __builtin_amdgcn_alignbit(w[(j >> 2) + 1], w[j >> 2], 24u)
+                                             : w[j >> 2] >> (8 * (j & 3));
+          const uint32_t bits = shared[LaneShared::kCuts + ((pair >> 5) & 2047u)];
+          ends |= __builtin_amdgcn_ubfe(bits, pair & 31u, 1u) << j;
+        }
+        const uint32_t ends_before = wave_shift_up(ends, 0u);            // (all lanes: not inside a branch)
+        uint32_t begins = (ends << 1) | (lane == 0 ? cut_before : ends_before >> 15);
+        if constexpr (SPECIAL) {
+          // an occurrence of a special token is one token on its first byte and nothing on the others: every marked
+          // byte is a segment of its own
+          const uint4 m = marks[pass];
+          uint32_t marked = 0;
+          if (__ballot((m.x | m.y | m.z | m.w) != 0)) {
+            any_marked = true;
+            const uint32_t mw[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) marked |= (((mw[j >> 2] >> (8 * (j & 3))) & 0xFFu) ? 1u : 0u) << j;
+            if (at < n && n - at < 16) marked &= (1u << (n - at)) - 1u;      // (the next string's, or none)
+          }
+          const uint32_t mine_before = wave_shift_up(marked, 0u);
+          begins |= marked | (marked << 1) | (lane == 0 ? marked_before : mine_before >> 15);
+          marked_before = (uint32_t)__builtin_amdgcn_readlane((int)marked, 63) >> 15;
+        }
+        cut_before = ((uint32_t)__builtin_amdgcn_readlane((int)ends, 63) >> 15) & 1u;
+        if constexpr (GROUPS) begins |= ((const uint16_t*)strings)[64 * pass + lane];
+        const int here = n - at;                       // bytes of the item from my first one on
+        begins &= here >= 16 ? 0xFFFFu : here > 0 ? (1u << here) - 1u : 0u;
+        if (here >= 0 && here < 16) begins |= 1u << here;                  // the item's end
+        ((uint16_t*)starts)[64 * pass + lane] = (uint16_t)begins;
+        // (the words after the pass's; the end itself if it lies there)
+        if (lane < 4) ((uint16_t*)starts)[64 * (pass + 1) + lane] = (uint16_t)(lane == 0 && n == 1024 * (pass + 1));
       }
     }
-    if (__ballot(too_long)) {                          // uniform: a segment no lane can take (nothing has left LDS)
+  }
+  wave_sync();
+  __builtin_amdgcn_s_setprio(0);
+
+  // ---- segments that no lane can take: more than 32 positions from a start to the next (nothing has left LDS) ----
+  const int n_words = (n + 31) >> 5;                   // words of the bitmap, a lane each (uniform)
+  uint64_t left = 0;                                   // strings that are not encoded here (uniform)
+  uint32_t my_starts = lane < n_words ? starts[lane] : 0u;
+  {
+    const uint32_t next = lane < n_words ? starts[lane + 1] : 0u;
+    const int top = 32 * lane + 31 - (int)__builtin_clz(my_starts | 1u);   // the word's last start
+    const bool empty = lane < n_words && my_starts == 0;
+    const bool gap = my_starts != 0 && next != 0 && top < n &&
+                     __builtin_clz(my_starts) + __builtin_ctz(next | 0x80000000u) + 1 > kLaneSegmentMax;
+    uint64_t too_long = __ballot(empty || gap);
+    if (too_long) {                                    // uniform
       if constexpr (!GROUPS) return 1;
-      // The strings that hold one: lane m asks for string m.  Their tokens are taken away and their segments dropped;
-      // the others' are listed anew.
-      int from = n, to = n;                            // where string `lane` begins and ends in the item
-      if (lane < members) {
-        from = (int)min(max(p.offsets[s + lane] - begin, (int64_t)0), (int64_t)n);
-        to = (int)min(max(p.offsets[s + lane + 1] - begin, (int64_t)0), (int64_t)n);
+      // The strings that hold one: lane m asks for string m.  Of their segments only the first start is kept; so long a
+      // one gets no token below.
+      const int inside = empty ? 32 * lane : top;
+      for (; too_long; too_long &= too_long - 1ull) {  // uniform
+        const int at = __builtin_amdgcn_readlane(inside, (int)__builtin_ctzll(too_long));
+        left |= __ballot(from <= at && at < to);
       }
-      n_segments = 0;
-      if (lane < 32) hist[lane] = 0;
+      for (uint64_t m = left; m; m &= m - 1ull) {      // uniform
+        const int lo = max(__builtin_amdgcn_readlane(from, (int)__builtin_ctzll(m)) + 1 - 32 * lane, 0);
+        const int hi = min(__builtin_amdgcn_readlane(to, (int)__builtin_ctzll(m)) - 32 * lane, 32);
+        if (lo < hi) my_starts &= ~((hi >= 32 ? 0xFFFFFFFFu : (1u << hi) - 1u) & (0xFFFFFFFFu << lo));
+      }
+    }
+  }
+  if (32 * lane + 31 >= n && lane < n_words && (n & 31)) my_starts &= (1u << (n & 31)) - 1u;   // the end is no start
+  const uint32_t my_count = (uint32_t)__builtin_popcount(my_starts);
+  const uint32_t starts_upto = wave_scan<OpAdd>(my_count, 0u);
+
+  int32_t* const dst = p.tmp_ids + begin;
+  // Single bytes all (blank lines, padding that no row joins): their ids are the bytes.  (64 strings of 64 KiB of spaces: 16 us,
+  // as segments 48.)
+  if ((int)__builtin_amdgcn_readlane((int)starts_upto, 63) == n && !any_marked) {        // uniform
+    for (int o = lane; o < n; o += 64) dst[o] = (int32_t)((text[o >> 2] >> (8 * (o & 3))) & 0xFFu);
+    if constexpr (GROUPS) {
+      if (lane < members) {
+        p.counts[s + lane] = to - from;
+        if (p.group_ids) p.group_ids[s + lane] = lane == 0 ? n : 0;
+      }
+    } else {
+      if (lane == 63) p.counts[s] = n;
+    }
+    wave_sync();
+    return 0;
+  }
+  uint32_t total = 0;                                  // tokens of the segments done (uniform)
+  uint32_t tokens_before = 0;                          // (groups) of string `lane`
+  uint32_t lack = 0;                                   // (apart) what the place of a token lacks to its string's own
+  bool text_gone = false;                              // its place in LDS has been used (uniform)
+  uint32_t listed_before = 0;                          // segments of earlier lists (uniform)
+  uint32_t my_segment = 0xFFFFFFFFu;                   // (groups) the one that string `lane` starts with
+  if constexpr (GROUPS) {
+    const int word = min(from >> 5, 63);
+    const uint32_t before = lane_read(starts_upto - my_count, word);
+    const uint32_t bits = lane_read(my_starts, word);
+    if (from < n) my_segment = before + (uint32_t)__builtin_popcount(bits & ((1u << (from & 31)) - 1u));
+  }
+  for (int word0 = 0; word0 < n_words;) {              // (a list of the whole item, unless it has very many segments)
+    // ---- list of the segments that start in words word0 ... word1 - 1 ----
+    const uint64_t in_list = __ballot(lane >= word0 && lane < n_words && starts_upto - listed_before <= (uint32_t)L::kListed);
+    const int word1 = word0 + (int)__builtin_popcountll(in_list);          // (at least one more: a word has 32 starts)
+    const uint32_t listed_upto = (uint32_t)__builtin_amdgcn_readlane((int)starts_upto, word1 - 1);
+    const int n_listed = (int)(listed_upto - listed_before);
+    {
+      const uint64_t later = __ballot(lane >= word1 && my_starts != 0);
+      const int first = 32 * lane + (int)__builtin_ctz(my_starts | 0x80000000u);
+      const int end = later ? __builtin_amdgcn_readlane(first, (int)__builtin_ctzll(later)) : n;
+      uint32_t at = starts_upto - my_count - listed_before;
+      uint32_t m = lane >= word0 && lane < word1 ? my_starts : 0u;
+      while (__ballot(m != 0)) {
+        if (m) list[at++] = (uint16_t)(32 * lane + (int)__builtin_ctz(m));
+        m &= m - 1u;
+      }
+      if (lane == 0) list[n_listed] = (uint16_t)end;
+    }
+    wave_sync();
+    word0 = word1;
+    const uint32_t list_first = listed_before;
+    listed_before = listed_upto;
+
+    for (int i0 = 0; i0 < n_listed;) {                 // uniform
+      if (text_gone) {                                 // uniform (a second round: very many segments or bytes to merge)
 #pragma unroll
-      for (int r = 0; r < kRounds; ++r) {
-        if ((uint32_t)(64 * r) < n_listed) {           // uniform
-          const uint32_t first = entry[r] & 1023u;
-          const uint32_t window = __builtin_amdgcn_alignbit(ends[(first >> 5) + 1], ends[first >> 5], first & 31u);
-          uint64_t owners = __ballot(64u * r + (uint32_t)lane < n_listed && window == 0);
-          for (; owners; owners &= owners - 1ull) {    // uniform
-            const int at = (int)__builtin_amdgcn_readlane((int)first, (int)__builtin_ctzll(owners));
-            left |= __ballot(from <= at && at < to);
+        for (int pass = 0; pass < kPasses; ++pass) {
+          const int at = 1024 * pass + 16 * lane;
+          if (at < n)
+            *(uint4*)(text + 256 * pass + 4 * lane) = load_16_bytes(p.bytes + begin, at, begin, p.total_bytes - begin);
+        }
+        wave_sync();
+      }
+      text_gone = true;
+      // ---- words: which segments are one token ----
+      int i1 = i0;                                     // segments from i0 to here are done in this round
+      uint32_t n_jobs = 0, used = 0;                   // those that need merges, and their places in the arena (uniform)
+      const int round_end = min(n_listed, i0 + L::kListed);
+      bool full = false;                               // uniform
+      while (i1 < round_end && !full) {                // uniform
+        uint32_t k[kLaneBatches][4], first[kLaneBatches], len[kLaneBatches], mark[kLaneBatches], tag[kLaneBatches];
+        uint4 bucket[kLaneBatches], key[kLaneBatches];
+        const int base = i1;
+#pragma unroll
+        for (int r = 0; r < kLaneBatches; ++r) {
+          const int i = min(base + 64 * r + lane, n_listed - 1);
+          first[r] = list[i];
+          len[r] = (uint32_t)list[i + 1] - first[r];
+        }
+#pragma unroll
+        for (int r = 0; r < kLaneBatches; ++r) {
+          if (base + 64 * r + lane >= n_listed) len[r] = 0;
+          const uint32_t* const word = text + (first[r] >> 2);
+          const uint32_t shift = 8u * (first[r] & 3u);
+          const uint4 mask = *(const uint4*)(shared + LaneShared::kMasks + 4 * min(len[r], (uint32_t)kWordBytes));
+          k[r][0] = __builtin_amdgcn_alignbit(word[1], word[0], shift) & mask.x;
+          k[r][1] = __builtin_amdgcn_alignbit(word[2], word[1], shift) & mask.y;
+          k[r][2] = __builtin_amdgcn_alignbit(word[3], word[2], shift) & mask.z;
+          k[r][3] = (__builtin_amdgcn_alignbit(word[4], word[3], shift) & mask.w) | (len[r] << 24);
+        }
+#pragma unroll
+        for (int r = 0; r < kLaneBatches; ++r) {
+          tag[r] = mark[r] = 0;
+          bucket[r] = make_uint4(kWordNone, kWordNone, kWordNone, kWordNone);
+          if (__ballot(len[r] > 1u)) {                 // uniform: else single bytes all, or nothing
+            const uint32_t hash = word_hash(k[r][0], k[r][1], k[r][2], k[r][3]);
+            tag[r] = word_tag(hash);
+            if (len[r] - 2u <= (uint32_t)kWordBytes - 2u)
+              bucket[r] = tab.word_buckets[word_bucket(hash, tab.log2_word_buckets)];
+          }
+          if constexpr (SPECIAL)
+            if (len[r] == 1u) mark[r] = p.cover[begin + first[r]];
+        }
+#pragma unroll
+        for (int r = 0; r < kLaneBatches; ++r) {
+          // (at most one slot of a bucket has the tag; an empty one leaves all ones in the id's bits at best)
+          tag[r] = min(min(bucket[r].x ^ tag[r], bucket[r].y ^ tag[r]), min(bucket[r].z ^ tag[r], bucket[r].w ^ tag[r]));
+          key[r] = make_uint4(0, 0, 0, 0);
+          if (tag[r] < (1u << kWordIdBits) - 1u) key[r] = tab.word_keys[tag[r]];
+        }
+#pragma unroll
+        for (int r = 0; r < kLaneBatches; ++r) {
+          if (base + 64 * r < round_end && !full) {    // uniform
+            const bool same = len[r] - 2u <= (uint32_t)kWordBytes - 2u &&          // (then no key of zeros is its own)
+                              ((key[r].x ^ k[r][0]) | (key[r].y ^ k[r][1]) | (key[r].z ^ k[r][2]) | (key[r].w ^ k[r][3])) == 0;
+            uint32_t what = same ? tag[r] : kRecNone;
+            const bool job = !same && len[r] - 2u <= (uint32_t)kLaneSegmentMax - 2u;
+            if (len[r] == 1u) {
+              what = k[r][0];
+              if constexpr (SPECIAL)
+                if (mark[r]) what = (mark[r] & kCoverFirst) ? p.special_base + (mark[r] & kCoverIndex) : kRecNone;
+            }
+            int taken = 64;
+            const uint64_t job_lanes = __ballot(job);
+            if (job_lanes) {                           // uniform
+              const uint32_t upto = used + wave_scan<OpAdd>(job ? (len[r] + 3u) & ~3u : 0u, 0u);
+              const uint32_t place = n_jobs + mbcnt64(job_lanes);
+              const uint64_t misfit = __ballot(job && (upto > (uint32_t)L::kArena || place >= (uint32_t)L::kMostJobs));
+              if (misfit) {                            // uniform: the round ends before this segment
+                taken = (int)__builtin_ctzll(misfit);
+                full = true;
+              }
+              if (job && lane < taken)
+                lds[L::kFirstJobs + place] = first[r] | ((len[r] - 1u) << 12) | ((uint32_t)(base - i0 + 64 * r + lane) << 17);
+              n_jobs += (uint32_t)__builtin_popcountll(taken < 64 ? job_lanes & ((1ull << taken) - 1ull) : job_lanes);
+              if (taken > 0) used = (uint32_t)__builtin_amdgcn_readlane((int)upto, taken - 1);
+            }
+            lds[L::kFound + base - i0 + 64 * r + lane] = what;     // (of what is not taken, looked up again)
+            i1 = min(base + 64 * r + taken, round_end);
           }
         }
       }
-      for (uint64_t m = left; m; m &= m - 1ull) {      // uniform
-        const int a = __builtin_amdgcn_readlane(from, (int)__builtin_ctzll(m));
-        const int b = __builtin_amdgcn_readlane(to, (int)__builtin_ctzll(m));
-        for (int i = a + lane; i < b; i += 64) T[i] = kTokNone;
+      if (lane < 32) hist[lane] = 0;
+      wave_sync();
+      uint32_t found[L::kListed / 64];                  // what becomes of segment i0 + 64 r + lane
+#pragma unroll
+      for (int r = 0; r < L::kListed / 64; ++r) found[r] = lds[L::kFound + 64 * r + lane];
+      wave_sync();
+
+      if (n_jobs) {                                    // uniform
+        // ---- list: the segments that need merges, longest first (counting sort over the 31 possible lengths) ----
+        constexpr int kRounds = L::kMostJobs / 64;
+        uint32_t entry[kRounds], place[kRounds];       // (entry: first position | (length - 1) << 12 | segment << 17)
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-          const int first = (int)(entry[r] & 1023u);
-          if (first >= a && first < b) entry[r] = 0;
+          entry[r] = place[r] = 0;
+          if (64u * r + (uint32_t)lane < n_jobs) {
+            entry[r] = lds[L::kFirstJobs + 64 * r + lane];
+            place[r] = atomicAdd(&hist[31u - ((entry[r] >> 12) & 31u)], 1u);   // my place among those of my length
+          }
         }
-      }
-      __syncthreads();
+        wave_sync();
+        {
+          const uint32_t mine = lane < 32 ? hist[lane] : 0u;
+          const uint32_t inc = wave_scan<OpAdd>(mine, 0u);
+          wave_sync();
+          if (lane < 32) hist[lane] = inc - mine;      // where the segments of length 32 - lane start
+        }
+        wave_sync();
 #pragma unroll
-      for (int r = 0; r < kRounds; ++r) {
-        if ((uint32_t)(64 * r) < n_listed) {           // uniform
-          n_segments += (uint32_t)__builtin_popcountll(__ballot(entry[r] != 0));
-          if (entry[r]) place[r] = atomicAdd(&hist[31u - (entry[r] >> 10)], 1u);
-        }
-      }
-    }
-    __syncthreads();
-    {
-      const uint32_t mine = lane < 32 ? hist[lane] : 0u;
-      const uint32_t inc = wave_scan<OpAdd>(mine, 0u);
-      __syncthreads();
-      if (lane < 32) hist[lane] = inc - mine;          // where the segments of length 32 - lane start
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-      if ((uint32_t)(64 * r) < n_listed) {             // uniform
-        if (GROUPS ? entry[r] != 0 : 64u * r + (uint32_t)lane < n_listed)
-          seg[hist[31u - (entry[r] >> 10)] + place[r]] = (uint16_t)entry[r];
-      }
-    }
-  }
-  __syncthreads();
-
-  // ---- merge: Algorithm 1 on one segment per lane ----
-  // The look-ups of the two pairs a merge creates stay in flight over the loop's edge: the next trip first scans
-  // the pair values that did not change and only then takes the two new ones.
-  uint32_t dead = 0xFFFFFFFFu;     // bit o: position o of my segment holds no token; all ones: I have no segment
-  uint32_t* t0 = T;                // my segment's first position in T ...
-  uint32_t* v0 = V;                // ... and in V
-  uint32_t next = 0;               // first segment nobody has taken (uniform)
-  ProbeInFlight f1, f2;            // (left token, merged token) and (merged token, token after it)
-  f1.q = f2.q = make_uint4(0, 0, 0, 0);
-  f1.pl.bucket = f1.pl.fingerprint = f2.pl.bucket = f2.pl.fingerprint = 0;
-  f1.live = f2.live = false;
-  bool pending = false, pending_left = false;          // look-ups of my last merge are in flight
-  uint32_t hold = 0;               // positions whose pair value is being looked up
-  uint32_t pk = 0, pl = 0;         // ... the merged token's position and its left neighbour's
-  // Every trip ends a segment or removes a token in each lane that has a segment, so 2 n trips cannot be needed;
-  // the bound only guarantees that the loop ends whatever the memory contents.
-  // A lane without a segment takes the next one of the list.
-  auto take_segments = [&]() {
-    const bool idle = dead == 0xFFFFFFFFu;             // (an idle lane has nothing in flight)
-    const uint64_t idle_lanes = __ballot(idle);
-    if (idle_lanes && next < n_segments) {             // uniform
-      const uint32_t mine = next + mbcnt64(idle_lanes);
-      next += (uint32_t)__builtin_popcountll(idle_lanes);
-      if (idle && mine < n_segments) {
-        const uint32_t e = seg[mine];
-        const uint32_t first = e & 1023u, len = (e >> 10) + 1u;
-        dead = len >= 32u ? 0u : 0xFFFFFFFFu << len;
-        t0 = T + first;
-        v0 = V + first;
-      }
-    }
-  };
-  take_segments();
-#pragma unroll 2                   // (measured: 1.5 % faster than the rolled loop; 3 and 4 are not)
-  for (int trip = 0; trip < 2 * n + 64; ++trip) {
-    if (!__ballot(dead != 0xFFFFFFFFu)) break;         // every segment is done
-
-    // the lowest value among my live pairs, left-most on ties: the position rides in the low bits
-    uint32_t best = 0xFFFFFFFFu;
-    {
-      const uint32_t skip = dead | hold;
-#pragma unroll
-      // (two halves: gating by eights or fours costs more in branches than it saves in positions, and no
-      // gating at all costs 15 %: one trip in five has a lane with a token beyond position 16)
-      for (int g = 0; g < kLaneSegmentMax; g += 16) {
-        if (g == 0 || __ballot((~dead >> g) != 0)) {   // uniform: some lane's segment reaches this far
-#pragma unroll
-          for (int o = g; o < g + 16; ++o)
-            best = min(best, v0[o] | (uint32_t)o | (uint32_t)__builtin_amdgcn_sbfe((int)skip, o, 1));
-        }
-      }
-    }
-    // From here to the issue of the new look-ups a wave is on its way to its next memory round trip: it goes
-    // before the waves that are scanning or loading (measured: 1 % on the large workloads).
-    __builtin_amdgcn_s_setprio(2);
-    {                                                  // the two pairs my last merge created (no "if any lane":
-                                                       // nearly every trip has one, and the branch costs more)
-      const uint32_t r1 = probe_finish(tab, f1), r2 = probe_finish(tab, f2);
-      if (pending) {
-        const uint32_t here = lane_value(r2);
-        v0[pk] = here;
-        best = min(best, here | pk);
-        if (pending_left) {
-          const uint32_t left = lane_value(r1);
-          v0[pl] = left;
-          best = min(best, left | pl);
-        }
-      }
-    }
-    const bool merge = best < kLaneInvalid;
-    if (!merge) dead = 0xFFFFFFFFu;                    // no pair left: my segment is finished
-    pending = merge;
-    pending_left = false;
-    hold = 0;
-    {
-      uint32_t x1 = 0, y1 = kTokNone, x2 = 0, y2 = kTokNone;
-      if (merge) {
-        const uint32_t k = best & 31u;
-        const uint32_t word = lane_merged_word(best);
-        const uint32_t alive = ~dead;
-        const uint32_t upper = alive & (0xFFFFFFFEu << k);         // not empty: the pair has a right token
-        const uint32_t r = (uint32_t)__builtin_ctz(upper);
-        const uint32_t after = upper & (upper - 1u);               // live positions beyond the right token
-        const uint32_t lower = alive & ((1u << k) - 1u);
-        dead |= 1u << r;
-        t0[k] = word;
-        t0[r] = kTokNone;
-        pk = k;
-        hold = 1u << k;
-        x2 = word;
-        if (after) y2 = t0[__builtin_ctz(after)];
-        if (lower) {
-          pl = 31u - (uint32_t)__builtin_clz(lower);
-          pending_left = true;
-          hold |= 1u << pl;
-          x1 = t0[pl];
-          y1 = word;
-        }
-        if (!(after | lower)) {                                    // the merged token is all that is left of the
-          dead = 0xFFFFFFFFu;                                      // segment (two segments in three end like this):
-          pending = false;                                         // finished, without a trip that finds no pair
-          hold = 0;
-        }
-      }
-      probe_start(tab, x1, y1, pending_left, f1);
-      probe_start(tab, x2, y2, merge, f2);
-    }
-    take_segments();                                   // lanes whose segment just ended go on at once
-    __builtin_amdgcn_s_setprio(0);
-  }
-  __syncthreads();
-
-  // ---- emit: the surviving tokens in order; a ballot per row gives every lane its place ----
-  {
-    int32_t* const dst = p.tmp_ids + begin;
-    uint32_t total = 0;                                // uniform
-    // (groups: the pair values are no longer needed; their words keep, per row, the ballot and the tokens before it)
-    auto keep_row = [&](int j, uint64_t live_row) {
-      if (lane == 0) {
-        *(uint64_t*)(V + 2 * j) = live_row;
-        V[2 * kLaneRows + j] = total;
-      }
-    };
-    if (GROUPS && left) {                              // uniform: strings at their own places
-      mark_string_ends(ends);
-      uint32_t lack = 0;   // what the place of the row's first token lacks to its string's own (uniform)
+        for (int r = 0; r < kRounds; ++r)
+          if (64u * r + (uint32_t)lane < n_jobs) sorted[hist[31u - ((entry[r] >> 12) & 31u)] + place[r]] = entry[r];
+        wave_sync();
+        // ---- their places in the arena: byte-level pre-tokenisation (section 4.1) and the initial pair values ----
+        uint32_t arena = 0;                            // uniform
 #pragma unroll 1
-      for (int j = 0; j < rows; ++j) {
-        const uint32_t tok = T[64 * j + lane];
-        const uint64_t live_row = __ballot(tok != kTokNone);
-        auto tokens_upto = [&](uint32_t pos) {         // tokens before the row's position pos (at most 64)
-          return total + (uint32_t)__builtin_popcountll(pos < 64u ? live_row & ((1ull << pos) - 1ull) : live_row);
-        };
-        const uint64_t last_row = *(const uint64_t*)(ends + 2 * j);      // last bytes of strings ...
-        const uint64_t before = last_row & ((1ull << lane) - 1ull);      // ... and those before my position
-        const uint32_t start = before ? 64u - (uint32_t)__builtin_clzll(before) : 0u;
-        const uint32_t at = total + mbcnt64(live_row) + (before ? 64u * j + start - tokens_upto(start) : lack);
-        if (tok != kTokNone) dst[at] = (int32_t)(tok & kTokIdMask);
-        keep_row(j, live_row);
-        if (last_row) {                                // uniform
-          const uint32_t next_start = 64u - (uint32_t)__builtin_clzll(last_row);
-          lack = 64u * j + next_start - tokens_upto(next_start);
-        }
-        total += (uint32_t)__builtin_popcountll(live_row);
-      }
-    } else {
+        for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) { // uniform
+          const uint32_t j = j0 + (uint32_t)lane;
+          const uint32_t e = sorted[min(j, n_jobs - 1u)];
+          const uint32_t at = e & 0xFFFu;
+          const uint32_t len = j < n_jobs ? ((e >> 12) & 31u) + 1u : 0u;
+          const uint32_t room = (len + 3u) & ~3u;
+          const uint32_t upto = arena + wave_scan<OpAdd>(room, 0u);
+          const uint32_t base = upto - room;
+          arena = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+          if (len) {
+            jobs[j] = (uint16_t)(base | ((len - 1u) << 11));
+            sorted[j] = (e >> 17) | (base << 16);
+          }
+          const uint32_t* word = text + (at >> 2);
+          const uint32_t shift = 8u * (at & 3u);
+          uint32_t w0 = word[0], w1 = word[1];
+#pragma unroll 1
+          for (uint32_t o = 0; __ballot(o < len) != 0; o += 8) {           // uniform; eight pairs' values in flight
+            if (o < len) {
+              const uint32_t w2 = word[(o >> 2) + 2], w3 = word[(o >> 2) + 3];
+              const uint32_t bytes[3] = {__builtin_amdgcn_alignbit(w1, w0, shift), __builtin_amdgcn_alignbit(w2, w1, shift),
+                                         __builtin_amdgcn_alignbit(w3, w2, shift)};
+              w0 = w2;
+              w1 = w3;
+              uint32_t v[8], t[8];
 #pragma unroll
-      for (int j = 0; j < kLaneRows; ++j) {
-        if (j < rows) {                                // uniform
-          const uint32_t tok = T[64 * j + lane];       // (positions from n on hold "no token")
-          const uint64_t live_row = __ballot(tok != kTokNone);
-          if (tok != kTokNone) dst[total + mbcnt64(live_row)] = (int32_t)(tok & kTokIdMask);
-          if constexpr (GROUPS) keep_row(j, live_row);
-          total += (uint32_t)__builtin_popcountll(live_row);
+              for (int c = 0; c < 8; ++c) {
+                // byte-pair table: first byte * 256 + second byte
+                const uint32_t pair = (c & 3) == 3 ? __builtin_amdgcn_alignbit(bytes[(c >> 2) + 1], bytes[c >> 2], 24u)
+                                                   : bytes[c >> 2] >> (8 * (c & 3));
+                const uint32_t swapped = __builtin_amdgcn_perm(0u, pair, 0x0C0C0001u);
+                v[c] = kLaneNoPair;
+                if (o + c + 1u < len) v[c] = tab.byte_pair[swapped];
+                t[c] = shared[LaneShared::kByteWord + ((bytes[c >> 2] >> (8 * (c & 3))) & 0xFFu)];
+              }
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const uint32_t at4 = o + 4 * h;
+                if (at4 < len) {
+                  *(uint4*)(T + base + at4) = make_uint4(t[4 * h], t[4 * h + 1], t[4 * h + 2], t[4 * h + 3]);
+                  *(uint4*)(V + base + at4) = make_uint4(lane_value(v[4 * h], at4), lane_value(v[4 * h + 1], at4 + 1u),
+                                                         lane_value(v[4 * h + 2], at4 + 2u), lane_value(v[4 * h + 3], at4 + 3u));
+                }
+              }
+            }
+          }
+        }
+        wave_sync();
+      }
+      // (the text is in the arena as far as it is needed: its place keeps what becomes of the segments)
+#pragma unroll
+      for (int r = 0; r < L::kListed / 64; ++r) rec[64 * r + lane] = found[r];
+      wave_sync();
+      if (n_jobs) {                                    // uniform
+#pragma unroll 1
+        for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) { // uniform
+          const uint32_t e = sorted[j0 + (uint32_t)lane];
+          if (j0 + (uint32_t)lane < n_jobs) rec[e & 0xFFFFu] = kRecJob | (e >> 16);
+        }
+
+        // ---- merge: Algorithm 1 on one segment per lane ----
+        // The look-ups of the two pairs a merge creates stay in flight over the loop's edge: the next trip first scans
+        // the pair values that did not change and only then takes the two new ones.
+        // A wave issues one instruction at a time, and what bounds a trip -- of a lone wave too -- is their number, the
+        // scalar ones of branches included: so a lane without a segment, or without a look-up, has an address of its own
+        // to read and write (kIdle) instead of a branch.
+        if (lane < 4) lds[L::kIdle + lane] = kLaneNoPair;
+        wave_sync();
+        uint32_t* const idle_v = lds + L::kIdle;
+        uint32_t alive = 0;            // bit o: position o of my segment holds a token; 0: I have no segment
+        uint32_t* v0 = idle_v;         // my segment's first position in V, where its tokens are left as a mask once it is
+        uint32_t last = 0;             // done; it has its place in T too.  Where its last four positions begin
+        uint32_t next = 0;             // first segment nobody has taken (uniform)
+        LaneProbe f1, f2;              // (left token, merged token) and (merged token, token after it)
+        f1.q = f2.q = make_uint4(0, 0, 0, 0);
+        f1.bucket = f2.bucket = 0;
+        f1.tag = f2.tag = kLaneNoTag;
+        uint32_t* to1 = idle_v;        // ... where their values go
+        uint32_t* to2 = idle_v;
+        uint32_t pk = 0, pl = 0;       // ... and their positions
+        // A lane without a segment takes the next one of the list.
+        auto take_segments = [&]() {
+          const uint64_t idle_lanes = __ballot(alive == 0);              // (an idle lane has nothing in flight)
+          if (idle_lanes && next < n_jobs) {           // uniform
+            const uint32_t mine = next + mbcnt64(idle_lanes);
+            next += (uint32_t)__builtin_popcountll(idle_lanes);
+            if (alive == 0 && mine < n_jobs) {
+              const uint32_t e = jobs[mine];
+              const uint32_t top = e >> 11;
+              alive = (2u << top) - 1u;
+              v0 = V + (e & 2047u);
+              last = top & ~3u;
+            }
+          }
+        };
+        take_segments();
+        // Every trip ends a segment or removes a token in each lane that has a segment, so so many trips cannot be needed;
+        // the bound only guarantees that the loop ends whatever the memory contents.
+        const int most_trips = 2 * (int)used + 64;
+        for (int trip = 0; trip < most_trips; ++trip) {
+          if (!__ballot(alive != 0)) break;            // every segment is done
+
+          // The lowest value among my pairs, left-most on ties, four positions a load; what is dead or being looked up
+          // holds "no pair".  (A lane whose segment does not reach so far reads its last four again.)
+          uint32_t best;
+          {
+            const uint4 a = *(const uint4*)v0, b = *(const uint4*)(v0 + min(4u, last)),
+                        c = *(const uint4*)(v0 + min(8u, last)), d = *(const uint4*)(v0 + min(12u, last));
+            __builtin_amdgcn_sched_barrier(0);         // (all four loads go out before the first is waited for)
+            best = min(min(min(a.x, a.y), min(a.z, a.w)), min(min(b.x, b.y), min(b.z, b.w)));
+            best = min(best, min(min(min(c.x, c.y), min(c.z, c.w)), min(min(d.x, d.y), min(d.z, d.w))));
+          }
+          if (__ballot(last >= 16u)) {                 // uniform
+            for (uint32_t o = 16; o < 32; o += 4) {
+              const uint4 a = *(const uint4*)(v0 + min(o, last));
+              best = min(best, min(min(a.x, a.y), min(a.z, a.w)));
+            }
+          }
+          // From here to the issue of the new look-ups a wave is on its way to its next memory round trip: it goes
+          // before the waves that are scanning or loading (measured: 1 % on the large workloads).
+          __builtin_amdgcn_s_setprio(2);
+          {                                            // the two pairs my last merge created
+            uint32_t r1, r2;
+            lane_probe_finish(tab, f1, f2, r1, r2);
+            r1 = lane_value(r1, pl);
+            r2 = lane_value(r2, pk);
+            *to1 = r1;                                 // (no left neighbour: the same place, to be overwritten)
+            *to2 = r2;
+            best = min(best, min(r1, r2));
+          }
+          uint32_t x1 = 0, x2 = 0, y2 = 0;             // (a word without capabilities: no look-up)
+          to1 = to2 = idle_v;
+          if (best < kLaneInvalid) {                   // (an idle lane has no pair)
+            pk = best & 31u;
+            const uint32_t upper = alive & (0xFFFFFFFEu << pk);          // not empty: the pair has a right token
+            const uint32_t right = (uint32_t)__builtin_ctz(upper);
+            const uint32_t after = upper & (upper - 1u);                 // live positions beyond the right token
+            const uint32_t lower = alive & ((1u << pk) - 1u);
+            pl = lower ? 31u - (uint32_t)__builtin_clz(lower) : pk;
+            to2 = v0 + pk;
+            to1 = v0 + pl;
+            const uint32_t next_word = (v0 + (L::kT - L::kV))[after ? __builtin_ctz(after) : 0];
+            const uint32_t left_word = to1[L::kT - L::kV];
+            y2 = after ? next_word : 0u;
+            x1 = lower ? left_word : 0u;
+            x2 = lane_merged_word(best);
+            to2[L::kT - L::kV] = x2;
+            *to2 = kLaneNoPair;
+            *to1 = kLaneNoPair;
+            v0[right] = kLaneNoPair;
+            alive &= ~(1u << right);
+          } else if (alive != 0) {                     // no pair left: my segment is finished
+            *v0 = alive;
+            alive = 0;
+            last = 0;
+            v0 = idle_v;
+          }
+          lane_probe_start(tab, x1, x2, f1);
+          lane_probe_start(tab, x2, y2, f2);
+          take_segments();                             // lanes whose segment just ended go on at once
+          __builtin_amdgcn_s_setprio(0);
+        }
+        wave_sync();
+      }
+
+      // ---- emit: a prefix sum of the segments' token counts gives every one its place ----
+      // First the segments that are one token, in the text's order; then the others, in the jobs' order: neighbours there
+      // have about as many tokens.  (In the text's order too, a store instruction per token of the longest of 64 segments,
+      // few lanes in each, was a fifth of the kernel.)
+#pragma unroll 1
+      for (int b = i0; b < i1; b += 64) {              // uniform
+        const int i = b + lane;
+        const uint32_t what = i < i1 ? rec[i - i0] : kRecNone;
+        const uint32_t at = what & 2047u;
+        uint32_t count = what < kRecJob ? 1u : 0u;
+        if (what & kRecJob) count = (uint32_t)__builtin_popcount(V[at]);
+        const uint32_t upto = total + wave_scan<OpAdd>(count, 0u);
+        uint32_t o = upto - count;
+        if constexpr (GROUPS) {                        // my string's first segment is one of these: its tokens begin there
+          const uint32_t which = my_segment - (list_first + (uint32_t)b);
+          const uint32_t its = lane_read(o, (int)(which & 63u));
+          if (which < 64u && b + (int)which < i1) tokens_before = its;
+          if (left) {                                  // uniform: strings at their own places
+            const uint32_t pos = i < i1 ? list[i] : 0u;
+            const uint64_t heads = __ballot(i < i1 && ((strings[pos >> 5] >> (pos & 31u)) & 1u));
+            const uint64_t upto_me = heads & (~0ull >> (63 - lane));
+            const uint32_t mine = pos - o;             // (of a string's first segment)
+            const uint32_t its_lack = lane_read(mine, upto_me ? 63 - (int)__builtin_clzll(upto_me) : lane);
+            o += upto_me ? its_lack : lack;
+            if (heads) lack = (uint32_t)__builtin_amdgcn_readlane((int)mine, 63 - (int)__builtin_clzll(heads));
+          }
+        }
+        if (what < kRecJob) dst[o] = (int32_t)what;
+        if (what & kRecJob) V[at + 1u] = o;            // (two positions or more: the mask lies in the first)
+        total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+      }
+      wave_sync();
+#pragma unroll 1
+      for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) {   // uniform
+        uint32_t tokens = 0, o = 0;
+        const uint32_t* t = T;
+        if (j0 + (uint32_t)lane < n_jobs) {
+          const uint32_t at = jobs[j0 + (uint32_t)lane] & 2047u;
+          tokens = V[at];
+          o = V[at + 1u];
+          t = T + at;
+        }
+        while (__ballot(tokens != 0)) {
+          if (tokens) dst[o++] = (int32_t)(t[__builtin_ctz(tokens)] & kTokIdMask);
+          tokens &= tokens - 1u;
         }
       }
+      wave_sync();                                     // the round's LDS is used again
+      i0 = i1;
     }
-    if (GROUPS && members > 1) {                       // uniform
-      __syncthreads();
-      auto tokens_before = [&](int64_t at) {           // tokens of the item that start before its byte `at`
-        if (at <= 0) return 0;
-        if (at >= n) return (int)total;
-        const int j = (int)at >> 6;
-        return (int)V[2 * kLaneRows + j] +
-               (int)__builtin_popcountll(*(const uint64_t*)(V + 2 * j) & ((1ull << (at & 63)) - 1ull));
-      };
-      if (lane < members)
-        p.counts[s + lane] =
-            max(tokens_before(p.offsets[s + lane + 1] - begin) - tokens_before(p.offsets[s + lane] - begin), 0);
-    } else {
-      if (lane == 63) p.counts[s] = (int32_t)total;
+  }
+  if constexpr (GROUPS) {
+    if (from >= n) tokens_before = total;              // (empty strings at the end, and lanes without one)
+    const uint32_t after = lane_read(tokens_before, min(lane + 1, 63));
+    if (lane < members) {
+      p.counts[s + lane] = (int32_t)((lane + 1 < members ? after : total) - tokens_before);
+      if (p.group_ids && !left) p.group_ids[s + lane] = lane == 0 ? (int32_t)total : 0;
     }
-    __syncthreads();                                   // LDS is reused by the next item
+  } else {
+    if (lane == 63) p.counts[s] = (int32_t)total;
   }
   return left;
 }
 
-// Persistent one-wave workgroups over the items of tier 0.  An item with a segment that no lane can take goes to
-// the wave-per-item encoder: in this kernel when INLINE (the launch that has no work list and no
-// kernel after it to pick such items up), else through p.fallback_list.
-// GROUPS: the items are groups of strings (see bin_scatter_kernel); the strings of a group that hold such a segment go
-// to p.fallback_list, and the group's descriptor is marked for the packing kernel.
-template <bool SPECIAL, bool INLINE, bool GROUPS>
-__global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
-  extern __shared__ uint32_t smem[];
-  uint32_t* const arrays = smem;                       // this wave's LaneLds
+// Persistent workgroups, whose waves go over the items of tier 0 on their own.  INLINE: there is no work list, item i is
+// string i, and one with a segment that no lane can take goes to the wave-per-item encoder in this kernel.  Else the items
+// are groups of strings, or of pieces of strings (see group_members); those of a group that hold such a segment go to
+// p.fallback_list, for the kernel that comes after this one, and the group's descriptor is marked for the packing kernel.
+template <class L, bool SPECIAL, bool INLINE>
+__global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodeParams p) {
+  constexpr bool GROUPS = !INLINE;
+  extern __shared__ __align__(16) uint32_t smem[];
   const uint32_t first = p.list ? p.tier_base[p.tier] : 0u;
   const uint32_t count = p.list ? p.tier_base[p.tier + 1] - first : p.direct_count;
-  // items per claim: as many as keep every workgroup of the grid busy, kLaneChunk at most
-  // The workgroups that take part: as many as make the rounds even.  5,120 items on 4,096 resident workgroups
+  // The waves that take part: as many as make the rounds even.  5,120 items on 4,096 resident waves
   // are two rounds of 2,560 -- the same two item times, with fewer waves sharing each SIMD.
-  const uint32_t rounds = (count + gridDim.x - 1) / gridDim.x;
+  const uint32_t n_waves = gridDim.x * L::kWaves;
+  const uint32_t rounds = (count + n_waves - 1) / n_waves;
   const uint32_t g = rounds ? (count + rounds - 1) / rounds : 1u;
+  // Items per claim: as many as keep every wave of the grid busy, kLaneChunk at most.
   // (Two or three rounds are dealt out whole: with count / g, which is one less unless g divides the count, all
-  // workgroups come back for a claim at the same moment -- 20,011 strings in some 6,000 groups, 50 us or 110.  Each
-  // workgroup's items are neighbours in a list sorted by length, so the first ones get only long items; it is never
+  // waves come back for a claim at the same moment -- 20,011 strings in some 6,000 groups, 50 us or 110.  Each
+  // wave's items are neighbours in a list sorted by length, so the first ones get only long items; it is never
   // slower for that: 5,000 pieces of 890 bytes and 5,000 strings of 20 bytes 134 us before, 103 so; 4,500 of each 102,
   // 101; 6,000 of each 110, 110.)
   const uint32_t per_claim = rounds < kLaneChunk ? max(1u, rounds)
                                                  : min(count / g >= 32u ? 2u * kLaneChunk : kLaneChunk, count / g);
+  // Neighbouring numbers are waves of different workgroups: few items are spread over the whole chip.
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t b = wave * gridDim.x + blockIdx.x;
   if (blockIdx.x >= g || (uint64_t)blockIdx.x * per_claim >= count) return;   // uniform: nothing for this workgroup
-  // the capability bits of the 256 byte tokens, packed 16 bytes to a word
-  if (threadIdx.x < 16) arrays[LaneLds::kFlags + threadIdx.x] = 0;
-  __syncthreads();
-  {
-    uint32_t bits = 0;
-    for (int k = 0; k < 4; ++k) bits |= (p.table.byte_word[4 * threadIdx.x + k] >> 30) << (2 * k);
-    atomicOr(&arrays[LaneLds::kFlags + (threadIdx.x >> 2)], bits << (8 * (threadIdx.x & 3)));
+  for (int i = (int)threadIdx.x; i < 2048 / 4; i += 64 * L::kWaves)
+    ((uint4*)(smem + LaneShared::kCuts))[i] = ((const uint4*)p.table.cuts)[i];
+  for (int i = (int)threadIdx.x; i < 256; i += 64 * L::kWaves) smem[LaneShared::kByteWord + i] = p.table.byte_word[i];
+  if (threadIdx.x < 64) {                              // word w of the first l bytes
+    const int bytes = (int)(threadIdx.x >> 2) - 4 * (int)(threadIdx.x & 3u);
+    smem[LaneShared::kMasks + threadIdx.x] = bytes >= 4 ? 0xFFFFFFFFu : bytes > 0 ? (1u << (8 * bytes)) - 1u : 0u;
   }
-  uint32_t* const byte_word = smem + LaneLds::kWords;  // INLINE only: the byte token words for the other encoder
-  if constexpr (INLINE)
-    for (int i = (int)threadIdx.x; i < 256; i += 64) byte_word[i] = p.table.byte_word[i];
   __syncthreads();
+  if (b >= g || (uint64_t)b * per_claim >= count) return;   // uniform in the wave; no barrier follows
+  uint32_t* const arrays = smem + LaneShared::kWords + wave * L::kWords;
 
-  // Items are claimed kLaneChunk at a time: the first chunk of a workgroup is its own index, later ones come from
+  // Items are claimed kLaneChunk at a time: the first chunk of a wave is its own index, later ones come from
   // the tier's queue head (which starts at zero).  One claim per item would make every wave wait for a round trip
   // to the one contended address after each item.  Lane i fetches the descriptor of the chunk's i-th item, so a
   // chunk costs one round trip for its claim and one for its descriptors.  (Claiming ahead does not pay: loads
@@ -497,39 +797,33 @@ __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
                             (uint32_t)__builtin_amdgcn_readlane((int)cur.begin, (int)i);
       const int members = GROUPS ? (n >> kGroupShift) & kGroupMask : 1;
       const uint64_t left =
-          encode_item_lanes<SPECIAL, GROUPS>(p, s, begin, GROUPS ? n & kGroupLen : n, members, arrays);
+          encode_item_lanes<L, SPECIAL, GROUPS>(p, s, begin, GROUPS ? n & kGroupLen : n, members, arrays, smem);
       if (left) {                                      // uniform
         if constexpr (INLINE) {
-          __syncthreads();
-          BlockShared<1> sh;
-          uint32_t* const other = byte_word + 256;     // the other encoder's arrays lie behind this one's
-          uint32_t* cur_word = other + 3 * kLaneItemBytes;
+          wave_sync();
+          BlockShared<1> sh;                           // the other encoder's arrays take the place of this one's
+          uint32_t* cur_word = arrays + 3 * 1024;
           sh.rec = (WaveRecord*)cur_word; cur_word += 2 * 8;
           sh.first_tok = cur_word; cur_word += 2;
           sh.part = cur_word; cur_word += 2;
           sh.item = cur_word;
-          sh.byte_word = byte_word;
-          encode_string_segmented<1, 16, true, SPECIAL>(p, s, other, other + kLaneItemBytes,
-                                                        other + 2 * kLaneItemBytes, sh);
-        } else if constexpr (GROUPS) {
+          sh.byte_word = smem + LaneShared::kByteWord;
+          encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2 * 1024, sh);
+          wave_sync();
+        } else {
           const uint32_t slot = uniform(
-              atomicAdd(p.fallback_count, threadIdx.x == 0 ? (uint32_t)__builtin_popcountll(left) : 0u));
+              atomicAdd(p.fallback_count, lane == 0 ? (uint32_t)__builtin_popcountll(left) : 0u));
           if ((left >> lane) & 1ull) p.fallback_list[slot + mbcnt64(left)] = s + lane;
           if (lane == 0) ((ItemDesc*)p.list_desc)[first + at + i].len = n | kGroupApart;
-        } else {
-          // every lane takes part in the atomic (lane 0 adds 1): no lane-dependent branch at the loop's edge
-          const uint32_t slot = uniform(atomicAdd(p.fallback_count, threadIdx.x == 0 ? 1u : 0u));
-          if (threadIdx.x == 0) p.fallback_list[slot] = s;
         }
       }
     }
   };
-  // A workgroup's own first chunk: per_claim items, and when the list is long zero to three more, by block index,
-  // so that the workgroups do not all come back for their first claim at the same moment (claims on one address
+  // A wave's own first chunk: per_claim items, and when the list is long zero to three more, by its number,
+  // so that the waves do not all come back for their first claim at the same moment (claims on one address
   // are served one after the other, some ten nanoseconds each).
   const uint32_t spread = per_claim >= kLaneChunk ? 1u : 0u;
-  const uint32_t b = blockIdx.x;
-  constexpr uint32_t kBefore[4] = {0, 0, 1, 3};        // extra items of the blocks before b within its group of four
+  constexpr uint32_t kBefore[4] = {0, 0, 1, 3};        // extra items of the waves before b within its group of four
   uint64_t first_item = (uint64_t)b * per_claim + spread * ((b >> 2) * 6u + kBefore[b & 3u]);
   const uint64_t own_items = (uint64_t)g * per_claim + spread * ((g >> 2) * 6u + kBefore[g & 3u]);
   if (first_item >= count) return;                     // uniform
@@ -540,17 +834,12 @@ __global__ __launch_bounds__(64) void encode_lanes_kernel(EncodeParams p) {
     encode_chunk(first_item, here, cur);
     if (own_items >= count) break;                     // uniform: the grid's own chunks cover the list
     // (lane 0 adds 1; every lane takes part, so that no lane-dependent branch sits at the loop's edge)
-    const uint32_t claimed = atomicAdd(p.queue_head + p.tier, threadIdx.x == 0 ? 1u : 0u);
+    const uint32_t claimed = atomicAdd(p.queue_head + p.tier, lane == 0 ? 1u : 0u);
     first_item = own_items + (uint64_t)uniform(claimed) * per_claim;
     if (first_item >= count) break;                    // uniform
     here = (uint32_t)min((uint64_t)per_claim, count - first_item);
     load_chunk(first_item, here, cur);
   }
-}
-
-template <bool INLINE>
-constexpr size_t lanes_lds_bytes() {
-  return lds_blocks(sizeof(uint32_t) * (LaneLds::kWords + (INLINE ? 256 + 3 * kLaneItemBytes + 24 : 0)));
 }
 
 }  // namespace bpe

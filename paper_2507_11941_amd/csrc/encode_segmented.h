@@ -67,7 +67,7 @@ __device__ void encode_string_segmented(const EncodeParams& p, int s, uint32_t* 
   static_assert(D % kGroup == 0 && D <= 16, "the per-position registers of the sweep are sized for 16");
   using mask_t = uint32_t;
   constexpr int W = NW * 64;
-  const int tid = (int)threadIdx.x;
+  const int tid = (int)threadIdx.x & (W - 1);          // (one wave: of a workgroup that may have others)
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const DeviceTable& tab = p.table;

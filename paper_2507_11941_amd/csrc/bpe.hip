@@ -47,56 +47,35 @@ static std::mutex g_scratch_mutex;
 
 namespace {
 
-// ---- kernel variants ------------------------------------------------------------------------------
-// A variant is (waves per workgroup, positions per lane, tokens staged in HBM or LDS); it encodes
-// strings of up to 64 * waves * positions bytes.
+// ---- encode kernels ---------------------------------------------------------------------------------
+// Each is compiled twice, plain and with the reading of special-token marks (tables that have special tokens set).
 
 struct Variant {
-  int waves, depth;
-  bool staged, limits;            // per-position arrays in HBM instead of LDS; a third array holds the pair limits
-  int capacity;                   // bytes
+  int waves;                      // of a workgroup
   size_t lds;
   const void* fn;
   void (*launch)(const EncodeParams&, int grid, hipStream_t);
   int max_grid = 0;               // resident workgroups on the whole device (filled on first use)
 };
 
-template <int NW, int D, bool ST, bool LIM, bool SEG, bool SPC>
-void launch_variant(const EncodeParams& p, int grid, hipStream_t stream) {
-  constexpr size_t lds = encode_lds_bytes<NW, D, ST, LIM>();
-  encode_kernel<NW, D, ST, LIM, SEG, SPC><<<dim3(grid), dim3(NW * 64), lds, stream>>>(p);
+// Items of tier t have up to kTierBytes[t] bytes: one wave, four, sixteen in LDS, sixteen with their arrays in HBM.
+constexpr int kTierBytes[kMaxTiers] = {kMemberBytes, 4096, 16384, 65536};
+template <bool SPC>
+void launch_short(const EncodeParams& p, int grid, hipStream_t stream) {
+  encode_short_kernel<SPC><<<dim3(grid), dim3(256), lds_blocks(4 * kShortWords), stream>>>(p);
 }
-
-template <int NW, int D, bool ST, bool LIM, bool SEG, bool SPC>
-Variant make_variant() {
-  Variant v;
-  v.waves = NW;
-  v.depth = D;
-  v.staged = ST;
-  v.limits = LIM;
-  v.capacity = 64 * NW * D;
-  v.lds = encode_lds_bytes<NW, D, ST, LIM>();
-  v.fn = (const void*)&encode_kernel<NW, D, ST, LIM, SEG, SPC>;
-  v.launch = &launch_variant<NW, D, ST, LIM, SEG, SPC>;
-  return v;
+template <bool SPC>
+void launch_long(const EncodeParams& p, int grid, hipStream_t stream) {
+  encode_long_kernel<SPC><<<dim3(grid), dim3(1024), lds_blocks(4 * kLongWords), stream>>>(p);
 }
+Variant g_short_variants[2] = {{4, lds_blocks(4 * kShortWords), (const void*)&encode_short_kernel<false>, &launch_short<false>},
+                               {4, lds_blocks(4 * kShortWords), (const void*)&encode_short_kernel<true>, &launch_short<true>}};
+Variant g_long_variants[2] = {{16, lds_blocks(4 * kLongWords), (const void*)&encode_long_kernel<false>, &launch_long<false>},
+                              {16, lds_blocks(4 * kLongWords), (const void*)&encode_long_kernel<true>, &launch_long<true>}};
 
-// Default plan: <= 1 KiB one wave, <= 4 KiB four waves, <= 16 KiB sixteen waves (all LDS-resident),
-// <= 64 KiB sixteen waves with the per-position arrays staged in HBM.  Second family: the same kernels with
-// the reading of special-token marks compiled in (tables that have special tokens set).
-Variant g_variant_families[2][kMaxTiers] = {
-    {make_variant<1, 16, false, true, true, false>(), make_variant<4, 16, false, true, true, false>(),
-     make_variant<16, 16, false, false, true, false>(),   // three arrays of 16 Ki words would not fit the 160 KB of LDS
-     make_variant<16, 64, true, true, false, false>()},   // whole-string horizon; arrays in HBM
-    {make_variant<1, 16, false, true, true, true>(), make_variant<4, 16, false, true, true, true>(),
-     make_variant<16, 16, false, false, true, true>(), make_variant<16, 64, true, true, false, true>()},
-};
-Variant (&g_variants)[kMaxTiers] = g_variant_families[0];   // sizes and capacities are those of either family
-
-// Items of tier 0 go to the lane-per-segment kernel first; the one-wave variant above then takes those strings and
-// pieces that this kernel passes on (they have a segment of more than 32 bytes).  [family][shape]: with kDirect item i is
-// string i, and the kernel encodes those itself (the launch without a work list); else the items are groups of strings or
-// pieces, of up to 1 KiB (kSmall) or 2 KiB (kLarge).
+// Items of tier 0 go to the lane-per-segment kernel; it passes those strings and pieces on that have a segment of more than
+// 32 bytes.  [family][shape]: with kDirect item i is string i, and the kernel encodes those itself (the launch without a
+// work list); else the items are groups of strings or pieces, of up to 1 KiB (kSmall) or 2 KiB (kLarge).
 enum { kDirect, kSmall, kLarge, kLaneShapes };
 template <class L, bool SPC, bool INL>
 void launch_lanes(const EncodeParams& p, int grid, hipStream_t stream) {
@@ -104,16 +83,7 @@ void launch_lanes(const EncodeParams& p, int grid, hipStream_t stream) {
 }
 template <class L, bool SPC, bool INL>
 Variant make_lanes_variant() {
-  Variant v;
-  v.waves = L::kWaves;
-  v.depth = 16;
-  v.staged = false;
-  v.limits = false;
-  v.capacity = L::kBytes;
-  v.lds = L::kLdsBytes;
-  v.fn = (const void*)&encode_lanes_kernel<L, SPC, INL>;
-  v.launch = &launch_lanes<L, SPC, INL>;
-  return v;
+  return {L::kWaves, L::kLdsBytes, (const void*)&encode_lanes_kernel<L, SPC, INL>, &launch_lanes<L, SPC, INL>};
 }
 Variant g_lanes_variants[2][kLaneShapes] = {
     {make_lanes_variant<InlineItems, false, true>(), make_lanes_variant<SmallItems, false, false>(),
@@ -134,7 +104,8 @@ void init_variants() {
   }
   g_num_cus = prop.multiProcessorCount;
   std::vector<Variant*> all;
-  for (auto& family : g_variant_families) for (auto& v : family) all.push_back(&v);
+  for (auto& v : g_short_variants) all.push_back(&v);
+  for (auto& v : g_long_variants) all.push_back(&v);
   for (auto& family : g_lanes_variants) for (auto& v : family) all.push_back(&v);
   for (Variant* vp : all) {
     Variant& v = *vp;
@@ -157,16 +128,12 @@ void init_variants() {
 // Variants that a batch with strings of up to max_len bytes can need.
 int n_tiers_for(int32_t max_len) {
   int n = 1;
-  while (n < kMaxTiers && g_variants[n - 1].capacity < max_len) ++n;
+  while (n < kMaxTiers && kTierBytes[n - 1] < max_len) ++n;
   return n;
 }
 
-// Staged variant: resident workgroups each own one staging slab; the grid is capped so that the slabs
-// stay modest (each is 768 KiB for 64 KiB strings).
-constexpr int kMaxStagedGrid = 256;
-size_t staged_slab_bytes(const Variant& v) {
-  return (size_t)(v.limits ? 3 : 2) * 64 * v.waves * v.depth * sizeof(uint32_t);
-}
+// Resident workgroups of the long variant each own one staging slab (768 KiB), where there is a tier that needs them.
+constexpr int kMaxLongGrid = 256;
 
 constexpr size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -185,7 +152,7 @@ struct WorkspaceLayout {
 
 WorkspaceLayout layout_for(int32_t batch, int64_t total_bytes, int32_t max_len) {
   WorkspaceLayout w;
-  w.split = max_len > g_variants[0].capacity;   // everything already fits the one-wave variant otherwise
+  w.split = max_len > kTierBytes[0];            // everything already fits one wave otherwise
   w.max_slots = w.split ? (int64_t)batch + total_bytes / kPieceTarget : (int64_t)batch;
   w.n_tiles = (int)((w.max_slots + kScanTile - 1) / kScanTile);
   size_t at = 0;
@@ -207,9 +174,7 @@ WorkspaceLayout layout_for(int32_t batch, int64_t total_bytes, int32_t max_len) 
     w.tile_sum = at; at += align_up((size_t)(w.n_tiles + 1) * sizeof(int64_t));
   }
   w.staged = at;
-  const int nt = n_tiers_for(max_len);
-  for (int t = 0; t < nt; ++t)
-    if (g_variants[t].staged) at += align_up(staged_slab_bytes(g_variants[t]) * kMaxStagedGrid);
+  if (n_tiers_for(max_len) > 3) at += align_up((size_t)kStagedWords * sizeof(uint32_t) * kMaxLongGrid);
   w.total = at;
   return w;
 }
@@ -586,7 +551,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
 
   TierPlan plan;
   plan.n_tiers = n_tiers_for(max_len);
-  for (int t = 0; t < kMaxTiers; ++t) plan.cap[t] = g_variants[t].capacity;
+  for (int t = 0; t < kMaxTiers; ++t) plan.cap[t] = kTierBytes[t];
 
   const uint8_t* cover = nullptr;                        // special tokens: mark their occurrences first
   if (table->d_specials && total_bytes > 0) {
@@ -602,7 +567,6 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   int32_t* group_ids = nullptr;
   const int n_items_max = (int)w.max_slots;              // grid bound for the encode kernels
   // A batch that one variant's resident grid covers needs no work list: workgroup i encodes string i.
-  const Variant* family = g_variant_families[cover ? 1 : 0];
   const Variant* lanes = g_lanes_variants[cover ? 1 : 0];
   const bool direct = !w.split && plan.n_tiers == 1 && batch <= lanes[kDirect].max_grid * lanes[kDirect].waves;
   const bool singles = !w.split && !direct && batch <= kSinglesMax;    // one item a string; above, groups of strings
@@ -614,7 +578,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const Variant& listed = lanes[small_items ? kSmall : kLarge];
   const int room = small_items ? -1
                                : (int)std::min<int64_t>(total_bytes / std::max(1, listed.max_grid * listed.waves * 3 / 4) +
-                                                            total_bytes / w.max_slots / 2, listed.capacity);
+                                                            total_bytes / w.max_slots / 2, kGroupBytes);
   if (direct) {
     list = nullptr;
   } else if (singles) {
@@ -686,6 +650,9 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.total_bytes = total_bytes;
   p.fallback_count = &ctrl->fallback_range[1];
   p.fallback_list = (int32_t*)(ws + w.fallback);
+  p.fallback_queue = &ctrl->fallback_queue;
+  p.n_tiers = plan.n_tiers;
+  p.staged = (uint32_t*)(ws + w.staged);
   // Warming L2 pays once the batch probes the table more often than it has lines: ~1 probe per input byte.
   const size_t table_bytes = table->bucket_bytes + (256 + 65536) * sizeof(uint32_t);
   p.prefetch_lines = (size_t)total_bytes >= table_bytes / 4 ? (uint32_t)(table_bytes / 128) : 0u;
@@ -698,32 +665,15 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
       if (hipEventRecord(g_prof.begin[prof_slot], stream) != hipSuccess) return BPE_EHIP;
     }
   }
-  size_t staged_at = w.staged;
-  for (int t = 0; t < plan.n_tiers; ++t) {
-    const Variant& v = family[t];
-    int grid = v.max_grid < n_items_max ? v.max_grid : n_items_max;
-    p.tier = t;
-    p.staged = nullptr;
-    if (v.staged) {
-      if (grid > kMaxStagedGrid) grid = kMaxStagedGrid;
-      p.staged = (uint32_t*)(ws + staged_at);
-      staged_at += align_up(staged_slab_bytes(v) * kMaxStagedGrid);
-    }
-    if (t == 0) {
-      // one lane per segment; what it cannot take (a segment of more than 32 bytes) it encodes itself when
-      // there is no work list, and else leaves on the fallback list for the wave-per-item variant
-      const Variant& lv = direct ? lanes[kDirect] : listed;
-      lv.launch(p, std::min(lv.max_grid, n_items_max), stream);
-      if (direct) continue;
-      EncodeParams rest = p;
-      rest.list = p.fallback_list;
-      rest.tier_base = ctrl->fallback_range;
-      rest.queue_head = &ctrl->fallback_queue;
-      rest.prefetch_lines = 0;
-      v.launch(rest, grid, stream);
-      continue;
-    }
-    v.launch(p, grid, stream);
+  const Variant& lv = direct ? lanes[kDirect] : listed;
+  lv.launch(p, std::min(lv.max_grid, n_items_max), stream);
+  if (!direct) {
+    const Variant& rest = g_short_variants[cover ? 1 : 0];
+    rest.launch(p, std::min(rest.max_grid, n_items_max), stream);
+  }
+  if (plan.n_tiers > 2) {
+    const Variant& longest = g_long_variants[cover ? 1 : 0];
+    longest.launch(p, std::min(std::min(longest.max_grid, kMaxLongGrid), n_items_max), stream);
   }
   if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
   if (direct || singles) {                               // (groups' ids do not lie string by string)

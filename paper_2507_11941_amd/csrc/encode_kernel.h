@@ -66,15 +66,16 @@ struct EncodeParams {
   int32_t* group_ids;         // pieces: how many ids the packing kernel copies from a piece's first byte on: those of all its
                               //   item, none for the item's other pieces, -1: its own
   const void* list_desc;      // ItemDesc of every entry of `list` (begin, length, item), in the same order
-  uint32_t* staged;           // HBM staging for the variant whose strings exceed LDS (else null)
+  uint32_t* staged;           // HBM staging for the strings that exceed LDS (a slab per workgroup; else null)
   uint32_t prefetch_lines;    // 128-byte lines of table memory to pull into L2 at kernel start (0 = none)
   uint32_t direct_count;      // when `list` is null: items are the strings 0..direct_count-1, one per workgroup
-  int tier;
+  int n_tiers;
   const uint8_t* cover;       // null, or one mark per input byte: where the special tokens lie (see kCover*)
   uint32_t special_base;      // token number of special 0 (256 + rows)
   int64_t total_bytes;        // size of `bytes`: wide loads must not run past it
   uint32_t* fallback_count;   // lane-per-segment kernel: items it cannot take are counted here ...
-  int32_t* fallback_list;     // ... and listed here, for the wave-per-item kernel that runs after it
+  int32_t* fallback_list;     // ... and listed here, for the wave-per-item kernel that runs after it ...
+  uint32_t* fallback_queue;   // ... and claims from here
 };
 
 // What the load phases make of them: "byte codes" above the byte values.  Any code >= 0x100 is no byte, so

@@ -98,7 +98,8 @@ struct LaneShape {
 };
 using LargeItems = LaneShape<kGroupBytes, 12, 448, 256, 992, 0>;
 using SmallItems = LaneShape<kMemberBytes, 16, 256, 128, 704, 0>;
-constexpr int kOtherWords = 3 * 1024 + 24;      // the arrays of the one-wave encoder that takes a string over
+// (the arrays of the one-wave encoder that takes a string over)
+constexpr int kOtherWords = encode_array_words<1, 16, false, true>() + encode_exchange_words<1>();
 using InlineItems = LaneShape<kMemberBytes, 12, 256, 128, 704, kOtherWords>;
 
 __device__ inline uint32_t mbcnt64(uint64_t mask) {                     // set bits of mask below my lane
@@ -737,8 +738,8 @@ template <class L, bool SPECIAL, bool INLINE>
 __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodeParams p) {
   constexpr bool GROUPS = !INLINE;
   extern __shared__ __align__(16) uint32_t smem[];
-  const uint32_t first = p.list ? p.tier_base[p.tier] : 0u;
-  const uint32_t count = p.list ? p.tier_base[p.tier + 1] - first : p.direct_count;
+  const uint32_t first = p.list ? p.tier_base[0] : 0u;
+  const uint32_t count = p.list ? p.tier_base[1] - first : p.direct_count;
   // The waves that take part: as many as make the rounds even.  5,120 items on 4,096 resident waves
   // are two rounds of 2,560 -- the same two item times, with fewer waves sharing each SIMD.
   const uint32_t n_waves = gridDim.x * L::kWaves;
@@ -801,13 +802,8 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
       if (left) {                                      // uniform
         if constexpr (INLINE) {
           wave_sync();
-          BlockShared<1> sh;                           // the other encoder's arrays take the place of this one's
-          uint32_t* cur_word = arrays + 3 * 1024;
-          sh.rec = (WaveRecord*)cur_word; cur_word += 2 * 8;
-          sh.first_tok = cur_word; cur_word += 2;
-          sh.part = cur_word; cur_word += 2;
-          sh.item = cur_word;
-          sh.byte_word = smem + LaneShared::kByteWord;
+          // (the other encoder's arrays take the place of this one's)
+          const BlockShared<1> sh = block_shared<1>(arrays + 3 * 1024, smem + LaneShared::kByteWord);
           encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2 * 1024, sh);
           wave_sync();
         } else {
@@ -834,7 +830,7 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
     encode_chunk(first_item, here, cur);
     if (own_items >= count) break;                     // uniform: the grid's own chunks cover the list
     // (lane 0 adds 1; every lane takes part, so that no lane-dependent branch sits at the loop's edge)
-    const uint32_t claimed = atomicAdd(p.queue_head + p.tier, lane == 0 ? 1u : 0u);
+    const uint32_t claimed = atomicAdd(p.queue_head, lane == 0 ? 1u : 0u);
     first_item = own_items + (uint64_t)uniform(claimed) * per_claim;
     if (first_item >= count) break;                    // uniform
     here = (uint32_t)min((uint64_t)per_claim, count - first_item);

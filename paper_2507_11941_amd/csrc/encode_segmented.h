@@ -477,62 +477,55 @@ __device__ void encode_string_segmented(const EncodeParams& p, int s, uint32_t* 
   block_sync<NW>();                                    // the LDS exchange arrays are reused by the next string
 }
 
-// Persistent workgroups: each claims the next string of its tier until the tier's list is exhausted.
-// SEGMENTED selects encode_string_segmented() (LDS variants with at most 16 positions per lane); SPECIAL
-// compiles in the reading of the special-token marks (EncodeParams::cover must then be set).
-template <int NW, int D, bool STAGED, bool LIMITS, bool SEGMENTED, bool SPECIAL>
-__global__ __launch_bounds__(NW * 64) void encode_kernel(EncodeParams p) {
-  static_assert(!(SEGMENTED && STAGED), "the segmented encoder keeps its arrays in LDS");
-  constexpr int W = NW * 64;
-  extern __shared__ uint32_t smem[];
-  uint32_t* cur = smem;
-  uint32_t *T, *V, *L;
-  if (STAGED) {
-    T = p.staged + (size_t)blockIdx.x * ((LIMITS ? 3u : 2u) * W * D);
-    V = T + W * D;
-    L = V + W * D;
-  } else {
-    T = cur; cur += W * D;
-    V = cur; cur += W * D;
-    L = cur;
-    if (LIMITS) cur += W * D;
-  }
-  // Work items: the first one is my workgroup index, later ones come from the tier's atomic counter (which
-  // starts at zero and is offset by the grid size).  When the grid covers the whole list no atomic is needed.
-  // (With a single variant in use and a grid that covers the batch there is no list at all: item = string.)
-  const uint32_t first = p.list ? p.tier_base[p.tier] : 0u;
-  const uint32_t count = p.list ? p.tier_base[p.tier + 1] - first : p.direct_count;
-  if (blockIdx.x >= count) return;                     // uniform: nothing for this workgroup (often: an empty tier)
+// LDS of a workgroup of the wave-per-item variants, in 32-bit words: the per-position arrays, then what its waves exchange.
+template <int NW, int D, bool STAGED, bool LIMITS>
+constexpr int encode_array_words() { return STAGED ? 0 : (LIMITS ? 3 : 2) * NW * 64 * D; }
+template <int NW>
+constexpr int encode_exchange_words() { return 20 * NW + 4; }
+template <int NW>
+__device__ inline BlockShared<NW> block_shared(uint32_t* cur, const uint32_t* byte_word) {
   BlockShared<NW> sh;
   sh.rec = (WaveRecord*)cur; cur += 2 * NW * 8;        // room for either record type
   sh.first_tok = cur; cur += 2 * NW;
   sh.part = cur; cur += 2 * NW;
-  sh.item = cur; cur += 4;
-  uint32_t* byte_word = cur;
+  sh.item = cur;
   sh.byte_word = byte_word;
-  for (int i = (int)threadIdx.x; i < 256; i += W) byte_word[i] = p.table.byte_word[i];
+  return sh;
+}
 
-  // Warm this XCD's L2 with the merge table.  L2 contents do not survive a kernel boundary, so without this
-  // every first probe of a bucket pays a trip to the Infinity Cache in the middle of a merge pass; here the
-  // same lines come in as one bandwidth-bound stream while the first strings are still being loaded.
-  // Workgroups are dealt to the 8 XCDs round robin, so workgroups b, b+8, b+16, ... share an L2 and split
-  // the table between them.  (Only a hint: a different placement just makes it less effective.)
-  if (p.prefetch_lines > 0) {
-    constexpr uint32_t kXcds = 8;
-    const uint32_t peers = (gridDim.x + kXcds - 1) / kXcds;            // workgroups that share my L2
-    const uint32_t me = blockIdx.x / kXcds;
-    const uint32_t per = (p.prefetch_lines + peers - 1) / peers;        // 128-byte lines for each of them
-    const uint32_t lo = me * per, hi = min(lo + per, p.prefetch_lines);
-    uint32_t sink = 0;
-    for (uint32_t line = lo + threadIdx.x; line < hi; line += W)
-      sink |= __builtin_nontemporal_load((const uint32_t*)p.table.buckets + (size_t)line * 32);
-    if (sink == 0x9E3779B9u && p.prefetch_lines == 0xFFFFFFFFu) byte_word[0] = sink;   // keeps the loads alive
-  }
-  __syncthreads();
+// Warm this XCD's L2 with the merge table.  L2 contents do not survive a kernel boundary, so without this
+// every first probe of a bucket pays a trip to the Infinity Cache in the middle of a merge pass; here the
+// same lines come in as one bandwidth-bound stream while the first strings are still being loaded.
+// Workgroups are dealt to the 8 XCDs round robin, so workgroups b, b+8, b+16, ... share an L2 and split
+// the table between them.  (Only a hint: a different placement just makes it less effective.)
+__device__ inline void warm_table(const EncodeParams& p, uint32_t* scratch) {
+  constexpr uint32_t kXcds = 8;
+  const uint32_t peers = (gridDim.x + kXcds - 1) / kXcds;                // workgroups that share my L2
+  const uint32_t me = blockIdx.x / kXcds;
+  const uint32_t per = (p.prefetch_lines + peers - 1) / peers;            // 128-byte lines for each of them
+  const uint32_t lo = me * per, hi = min(lo + per, p.prefetch_lines);
+  uint32_t sink = 0;
+  for (uint32_t line = lo + threadIdx.x; line < hi; line += blockDim.x)
+    sink |= __builtin_nontemporal_load((const uint32_t*)p.table.buckets + (size_t)line * 32);
+  if (sink == 0x9E3779B9u && p.prefetch_lines == 0xFFFFFFFFu) *scratch = sink;   // keeps the loads alive
+}
 
+// A persistent workgroup's share of a tier: its first item is its own index, later ones come from the tier's atomic counter
+// (which starts at zero and is offset by the grid size) until the tier's list is exhausted.  When the grid covers the whole
+// list no atomic is needed.  SEGMENTED selects encode_string_segmented() (LDS variants with at most 16 positions per
+// lane); SPECIAL compiles in the reading of the special-token marks (EncodeParams::cover must then be set).
+template <int NW, int D, bool STAGED, bool LIMITS, bool SEGMENTED, bool SPECIAL>
+__device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uint32_t count, uint32_t* arrays,
+                                            const BlockShared<NW>& sh) {
+  static_assert(!(SEGMENTED && STAGED), "the segmented encoder keeps its arrays in LDS");
+  constexpr int W = NW * 64;
+  uint32_t* const T = arrays;
+  uint32_t* const V = T + W * D;
+  uint32_t* const L = LIMITS ? V + W * D : V;
+  const int32_t* const list = p.list + p.tier_base[tier];
   uint32_t item = blockIdx.x;
   while (item < count) {
-    const int s = p.list ? (int)uniform((uint32_t)p.list[first + item]) : (int)item;
+    const int s = (int)uniform((uint32_t)list[item]);
     if constexpr (SEGMENTED) encode_string_segmented<NW, D, LIMITS, SPECIAL>(p, s, T, V, L, sh);
     else encode_string<NW, D, STAGED, LIMITS, SPECIAL>(p, s, T, V, L, sh);
     if (gridDim.x >= count) break;                     // uniform: one item per workgroup at most
@@ -541,17 +534,77 @@ __global__ __launch_bounds__(NW * 64) void encode_kernel(EncodeParams p) {
     // next to a single-lane store that ends the previous string, lets the compiler send the other lanes
     // round the loop on their own, past the lane-0 broadcast below.
     uint32_t claimed = 0;
-    if (NW == 1) {
-      claimed = atomicAdd(p.queue_head + p.tier, threadIdx.x == 0 ? 1u : 0u);
-    } else {
-      if (threadIdx.x < 64) claimed = atomicAdd(p.queue_head + p.tier, threadIdx.x == 0 ? 1u : 0u);
-      if (threadIdx.x == 0) *sh.item = claimed;
-      __syncthreads();
-      claimed = *sh.item;
-      __syncthreads();
-    }
+    if (threadIdx.x < 64) claimed = atomicAdd(p.queue_head + tier, threadIdx.x == 0 ? 1u : 0u);
+    if (threadIdx.x == 0) *sh.item = claimed;
+    __syncthreads();
+    claimed = *sh.item;
+    __syncthreads();
     item = gridDim.x + uniform(claimed);               // lane 0's value, as a scalar
   }
+}
+// The same for the strings and pieces that the lane-per-segment kernel has passed on: each wave takes items of its own.
+template <bool SPECIAL>
+__device__ __forceinline__ void encode_passed(const EncodeParams& p, uint32_t count, int n_waves, uint32_t* arrays,
+                                              const BlockShared<1>& sh) {
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t grid = gridDim.x * (uint32_t)n_waves;
+  uint32_t item = wave * gridDim.x + blockIdx.x;       // (few items are spread over the workgroups)
+  while (item < count) {
+    const int s = (int)uniform((uint32_t)p.fallback_list[item]);
+    encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2048, sh);
+    if (grid >= count) break;                          // uniform
+    // (all lanes take part, as above)
+    item = grid + uniform(atomicAdd(p.fallback_queue, (threadIdx.x & 63) == 0 ? 1u : 0u));
+  }
+}
+
+// What one wave or four encode: the items passed on, up to 1 KiB, then tier 1, up to 4 KiB, if it is there.  One launch for
+// both: mostly there is nothing to do, and a launch costs 3 to 4 us (one document of 60,001 bytes: 46 us with a launch for
+// each of four variants); where there is, a wave that finds no more of the first goes on to the second.
+constexpr int kShortArrayWords = encode_array_words<4, 16, false, true>();
+constexpr int kShortWords = kShortArrayWords + 4 * encode_exchange_words<1>() + encode_exchange_words<4>() + 256;
+template <bool SPECIAL>
+__global__ __launch_bounds__(256) void encode_short_kernel(EncodeParams p) {
+  static_assert(4 * encode_array_words<1, 16, false, true>() <= kShortArrayWords, "four one-wave items in the space of one");
+  extern __shared__ __align__(16) uint32_t smem[];
+  const uint32_t passed = *p.fallback_count;
+  const uint32_t count = p.n_tiers > 1 ? p.tier_base[2] - p.tier_base[1] : 0u;
+  if (blockIdx.x >= passed && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
+  uint32_t* const byte_word = smem + kShortWords - 256;
+  byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
+  if (p.prefetch_lines > 0 && blockIdx.x < count) warm_table(p, byte_word);
+  __syncthreads();
+  const int wave = (int)threadIdx.x >> 6;
+  uint32_t* const exchange = smem + kShortArrayWords;
+  encode_passed<SPECIAL>(p, passed, 4, smem + wave * encode_array_words<1, 16, false, true>(),
+                         block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word));
+  if (blockIdx.x >= count) return;                     // uniform
+  __syncthreads();                                     // the arrays are used again
+  encode_tier<4, 16, false, true, true, SPECIAL>(p, 1, count, smem,
+                                                 block_shared<4>(exchange + 4 * encode_exchange_words<1>(), byte_word));
+}
+
+// What sixteen waves encode: tier 2, up to 16 KiB, in LDS (two arrays: three of 16 Ki words would not fit), and tier 3, up to
+// 64 KiB, whose arrays are a slab in HBM.
+constexpr int kLongArrayWords = encode_array_words<16, 16, false, false>();
+constexpr int kLongWords = kLongArrayWords + encode_exchange_words<16>() + 256;
+constexpr int kStagedWords = 3 * 16 * 64 * 64;         // of a slab
+template <bool SPECIAL>
+__global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
+  extern __shared__ __align__(16) uint32_t smem[];
+  const uint32_t longest = p.n_tiers > 3 ? p.tier_base[4] - p.tier_base[3] : 0u;
+  const uint32_t count = p.tier_base[3] - p.tier_base[2];
+  if (blockIdx.x >= longest && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
+  uint32_t* const byte_word = smem + kLongWords - 256;
+  if (threadIdx.x < 256) byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
+  if (p.prefetch_lines > 0) warm_table(p, byte_word);
+  __syncthreads();
+  const BlockShared<16> sh = block_shared<16>(smem + kLongArrayWords, byte_word);
+  if (blockIdx.x < longest) {                          // uniform
+    encode_tier<16, 64, true, true, false, SPECIAL>(p, 3, longest, p.staged + (size_t)blockIdx.x * kStagedWords, sh);
+    __syncthreads();
+  }
+  encode_tier<16, 16, false, false, true, SPECIAL>(p, 2, count, smem, sh);
 }
 
 // LDS is handed out in blocks, and the occupancy the runtime reports is for the bytes asked for: for 9,552 bytes it
@@ -561,10 +614,5 @@ __global__ __launch_bounds__(NW * 64) void encode_kernel(EncodeParams p) {
 // and the reported figure is the true one.
 constexpr size_t kLdsBlockBytes = 1280;
 constexpr size_t lds_blocks(size_t bytes) { return (bytes + kLdsBlockBytes - 1) / kLdsBlockBytes * kLdsBlockBytes; }
-
-template <int NW, int D, bool STAGED, bool LIMITS>
-constexpr size_t encode_lds_bytes() {
-  return lds_blocks(sizeof(uint32_t) * ((STAGED ? 0 : (LIMITS ? 3 : 2) * NW * 64 * D) + 20 * NW + 4 + 256));
-}
 
 }  // namespace bpe

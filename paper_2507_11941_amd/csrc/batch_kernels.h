@@ -578,45 +578,161 @@ __global__ __launch_bounds__(256) void piece_scatter_kernel(TierPlan plan, int r
   }
 }
 
-// piece_hist_kernel, piece_scan_kernel and piece_scatter_kernel in one workgroup, for batches of at most
-// kSmallSlots slots (a launch costs more than the work of a small batch).  Thread t takes slots t, t + 1024, ...
+// The whole listing of a batch of at most kSmallSlots slots in one workgroup: slots, cuts, piece lengths, work list.  A launch
+// costs more than the work of a small batch, and what bounds this one is a chain of some ten memory and LDS round trips.
+// Each piece is an item.  Positions fit 32 bits: so few slots are less than 4 MiB.  Thread t takes the strings 4 t ... 4 t + 3
+// and the slots t, t + 1024, ...; a slot's cut is searched by its thread, sixteen candidates a round: the seventeen bytes
+// around them come in one load of 16 and one of 1, and the bit set of the cuts from LDS.
 constexpr int kSmallSlots = 4096;
-__global__ __launch_bounds__(1024) void piece_list_small_kernel(const int64_t* offsets, TierPlan plan, int room, Control* c,
-                                                                const int32_t* slot_base, const int32_t* slot_string,
-                                                                const int64_t* piece_begin, int32_t* piece_len,
-                                                                int32_t* counts, int32_t* group_ids, int32_t* list,
-                                                                ItemDesc* desc) {
-  __shared__ uint32_t hist[kBinKeys], scan[kBinKeys];
-  const int t = threadIdx.x;
-  if (t < kBinKeys) hist[t] = 0;
-  __syncthreads();
-  const uint32_t n_slots = c->n_slots;
+__global__ __launch_bounds__(1024) void small_list_kernel(const uint8_t* bytes, const int64_t* offsets, int batch,
+                                                          const uint32_t* cut_bits, const uint8_t* cover, int piece_target,
+                                                          int max_string, TierPlan plan, Control* c, int32_t* slot_string,
+                                                          int64_t* piece_begin, int32_t* piece_len, int32_t* counts,
+                                                          int32_t* list, ItemDesc* desc) {
   constexpr int kPer = kSmallSlots / 1024;
+  __shared__ uint32_t cuts[2048];
+  __shared__ int32_t string_begin[kSmallSlots + 1], first_slot[kSmallSlots + 1], begin[kSmallSlots];
+  __shared__ uint32_t hist[kBinKeys], scan[kBinKeys], wave_sum[16];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (t < 512) ((uint4*)cuts)[t] = ((const uint4*)cut_bits)[t];
+  if (t < kBinKeys) hist[t] = 0;
+  // ---- slots: how many each string has, and their scan ----
+  int32_t at[kPer + 1];
+  uint32_t slots[kPer], own = 0;
+#pragma unroll
+  for (int i = 0; i <= kPer; ++i) at[i] = (int32_t)offsets[min(kPer * t + i, batch)];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    slots[i] = kPer * t + i < batch ? slots_of_length((int64_t)at[i + 1] - at[i], piece_target, max_string) : 0u;
+    own += slots[i];
+  }
+  uint32_t upto = own;
+  for (int step = 1; step < 64; step <<= 1) {
+    const uint32_t o = (uint32_t)__shfl_up((int)upto, step, 64);
+    if (lane >= step) upto += o;
+  }
+  if (lane == 63) wave_sum[wave] = upto;
+  __syncthreads();
+  uint32_t all = 0, place = upto - own;
+  for (int w = 0; w < 16; ++w) {
+    if (w < wave) place += wave_sum[w];
+    all += wave_sum[w];
+  }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (kPer * t + i <= batch) {
+      string_begin[kPer * t + i] = at[i];
+      first_slot[kPer * t + i] = (int32_t)place;
+    }
+    place += slots[i];
+  }
+  if (t == 1023 && batch == kSmallSlots) {
+    string_begin[kSmallSlots] = at[kPer];
+    first_slot[kSmallSlots] = (int32_t)place;
+  }
+  const int n_slots = (int)min(all, (uint32_t)kSmallSlots);
+  __syncthreads();
+  // ---- where each slot's piece starts ----
+  int owner[kPer];
+  int32_t start[kPer], from[kPer];                     // from: the highest candidate of the next round; 0: not searching
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int g = t + 1024 * j;
+    owner[j] = 0;
+    start[j] = -1;                                     // void unless a cut is found
+    from[j] = 0;
+    if (g < n_slots) {
+      int lo = 0, hi = batch - 1;                      // the last string whose first slot is <= g
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (first_slot[mid] <= g) lo = mid; else hi = mid - 1;
+      }
+      owner[j] = lo;
+      const int32_t first = string_begin[lo], len = string_begin[lo + 1] - first;
+      const int i = g - first_slot[lo];
+      if (len < 0 || len > max_string) continue;       // not encodable: the string yields no tokens
+      if (i == 0) start[j] = first;
+      else from[j] = first + i * piece_target;         // (at least twice the window: the search stays inside the string)
+    }
+  }
+  for (int round = 0; round < kCutWindow / 16; ++round) {
+    uint4 v[kPer], m[kPer];
+    uint32_t v4[kPer], m4[kPer];
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      v[j] = m[j] = make_uint4(0, 0, 0, 0);
+      v4[j] = m4[j] = 0;
+      if (from[j]) {
+        __builtin_memcpy(&v[j], bytes + from[j] - 16, 16);
+        v4[j] = bytes[from[j]];
+        if (cover) {
+          __builtin_memcpy(&m[j], cover + from[j] - 16, 16);
+          m4[j] = cover[from[j]];
+        }
+        any = true;
+      }
+    }
+    if (!__ballot(any)) break;                         // uniform
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      if (from[j]) {
+        const uint32_t w[5] = {v[j].x, v[j].y, v[j].z, v[j].w, v4[j]};
+        const uint32_t mark[5] = {m[j].x, m[j].y, m[j].z, m[j].w, m4[j]};
+        uint32_t found = 0;                            // bit i: a cut before byte from - 15 + i
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const uint32_t pair = (i & 3) == 3 ? __builtin_amdgcn_alignbit(w[(i >> 2) + 1], w[i >> 2], 24u) : w[i >> 2] >> (8 * (i & 3));
+          uint32_t cut = (cuts[(pair >> 5) & 2047u] >> (pair & 31u)) & 1u;
+          if (cover) {                                 // special tokens: their ends are cuts, their inside is not
+            const uint32_t two = ((i & 3) == 3 ? __builtin_amdgcn_alignbit(mark[(i >> 2) + 1], mark[i >> 2], 24u)
+                                               : mark[i >> 2] >> (8 * (i & 3))) & 0xFFFFu;
+            if (two) cut = 1u;
+            if (two >> 8 == kCoverRest) cut = 0u;
+          }
+          found |= cut << i;
+        }
+        if (found) {
+          start[j] = from[j] - 15 + (31 - __builtin_clz(found));         // the last one
+          from[j] = 0;
+        } else {
+          from[j] -= 16;
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (t + 1024 * j < n_slots) begin[t + 1024 * j] = start[j];
+  __syncthreads();
+  // ---- the pieces: to the next one of their string, or to the string's end ----
   int32_t len[kPer];
   int key[kPer];
   uint32_t rank[kPer];
-  int64_t start[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const uint32_t g = (uint32_t)t + 1024u * j;
+    const int g = t + 1024 * j;
     len[j] = 0;
     key[j] = -1;
     rank[j] = 0;
-    start[j] = -1;
     if (g < n_slots) {
-      start[j] = piece_begin[g];
-      const int s = slot_string[g];
+      const bool head = first_slot[owner[j]] == g;
       if (start[j] >= 0) {
-        len[j] = (int32_t)(piece_end(offsets, s, g, slot_base, piece_begin, piece_len) - start[j]);
+        const int end = first_slot[owner[j] + 1];
+        int h = g + 1;
+        while (h < end && begin[h] < 0) {              // (the slots that it runs over get their shares of the copying)
+          piece_len[h] = g - h;
+          ++h;
+        }
+        len[j] = (h < end ? begin[h] : string_begin[owner[j] + 1]) - start[j];
+        key[j] = bin_key(len[j], plan);
+        if (key[j] >= 0) rank[j] = atomicAdd(&hist[key[j]], 1u);
       }
-      if (start[j] >= 0 || slot_base[s] == (int32_t)g) piece_len[g] = len[j];
-      if (start[j] < 0 || bin_key(len[j], plan) < 0) counts[g] = 0;       // void slot, or too long for the launched variants
-      group_ids[g] = -1;
+      if (start[j] >= 0 || head) piece_len[g] = len[j];
+      piece_begin[g] = start[j];
+      slot_string[g] = head ? owner[j] : -1;
+      if (key[j] < 0) counts[g] = 0;                   // void slot, or too long for the launched variants
     }
-    const PieceItem item = piece_item(start[j], len[j], g & ~63u, n_slots, plan, room);
-    key[j] = item.key;
-    len[j] = item.len;
-    if (key[j] >= 0) rank[j] = atomicAdd(&hist[key[j]], 1u);
   }
   __syncthreads();
   if (t < kBinKeys) scan[t] = hist[t];
@@ -629,12 +745,17 @@ __global__ __launch_bounds__(1024) void piece_list_small_kernel(const int64_t* o
     __syncthreads();
   }
   if (t <= kMaxTiers) c->tier_base[t] = t == 0 ? 0 : scan[(t <= plan.n_tiers ? t : plan.n_tiers) * kLenBuckets - 1];
+  if (t < kMaxTiers) c->queue_head[t] = 0;
+  if (t < 2) c->fallback_range[t] = 0;
+  if (t == 2) c->fallback_queue = 0;
+  if (t == 3) c->n_slots = (uint32_t)n_slots;
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     if (key[j] >= 0) {
+      const int g = t + 1024 * j;
       const uint32_t pos = scan[key[j]] - hist[key[j]] + rank[j];
-      list[pos] = (int32_t)((uint32_t)t + 1024u * j);
-      desc[pos] = ItemDesc{start[j], len[j], (int32_t)((uint32_t)t + 1024u * j)};
+      list[pos] = g;
+      desc[pos] = ItemDesc{start[j], key[j] < kLenBuckets ? len[j] | 1 << kGroupShift : len[j], g};
     }
   }
 }
@@ -713,41 +834,6 @@ __global__ __launch_bounds__(1024) void slot_offsets_kernel(const int32_t* count
     if (tid == 1023) carry_s = before + v;
     __syncthreads();
   }
-}
-
-// tile_sum_kernel, tile_scan_kernel and slot_offsets_kernel in one workgroup, for at most kSmallSlots slots.
-__global__ __launch_bounds__(1024) void slot_offsets_small_kernel(const int32_t* counts, const Control* c,
-                                                                  const int32_t* slot_base, const int32_t* slot_string,
-                                                                  int64_t* slot_out, int64_t* out_offsets, int batch) {
-  __shared__ int64_t wave_sum[16];
-  __shared__ int64_t carry_s;
-  const uint32_t n_slots = c->n_slots;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) carry_s = 0;
-  __syncthreads();
-  for (int j = 0; j < kSmallSlots / 1024; ++j) {
-    const uint32_t g = (uint32_t)j * 1024u + (uint32_t)tid;
-    const int64_t m = g < n_slots ? (int64_t)counts[g] : 0;
-    int64_t v = m;
-    for (int step = 1; step < 64; step <<= 1) {
-      const int64_t o = __shfl_up(v, step, 64);
-      if (lane >= step) v += o;
-    }
-    if (lane == 63) wave_sum[wave] = v;
-    __syncthreads();
-    int64_t before = carry_s;
-    for (int w = 0; w < wave; ++w) before += wave_sum[w];
-    if (g < n_slots) {
-      const int64_t at = before + v - m;
-      slot_out[g] = at;
-      const int s = slot_string[g];
-      if ((uint32_t)slot_base[s] == g) out_offsets[s] = at;   // a string starts at its first slot
-    }
-    __syncthreads();
-    if (tid == 1023) carry_s = before + v;
-    __syncthreads();
-  }
-  if (tid == 0) out_offsets[batch] = carry_s;
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -988,6 +1074,68 @@ __global__ __launch_bounds__(256) void piece_pack_kernel(const int32_t* tmp_ids,
     g = g_next;
     a = a_next;
     b = b_next;
+  }
+}
+
+// Offsets and packing of a batch of at most kSmallSlots slots in one launch: a workgroup sums the counts before its four
+// slots itself, four loads of 16 bytes a thread at most, and each of its waves copies one.
+__global__ __launch_bounds__(256) void small_pack_kernel(const int32_t* tmp_ids, const Control* c, const int32_t* slot_string,
+                                                         const int64_t* piece_begin, const int32_t* piece_len,
+                                                         const int32_t* counts, int64_t* out_offsets, int batch,
+                                                         int32_t* out_ids, const int32_t* id_map) {
+  __shared__ int32_t wave_sum[4];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int n_slots = (int)c->n_slots;
+  const int g = 4 * (int)blockIdx.x + wave;
+  if (4 * (int)blockIdx.x >= n_slots) return;          // uniform
+  int32_t before = 0;
+  for (int q = t; q < (int)blockIdx.x; q += 256) {
+    const int4 v = ((const int4*)counts)[q];
+    before += (v.x + v.y) + (v.z + v.w);
+  }
+  for (int step = 32; step >= 1; step >>= 1) before += __shfl_xor(before, step, 64);
+  if (lane == 0) wave_sum[wave] = before;
+  int k = 0, own = 0;                                  // this slot's ids, and those of the workgroup's slots before it
+  for (int w = 0; w <= wave; ++w) {
+    const int n = 4 * (int)blockIdx.x + w < n_slots ? counts[4 * blockIdx.x + w] : 0;
+    if (w < wave) own += n; else k = n;
+  }
+  __syncthreads();
+  if (g >= n_slots) return;
+  int64_t dst = (int64_t)wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3] + own;
+  const int s = slot_string[g];
+  if (lane == 0) {
+    if (s >= 0) out_offsets[s] = dst;                  // a string starts at its first slot
+    if (g == n_slots - 1) out_offsets[batch] = dst + k;
+  }
+  int64_t src = piece_begin[g];
+  if (src < 0) {                                       // a void slot: its share of the piece that runs over it, whose ids end here
+    const int back = piece_len[g];
+    if (back < 0) {
+      const int skip = -back * kPackShare;
+      const int all = counts[g + back];
+      dst += skip - all;
+      src = piece_begin[g + back] + skip;
+      k = all - skip;
+    }
+  }
+  k = min(k, kPackShare);
+  for (int i0 = 0; i0 < k; i0 += 256) {
+    int32_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + 64 * u + lane;
+      v[u] = i < k ? tmp_ids[src + i] : 0;             // (token 0 exists in every table)
+    }
+    if (id_map) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = id_map[v[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + 64 * u + lane;
+      if (i < k) out_ids[dst + i] = v[u];
+    }
   }
 }
 

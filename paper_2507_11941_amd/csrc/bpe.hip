@@ -579,6 +579,8 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const int room = small_items ? -1
                                : (int)std::min<int64_t>(total_bytes / std::max(1, listed.max_grid * listed.waves * 3 / 4) +
                                                             total_bytes / w.max_slots / 2, kGroupBytes);
+  const bool small_split = w.split && small_items && w.max_slots <= kSmallSlots;
+  const uint32_t* cuts = (const uint32_t*)table->d_words;
   if (direct) {
     list = nullptr;
   } else if (singles) {
@@ -598,20 +600,19 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     int32_t* ss = (int32_t*)(ws + w.slot_string);
     int64_t* pb = (int64_t*)(ws + w.piece_begin);
     int32_t* pl = (int32_t*)(ws + w.piece_len);
-    int32_t* gi = (int32_t*)(ws + w.group_ids);
-    const uint32_t* byte_pair =
-        (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes) + 256;
-    const int per_slot_grid = (int)std::min<int64_t>((w.max_slots + 255) / 256, 256);   // (each workgroup ends with a few global atomics)
-    hipLaunchKernelGGL(slot_layout_kernel, dim3((unsigned)((batch + 1023) / 1024)), dim3(1024), 0, stream, offsets, batch, kPieceTarget,
-                       BPE_MAX_STRING_BYTES, ctrl, sb, ss);
-    hipLaunchKernelGGL(cut_search_kernel, dim3((unsigned)((w.max_slots + 4 * kCutSlotsPerWave - 1) / (4 * kCutSlotsPerWave))), dim3(256), 0, stream, bytes,
-                       offsets, byte_pair, kPieceTarget, BPE_MAX_STRING_BYTES, ctrl, sb, ss, pb, cover);
-    if (w.max_slots <= kSmallSlots) {
-      hipLaunchKernelGGL(piece_list_small_kernel, dim3(1), dim3(1024), 0, stream, offsets, plan, room, ctrl, sb, ss, pb, pl,
-                         counts, gi, list, (ItemDesc*)(ws + w.list_desc));
+    if (small_split) {
+      hipLaunchKernelGGL(small_list_kernel, dim3(1), dim3(1024), 0, stream, bytes, offsets, batch, cuts, cover, kPieceTarget,
+                         BPE_MAX_STRING_BYTES, plan, ctrl, ss, pb, pl, counts, list, (ItemDesc*)(ws + w.list_desc));
     } else {
+      const uint32_t* byte_pair = (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes) + 256;
+      const int per_slot_grid = (int)std::min<int64_t>((w.max_slots + 255) / 256, 256);   // (each workgroup ends with a few global atomics)
+      group_ids = (int32_t*)(ws + w.group_ids);
+      hipLaunchKernelGGL(slot_layout_kernel, dim3((unsigned)((batch + 1023) / 1024)), dim3(1024), 0, stream, offsets, batch, kPieceTarget,
+                         BPE_MAX_STRING_BYTES, ctrl, sb, ss);
+      hipLaunchKernelGGL(cut_search_kernel, dim3((unsigned)((w.max_slots + 4 * kCutSlotsPerWave - 1) / (4 * kCutSlotsPerWave))), dim3(256), 0, stream, bytes,
+                         offsets, byte_pair, kPieceTarget, BPE_MAX_STRING_BYTES, ctrl, sb, ss, pb, cover);
       hipLaunchKernelGGL(piece_hist_kernel, dim3(per_slot_grid), dim3(256), 0, stream, offsets, plan, room, ctrl, sb, ss,
-                         pb, pl, counts, gi);
+                         pb, pl, counts, group_ids);
       hipLaunchKernelGGL(piece_scan_kernel, dim3(1), dim3(256), 0, stream, ctrl, plan.n_tiers);
       hipLaunchKernelGGL(piece_scatter_kernel, dim3((unsigned)((w.max_slots + 256 * kScatterPer - 1) / (256 * kScatterPer))), dim3(256), 0, stream, plan,
                          room, ctrl, pb, pl, list, (ItemDesc*)(ws + w.list_desc));
@@ -620,7 +621,6 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     piece_len = pl;
     slot_base = sb;
     slot_string = ss;
-    group_ids = gi;
   }
 
   EncodeParams p;
@@ -628,7 +628,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.table.byte_word = (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes);
   p.table.byte_pair = p.table.byte_word + 256;
   p.table.log2_buckets = table->log2_buckets;
-  p.table.cuts = (const uint32_t*)table->d_words;
+  p.table.cuts = cuts;
   p.table.word_buckets = (const uint4*)(p.table.cuts + 2048);
   p.table.word_keys = p.table.word_buckets + ((size_t)1 << table->log2_word_buckets);
   p.table.log2_word_buckets = table->log2_word_buckets;
@@ -687,18 +687,16 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     const int grid = (int)std::min<int64_t>(((int64_t)batch + 3) / 4, 8192);        // (there are fewer groups than strings)
     hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, offsets, out_offsets, ctrl,
                        (const ItemDesc*)(ws + w.list_desc), out_ids, table->d_id_map);
+  } else if (small_split) {
+    hipLaunchKernelGGL(small_pack_kernel, dim3((unsigned)((w.max_slots + 3) / 4)), dim3(256), 0, stream, tmp_ids, ctrl, slot_string,
+                       piece_begin, piece_len, counts, out_offsets, batch, out_ids, table->d_id_map);
   } else {
     int64_t* tile_sum = (int64_t*)(ws + w.tile_sum);
     int64_t* slot_out = (int64_t*)(ws + w.slot_out);
-    if (w.max_slots <= kSmallSlots) {
-      hipLaunchKernelGGL(slot_offsets_small_kernel, dim3(1), dim3(1024), 0, stream, counts, ctrl, slot_base, slot_string,
-                         slot_out, out_offsets, batch);
-    } else {
-      hipLaunchKernelGGL(tile_sum_kernel, dim3(w.n_tiles), dim3(1024), 0, stream, counts, ctrl, tile_sum);
-      hipLaunchKernelGGL(tile_scan_kernel, dim3(1), dim3(64), 0, stream, tile_sum, w.n_tiles, ctrl, out_offsets, batch);
-      hipLaunchKernelGGL(slot_offsets_kernel, dim3(w.n_tiles), dim3(1024), 0, stream, counts, ctrl, tile_sum, slot_base,
-                         slot_string, slot_out, out_offsets);
-    }
+    hipLaunchKernelGGL(tile_sum_kernel, dim3(w.n_tiles), dim3(1024), 0, stream, counts, ctrl, tile_sum);
+    hipLaunchKernelGGL(tile_scan_kernel, dim3(1), dim3(64), 0, stream, tile_sum, w.n_tiles, ctrl, out_offsets, batch);
+    hipLaunchKernelGGL(slot_offsets_kernel, dim3(w.n_tiles), dim3(1024), 0, stream, counts, ctrl, tile_sum, slot_base,
+                       slot_string, slot_out, out_offsets);
     const int grid = (int)std::min<int64_t>((w.max_slots + 7) / 8, 32768);   // two pieces per wave and round
     hipLaunchKernelGGL(piece_pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, ctrl, piece_begin, piece_len,
                        counts, group_ids, slot_out, out_ids, table->d_id_map);

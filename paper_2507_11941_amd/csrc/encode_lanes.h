@@ -26,9 +26,9 @@
 // words to emit run over as many segments at a time as the arena and the lists hold: in text, all of the item's.
 //
 // What bounds it is instruction issue: some 1,700 vector and 900 scalar instructions per KiB of text, of which the merge
-// loop is two fifths, on three or four waves a SIMD.  With every segment going through the merges, one item of 1 KiB a wave
+// loop is two fifths, on four waves a SIMD.  With every segment going through the merges, one item of 1 KiB a wave
 // (14.9 trips of the loop per KiB instead of 6.3), the 65,536 documents of the throughput workload took 1,480 us in this
-// kernel; they take 1,060.
+// kernel; they take 920.
 #pragma once
 #include "encode_segmented.h"
 
@@ -40,22 +40,29 @@ constexpr uint32_t kLaneChunk = 4;              // work items a wave claims at a
                                                 // 270,000 pieces of the throughput workload, 2: 2.2, 4: 2.1, 8: 2.1);
                                                 // twice as many when the list holds 32 or more items per wave
 
-// Pair values as the lanes keep them: the table's value (rank in bits 12..31, the two operand-capability flags
-// in bits 10 and 11) with the pair's position in its segment in the bits below, so that the lowest value says where it is.
+// What the lanes keep of a segment is one word for each of its positions.  It is the value of the pair that begins there,
+// with the position in its lowest bits, so that the lowest value says where it is:
+//   bits 0..4 position in the segment, 5 and 6 the merged token can be a left / right operand, 7..26 rank
+// or, behind a token that merges have made (the position after its first is always a dead one), that token's word:
+//   bits 0..19 id, 20 and 21 it can be a left / right operand, 31 set (above every pair)
+// A token that no merge has made is its byte, which is still in the text.
 constexpr uint32_t kLaneNoPair = 0xFFFFFFFFu;
 constexpr uint32_t kLaneNoTag = 0xF8000000u;    // no slot's tag: fingerprints have 27 bits, an empty slot is all ones
-constexpr uint32_t kLaneNowhere = 0xFFFFFFFFu;  // no position
-constexpr uint32_t kLaneInvalid = 0xFFFFE000u;  // values from here on are no pair (ranks stay below 0xFFFFE)
+constexpr uint32_t kLaneInvalid = 0xFFFFEu << 7;       // values from here on are no pair (ranks stay below 0xFFFFE)
+constexpr uint32_t kLaneCanLeft = 1u << 20, kLaneCanRight = 1u << 21;
 
-__device__ inline uint32_t lane_value(uint32_t v, uint32_t position) { return (v & ~((1u << 10) - 1u)) | position; }
-__device__ inline uint32_t lane_merged_word(uint32_t lv) {
-  static_assert(kFlagLeft == 1u << 10 && kFlagRight == 1u << 11 && (kFlagLeft << 20) == kTokCanLeft &&
-                (kFlagRight << 20) == kTokCanRight, "flag positions");
-  return (256u + (lv >> kRankShift)) | ((lv & (kFlagLeft | kFlagRight)) << 20);
+__device__ inline uint32_t lane_value(uint32_t v, uint32_t position) {
+  static_assert(kFlagLeft == 1u << 10 && kFlagRight == 1u << 11 && kRankShift == 12, "flag positions");
+  return ((v >> 10) << 5) | position;
 }
+__device__ inline uint32_t lane_merged_word(uint32_t lv) {
+  return ((lv >> 7) + (256u | 1u << 31)) | ((lv & 0x60u) << 15);
+}
+// (a byte that no row can use costs a look-up that finds nothing; asking for its bits costs another LDS round trip)
+__device__ inline uint32_t lane_byte_word(uint32_t byte) { return byte | kLaneCanLeft | kLaneCanRight; }
 
 // What becomes of a segment: its token's number, or one of these.
-constexpr uint32_t kRecJob = 1u << 30;          // | its first position in the arena, where its tokens are
+constexpr uint32_t kRecJob = 1u << 30;          // | its place among the jobs in the text's order
 constexpr uint32_t kRecNone = 1u << 31;         // no token
 
 // LDS of a workgroup, in 32-bit words: read-only, shared by its waves.
@@ -67,36 +74,37 @@ struct LaneShared {
 };
 // Shape of a workgroup, and the LDS of one of its waves.  WAVES: they take items of their own; BYTES: an item's capacity;
 // LIST: segments listed at a time; JOBS: those of them that need merges; ARENA: the bytes of those, in fours.  What bounds
-// the number of waves is LDS.  Twice as long an item takes less than half as many trips of the merge loop for each of its
-// bytes (5.4 instead of 12.2 per KiB: the longest chain of merges is 10 long in either), which is why a large batch does
-// with 12 waves a CU; a small one wants each piece of text to have a wave, and 16 of them.
+// the number of waves is LDS, and what bounds the kernel is how many waves there are to wait at once: 65,536 documents take
+// 1,554 us with 8 waves a CU, 1,379 with 10, 1,232 with 12 (that was with the tokens in a second array beside V) and 1,107
+// with the 16 that one array leaves room for.  Twice as long an item takes less than half as many trips of the merge loop
+// for each of its bytes (5.4 instead of 12.2 per KiB: the longest chain of merges is 10 long in either): the same batch in
+// items of 1 KiB took 1,443 instead of 1,232.  A small batch wants each piece of text to have a wave.
 template <int BYTES, int WAVES, int LIST, int JOBS, int ARENA, int AT_LEAST>
 struct LaneShape {
   static constexpr int kBytes = BYTES, kWaves = WAVES, kListed = LIST, kMostJobs = JOBS, kArena = ARENA;
   static constexpr int kText = 0;                                       // the item's bytes; a key's words reach beyond them
-  static constexpr int kRec = kText;                                    // once they are in the arena: what becomes of a segment
   static constexpr int kStrings = kText + BYTES / 4 + 8;                // (groups) bit p: a string starts at p
   static constexpr int kList = kStrings + BYTES / 32;                   // uint16 first position of a segment
-  static constexpr int kJobs = kList + LIST / 2 + 2;                    // uint16 arena position | (length - 1) << 11
-  static constexpr int kHist = kJobs + JOBS / 2;                        // jobs of each length, then list bases
-  static constexpr int kSorted = kHist + 32;                            // the jobs, sorted
-  static constexpr int kT = (kSorted + JOBS + 3) / 4 * 4;               // token word of every arena position
-  static constexpr int kV = kT + ARENA;                                 // pair value
+  static constexpr int kJobs = kList + LIST / 2 + 2;                    // the jobs sorted: first position | (length - 1) << 11 |
+                                                                        //   place << 16, then arena position / 4 << 16 instead
+  static constexpr int kPlaces = kJobs + JOBS;                          // uint16 arena position of the jobs in the text's order
+  static constexpr int kHist = kPlaces + JOBS / 2;                      // jobs of each length, then list bases
+  static constexpr int kV = (kHist + 32 + 3) / 4 * 4;                   // a word for every arena position
   static constexpr int kIdle = kV + ARENA;                              // what a lane without a segment reads and writes
   static constexpr int kEnd = kIdle + 4;
   // before the arena is used:
   static constexpr int kStarts = kV;                                    // bit p: a segment starts at p, or the item ends
-  static constexpr int kFound = kV;                                     // what becomes of a segment
-  static constexpr int kFirstJobs = kT;                                 // the jobs in the text's order
+  static constexpr int kFirstJobs = kV;                                 // the jobs in the text's order
+  static constexpr int kFound = kV + JOBS;                              // what becomes of a segment
   static constexpr int kWords = ((kEnd > AT_LEAST ? kEnd : AT_LEAST) + 3) / 4 * 4;
   static constexpr size_t kLdsBytes = lds_blocks(sizeof(uint32_t) * (LaneShared::kWords + WAVES * kWords));
   static_assert(kText % 4 == 0 && ARENA % 4 == 0, "wide loads and stores");
   static_assert(ARENA <= 2048 && BYTES <= 2048 && BYTES % 1024 == 0 && LIST % 64 == 0 && LIST <= 512 && JOBS % 64 == 0,
                 "fields of the packed words; a lane per word of the bitmap");
-  static_assert(JOBS <= ARENA && LIST <= ARENA && BYTES / 32 + 4 <= ARENA && LIST <= BYTES / 4 + 8, "what shares a place fits it");
+  static_assert(JOBS + LIST <= ARENA && BYTES / 32 + 4 <= ARENA, "what shares a place fits it");
   static_assert(kLdsBytes <= 160 * 1024, "one workgroup a CU");
 };
-using LargeItems = LaneShape<kGroupBytes, 12, 448, 256, 992, 0>;
+using LargeItems = LaneShape<kGroupBytes, 16, 448, 256, 1152, 0>;
 using SmallItems = LaneShape<kMemberBytes, 16, 256, 128, 704, 0>;
 // (the arrays of the one-wave encoder that takes a string over)
 constexpr int kOtherWords = encode_array_words<1, 16, false, true>() + encode_exchange_words<1>();
@@ -111,15 +119,21 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Where a segment that is done keeps its place in the output, its tokens being the mask in its first word: at its second
+// token, whose pair no longer counts, or behind the one token's word (a segment has four words at least).
+__device__ inline uint32_t lane_spare(uint32_t tokens) {
+  return tokens & (tokens - 1u) ? (uint32_t)__builtin_ctz(tokens & (tokens - 1u)) : 2u;
+}
+
 // A look-up in the merge table on its way: two start at the end of every trip of the merge loop.
 struct LaneProbe {
   uint4 q;                                             // the home bucket: two slots of {value, tag}
   uint32_t bucket, tag;                                // kLaneNoTag: no look-up
 };
 __device__ inline void lane_probe_start(const DeviceTable& t, uint32_t xw, uint32_t yw, LaneProbe& f) {
-  static_assert(kTokCanLeft == 1u << 30 && kTokCanRight == 1u << 31, "one bit beside the other");
+  static_assert(kLaneCanLeft << 1 == kLaneCanRight, "one bit beside the other");
   f.tag = kLaneNoTag;
-  if ((int32_t)((xw << 1) & yw) < 0) {                 // the left token can be a left operand, the right one a right one
+  if ((xw << 1) & yw & kLaneCanRight) {                // the left token can be a left operand, the right one a right one
     const Placement pl = place_pair(xw & kTokIdMask, yw & kTokIdMask, t.log2_buckets);
     f.bucket = pl.bucket;
     f.tag = slot_tag(pl.fingerprint, 0);
@@ -200,12 +214,10 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
   uint32_t* const starts = lds + L::kStarts;
   uint32_t* const strings = lds + L::kStrings;
   uint16_t* const list = (uint16_t*)(lds + L::kList);
-  uint16_t* const jobs = (uint16_t*)(lds + L::kJobs);
+  uint32_t* const jobs = lds + L::kJobs;
+  uint16_t* const places = (uint16_t*)(lds + L::kPlaces);
   uint32_t* const hist = lds + L::kHist;
-  uint32_t* const T = lds + L::kT;
   uint32_t* const V = lds + L::kV;
-  uint32_t* const rec = lds + L::kRec;
-  uint32_t* const sorted = lds + L::kSorted;
 
   if (n <= 0 || n > L::kBytes) {                  // uniform; too long only if max_len was wrong
     if constexpr (GROUPS) {
@@ -346,7 +358,6 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
   uint32_t total = 0;                                  // tokens of the segments done (uniform)
   uint32_t tokens_before = 0;                          // (groups) of string `lane`
   uint32_t lack = 0;                                   // (apart) what the place of a token lacks to its string's own
-  bool text_gone = false;                              // its place in LDS has been used (uniform)
   uint32_t listed_before = 0;                          // segments of earlier lists (uniform)
   uint32_t my_segment = 0xFFFFFFFFu;                   // (groups) the one that string `lane` starts with
   if constexpr (GROUPS) {
@@ -379,16 +390,6 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     listed_before = listed_upto;
 
     for (int i0 = 0; i0 < n_listed;) {                 // uniform
-      if (text_gone) {                                 // uniform (a second round: very many segments or bytes to merge)
-#pragma unroll
-        for (int pass = 0; pass < kPasses; ++pass) {
-          const int at = 1024 * pass + 16 * lane;
-          if (at < n)
-            *(uint4*)(text + 256 * pass + 4 * lane) = load_16_bytes(p.bytes + begin, at, begin, p.total_bytes - begin);
-        }
-        wave_sync();
-      }
-      text_gone = true;
       // ---- words: which segments are one token ----
       int i1 = i0;                                     // segments from i0 to here are done in this round
       uint32_t n_jobs = 0, used = 0;                   // those that need merges, and their places in the arena (uniform)
@@ -457,8 +458,10 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
                 taken = (int)__builtin_ctzll(misfit);
                 full = true;
               }
-              if (job && lane < taken)
-                lds[L::kFirstJobs + place] = first[r] | ((len[r] - 1u) << 12) | ((uint32_t)(base - i0 + 64 * r + lane) << 17);
+              if (job && lane < taken) {
+                lds[L::kFirstJobs + place] = first[r] | ((len[r] - 1u) << 11) | (place << 16);
+                what = kRecJob | place;
+              }
               n_jobs += (uint32_t)__builtin_popcountll(taken < 64 ? job_lanes & ((1ull << taken) - 1ull) : job_lanes);
               if (taken > 0) used = (uint32_t)__builtin_amdgcn_readlane((int)upto, taken - 1);
             }
@@ -477,13 +480,13 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
       if (n_jobs) {                                    // uniform
         // ---- list: the segments that need merges, longest first (counting sort over the 31 possible lengths) ----
         constexpr int kRounds = L::kMostJobs / 64;
-        uint32_t entry[kRounds], place[kRounds];       // (entry: first position | (length - 1) << 12 | segment << 17)
+        uint32_t entry[kRounds], place[kRounds];       // (entry: as in kJobs)
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
           entry[r] = place[r] = 0;
           if (64u * r + (uint32_t)lane < n_jobs) {
             entry[r] = lds[L::kFirstJobs + 64 * r + lane];
-            place[r] = atomicAdd(&hist[31u - ((entry[r] >> 12) & 31u)], 1u);   // my place among those of my length
+            place[r] = atomicAdd(&hist[31u - ((entry[r] >> 11) & 31u)], 1u);   // my place among those of my length
           }
         }
         wave_sync();
@@ -496,23 +499,24 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         wave_sync();
 #pragma unroll
         for (int r = 0; r < kRounds; ++r)
-          if (64u * r + (uint32_t)lane < n_jobs) sorted[hist[31u - ((entry[r] >> 12) & 31u)] + place[r]] = entry[r];
+          if (64u * r + (uint32_t)lane < n_jobs) jobs[hist[31u - ((entry[r] >> 11) & 31u)] + place[r]] = entry[r];
         wave_sync();
         // ---- their places in the arena: byte-level pre-tokenisation (section 4.1) and the initial pair values ----
         uint32_t arena = 0;                            // uniform
 #pragma unroll 1
         for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) { // uniform
           const uint32_t j = j0 + (uint32_t)lane;
-          const uint32_t e = sorted[min(j, n_jobs - 1u)];
-          const uint32_t at = e & 0xFFFu;
-          const uint32_t len = j < n_jobs ? ((e >> 12) & 31u) + 1u : 0u;
+          const uint32_t e = jobs[min(j, n_jobs - 1u)];
+          const uint32_t at = e & 2047u;
+          const uint32_t len = j < n_jobs ? ((e >> 11) & 31u) + 1u : 0u;
           const uint32_t room = (len + 3u) & ~3u;
           const uint32_t upto = arena + wave_scan<OpAdd>(room, 0u);
           const uint32_t base = upto - room;
           arena = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+          wave_sync();                                 // (all lanes have read their entries)
           if (len) {
-            jobs[j] = (uint16_t)(base | ((len - 1u) << 11));
-            sorted[j] = (e >> 17) | (base << 16);
+            jobs[j] = (e & 0xFFFFu) | (base << 14);
+            places[e >> 16] = (uint16_t)base;
           }
           const uint32_t* word = text + (at >> 2);
           const uint32_t shift = 8u * (at & 3u);
@@ -525,7 +529,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
                                          __builtin_amdgcn_alignbit(w3, w2, shift)};
               w0 = w2;
               w1 = w3;
-              uint32_t v[8], t[8];
+              uint32_t v[8];
 #pragma unroll
               for (int c = 0; c < 8; ++c) {
                 // byte-pair table: first byte * 256 + second byte
@@ -534,13 +538,11 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
                 const uint32_t swapped = __builtin_amdgcn_perm(0u, pair, 0x0C0C0001u);
                 v[c] = kLaneNoPair;
                 if (o + c + 1u < len) v[c] = tab.byte_pair[swapped];
-                t[c] = shared[LaneShared::kByteWord + ((bytes[c >> 2] >> (8 * (c & 3))) & 0xFFu)];
               }
 #pragma unroll
               for (int h = 0; h < 2; ++h) {
                 const uint32_t at4 = o + 4 * h;
                 if (at4 < len) {
-                  *(uint4*)(T + base + at4) = make_uint4(t[4 * h], t[4 * h + 1], t[4 * h + 2], t[4 * h + 3]);
                   *(uint4*)(V + base + at4) = make_uint4(lane_value(v[4 * h], at4), lane_value(v[4 * h + 1], at4 + 1u),
                                                          lane_value(v[4 * h + 2], at4 + 2u), lane_value(v[4 * h + 3], at4 + 3u));
                 }
@@ -550,17 +552,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         }
         wave_sync();
       }
-      // (the text is in the arena as far as it is needed: its place keeps what becomes of the segments)
-#pragma unroll
-      for (int r = 0; r < L::kListed / 64; ++r) rec[64 * r + lane] = found[r];
-      wave_sync();
       if (n_jobs) {                                    // uniform
-#pragma unroll 1
-        for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) { // uniform
-          const uint32_t e = sorted[j0 + (uint32_t)lane];
-          if (j0 + (uint32_t)lane < n_jobs) rec[e & 0xFFFFu] = kRecJob | (e >> 16);
-        }
-
         // ---- merge: Algorithm 1 on one segment per lane ----
         // The look-ups of the two pairs a merge creates stay in flight over the loop's edge: the next trip first scans
         // the pair values that did not change and only then takes the two new ones.
@@ -571,8 +563,10 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         wave_sync();
         uint32_t* const idle_v = lds + L::kIdle;
         uint32_t alive = 0;            // bit o: position o of my segment holds a token; 0: I have no segment
-        uint32_t* v0 = idle_v;         // my segment's first position in V, where its tokens are left as a mask once it is
-        uint32_t last = 0;             // done; it has its place in T too.  Where its last four positions begin
+        uint32_t joined = 0;           // bit o: ... one that a merge has made
+        uint32_t* v0 = idle_v;         // my segment's first position in V, where its tokens are left as a mask once it is done
+        const uint8_t* b0 = (const uint8_t*)text;      // ... and in the text
+        uint32_t last = 0;             // where its last four positions begin
         uint32_t next = 0;             // first segment nobody has taken (uniform)
         LaneProbe f1, f2;              // (left token, merged token) and (merged token, token after it)
         f1.q = f2.q = make_uint4(0, 0, 0, 0);
@@ -589,9 +583,11 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
             next += (uint32_t)__builtin_popcountll(idle_lanes);
             if (alive == 0 && mine < n_jobs) {
               const uint32_t e = jobs[mine];
-              const uint32_t top = e >> 11;
+              const uint32_t top = (e >> 11) & 31u;
               alive = (2u << top) - 1u;
-              v0 = V + (e & 2047u);
+              joined = 0;
+              v0 = V + 4u * (e >> 16);
+              b0 = (const uint8_t*)text + (e & 2047u);
               last = top & ~3u;
             }
           }
@@ -642,16 +638,20 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
             pl = lower ? 31u - (uint32_t)__builtin_clz(lower) : pk;
             to2 = v0 + pk;
             to1 = v0 + pl;
-            const uint32_t next_word = (v0 + (L::kT - L::kV))[after ? __builtin_ctz(after) : 0];
-            const uint32_t left_word = to1[L::kT - L::kV];
-            y2 = after ? next_word : 0u;
-            x1 = lower ? left_word : 0u;
+            const uint32_t next_at = after ? (uint32_t)__builtin_ctz(after) : 0u;
+            const uint32_t next_word = v0[next_at + 1u], next_byte = b0[next_at];
+            const uint32_t left_word = to1[1], left_byte = b0[pl];
+            y2 = (joined >> next_at) & 1u ? next_word : lane_byte_word(next_byte);
+            x1 = (joined >> pl) & 1u ? left_word : lane_byte_word(left_byte);
+            y2 = after ? y2 : 0u;
+            x1 = lower ? x1 : 0u;
             x2 = lane_merged_word(best);
-            to2[L::kT - L::kV] = x2;
             *to2 = kLaneNoPair;
             *to1 = kLaneNoPair;
             v0[right] = kLaneNoPair;
+            to2[1] = x2;                               // (that position is dead, or has just died)
             alive &= ~(1u << right);
+            joined |= 1u << pk;
           } else if (alive != 0) {                     // no pair left: my segment is finished
             *v0 = alive;
             alive = 0;
@@ -670,13 +670,19 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
       // First the segments that are one token, in the text's order; then the others, in the jobs' order: neighbours there
       // have about as many tokens.  (In the text's order too, a store instruction per token of the longest of 64 segments,
       // few lanes in each, was a fifth of the kernel.)
-#pragma unroll 1
-      for (int b = i0; b < i1; b += 64) {              // uniform
+#pragma unroll
+      for (int r = 0; r < L::kListed / 64; ++r) {
+        const int b = i0 + 64 * r;
+        if (b >= i1) continue;                         // uniform
         const int i = b + lane;
-        const uint32_t what = i < i1 ? rec[i - i0] : kRecNone;
-        const uint32_t at = what & 2047u;
+        const uint32_t what = i < i1 ? found[r] : kRecNone;
         uint32_t count = what < kRecJob ? 1u : 0u;
-        if (what & kRecJob) count = (uint32_t)__builtin_popcount(V[at]);
+        uint32_t at = 0, tokens = 0;
+        if (what & kRecJob) {
+          at = places[what & (uint32_t)(L::kMostJobs - 1)];
+          tokens = V[at];
+          count = (uint32_t)__builtin_popcount(tokens);
+        }
         const uint32_t upto = total + wave_scan<OpAdd>(count, 0u);
         uint32_t o = upto - count;
         if constexpr (GROUPS) {                        // my string's first segment is one of these: its tokens begin there
@@ -694,22 +700,29 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
           }
         }
         if (what < kRecJob) dst[o] = (int32_t)what;
-        if (what & kRecJob) V[at + 1u] = o;            // (two positions or more: the mask lies in the first)
+        if (what & kRecJob) V[at + lane_spare(tokens)] = o;
         total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
       }
       wave_sync();
 #pragma unroll 1
       for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) {   // uniform
-        uint32_t tokens = 0, o = 0;
-        const uint32_t* t = T;
+        uint32_t tokens = 0, o = 0, made = 0;
+        const uint32_t* v = V;
+        const uint8_t* bytes = (const uint8_t*)text;
         if (j0 + (uint32_t)lane < n_jobs) {
-          const uint32_t at = jobs[j0 + (uint32_t)lane] & 2047u;
-          tokens = V[at];
-          o = V[at + 1u];
-          t = T + at;
+          const uint32_t e = jobs[j0 + (uint32_t)lane];
+          v = V + 4u * (e >> 16);
+          bytes += e & 2047u;
+          tokens = v[0];
+          o = v[lane_spare(tokens)];
+          made = (~tokens >> 1) & ((1u << ((e >> 11) & 31u)) - 1u);      // (the position after is of the segment, and dead)
         }
         while (__ballot(tokens != 0)) {
-          if (tokens) dst[o++] = (int32_t)(t[__builtin_ctz(tokens)] & kTokIdMask);
+          if (tokens) {
+            const uint32_t q = (uint32_t)__builtin_ctz(tokens);
+            const uint32_t word = v[q + 1u], byte = bytes[q];
+            dst[o++] = (int32_t)((made >> q) & 1u ? word & kTokIdMask : byte);
+          }
           tokens &= tokens - 1u;
         }
       }

@@ -27,11 +27,7 @@ struct Control {
   uint32_t queue_head[kMaxTiers];                    // work-queue heads of the encode kernels
   uint32_t fallback_range[2];                        // {0, items the lane-per-segment kernel passed on}
   uint32_t fallback_queue;                           // work-queue head of the kernel that takes those
-  // used only when strings are split into pieces:
-  uint32_t n_slots;                                  // piece slots in the batch
-  uint32_t hist[kBinKeys];                           // pieces per (tier, length bucket)
-  uint32_t key_base[kBinKeys];                       // exclusive scan of hist
-  uint32_t cursor[kBinKeys];                         // scatter cursors
+  uint32_t n_slots;                                  // piece slots in the batch (small split batches)
 };
 
 __device__ inline int bin_key(int len, const TierPlan& plan) {
@@ -316,265 +312,235 @@ __device__ inline uint32_t slots_of_length(int64_t len, int piece_target, int ma
   // (a 32-bit division: a valid length fits, and the 64-bit one is a long software routine)
   return (len <= 0 || len > max_string) ? 1u : ((uint32_t)len + (uint32_t)piece_target - 1u) / (uint32_t)piece_target;
 }
-__device__ inline uint32_t slots_of(const int64_t* offsets, int s, int piece_target, int max_string) {
-  return slots_of_length(offsets[s + 1] - offsets[s], piece_target, max_string);
+
+// Orders a wave's own LDS traffic (which the hardware executes in order) for the compiler.
+__device__ inline void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Slots per string, their exclusive scan (slot_base), and the owner string of every slot.  Workgroup b owns
-// strings [1024 b, 1024 b + 1024): it counts the slots of all strings before its tile itself (the lengths are
-// 8 bytes per string and come from L2), scans its own tile, and fills the tile's stretch of slot_string by
-// binary search in the tile's prefix sums, one slot per thread and step.
-__global__ __launch_bounds__(1024) void slot_layout_kernel(const int64_t* offsets, int batch, int piece_target,
-                                                           int max_string, Control* c, int32_t* slot_base,
-                                                           int32_t* slot_string) {
-  __shared__ uint32_t wave_sum[16];
-  __shared__ uint32_t first_s[1025];                   // slot_base of the tile's strings, relative to the tile
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int base = blockIdx.x * 1024;
-  if (blockIdx.x == 0) {
-    if (tid < kBinKeys) { c->hist[tid] = 0; c->cursor[tid] = 0; }
-    if (tid < kMaxTiers) c->queue_head[tid] = 0;
-    if (tid < 2) c->fallback_range[tid] = 0;
-    if (tid == 2) c->fallback_queue = 0;
-  }
-  // slots of all strings before the tile
-  uint32_t before = 0;
-  for (int s0 = tid; s0 < base; s0 += 8 * 1024) {      // eight strings' loads in flight per thread: the loads
-    int64_t lo[8], hi[8];                              // are unconditional (index clamped), the test comes after
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int s = min(s0 + u * 1024, base - 1);
-      lo[u] = offsets[s];
-      hi[u] = offsets[s + 1];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      before += s0 + u * 1024 < base ? slots_of_length(hi[u] - lo[u], piece_target, max_string) : 0u;
-  }
-  for (int step = 32; step >= 1; step >>= 1) before += (uint32_t)__shfl_xor((int)before, step, 64);
-  if (lane == 0) wave_sum[wave] = before;
-  __syncthreads();
-  uint32_t tile_first = 0;
-  for (int w = 0; w < 16; ++w) tile_first += wave_sum[w];
-  __syncthreads();
-  // the tile itself
-  const int s = base + tid;
-  const uint32_t m = s < batch ? slots_of(offsets, s, piece_target, max_string) : 0u;
-  uint32_t v = m;
-  for (int step = 1; step < 64; step <<= 1) {
-    const uint32_t o = (uint32_t)__shfl_up((int)v, step, 64);
-    if (lane >= step) v += o;
-  }
-  if (lane == 63) wave_sum[wave] = v;
-  __syncthreads();
-  uint32_t in_tile = v - m;
-  for (int w = 0; w < wave; ++w) in_tile += wave_sum[w];
-  first_s[tid] = in_tile;
-  if (tid == 1023) first_s[1024] = in_tile + m;
-  if (s < batch) slot_base[s] = (int32_t)(tile_first + in_tile);
-  __syncthreads();
-  const uint32_t tile_total = first_s[1024];
-  for (uint32_t g = tid; g < tile_total; g += 1024) {
-    int lo = 0, hi = 1023;                             // the last string of the tile whose first slot is <= g
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (first_s[mid] <= g) lo = mid; else hi = mid - 1;
-    }
-    slot_string[tile_first + g] = base + lo;
-  }
-  if (blockIdx.x == gridDim.x - 1 && tid == 0) {
-    slot_base[batch] = (int32_t)(tile_first + tile_total);
-    c->n_slots = tile_first + tile_total;
-  }
+// Slots are numbered without a scan: string s's first slot is s + offsets[s] / P, and a string of ceil(len / P) slots never
+// reaches the next one's.  Numbers in between that no string uses (one for every other string) are void slots too.
+__device__ inline uint32_t slot_base(int64_t offset, int s, int piece_target) {
+  return (uint32_t)s + (uint32_t)(offset >> 7) / ((uint32_t)piece_target >> 7);        // (the target is a multiple of 128)
 }
 
-// Sixteen lanes per slot, four slots per wave: where does the slot's piece start?  The candidates are the 128
-// positions q = t, t-1, ..., t-127 below the slot's nominal start t (a cut "before q" lies between bytes q-1 and
-// q); the largest one with a cut wins.  A group looks at sixteen candidates per round -- in text the first round
-// nearly always finds one -- and the wave goes on while any of its groups is still looking.
-constexpr int kCutSlotsPerWave = 4;
-__global__ __launch_bounds__(256) void cut_search_kernel(const uint8_t* bytes, const int64_t* offsets,
-                                                         const uint32_t* byte_pair, int piece_target,
-                                                         int max_string, const Control* c, const int32_t* slot_base,
-                                                         const int32_t* slot_string, int64_t* piece_begin,
-                                                         const uint8_t* cover) {
-  const int lane = threadIdx.x & 63, sub = lane & 15, group = lane >> 4;
-  const uint32_t g = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kCutSlotsPerWave + group;
-  const bool valid = g < c->n_slots;
-  int64_t start = -1;                                  // void unless a cut is found
-  int64_t t = 0;
-  bool searching = false;
-  if (valid) {
-    const int s = slot_string[g];
-    const int i = (int)g - slot_base[s];
-    const int64_t begin = offsets[s];
-    const int64_t len = offsets[s + 1] - begin;
-    if (len < 0 || len > max_string) {
-      start = -1;                                      // not encodable: the string yields no tokens
-    } else if (i == 0) {
-      start = begin;
-    } else {
-      t = begin + (int64_t)i * piece_target;           // piece_target >= 2 * kCutWindow keeps q-1 inside the string
-      searching = true;
+// Which of the sixteen candidates q = p - 15 ... p have a cut before byte q, a bit each?  v, last: the seventeen bytes
+// p - 16 ... p; m, last_m: their marks; cuts: the bit set of the cuts.
+__device__ inline uint32_t cut_candidates(const uint4& v, uint32_t last, const uint4& m, uint32_t last_m, bool marked,
+                                          const uint32_t* cuts) {
+  const uint32_t w[5] = {v.x, v.y, v.z, v.w, last};
+  uint32_t found = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const uint32_t pair = (i & 3) == 3 ? __builtin_amdgcn_alignbit(w[(i >> 2) + 1], w[i >> 2], 24u) : w[i >> 2] >> (8 * (i & 3));
+    found |= ((cuts[(pair >> 5) & 2047u] >> (pair & 31u)) & 1u) << i;
+  }
+  if (marked) {                                        // special tokens: their ends are cuts, their inside is not
+    const uint32_t mark[5] = {m.x, m.y, m.z, m.w, last_m};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t two = ((i & 3) == 3 ? __builtin_amdgcn_alignbit(mark[(i >> 2) + 1], mark[i >> 2], 24u)
+                                         : mark[i >> 2] >> (8 * (i & 3))) & 0xFFFFu;
+      if (two) found |= 1u << i;
+      if (two >> 8 == kCoverRest) found &= ~(1u << i);
     }
   }
+  return found;
+}
+// The last cut within the kCutWindow positions up to t, or -1: a thread's own search, sixteen candidates a round; in text
+// the first round nearly always finds one.  Whole waves take part, with `searching` unset where there is nothing to find.
+__device__ inline int64_t last_cut(const uint8_t* bytes, const uint8_t* cover, const uint32_t* cuts, int64_t t, bool searching) {
+  int64_t at = -1;
   for (int round = 0; round < kCutWindow / 16; ++round) {
     if (!__ballot(searching)) break;                   // uniform
-    bool cut = false;
     if (searching) {
-      const int64_t q = t - 16 * round - sub;
-      const uint32_t a = bytes[q - 1], b = bytes[q];
-      cut = byte_pair[(a << 8) | b] == kCut;
-      if (cover) {                                     // special tokens: their ends are cuts, their inside is not
-        const uint32_t ma = cover[q - 1], mb = cover[q];
-        cut = (cut || ma != 0 || mb != 0) && mb != kCoverRest;
+      const int64_t p = t - 16 * round;
+      uint4 v, m = make_uint4(0, 0, 0, 0);
+      uint32_t last_m = 0;
+      __builtin_memcpy(&v, bytes + p - 16, 16);
+      if (cover) {
+        __builtin_memcpy(&m, cover + p - 16, 16);
+        last_m = cover[p];
+      }
+      const uint32_t found = cut_candidates(v, bytes[p], m, last_m, cover != nullptr, cuts);
+      if (found) {
+        at = p - 15 + (31 - __builtin_clz(found));
+        searching = false;
       }
     }
-    const uint32_t mine = (uint32_t)(__ballot(cut) >> (16 * group)) & 0xFFFFu;
-    if (searching && mine) {
-      start = t - 16 * round - __builtin_ctz(mine);    // the largest candidate of the round
-      searching = false;
-    }
   }
-  if (valid && sub == 0) piece_begin[g] = start;
+  return at;
 }
 
-// Where the piece that starts in slot g ends: at the next piece of its string, or at the string's end.  The slots it
-// runs over are void; piece_len tells each how many slots back its piece starts (negative), so that the packing kernel
-// can give it a share of the copying.  (A void first slot, of a string that cannot be encoded, holds 0.)  In text the
-// next slot nearly always holds a piece; after it, eight slots are asked at a time: a 64 KiB run has 73 void slots.
-__device__ inline int64_t piece_end(const int64_t* offsets, int s, uint32_t g, const int32_t* slot_base,
-                                    const int64_t* piece_begin, int32_t* piece_len) {
-  const int end = slot_base[s + 1];
-  int h = (int)g + 1;
-  if (h < end) {
-    const int64_t next = piece_begin[h];
-    if (next >= 0) return next;
-  }
-  while (h < end) {
-    int64_t next[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) next[u] = piece_begin[min(h + u, end - 1)];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (h + u < end) {
-        if (next[u] >= 0) return next[u];
-        piece_len[h + u] = (int32_t)g - (h + u);
-      }
-    }
-    h += 8;
-  }
-  return offsets[s + 1];
-}
-
-// What a slot's piece is to the work list.  Pieces that one wave can take (tier 0) go together while they lie within
-// `room` bytes, like short strings do, whichever strings they are of; a longer one is an item of its own.  Whole waves
-// take part.
-struct PieceItem {
-  int key;                                             // -1: no item begins here
-  int32_t len;                                         // as in ItemDesc
-};
-__device__ inline PieceItem piece_item(int64_t start, int32_t len, int64_t wave_first, uint32_t n_slots, const TierPlan& plan,
-                                       int room) {
-  const int n = (int)min((int64_t)n_slots - wave_first, (int64_t)64);
-  const int key = start >= 0 ? bin_key(len, plan) : -1;
-  const bool single = key >= 0 && key < kLenBuckets;
-  const StringGroup g = group_members(start, start + len, !single, n, room);
-  if (!single) return PieceItem{key, len};
-  return PieceItem{g.members ? group_key(g.len) : -1, g.len | (g.members << kGroupShift)};
-}
-
-// One thread per slot: piece lengths, and the histogram of (tier, length bucket) keys of the items.
-__global__ __launch_bounds__(256) void piece_hist_kernel(const int64_t* offsets, TierPlan plan, int room, Control* c,
-                                                         const int32_t* slot_base, const int32_t* slot_string,
-                                                         const int64_t* piece_begin, int32_t* piece_len,
-                                                         int32_t* counts, int32_t* group_ids) {
+// The pieces of a batch's strings and the histogram of their items' keys.  A wave takes 63 slots at a time and looks at one
+// more, where its last piece may end; its 64 lanes hold the strings they can belong to.  Pieces that one wave can take
+// (tier 0) go together while they lie within `room` bytes, like short strings do, whichever strings they are of; a longer
+// one is an item of its own.  The slots that a piece runs over are void; piece_len tells each how many slots back its
+// piece starts (negative), so that the packing kernel can give it a share of the copying.  (Other void slots hold 0.)
+// item_len: what the list will hold of the item that begins in a slot, an ItemDesc's len for tier 0, minus the length for
+// the others, 0 for none.
+// Each workgroup leaves its histogram in `part`, from which the next kernel, with the same workgroups, knows where each key
+// begins and where its own part of it does: no atomics on memory, and nothing to clear.  What bounds them is latency: some
+// ten dependent reads.  8,192 strings of 4 KiB: 11 and 6 us, where numbering the slots, finding the cuts, the histogram, its
+// scan and the list were five kernels and 42 us.
+constexpr int kListGrid = 256;
+constexpr int kListSlots = 63;                         // of a wave's step
+__global__ __launch_bounds__(1024) void piece_list_kernel(const uint8_t* bytes, const int64_t* offsets, int batch,
+                                                          const uint32_t* cut_bits, const uint8_t* cover, int piece_target,
+                                                          int max_string, TierPlan plan, int room, uint32_t n_slots,
+                                                          uint32_t steps_each, int32_t* slot_string, int64_t* piece_begin,
+                                                          int32_t* piece_len, int32_t* item_len, int32_t* counts,
+                                                          int32_t* group_ids, uint32_t* part) {
+  __shared__ __align__(16) uint32_t cuts[2048];
   __shared__ uint32_t hist[kBinKeys];
-  hist[threadIdx.x] = 0;                               // 256 threads, 256 keys
+  __shared__ int32_t string_at[16][64];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (t < 512) ((uint4*)cuts)[t] = ((const uint4*)cut_bits)[t];
+  if (t < kBinKeys) hist[t] = 0;
   __syncthreads();
-  const uint32_t n_slots = c->n_slots;
-  for (uint32_t first = blockIdx.x * 256; first < n_slots; first += gridDim.x * 256) {                // uniform
-    const uint32_t g = first + threadIdx.x;
-    int64_t start = -1;
-    int32_t len = 0;
-    if (g < n_slots) {
-      start = piece_begin[g];
-      const int s = slot_string[g];
-      if (start >= 0) len = (int32_t)(piece_end(offsets, s, g, slot_base, piece_begin, piece_len) - start);
-      if (start >= 0 || slot_base[s] == (int32_t)g) piece_len[g] = len;   // (other void slots: the piece's own thread)
-      if (start < 0 || bin_key(len, plan) < 0) counts[g] = 0;             // void slot, or too long for the launched variants
-      group_ids[g] = -1;
+  const uint32_t first_step = (blockIdx.x * 16u + (uint32_t)wave) * steps_each;
+  int s0 = 0;                                          // the string of the step's first slot (uniform)
+  for (uint32_t step = 0; step < steps_each; ++step) { // uniform
+    const uint32_t g0 = (first_step + step) * kListSlots;
+    if (g0 >= n_slots) break;                          // uniform
+    if (step == 0) {                                   // the last string with its base <= g0: 64 asked at a time
+      int n = batch;
+      while (n > 1) {                                  // uniform; n shrinks every round
+        const int stride = (n + 63) >> 6;
+        const int64_t i = (int64_t)s0 + (int64_t)(lane + 1) * stride;
+        const bool upto = i < (int64_t)s0 + n && slot_base(offsets[i], (int)i, piece_target) <= g0;
+        const int64_t skipped = (int64_t)__builtin_popcountll(__ballot(upto)) * stride;
+        s0 += (int)skipped;
+        n = (int)min((int64_t)stride, (int64_t)n - skipped);
+      }
     }
-    const PieceItem item = piece_item(start, len, g & ~63u, n_slots, plan, room);
-    if (item.key >= 0) atomicAdd(&hist[item.key], 1u);
+    // my string, one of the 64 from s0 on, and the string of my slot
+    const int mine = min(s0 + lane, batch - 1);
+    const int64_t my_begin = offsets[mine], my_end = offsets[mine + 1];
+    const uint32_t my_base = s0 + lane < batch ? slot_base(my_begin, mine, piece_target) : 0xFFFFFFFFu;
+    string_at[wave][lane] = 0;
+    wave_order();
+    if (lane > 0 && my_base - g0 < 64u) string_at[wave][my_base - g0] = lane;
+    wave_order();
+    int owner = string_at[wave][lane];
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(owner, d, 64);
+      if (lane >= d) owner = max(owner, o);
+    }
+    wave_order();
+    const int64_t begin = __shfl(my_begin, owner, 64), end = __shfl(my_end, owner, 64);
+    const uint32_t base = (uint32_t)__shfl((int)my_base, owner, 64);
+    const uint32_t g = g0 + (uint32_t)lane;
+    const int i = (int)(g - base);
+    const uint32_t end_slot = base + slots_of_length(end - begin, piece_target, max_string);
+    const bool used = g < n_slots && g < end_slot && end >= begin && end - begin <= max_string;
+    int64_t start = last_cut(bytes, cover, cuts, begin + (int64_t)i * piece_target, used && i > 0);
+    if (used && i == 0) start = begin;
+    // ---- where my piece ends: at the next one of its string, or at the string's end ----
+    const uint64_t pieces = __ballot(start >= 0);
+    const uint64_t later = lane < 63 ? pieces & (~0ull << (lane + 1)) : 0ull;
+    const int next = later ? (int)__builtin_ctzll(later) : 64;
+    int64_t piece_end = __shfl(start, next & 63, 64);
+    const bool beyond = start >= 0 && lane < kListSlots && (next == 64 || g0 + (uint32_t)next >= end_slot);
+    if (beyond) piece_end = end;
+    // (one piece at most runs on past the slots of this step)
+    uint64_t runs_on = __ballot(beyond && next == 64 && end_slot > g0 + 64u);
+    if (runs_on) {                                     // uniform
+      const int from = (int)__builtin_ctzll(runs_on);
+      const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)end_slot, from);
+      const uint32_t its_base = (uint32_t)__builtin_amdgcn_readlane((int)base, from);
+      const int64_t its_begin = __shfl(begin, from, 64);
+      for (uint32_t h0 = g0 + 64u; h0 < last; h0 += 64u) {               // uniform
+        const uint32_t h = h0 + (uint32_t)lane;
+        const int64_t at = last_cut(bytes, cover, cuts, its_begin + (int64_t)(h - its_base) * piece_target, h < last);
+        const uint64_t found = __ballot(at >= 0);
+        const uint32_t stop = found ? h0 + (uint32_t)__builtin_ctzll(found) : last;
+        if (h < stop) piece_len[h] = (int32_t)(g0 + (uint32_t)from) - (int32_t)h;
+        if (found) {
+          const int64_t its_end = __shfl(at, (int)__builtin_ctzll(found), 64);
+          if (lane == from) piece_end = its_end;
+          break;                                       // uniform
+        }
+      }
+    }
+    const int32_t len = start >= 0 ? (int32_t)(piece_end - start) : 0;
+    // ---- what there is to say of the slot ----
+    const int key = start >= 0 && lane < kListSlots ? bin_key(len, plan) : -1;
+    const bool single = key >= 0 && key < kLenBuckets;
+    const StringGroup group = group_members(start, start + len, !single, (int)min(n_slots - g0, (uint32_t)kListSlots), room);
+    const int item_key = !single ? key : group.members ? group_key(group.len) : -1;
+    if (item_key >= 0) atomicAdd(&hist[item_key], 1u);
+    const uint64_t before = pieces & ((1ull << lane) - 1ull);
+    const int piece = before ? 63 - (int)__builtin_clzll(before) : -1;   // the piece before my slot, if it is of my string
+    const bool of_my_string = piece >= 0 && g0 + (uint32_t)max(piece, 0) >= base;
+    if (g < n_slots) {
+      if (lane < kListSlots) {
+        piece_begin[g] = start;
+        slot_string[g] = i == 0 ? s0 + owner : -1;
+        group_ids[g] = -1;
+        item_len[g] = item_key < 0 ? 0 : single ? group.len | (group.members << kGroupShift) : -len;
+        if (key < 0) counts[g] = 0;                    // void slot, or too long for the launched variants
+      }
+      if (start >= 0) {
+        if (lane < kListSlots) piece_len[g] = len;
+      } else if (used && of_my_string) {               // (of earlier steps' pieces: theirs to say)
+        piece_len[g] = piece - lane;
+      } else if (!used && lane < kListSlots) {
+        piece_len[g] = 0;
+      }
+    }
+    s0 += __builtin_amdgcn_readlane(owner, 63);
   }
   __syncthreads();
-  if (hist[threadIdx.x]) atomicAdd(&c->hist[threadIdx.x], hist[threadIdx.x]);
+  if (t < kBinKeys) part[blockIdx.x * kBinKeys + t] = hist[t];
 }
 
-// One workgroup of 256: exclusive scan of the key histogram, list bases of the tiers.
-__global__ __launch_bounds__(256) void piece_scan_kernel(Control* c, int n_tiers) {
-  __shared__ uint32_t scan[kBinKeys];
-  const int t = threadIdx.x;
-  const uint32_t mine = c->hist[t];
-  scan[t] = mine;
+// The work list, tier-major, longest bucket first.  Also resets the work-queue heads.
+__global__ __launch_bounds__(1024) void piece_scatter_kernel(TierPlan plan, uint32_t n_slots, uint32_t slots_each, Control* c,
+                                                             const uint32_t* part, const int64_t* piece_begin,
+                                                             const int32_t* item_len, int32_t* list, ItemDesc* desc) {
+  __shared__ uint32_t sum_all[4][kBinKeys], sum_before[4][kBinKeys];
+  __shared__ uint32_t scan[kBinKeys], cursor[kBinKeys];
+  const int t = threadIdx.x, k = t & (kBinKeys - 1), quarter = t / kBinKeys;
+  uint32_t all = 0, before = 0;                        // of key k: items, and those of earlier workgroups
+#pragma unroll 8
+  for (int b = quarter; b < (int)gridDim.x; b += 4) {
+    const uint32_t n = part[b * kBinKeys + k];
+    all += n;
+    before += b < (int)blockIdx.x ? n : 0u;
+  }
+  sum_all[quarter][k] = all;
+  sum_before[quarter][k] = before;
   __syncthreads();
-  for (int step = 1; step < kBinKeys; step <<= 1) {
-    const uint32_t v = t >= step ? scan[t - step] : 0;
+  uint32_t total = 0;
+  if (t < kBinKeys) {
+    for (int q = 0; q < 4; ++q) total += sum_all[q][t];
+    scan[t] = total;
+  }
+  __syncthreads();
+  for (int step = 1; step < kBinKeys; step <<= 1) {    // inclusive scan, all threads reach the barriers
+    uint32_t v = 0;
+    if (t < kBinKeys && t >= step) v = scan[t - step];
     __syncthreads();
-    scan[t] += v;
+    if (t < kBinKeys) scan[t] += v;
     __syncthreads();
   }
-  c->key_base[t] = scan[t] - mine;
-  if (t <= kMaxTiers) c->tier_base[t] = t == 0 ? 0 : scan[(t <= n_tiers ? t : n_tiers) * kLenBuckets - 1];
-}
-
-// Scatter the pieces into the work list, tier-major, longest bucket first.  Pieces of a long text all have about
-// the same length, hence the same key: a workgroup first ranks its pieces per key in LDS and then reserves each
-// key's range of the list with one global atomic.  Those atomics land on a handful of addresses and are served
-// one after the other, so a workgroup takes kScatterPer slots per thread: fewer workgroups, fewer atomics.
-constexpr int kScatterPer = 4;
-__global__ __launch_bounds__(256) void piece_scatter_kernel(TierPlan plan, int room, Control* c, const int64_t* piece_begin,
-                                                            const int32_t* piece_len, int32_t* list, ItemDesc* desc) {
-  __shared__ uint32_t local[kBinKeys];                 // 256 threads, 256 keys
-  local[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t n_slots = c->n_slots;
-  int key[kScatterPer];
-  uint32_t rank[kScatterPer];
-  int64_t begin[kScatterPer];
-  int32_t len[kScatterPer];
-#pragma unroll
-  for (int j = 0; j < kScatterPer; ++j) {
-    const uint32_t g = (blockIdx.x * kScatterPer + j) * 256 + threadIdx.x;
-    key[j] = -1;
-    rank[j] = 0;
-    begin[j] = -1;
-    len[j] = 0;
-    if (g < n_slots) {
-      begin[j] = piece_begin[g];
-      len[j] = piece_len[g];
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < kScatterPer; ++j) {
-    const PieceItem item = piece_item(begin[j], len[j], ((blockIdx.x * kScatterPer + j) * 256 + threadIdx.x) & ~63u, n_slots, plan, room);
-    key[j] = item.key;
-    len[j] = item.len;
-    if (key[j] >= 0) rank[j] = atomicAdd(&local[key[j]], 1u);
+  if (t < kBinKeys) cursor[t] = scan[t] - total + sum_before[0][t] + sum_before[1][t] + sum_before[2][t] + sum_before[3][t];
+  if (blockIdx.x == 0) {
+    if (t <= kMaxTiers) c->tier_base[t] = t == 0 ? 0 : scan[(t <= plan.n_tiers ? t : plan.n_tiers) * kLenBuckets - 1];
+    if (t < kMaxTiers) c->queue_head[t] = 0;
+    if (t < 2) c->fallback_range[t] = 0;
+    if (t == 2) c->fallback_queue = 0;
   }
   __syncthreads();
-  const uint32_t mine = local[threadIdx.x];
-  __syncthreads();
-  if (mine) local[threadIdx.x] = c->key_base[threadIdx.x] + atomicAdd(&c->cursor[threadIdx.x], mine);
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kScatterPer; ++j) {
-    if (key[j] >= 0) {
-      const uint32_t g = (blockIdx.x * kScatterPer + j) * 256 + threadIdx.x;
-      list[local[key[j]] + rank[j]] = (int32_t)g;
-      desc[local[key[j]] + rank[j]] = ItemDesc{begin[j], len[j], (int32_t)g};
-    }
+  const uint32_t first = blockIdx.x * slots_each, last = min(first + slots_each, n_slots);
+  for (uint32_t g = first + (uint32_t)t; g < last; g += 1024u) {
+    const int32_t len = item_len[g];
+    if (len == 0) continue;
+    const uint32_t at = atomicAdd(&cursor[len > 0 ? group_key(len & kGroupLen) : bin_key(-len, plan)], 1u);
+    list[at] = (int32_t)g;
+    desc[at] = ItemDesc{piece_begin[g], len > 0 ? len : -len, (int32_t)g};
   }
 }
 
@@ -657,18 +623,18 @@ __global__ __launch_bounds__(1024) void small_list_kernel(const uint8_t* bytes, 
   }
   for (int round = 0; round < kCutWindow / 16; ++round) {
     uint4 v[kPer], m[kPer];
-    uint32_t v4[kPer], m4[kPer];
+    uint32_t last[kPer], last_m[kPer];
     bool any = false;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       v[j] = m[j] = make_uint4(0, 0, 0, 0);
-      v4[j] = m4[j] = 0;
+      last[j] = last_m[j] = 0;
       if (from[j]) {
         __builtin_memcpy(&v[j], bytes + from[j] - 16, 16);
-        v4[j] = bytes[from[j]];
+        last[j] = bytes[from[j]];
         if (cover) {
           __builtin_memcpy(&m[j], cover + from[j] - 16, 16);
-          m4[j] = cover[from[j]];
+          last_m[j] = cover[from[j]];
         }
         any = true;
       }
@@ -677,21 +643,7 @@ __global__ __launch_bounds__(1024) void small_list_kernel(const uint8_t* bytes, 
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       if (from[j]) {
-        const uint32_t w[5] = {v[j].x, v[j].y, v[j].z, v[j].w, v4[j]};
-        const uint32_t mark[5] = {m[j].x, m[j].y, m[j].z, m[j].w, m4[j]};
-        uint32_t found = 0;                            // bit i: a cut before byte from - 15 + i
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const uint32_t pair = (i & 3) == 3 ? __builtin_amdgcn_alignbit(w[(i >> 2) + 1], w[i >> 2], 24u) : w[i >> 2] >> (8 * (i & 3));
-          uint32_t cut = (cuts[(pair >> 5) & 2047u] >> (pair & 31u)) & 1u;
-          if (cover) {                                 // special tokens: their ends are cuts, their inside is not
-            const uint32_t two = ((i & 3) == 3 ? __builtin_amdgcn_alignbit(mark[(i >> 2) + 1], mark[i >> 2], 24u)
-                                               : mark[i >> 2] >> (8 * (i & 3))) & 0xFFFFu;
-            if (two) cut = 1u;
-            if (two >> 8 == kCoverRest) cut = 0u;
-          }
-          found |= cut << i;
-        }
+        const uint32_t found = cut_candidates(v[j], last[j], m[j], last_m[j], cover != nullptr, cuts);
         if (found) {
           start[j] = from[j] - 15 + (31 - __builtin_clz(found));         // the last one
           from[j] = 0;
@@ -760,12 +712,11 @@ __global__ __launch_bounds__(1024) void small_list_kernel(const uint8_t* bytes, 
   }
 }
 
-// Token offsets of the slots: per-tile sums, scan of the tile sums, then the scan inside each tile.
+// Token offsets of the slots: per-tile sums, then the scan inside each tile.
 constexpr int kScanTile = 4096;
 
-__global__ __launch_bounds__(1024) void tile_sum_kernel(const int32_t* counts, const Control* c, int64_t* tile_sum) {
+__global__ __launch_bounds__(1024) void tile_sum_kernel(const int32_t* counts, uint32_t n_slots, int64_t* tile_sum) {
   __shared__ int64_t wave_sum[16];
-  const uint32_t n_slots = c->n_slots;
   const uint32_t base = blockIdx.x * kScanTile;
   int64_t v = 0;
   for (int j = 0; j < kScanTile / 1024; ++j) {
@@ -782,35 +733,23 @@ __global__ __launch_bounds__(1024) void tile_sum_kernel(const int32_t* counts, c
   }
 }
 
-__global__ __launch_bounds__(64) void tile_scan_kernel(int64_t* tile_sum, int n_tiles, const Control* c,
-                                                       int64_t* out_offsets, int batch) {
-  // one wave walks the tiles (there are few: one per 4096 slots); tile_sum becomes the exclusive scan
-  const int lane = threadIdx.x;
-  const int used = (int)((c->n_slots + kScanTile - 1) / kScanTile);
-  int64_t carry = 0;
-  for (int base = 0; base < n_tiles; base += 64) {
-    const int i = base + lane;
-    const int64_t m = (i < n_tiles && i < used) ? tile_sum[i] : 0;
-    int64_t v = m;
-    for (int step = 1; step < 64; step <<= 1) {
-      const int64_t o = __shfl_up(v, step, 64);
-      if (lane >= step) v += o;
-    }
-    if (i < n_tiles) tile_sum[i] = carry + v - m;
-    carry += __shfl(v, 63, 64);
-  }
-  if (lane == 0) out_offsets[batch] = carry;
-}
-
-__global__ __launch_bounds__(1024) void slot_offsets_kernel(const int32_t* counts, const Control* c,
-                                                            const int64_t* tile_base, const int32_t* slot_base,
+// (Each workgroup adds up the tiles before its own: there is one per 4,096 slots.)
+__global__ __launch_bounds__(1024) void slot_offsets_kernel(const int32_t* counts, uint32_t n_slots, const int64_t* tile_sum,
                                                             const int32_t* slot_string, int64_t* slot_out,
-                                                            int64_t* out_offsets) {
+                                                            int64_t* out_offsets, int batch) {
   __shared__ int64_t wave_sum[16];
   __shared__ int64_t carry_s;
-  const uint32_t n_slots = c->n_slots;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) carry_s = tile_base[blockIdx.x];
+  int64_t before = 0;
+  for (int i = tid; i < (int)blockIdx.x; i += 1024) before += tile_sum[i];
+  for (int step = 32; step >= 1; step >>= 1) before += __shfl_xor(before, step, 64);
+  if (lane == 0) wave_sum[wave] = before;
+  __syncthreads();
+  if (tid == 0) {
+    int64_t t = 0;
+    for (int w = 0; w < 16; ++w) t += wave_sum[w];
+    carry_s = t;
+  }
   __syncthreads();
   for (int j = 0; j < kScanTile / 1024; ++j) {
     const uint32_t g = blockIdx.x * kScanTile + j * 1024 + tid;
@@ -822,18 +761,18 @@ __global__ __launch_bounds__(1024) void slot_offsets_kernel(const int32_t* count
     }
     if (lane == 63) wave_sum[wave] = v;
     __syncthreads();
-    int64_t before = carry_s;
-    for (int w = 0; w < wave; ++w) before += wave_sum[w];
+    int64_t at = carry_s + v - m;
+    for (int w = 0; w < wave; ++w) at += wave_sum[w];
     if (g < n_slots) {
-      const int64_t at = before + v - m;
       slot_out[g] = at;
       const int s = slot_string[g];
-      if ((uint32_t)slot_base[s] == g) out_offsets[s] = at;   // a string starts at its first slot
+      if (s >= 0) out_offsets[s] = at;                 // a string starts at its first slot
     }
     __syncthreads();
-    if (tid == 1023) carry_s = before + v;
+    if (tid == 1023) carry_s = at + m;
     __syncthreads();
   }
+  if (blockIdx.x == gridDim.x - 1 && tid == 0) out_offsets[batch] = carry_s;
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1031,12 +970,11 @@ __device__ inline void pack_share(PackItem& it, const int64_t* piece_begin, cons
   }
   it.k = it.group >= 0 ? it.group : min(it.k, kPackShare);
 }
-__global__ __launch_bounds__(256) void piece_pack_kernel(const int32_t* tmp_ids, const Control* c,
+__global__ __launch_bounds__(256) void piece_pack_kernel(const int32_t* tmp_ids, uint32_t n_slots,
                                                          const int64_t* piece_begin, const int32_t* piece_len,
                                                          const int32_t* counts, const int32_t* group_ids,
                                                          const int64_t* slot_out, int32_t* out_ids,
                                                          const int32_t* id_map) {
-  const uint32_t n_slots = c->n_slots;
   const int lane = threadIdx.x & 63;
   const uint32_t stride = gridDim.x * 4;               // slots one round of the grid takes: wave w takes w and w + stride
   uint32_t g = blockIdx.x * 4 + (threadIdx.x >> 6);

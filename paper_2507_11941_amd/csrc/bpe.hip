@@ -146,7 +146,7 @@ struct WorkspaceLayout {
   int64_t max_slots;                 // upper bound on the number of work items (strings or piece slots)
   int n_tiles;                       // scan tiles over the slots
   size_t control, list, list_desc, fallback, counts, tmp_ids, cover, staged;
-  size_t slot_base, slot_string, piece_begin, piece_len, group_ids, slot_out, tile_sum;   // split only
+  size_t slot_string, piece_begin, piece_len, item_len, group_ids, slot_out, tile_sum, part;   // split only
   size_t total;
 };
 
@@ -163,15 +163,16 @@ WorkspaceLayout layout_for(int32_t batch, int64_t total_bytes, int32_t max_len) 
   w.counts = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
   w.tmp_ids = at; at += align_up((size_t)total_bytes * sizeof(int32_t));
   w.cover = at; at += align_up((size_t)total_bytes + 4);      // special-token marks, one per byte, whole chunks of 16
-  w.slot_base = w.slot_string = w.piece_begin = w.piece_len = w.group_ids = w.slot_out = w.tile_sum = 0;
+  w.slot_string = w.piece_begin = w.piece_len = w.item_len = w.group_ids = w.slot_out = w.tile_sum = w.part = 0;
   if (w.split) {
-    w.slot_base = at; at += align_up(((size_t)batch + 1) * sizeof(int32_t));
     w.slot_string = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
     w.piece_begin = at; at += align_up((size_t)w.max_slots * sizeof(int64_t));
     w.piece_len = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
+    w.item_len = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
     w.group_ids = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
     w.slot_out = at; at += align_up((size_t)w.max_slots * sizeof(int64_t));
-    w.tile_sum = at; at += align_up((size_t)(w.n_tiles + 1) * sizeof(int64_t));
+    w.tile_sum = at; at += align_up((size_t)w.n_tiles * sizeof(int64_t));
+    w.part = at; at += align_up((size_t)kListGrid * kBinKeys * sizeof(uint32_t));
   }
   w.staged = at;
   if (n_tiers_for(max_len) > 3) at += align_up((size_t)kStagedWords * sizeof(uint32_t) * kMaxLongGrid);
@@ -562,7 +563,6 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   }
   const int64_t* piece_begin = nullptr;
   const int32_t* piece_len = nullptr;
-  const int32_t* slot_base = nullptr;
   const int32_t* slot_string = nullptr;
   int32_t* group_ids = nullptr;
   const int n_items_max = (int)w.max_slots;              // grid bound for the encode kernels
@@ -596,7 +596,6 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, part);
     hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, ctrl, part, (ItemDesc*)(ws + w.list_desc));
   } else {
-    int32_t* sb = (int32_t*)(ws + w.slot_base);
     int32_t* ss = (int32_t*)(ws + w.slot_string);
     int64_t* pb = (int64_t*)(ws + w.piece_begin);
     int32_t* pl = (int32_t*)(ws + w.piece_len);
@@ -604,22 +603,20 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
       hipLaunchKernelGGL(small_list_kernel, dim3(1), dim3(1024), 0, stream, bytes, offsets, batch, cuts, cover, kPieceTarget,
                          BPE_MAX_STRING_BYTES, plan, ctrl, ss, pb, pl, counts, list, (ItemDesc*)(ws + w.list_desc));
     } else {
-      const uint32_t* byte_pair = (const uint32_t*)((const char*)table->d_mem + table->bucket_bytes) + 256;
-      const int per_slot_grid = (int)std::min<int64_t>((w.max_slots + 255) / 256, 256);   // (each workgroup ends with a few global atomics)
+      uint32_t* part = (uint32_t*)(ws + w.part);
+      int32_t* il = (int32_t*)(ws + w.item_len);
       group_ids = (int32_t*)(ws + w.group_ids);
-      hipLaunchKernelGGL(slot_layout_kernel, dim3((unsigned)((batch + 1023) / 1024)), dim3(1024), 0, stream, offsets, batch, kPieceTarget,
-                         BPE_MAX_STRING_BYTES, ctrl, sb, ss);
-      hipLaunchKernelGGL(cut_search_kernel, dim3((unsigned)((w.max_slots + 4 * kCutSlotsPerWave - 1) / (4 * kCutSlotsPerWave))), dim3(256), 0, stream, bytes,
-                         offsets, byte_pair, kPieceTarget, BPE_MAX_STRING_BYTES, ctrl, sb, ss, pb, cover);
-      hipLaunchKernelGGL(piece_hist_kernel, dim3(per_slot_grid), dim3(256), 0, stream, offsets, plan, room, ctrl, sb, ss,
-                         pb, pl, counts, group_ids);
-      hipLaunchKernelGGL(piece_scan_kernel, dim3(1), dim3(256), 0, stream, ctrl, plan.n_tiers);
-      hipLaunchKernelGGL(piece_scatter_kernel, dim3((unsigned)((w.max_slots + 256 * kScatterPer - 1) / (256 * kScatterPer))), dim3(256), 0, stream, plan,
-                         room, ctrl, pb, pl, list, (ItemDesc*)(ws + w.list_desc));
+      const uint32_t n_slots = (uint32_t)w.max_slots;
+      const uint32_t steps = (n_slots + kListSlots - 1) / kListSlots;       // of a wave, sixteen waves to a workgroup
+      const uint32_t steps_each = (steps + 16 * kListGrid - 1) / (16 * kListGrid);
+      const unsigned grid = (steps + 16 * steps_each - 1) / (16 * steps_each);
+      hipLaunchKernelGGL(piece_list_kernel, dim3(grid), dim3(1024), 0, stream, bytes, offsets, batch, cuts, cover, kPieceTarget,
+                         BPE_MAX_STRING_BYTES, plan, room, n_slots, steps_each, ss, pb, pl, il, counts, group_ids, part);
+      hipLaunchKernelGGL(piece_scatter_kernel, dim3(grid), dim3(1024), 0, stream, plan, n_slots, 16 * steps_each * kListSlots,
+                         ctrl, part, pb, il, list, (ItemDesc*)(ws + w.list_desc));
     }
     piece_begin = pb;
     piece_len = pl;
-    slot_base = sb;
     slot_string = ss;
   }
 
@@ -693,12 +690,12 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   } else {
     int64_t* tile_sum = (int64_t*)(ws + w.tile_sum);
     int64_t* slot_out = (int64_t*)(ws + w.slot_out);
-    hipLaunchKernelGGL(tile_sum_kernel, dim3(w.n_tiles), dim3(1024), 0, stream, counts, ctrl, tile_sum);
-    hipLaunchKernelGGL(tile_scan_kernel, dim3(1), dim3(64), 0, stream, tile_sum, w.n_tiles, ctrl, out_offsets, batch);
-    hipLaunchKernelGGL(slot_offsets_kernel, dim3(w.n_tiles), dim3(1024), 0, stream, counts, ctrl, tile_sum, slot_base,
-                       slot_string, slot_out, out_offsets);
+    const uint32_t n_slots = (uint32_t)w.max_slots;
+    hipLaunchKernelGGL(tile_sum_kernel, dim3(w.n_tiles), dim3(1024), 0, stream, counts, n_slots, tile_sum);
+    hipLaunchKernelGGL(slot_offsets_kernel, dim3(w.n_tiles), dim3(1024), 0, stream, counts, n_slots, tile_sum, slot_string,
+                       slot_out, out_offsets, batch);
     const int grid = (int)std::min<int64_t>((w.max_slots + 7) / 8, 32768);   // two pieces per wave and round
-    hipLaunchKernelGGL(piece_pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, ctrl, piece_begin, piece_len,
+    hipLaunchKernelGGL(piece_pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, n_slots, piece_begin, piece_len,
                        counts, group_ids, slot_out, out_ids, table->d_id_map);
   }
   return hipGetLastError() == hipSuccess ? BPE_OK : BPE_EHIP;

@@ -113,12 +113,6 @@ using InlineItems = LaneShape<kMemberBytes, 12, 256, 128, 704, kOtherWords>;
 __device__ inline uint32_t mbcnt64(uint64_t mask) {                     // set bits of mask below my lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
-// Orders a wave's own LDS traffic (which the hardware executes in order) for the compiler.
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Where a segment that is done keeps its place in the output, its tokens being the mask in its first word: at its second
 // token, whose pair no longer counts, or behind the one token's word (a segment has four words at least).
 __device__ inline uint32_t lane_spare(uint32_t tokens) {
@@ -248,9 +242,9 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     to = (int)lane_read((uint32_t)from, min(lane + 1, 63));
     if (lane + 1 >= members) to = n;
     if (lane < L::kBytes / 32) strings[lane] = 0;
-    wave_sync();
+    wave_order();
     if (from < n) atomicOr(&strings[from >> 5], 1u << (from & 31));
-    wave_sync();
+    wave_order();
   }
   bool any_marked = false;                             // (special tokens) uniform
   {
@@ -305,7 +299,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
       }
     }
   }
-  wave_sync();
+  wave_order();
   __builtin_amdgcn_s_setprio(0);
 
   // ---- segments that no lane can take: more than 32 positions from a start to the next (nothing has left LDS) ----
@@ -352,7 +346,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     } else {
       if (lane == 63) p.counts[s] = n;
     }
-    wave_sync();
+    wave_order();
     return 0;
   }
   uint32_t total = 0;                                  // tokens of the segments done (uniform)
@@ -384,7 +378,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
       }
       if (lane == 0) list[n_listed] = (uint16_t)end;
     }
-    wave_sync();
+    wave_order();
     word0 = word1;
     const uint32_t list_first = listed_before;
     listed_before = listed_upto;
@@ -471,11 +465,11 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         }
       }
       if (lane < 32) hist[lane] = 0;
-      wave_sync();
+      wave_order();
       uint32_t found[L::kListed / 64];                  // what becomes of segment i0 + 64 r + lane
 #pragma unroll
       for (int r = 0; r < L::kListed / 64; ++r) found[r] = lds[L::kFound + 64 * r + lane];
-      wave_sync();
+      wave_order();
 
       if (n_jobs) {                                    // uniform
         // ---- list: the segments that need merges, longest first (counting sort over the 31 possible lengths) ----
@@ -489,18 +483,18 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
             place[r] = atomicAdd(&hist[31u - ((entry[r] >> 11) & 31u)], 1u);   // my place among those of my length
           }
         }
-        wave_sync();
+        wave_order();
         {
           const uint32_t mine = lane < 32 ? hist[lane] : 0u;
           const uint32_t inc = wave_scan<OpAdd>(mine, 0u);
-          wave_sync();
+          wave_order();
           if (lane < 32) hist[lane] = inc - mine;      // where the segments of length 32 - lane start
         }
-        wave_sync();
+        wave_order();
 #pragma unroll
         for (int r = 0; r < kRounds; ++r)
           if (64u * r + (uint32_t)lane < n_jobs) jobs[hist[31u - ((entry[r] >> 11) & 31u)] + place[r]] = entry[r];
-        wave_sync();
+        wave_order();
         // ---- their places in the arena: byte-level pre-tokenisation (section 4.1) and the initial pair values ----
         uint32_t arena = 0;                            // uniform
 #pragma unroll 1
@@ -513,7 +507,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
           const uint32_t upto = arena + wave_scan<OpAdd>(room, 0u);
           const uint32_t base = upto - room;
           arena = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-          wave_sync();                                 // (all lanes have read their entries)
+          wave_order();                                 // (all lanes have read their entries)
           if (len) {
             jobs[j] = (e & 0xFFFFu) | (base << 14);
             places[e >> 16] = (uint16_t)base;
@@ -550,7 +544,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
             }
           }
         }
-        wave_sync();
+        wave_order();
       }
       if (n_jobs) {                                    // uniform
         // ---- merge: Algorithm 1 on one segment per lane ----
@@ -560,7 +554,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         // scalar ones of branches included: so a lane without a segment, or without a look-up, has an address of its own
         // to read and write (kIdle) instead of a branch.
         if (lane < 4) lds[L::kIdle + lane] = kLaneNoPair;
-        wave_sync();
+        wave_order();
         uint32_t* const idle_v = lds + L::kIdle;
         uint32_t alive = 0;            // bit o: position o of my segment holds a token; 0: I have no segment
         uint32_t joined = 0;           // bit o: ... one that a merge has made
@@ -663,7 +657,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
           take_segments();                             // lanes whose segment just ended go on at once
           __builtin_amdgcn_s_setprio(0);
         }
-        wave_sync();
+        wave_order();
       }
 
       // ---- emit: a prefix sum of the segments' token counts gives every one its place ----
@@ -703,7 +697,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         if (what & kRecJob) V[at + lane_spare(tokens)] = o;
         total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
       }
-      wave_sync();
+      wave_order();
 #pragma unroll 1
       for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) {   // uniform
         uint32_t tokens = 0, o = 0, made = 0;
@@ -726,7 +720,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
           tokens &= tokens - 1u;
         }
       }
-      wave_sync();                                     // the round's LDS is used again
+      wave_order();                                     // the round's LDS is used again
       i0 = i1;
     }
   }
@@ -814,11 +808,11 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
           encode_item_lanes<L, SPECIAL, GROUPS>(p, s, begin, GROUPS ? n & kGroupLen : n, members, arrays, smem);
       if (left) {                                      // uniform
         if constexpr (INLINE) {
-          wave_sync();
+          wave_order();
           // (the other encoder's arrays take the place of this one's)
           const BlockShared<1> sh = block_shared<1>(arrays + 3 * 1024, smem + LaneShared::kByteWord);
           encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2 * 1024, sh);
-          wave_sync();
+          wave_order();
         } else {
           const uint32_t slot = uniform(
               atomicAdd(p.fallback_count, lane == 0 ? (uint32_t)__builtin_popcountll(left) : 0u));

@@ -1,4 +1,4 @@
-"""Split batches around the size up to which one workgroup lists them (4,096 slots: strings + bytes // 896): the most strings,
+"""Split batches around the size up to which one workgroup lists them (4,096 slots: strings + bytes // 896) and beyond: the most strings,
 the most slots of one string each, stretches without a cut over many slots, special tokens on the nominal cut positions."""
 import random
 
@@ -27,7 +27,8 @@ def fill(n_strings, slots, longest):
 @pytest.mark.parametrize("specials", [False, True])
 @pytest.mark.parametrize("lens", [
     [1025], [65536], [0, 0, 2000, 0], fill(4094, SLOTS, 1025), fill(4095, SLOTS + 1, 1025), fill(60, SLOTS, 65536),
-    fill(1024, SLOTS, 4096), fill(1025, SLOTS - 1, 5000), fill(3000, SLOTS, 60000)], ids=lambda x: f"{len(x)}x{max(x)}")
+    fill(1024, SLOTS, 4096), fill(1025, SLOTS - 1, 5000), fill(3000, SLOTS, 60000), fill(200, 5500, 65536),
+    fill(4000, 8000, 65536), fill(9000, 9800, 3000)], ids=lambda x: f"{len(x)}x{max(x)}")
 def test_small_split_batches(lens, specials):
     import torch
 

@@ -27,7 +27,6 @@ struct Control {
   uint32_t queue_head[kMaxTiers];                    // work-queue heads of the encode kernels
   uint32_t fallback_range[2];                        // {0, items the lane-per-segment kernel passed on}
   uint32_t fallback_queue;                           // work-queue head of the kernel that takes those
-  uint32_t n_slots;                                  // piece slots in the batch (small split batches)
 };
 
 __device__ inline int bin_key(int len, const TierPlan& plan) {
@@ -544,172 +543,74 @@ __global__ __launch_bounds__(1024) void piece_scatter_kernel(TierPlan plan, uint
   }
 }
 
-// The whole listing of a batch of at most kSmallSlots slots in one workgroup: slots, cuts, piece lengths, work list.  A launch
-// costs more than the work of a small batch, and what bounds this one is a chain of some ten memory and LDS round trips.
-// Each piece is an item.  Positions fit 32 bits: so few slots are less than 4 MiB.  Thread t takes the strings 4 t ... 4 t + 3
-// and the slots t, t + 1024, ...; a slot's cut is searched by its thread, sixteen candidates a round: the seventeen bytes
-// around them come in one load of 16 and one of 1, and the bit set of the cuts from LDS.
+// A batch of at most kSmallSlots slots, which are all resident at once, is not listed: each wave of the encode kernel takes a
+// slot and finds its piece itself (slot_piece).  It leaves what is to be done with the piece, for the kernels that come after.
 constexpr int kSmallSlots = 4096;
-__global__ __launch_bounds__(1024) void small_list_kernel(const uint8_t* bytes, const int64_t* offsets, int batch,
-                                                          const uint32_t* cut_bits, const uint8_t* cover, int piece_target,
-                                                          int max_string, TierPlan plan, Control* c, int32_t* slot_string,
-                                                          int64_t* piece_begin, int32_t* piece_len, int32_t* counts,
-                                                          int32_t* list, ItemDesc* desc) {
-  constexpr int kPer = kSmallSlots / 1024;
-  __shared__ uint32_t cuts[2048];
-  __shared__ int32_t string_begin[kSmallSlots + 1], first_slot[kSmallSlots + 1], begin[kSmallSlots];
-  __shared__ uint32_t hist[kBinKeys], scan[kBinKeys], wave_sum[16];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  if (t < 512) ((uint4*)cuts)[t] = ((const uint4*)cut_bits)[t];
-  if (t < kBinKeys) hist[t] = 0;
-  // ---- slots: how many each string has, and their scan ----
-  int32_t at[kPer + 1];
-  uint32_t slots[kPer], own = 0;
-#pragma unroll
-  for (int i = 0; i <= kPer; ++i) at[i] = (int32_t)offsets[min(kPer * t + i, batch)];
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    slots[i] = kPer * t + i < batch ? slots_of_length((int64_t)at[i + 1] - at[i], piece_target, max_string) : 0u;
-    own += slots[i];
-  }
-  uint32_t upto = own;
-  for (int step = 1; step < 64; step <<= 1) {
-    const uint32_t o = (uint32_t)__shfl_up((int)upto, step, 64);
-    if (lane >= step) upto += o;
-  }
-  if (lane == 63) wave_sum[wave] = upto;
-  __syncthreads();
-  uint32_t all = 0, place = upto - own;
-  for (int w = 0; w < 16; ++w) {
-    if (w < wave) place += wave_sum[w];
-    all += wave_sum[w];
-  }
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    if (kPer * t + i <= batch) {
-      string_begin[kPer * t + i] = at[i];
-      first_slot[kPer * t + i] = (int32_t)place;
+enum { kSlotDone, kSlotPassed, kSlotTier1, kSlotTier2, kSlotTier3 };   // (tier t is kSlotDone + 1 + t)
+struct SlotPiece {
+  int64_t begin;
+  int32_t len;                                         // -1: no piece starts in the slot
+};
+// The last cut within the kCutWindow positions up to t, or -1, by a whole wave: 64 candidates at a time.
+__device__ inline int64_t wave_last_cut(const uint8_t* bytes, const uint8_t* cover, const uint32_t* cuts, int64_t t) {
+  const int lane = threadIdx.x & 63;
+  for (int round = 0; round < kCutWindow / 64; ++round) {
+    const int64_t q = t - 64 * round - lane;
+    const uint32_t pair = bytes[q - 1] | (uint32_t)bytes[q] << 8;
+    bool cut = (cuts[pair >> 5] >> (pair & 31u)) & 1u;
+    if (cover) {                                       // special tokens: their ends are cuts, their inside is not
+      const uint32_t before = cover[q - 1], here = cover[q];
+      cut = (cut || before != 0 || here != 0) && here != kCoverRest;
     }
-    place += slots[i];
+    const uint64_t found = __ballot(cut);
+    if (found) return t - 64 * round - (int)__builtin_ctzll(found);
   }
-  if (t == 1023 && batch == kSmallSlots) {
-    string_begin[kSmallSlots] = at[kPer];
-    first_slot[kSmallSlots] = (int32_t)place;
+  return -1;
+}
+// The piece that starts in slot g, and what the packing kernel wants to know of the slots it covers.  A wave's work; all
+// arguments are uniform.
+__device__ inline SlotPiece slot_piece(const uint8_t* bytes, const int64_t* offsets, int batch, const uint8_t* cover,
+                                       const uint32_t* cuts, int piece_target, int max_string, uint32_t g,
+                                       int32_t* slot_string, int64_t* piece_begin, int32_t* piece_len) {
+  const int lane = threadIdx.x & 63;
+  int s = 0, n = batch;                                // the last string with its base <= g: 64 asked at a time
+  while (n > 1) {                                      // uniform; n shrinks every round
+    const int stride = (n + 63) >> 6;
+    const int64_t i = (int64_t)s + (int64_t)(lane + 1) * stride;
+    const bool upto = i < (int64_t)s + n && slot_base(offsets[i], (int)i, piece_target) <= g;
+    const int64_t skipped = (int64_t)__builtin_popcountll(__ballot(upto)) * stride;
+    s += (int)skipped;
+    n = (int)min((int64_t)stride, (int64_t)n - skipped);
   }
-  const int n_slots = (int)min(all, (uint32_t)kSmallSlots);
-  __syncthreads();
-  // ---- where each slot's piece starts ----
-  int owner[kPer];
-  int32_t start[kPer], from[kPer];                     // from: the highest candidate of the next round; 0: not searching
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int g = t + 1024 * j;
-    owner[j] = 0;
-    start[j] = -1;                                     // void unless a cut is found
-    from[j] = 0;
-    if (g < n_slots) {
-      int lo = 0, hi = batch - 1;                      // the last string whose first slot is <= g
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (first_slot[mid] <= g) lo = mid; else hi = mid - 1;
-      }
-      owner[j] = lo;
-      const int32_t first = string_begin[lo], len = string_begin[lo + 1] - first;
-      const int i = g - first_slot[lo];
-      if (len < 0 || len > max_string) continue;       // not encodable: the string yields no tokens
-      if (i == 0) start[j] = first;
-      else from[j] = first + i * piece_target;         // (at least twice the window: the search stays inside the string)
+  const int64_t begin = offsets[s], end = offsets[s + 1];
+  const uint32_t base = slot_base(begin, s, piece_target);
+  const uint32_t end_slot = base + slots_of_length(end - begin, piece_target, max_string);
+  const bool used = g < end_slot && end >= begin && end - begin <= max_string;
+  const int64_t t = begin + (int64_t)(g - base) * piece_target;
+  SlotPiece piece{-1, -1};
+  if (used) piece.begin = g == base ? begin : wave_last_cut(bytes, cover, cuts, t);
+  if (lane == 0) {
+    slot_string[g] = g == base ? s : -1;
+    piece_begin[g] = piece.begin;
+    if (!used) piece_len[g] = 0;                       // (of a void slot that a piece runs over: the piece's wave)
+  }
+  if (piece.begin < 0) return piece;
+  int64_t piece_end = end;
+  if (g + 1u < end_slot) {
+    int64_t next = wave_last_cut(bytes, cover, cuts, t + piece_target);
+    for (uint32_t h0 = g + 1u; next < 0 && h0 < end_slot; h0 += 64u) {   // a slot a lane
+      const uint32_t h = h0 + (uint32_t)lane;
+      const int64_t at = last_cut(bytes, cover, cuts, begin + (int64_t)(h - base) * piece_target, h < end_slot);
+      const uint64_t found = __ballot(at >= 0);
+      const uint32_t stop = found ? h0 + (uint32_t)__builtin_ctzll(found) : end_slot;
+      if (h < stop) piece_len[h] = (int32_t)g - (int32_t)h;
+      if (found) next = __shfl(at, (int)__builtin_ctzll(found), 64);
     }
+    if (next >= 0) piece_end = next;
   }
-  for (int round = 0; round < kCutWindow / 16; ++round) {
-    uint4 v[kPer], m[kPer];
-    uint32_t last[kPer], last_m[kPer];
-    bool any = false;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      v[j] = m[j] = make_uint4(0, 0, 0, 0);
-      last[j] = last_m[j] = 0;
-      if (from[j]) {
-        __builtin_memcpy(&v[j], bytes + from[j] - 16, 16);
-        last[j] = bytes[from[j]];
-        if (cover) {
-          __builtin_memcpy(&m[j], cover + from[j] - 16, 16);
-          last_m[j] = cover[from[j]];
-        }
-        any = true;
-      }
-    }
-    if (!__ballot(any)) break;                         // uniform
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      if (from[j]) {
-        const uint32_t found = cut_candidates(v[j], last[j], m[j], last_m[j], cover != nullptr, cuts);
-        if (found) {
-          start[j] = from[j] - 15 + (31 - __builtin_clz(found));         // the last one
-          from[j] = 0;
-        } else {
-          from[j] -= 16;
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < kPer; ++j)
-    if (t + 1024 * j < n_slots) begin[t + 1024 * j] = start[j];
-  __syncthreads();
-  // ---- the pieces: to the next one of their string, or to the string's end ----
-  int32_t len[kPer];
-  int key[kPer];
-  uint32_t rank[kPer];
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int g = t + 1024 * j;
-    len[j] = 0;
-    key[j] = -1;
-    rank[j] = 0;
-    if (g < n_slots) {
-      const bool head = first_slot[owner[j]] == g;
-      if (start[j] >= 0) {
-        const int end = first_slot[owner[j] + 1];
-        int h = g + 1;
-        while (h < end && begin[h] < 0) {              // (the slots that it runs over get their shares of the copying)
-          piece_len[h] = g - h;
-          ++h;
-        }
-        len[j] = (h < end ? begin[h] : string_begin[owner[j] + 1]) - start[j];
-        key[j] = bin_key(len[j], plan);
-        if (key[j] >= 0) rank[j] = atomicAdd(&hist[key[j]], 1u);
-      }
-      if (start[j] >= 0 || head) piece_len[g] = len[j];
-      piece_begin[g] = start[j];
-      slot_string[g] = head ? owner[j] : -1;
-      if (key[j] < 0) counts[g] = 0;                   // void slot, or too long for the launched variants
-    }
-  }
-  __syncthreads();
-  if (t < kBinKeys) scan[t] = hist[t];
-  __syncthreads();
-  for (int step = 1; step < kBinKeys; step <<= 1) {    // inclusive scan, all threads reach the barriers
-    uint32_t v = 0;
-    if (t < kBinKeys && t >= step) v = scan[t - step];
-    __syncthreads();
-    if (t < kBinKeys) scan[t] += v;
-    __syncthreads();
-  }
-  if (t <= kMaxTiers) c->tier_base[t] = t == 0 ? 0 : scan[(t <= plan.n_tiers ? t : plan.n_tiers) * kLenBuckets - 1];
-  if (t < kMaxTiers) c->queue_head[t] = 0;
-  if (t < 2) c->fallback_range[t] = 0;
-  if (t == 2) c->fallback_queue = 0;
-  if (t == 3) c->n_slots = (uint32_t)n_slots;
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    if (key[j] >= 0) {
-      const int g = t + 1024 * j;
-      const uint32_t pos = scan[key[j]] - hist[key[j]] + rank[j];
-      list[pos] = g;
-      desc[pos] = ItemDesc{start[j], key[j] < kLenBuckets ? len[j] | 1 << kGroupShift : len[j], g};
-    }
-  }
+  piece.len = (int32_t)(piece_end - piece.begin);
+  if (lane == 0) piece_len[g] = piece.len;
+  return piece;
 }
 
 // Token offsets of the slots: per-tile sums, then the scan inside each tile.
@@ -1017,15 +918,13 @@ __global__ __launch_bounds__(256) void piece_pack_kernel(const int32_t* tmp_ids,
 
 // Offsets and packing of a batch of at most kSmallSlots slots in one launch: a workgroup sums the counts before its four
 // slots itself, four loads of 16 bytes a thread at most, and each of its waves copies one.
-__global__ __launch_bounds__(256) void small_pack_kernel(const int32_t* tmp_ids, const Control* c, const int32_t* slot_string,
+__global__ __launch_bounds__(256) void small_pack_kernel(const int32_t* tmp_ids, int n_slots, const int32_t* slot_string,
                                                          const int64_t* piece_begin, const int32_t* piece_len,
                                                          const int32_t* counts, int64_t* out_offsets, int batch,
                                                          int32_t* out_ids, const int32_t* id_map) {
   __shared__ int32_t wave_sum[4];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int n_slots = (int)c->n_slots;
   const int g = 4 * (int)blockIdx.x + wave;
-  if (4 * (int)blockIdx.x >= n_slots) return;          // uniform
   int32_t before = 0;
   for (int q = t; q < (int)blockIdx.x; q += 256) {
     const int4 v = ((const int4*)counts)[q];

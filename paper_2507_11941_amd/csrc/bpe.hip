@@ -60,36 +60,46 @@ struct Variant {
 
 // Items of tier t have up to kTierBytes[t] bytes: one wave, four, sixteen in LDS, sixteen with their arrays in HBM.
 constexpr int kTierBytes[kMaxTiers] = {kMemberBytes, 4096, 16384, 65536};
-template <bool SPC>
+template <bool SPC, bool SLT>
 void launch_short(const EncodeParams& p, int grid, hipStream_t stream) {
-  encode_short_kernel<SPC><<<dim3(grid), dim3(256), lds_blocks(4 * kShortWords), stream>>>(p);
+  encode_short_kernel<SPC, SLT><<<dim3(grid), dim3(256), lds_blocks(4 * kShortWords), stream>>>(p);
 }
-template <bool SPC>
+template <bool SPC, bool SLT>
 void launch_long(const EncodeParams& p, int grid, hipStream_t stream) {
-  encode_long_kernel<SPC><<<dim3(grid), dim3(1024), lds_blocks(4 * kLongWords), stream>>>(p);
+  encode_long_kernel<SPC, SLT><<<dim3(grid), dim3(1024), lds_blocks(4 * kLongWords), stream>>>(p);
 }
-Variant g_short_variants[2] = {{4, lds_blocks(4 * kShortWords), (const void*)&encode_short_kernel<false>, &launch_short<false>},
-                               {4, lds_blocks(4 * kShortWords), (const void*)&encode_short_kernel<true>, &launch_short<true>}};
-Variant g_long_variants[2] = {{16, lds_blocks(4 * kLongWords), (const void*)&encode_long_kernel<false>, &launch_long<false>},
-                              {16, lds_blocks(4 * kLongWords), (const void*)&encode_long_kernel<true>, &launch_long<true>}};
+template <bool SPC, bool SLT>
+Variant make_short_variant() {
+  return {4, lds_blocks(4 * kShortWords), (const void*)&encode_short_kernel<SPC, SLT>, &launch_short<SPC, SLT>};
+}
+template <bool SPC, bool SLT>
+Variant make_long_variant() {
+  return {16, lds_blocks(4 * kLongWords), (const void*)&encode_long_kernel<SPC, SLT>, &launch_long<SPC, SLT>};
+}
+// [family][the batch is split, and small enough not to be listed]
+Variant g_short_variants[2][2] = {{make_short_variant<false, false>(), make_short_variant<false, true>()},
+                                  {make_short_variant<true, false>(), make_short_variant<true, true>()}};
+Variant g_long_variants[2][2] = {{make_long_variant<false, false>(), make_long_variant<false, true>()},
+                                 {make_long_variant<true, false>(), make_long_variant<true, true>()}};
 
 // Items of tier 0 go to the lane-per-segment kernel; it passes those strings and pieces on that have a segment of more than
 // 32 bytes.  [family][shape]: with kDirect item i is string i, and the kernel encodes those itself (the launch without a
-// work list); else the items are groups of strings or pieces, of up to 1 KiB (kSmall) or 2 KiB (kLarge).
-enum { kDirect, kSmall, kLarge, kLaneShapes };
-template <class L, bool SPC, bool INL>
+// work list); with kSlots item i is the piece that starts in slot i; else the items are groups of strings or pieces, of up
+// to 1 KiB (kSmall) or 2 KiB (kLarge).
+enum { kDirect, kSlots, kSmall, kLarge, kLaneShapes };
+template <class L, bool SPC, bool INL, bool SLT>
 void launch_lanes(const EncodeParams& p, int grid, hipStream_t stream) {
-  encode_lanes_kernel<L, SPC, INL><<<dim3(grid), dim3(64 * L::kWaves), L::kLdsBytes, stream>>>(p);
+  encode_lanes_kernel<L, SPC, INL, SLT><<<dim3(grid), dim3(64 * L::kWaves), L::kLdsBytes, stream>>>(p);
 }
-template <class L, bool SPC, bool INL>
+template <class L, bool SPC, bool INL, bool SLT>
 Variant make_lanes_variant() {
-  return {L::kWaves, L::kLdsBytes, (const void*)&encode_lanes_kernel<L, SPC, INL>, &launch_lanes<L, SPC, INL>};
+  return {L::kWaves, L::kLdsBytes, (const void*)&encode_lanes_kernel<L, SPC, INL, SLT>, &launch_lanes<L, SPC, INL, SLT>};
 }
 Variant g_lanes_variants[2][kLaneShapes] = {
-    {make_lanes_variant<InlineItems, false, true>(), make_lanes_variant<SmallItems, false, false>(),
-     make_lanes_variant<LargeItems, false, false>()},
-    {make_lanes_variant<InlineItems, true, true>(), make_lanes_variant<SmallItems, true, false>(),
-     make_lanes_variant<LargeItems, true, false>()},
+    {make_lanes_variant<InlineItems, false, true, false>(), make_lanes_variant<SmallItems, false, false, true>(),
+     make_lanes_variant<SmallItems, false, false, false>(), make_lanes_variant<LargeItems, false, false, false>()},
+    {make_lanes_variant<InlineItems, true, true, false>(), make_lanes_variant<SmallItems, true, false, true>(),
+     make_lanes_variant<SmallItems, true, false, false>(), make_lanes_variant<LargeItems, true, false, false>()},
 };
 std::once_flag g_variants_once;
 int g_variants_status = BPE_OK;
@@ -104,8 +114,8 @@ void init_variants() {
   }
   g_num_cus = prop.multiProcessorCount;
   std::vector<Variant*> all;
-  for (auto& v : g_short_variants) all.push_back(&v);
-  for (auto& v : g_long_variants) all.push_back(&v);
+  for (auto& family : g_short_variants) for (auto& v : family) all.push_back(&v);
+  for (auto& family : g_long_variants) for (auto& v : family) all.push_back(&v);
   for (auto& family : g_lanes_variants) for (auto& v : family) all.push_back(&v);
   for (Variant* vp : all) {
     Variant& v = *vp;
@@ -580,7 +590,8 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const int room = small_items ? -1
                                : (int)std::min<int64_t>(total_bytes / std::max(1, listed.max_grid * listed.waves / 2) +
                                                             total_bytes / w.max_slots / 2, kGroupBytes);
-  const bool small_split = w.split && small_items && w.max_slots <= kSmallSlots;
+  const bool small_split = w.split && w.max_slots <= kSmallSlots &&
+                           w.max_slots <= (int64_t)lanes[kSlots].max_grid * lanes[kSlots].waves;
   const uint32_t* cuts = (const uint32_t*)table->d_words;
   if (direct) {
     list = nullptr;
@@ -598,12 +609,10 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, ctrl, part, (ItemDesc*)(ws + w.list_desc));
   } else {
     int32_t* ss = (int32_t*)(ws + w.slot_string);
+    if (small_split) list = nullptr;
     int64_t* pb = (int64_t*)(ws + w.piece_begin);
     int32_t* pl = (int32_t*)(ws + w.piece_len);
-    if (small_split) {
-      hipLaunchKernelGGL(small_list_kernel, dim3(1), dim3(1024), 0, stream, bytes, offsets, batch, cuts, cover, kPieceTarget,
-                         BPE_MAX_STRING_BYTES, plan, ctrl, ss, pb, pl, counts, list, (ItemDesc*)(ws + w.list_desc));
-    } else {
+    if (!small_split) {
       uint32_t* part = (uint32_t*)(ws + w.part);
       int32_t* il = (int32_t*)(ws + w.item_len);
       group_ids = (int32_t*)(ws + w.group_ids);
@@ -642,7 +651,14 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.queue_head = ctrl->queue_head;
   p.tmp_ids = tmp_ids;
   p.counts = counts;
-  p.direct_count = (uint32_t)batch;
+  p.direct_count = small_split ? (uint32_t)w.max_slots : (uint32_t)batch;
+  p.slot_kind = small_split ? (int32_t*)(ws + w.item_len) : nullptr;
+  p.slot_string = (int32_t*)(ws + w.slot_string);
+  p.slot_begin = (int64_t*)(ws + w.piece_begin);
+  p.slot_len = (int32_t*)(ws + w.piece_len);
+  p.piece_target = kPieceTarget;
+  p.max_string = BPE_MAX_STRING_BYTES;
+  p.batch = batch;
   p.cover = cover;
   p.special_base = 256u + (uint32_t)table->n_merges;
   p.total_bytes = total_bytes;
@@ -663,14 +679,14 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
       if (hipEventRecord(g_prof.begin[prof_slot], stream) != hipSuccess) return BPE_EHIP;
     }
   }
-  const Variant& lv = direct ? lanes[kDirect] : listed;
+  const Variant& lv = direct ? lanes[kDirect] : small_split ? lanes[kSlots] : listed;
   lv.launch(p, std::min(lv.max_grid, n_items_max), stream);
   if (!direct) {
-    const Variant& rest = g_short_variants[cover ? 1 : 0];
+    const Variant& rest = g_short_variants[cover ? 1 : 0][small_split ? 1 : 0];
     rest.launch(p, std::min(rest.max_grid, n_items_max), stream);
   }
   if (plan.n_tiers > 2) {
-    const Variant& longest = g_long_variants[cover ? 1 : 0];
+    const Variant& longest = g_long_variants[cover ? 1 : 0][small_split ? 1 : 0];
     longest.launch(p, std::min(std::min(longest.max_grid, kMaxLongGrid), n_items_max), stream);
   }
   if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
@@ -686,7 +702,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, offsets, out_offsets, ctrl,
                        (const ItemDesc*)(ws + w.list_desc), out_ids, table->d_id_map);
   } else if (small_split) {
-    hipLaunchKernelGGL(small_pack_kernel, dim3((unsigned)((w.max_slots + 3) / 4)), dim3(256), 0, stream, tmp_ids, ctrl, slot_string,
+    hipLaunchKernelGGL(small_pack_kernel, dim3((unsigned)((w.max_slots + 3) / 4)), dim3(256), 0, stream, tmp_ids, (int)w.max_slots, slot_string,
                        piece_begin, piece_len, counts, out_offsets, batch, out_ids, table->d_id_map);
   } else {
     int64_t* tile_sum = (int64_t*)(ws + w.tile_sum);

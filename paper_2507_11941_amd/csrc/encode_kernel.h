@@ -70,6 +70,12 @@ struct EncodeParams {
   uint32_t prefetch_lines;    // 128-byte lines of table memory to pull into L2 at kernel start (0 = none)
   uint32_t direct_count;      // when `list` is null: items are the strings 0..direct_count-1, one per workgroup
   int n_tiers;
+  // when the items are the slots of a small split batch (no list):
+  int32_t* slot_kind;         // kSlot... of every slot, else null
+  int32_t* slot_string;
+  int64_t* slot_begin;        // (piece_begin and piece_len)
+  int32_t* slot_len;
+  int piece_target, max_string, batch;
   const uint8_t* cover;       // null, or one mark per input byte: where the special tokens lie (see kCover*)
   uint32_t special_base;      // token number of special 0 (256 + rows)
   int64_t total_bytes;        // size of `bytes`: wide loads must not run past it

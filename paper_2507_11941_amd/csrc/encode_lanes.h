@@ -741,9 +741,10 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
 // string i, and one with a segment that no lane can take goes to the wave-per-item encoder in this kernel.  Else the items
 // are groups of strings, or of pieces of strings (see group_members); those of a group that hold such a segment go to
 // p.fallback_list, for the kernel that comes after this one, and the group's descriptor is marked for the packing kernel.
-template <class L, bool SPECIAL, bool INLINE>
+// SLOTS: the items are the slots of a small split batch; each wave takes one and finds its piece.
+template <class L, bool SPECIAL, bool INLINE, bool SLOTS>
 __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodeParams p) {
-  constexpr bool GROUPS = !INLINE;
+  constexpr bool GROUPS = !INLINE && !SLOTS;
   extern __shared__ __align__(16) uint32_t smem[];
   const uint32_t first = p.list ? p.tier_base[0] : 0u;
   const uint32_t count = p.list ? p.tier_base[1] - first : p.direct_count;
@@ -781,6 +782,21 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   // chunk costs one round trip for its claim and one for its descriptors.  (Claiming ahead does not pay: loads
   // return in order, so whatever is loaded after the claim waits for it.)
   const int lane = (int)threadIdx.x & 63;
+  if constexpr (SLOTS) {                               // (the grid covers the slots)
+    const SlotPiece piece = slot_piece(p.bytes, p.offsets, p.batch, p.cover, smem + LaneShared::kCuts, p.piece_target,
+                                       p.max_string, b, p.slot_string, p.slot_begin, p.slot_len);
+    int kind = kSlotDone;
+    const int tier = piece.len <= kMemberBytes ? 0 : piece.len <= 4096 ? 1 : piece.len <= 16384 ? 2 : 3;
+    if (piece.len < 0 || tier >= p.n_tiers) {          // void, or longer than the host said: nobody encodes it
+      if (lane == 0) p.counts[b] = 0;
+    } else if (tier > 0) {
+      kind = kSlotDone + 1 + tier;
+    } else if (encode_item_lanes<L, SPECIAL, false>(p, (int)b, piece.begin, piece.len, 1, arrays, smem)) {
+      kind = kSlotPassed;
+    }
+    if (lane == 0) p.slot_kind[b] = kind;
+    return;
+  }
   const ItemDesc* const descs = (const ItemDesc*)p.list_desc;
   auto load_chunk = [&](uint64_t first_item, uint32_t n_items, ItemDesc& d) {
     d.begin = 0;

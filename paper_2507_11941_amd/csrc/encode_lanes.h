@@ -199,7 +199,7 @@ __device__ inline uint4 load_16_bytes(const uint8_t* src, int at, int64_t before
 // string, each one's ids lie at its own place in tmp_ids instead of one after the other.  (100,000 rows of up to 60 bytes,
 // one in twenty with such a segment: 183 us.  With the whole group given away, five rows in six went to the
 // wave-per-item encoder: 1,029 us; with each row an item of its own 728.)
-template <class L, bool SPECIAL, bool GROUPS>
+template <class L, bool SPECIAL, bool GROUPS, bool ALONE>
 __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int s, int64_t begin, int n, int members,
                                                       uint32_t* lds, const uint32_t* shared) {
   const int lane = (int)threadIdx.x & 63;
@@ -333,7 +333,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
   const uint32_t my_count = (uint32_t)__builtin_popcount(my_starts);
   const uint32_t starts_upto = wave_scan<OpAdd>(my_count, 0u);
 
-  int32_t* const dst = p.tmp_ids + begin;
+  int32_t* const dst = ALONE && p.out_ids ? p.out_ids : p.tmp_ids + begin;
   // Single bytes all (blank lines, padding that no row joins): their ids are the bytes.  (64 strings of 64 KiB of spaces: 16 us,
   // as segments 48.)
   if ((int)__builtin_amdgcn_readlane((int)starts_upto, 63) == n && !any_marked) {        // uniform
@@ -791,7 +791,7 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
       if (lane == 0) p.counts[b] = 0;
     } else if (tier > 0) {
       kind = kSlotDone + 1 + tier;
-    } else if (encode_item_lanes<L, SPECIAL, false>(p, (int)b, piece.begin, piece.len, 1, arrays, smem)) {
+    } else if (encode_item_lanes<L, SPECIAL, false, false>(p, (int)b, piece.begin, piece.len, 1, arrays, smem)) {
       kind = kSlotPassed;
     }
     if (lane == 0) p.slot_kind[b] = kind;
@@ -821,7 +821,7 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
                             (uint32_t)__builtin_amdgcn_readlane((int)cur.begin, (int)i);
       const int members = GROUPS ? (n >> kGroupShift) & kGroupMask : 1;
       const uint64_t left =
-          encode_item_lanes<L, SPECIAL, GROUPS>(p, s, begin, GROUPS ? n & kGroupLen : n, members, arrays, smem);
+          encode_item_lanes<L, SPECIAL, GROUPS, INLINE>(p, s, begin, GROUPS ? n & kGroupLen : n, members, arrays, smem);
       if (left) {                                      // uniform
         if constexpr (INLINE) {
           wave_order();
@@ -834,6 +834,20 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
               atomicAdd(p.fallback_count, lane == 0 ? (uint32_t)__builtin_popcountll(left) : 0u));
           if ((left >> lane) & 1ull) p.fallback_list[slot + mbcnt64(left)] = s + lane;
           if (lane == 0) ((ItemDesc*)p.list_desc)[first + at + i].len = n | kGroupApart;
+        }
+      }
+      if constexpr (INLINE) {
+        // The only string of its batch: this wave finishes the output, for which there is no other launch.
+        if (p.out_ids) {                               // uniform
+          __threadfence();                             // (it reads what it has just written)
+          const int k = __hip_atomic_load(p.counts + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const int32_t* const ids = left ? p.tmp_ids + begin : p.out_ids;
+          if (left || p.id_map)
+            for (int o = lane; o < k; o += 64) {
+              const int32_t id = __hip_atomic_load(ids + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              p.out_ids[o] = vocabulary_id(p.id_map, id);
+            }
+          if (lane < 2) p.out_offsets[lane] = lane == 0 ? 0 : k;
         }
       }
     }

@@ -88,3 +88,16 @@ def test_words(shape, kind):
         ids, off = gpu_encode(t, data, offsets)
         want_ids, want_off = o.encode_batch(data, offsets, tier=oracle.HEAP)
         assert_same_encoding(ids, off, want_ids, want_off, f"{shape}, {kind}, {len(strings)} strings")
+
+
+@pytest.mark.parametrize("n_bytes", [0, 1, 96, 97, 5000, 300000])
+def test_host_strings_of_a_token_a_byte(n_bytes):
+    """More tokens than are fetched at first (a third of the bytes, and 64)."""
+    import paper_2507_11941_amd as bpe
+
+    rng = np.random.default_rng(n_bytes)
+    data = rng.integers(0, 256, size=n_bytes, dtype=np.uint8).tobytes()
+    strings = [data[i:i + 777] for i in range(0, n_bytes, 777)] + [b"", "aé"]
+    got = bpe.encode_strings(bpe.build_table([]), strings)
+    assert [x.dtype for x in got] == [np.int32] * len(strings)
+    assert [x.tolist() for x in got] == [list(s if isinstance(s, bytes) else s.encode()) for s in strings]

@@ -603,9 +603,11 @@ __device__ inline uint32_t own_items(const EncodeParams& p, int kind, uint16_t* 
   return all > blockIdx.x ? min((all - 1u - blockIdx.x) / gridDim.x + 1u, (uint32_t)kOwnItems) : 0u;
 }
 
-// What one wave or four encode: the items passed on, up to 1 KiB, then tier 1, up to 4 KiB, if it is there.  One launch for
-// both: mostly there is nothing to do, and a launch costs 3 to 4 us (one document of 60,001 bytes: 46 us with a launch for
-// each of four variants); where there is, a wave that finds no more of the first goes on to the second.
+// What four waves or one encode: tier 1, up to 4 KiB, if it is there, then the items passed on, up to 1 KiB.  One launch for
+// both: mostly there is nothing to do, and a launch costs some 2 us (one document of 60,001 bytes: 46 us with a launch for
+// each of four variants, 43 with two); where there is, the long items come first and the waves that find no more of them go
+// on to the short ones, each by itself (2,048 x 16 KiB of runs and motifs: 936 us with the short ones
+// first, whose end then waited for the last long item; 896 this way round).
 constexpr int kShortArrayWords = encode_array_words<4, 16, false, true>();
 constexpr int kShortWords = kShortArrayWords + 4 * encode_exchange_words<1>() + encode_exchange_words<4>() + 256;
 // SLOTS: for a small split batch, whose items are found by their kind.
@@ -630,12 +632,13 @@ __global__ __launch_bounds__(256) void encode_short_kernel(EncodeParams p) {
   __syncthreads();
   const int wave = (int)threadIdx.x >> 6;
   uint32_t* const exchange = smem + kShortArrayWords;
+  if (SLOTS ? count > 0 : blockIdx.x < count) {        // uniform
+    encode_tier<4, 16, false, true, true, SPECIAL, SLOTS>(p, 1, count, own[1], smem,
+                                                          block_shared<4>(exchange + 4 * encode_exchange_words<1>(), byte_word));
+    __syncthreads();                                   // the arrays are used again
+  }
   encode_passed<SPECIAL, SLOTS>(p, passed, 4, own[0], smem + wave * encode_array_words<1, 16, false, true>(),
-                         block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word));
-  if (SLOTS ? !count : blockIdx.x >= count) return;    // uniform
-  __syncthreads();                                     // the arrays are used again
-  encode_tier<4, 16, false, true, true, SPECIAL, SLOTS>(p, 1, count, own[1], smem,
-                                                 block_shared<4>(exchange + 4 * encode_exchange_words<1>(), byte_word));
+                                block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word));
 }
 
 // What sixteen waves encode: tier 2, up to 16 KiB, in LDS (two arrays: three of 16 Ki words would not fit), and tier 3, up to

@@ -57,50 +57,6 @@ struct ItemDesc {
   int32_t item;                                      // string index, or slot index when strings are split
 };
 
-// One workgroup bins the whole batch: histogram of (class, length bucket) keys in LDS, exclusive scan of the
-// 256 keys, then the scatter of string indices into the work list (class-major, longest bucket first).
-// Also resets the work-queue heads.  A second pass over the offsets is cheaper than a second launch.  For batches of up
-// to kSinglesMax strings, one item each: all of them are resident within a round or so, and the launches that groups
-// need cost more than they save (2,000 strings of up to 400 bytes: 30 us, in groups 40; 4,096 of 60, of up to 400 and of
-// 1,000 bytes: 40, 39 and 57 us, in groups 42, 41 and 61).  Beyond, where an item a string needs a second round, groups
-// win (6,000 of 100, 250 and 1,000 bytes: 61, 66 and 88 us, in groups 40, 45 and 82).
-constexpr int kSinglesMax = 4096;
-__global__ __launch_bounds__(1024) void bin_kernel(const int64_t* offsets, int batch, TierPlan plan, Control* c,
-                                                   int32_t* list, ItemDesc* desc, int32_t* counts) {
-  __shared__ uint32_t hist[kBinKeys], scan[kBinKeys], cursor[kBinKeys];
-  const int t = threadIdx.x;
-  if (t < kBinKeys) { hist[t] = 0; cursor[t] = 0; }
-  __syncthreads();
-  for (int s = t; s < batch; s += 1024) {
-    const int64_t len = offsets[s + 1] - offsets[s];
-    const int key = (len < 0 || len > 0x7FFFFFFF) ? -1 : bin_key((int)len, plan);
-    if (key >= 0) atomicAdd(&hist[key], 1u);
-    else counts[s] = 0;                              // never encoded: contributes no tokens
-  }
-  __syncthreads();
-  if (t < kBinKeys) scan[t] = hist[t];
-  __syncthreads();
-  for (int step = 1; step < kBinKeys; step <<= 1) {  // inclusive scan, all threads reach the barriers
-    uint32_t v = 0;
-    if (t < kBinKeys && t >= step) v = scan[t - step];
-    __syncthreads();
-    if (t < kBinKeys) scan[t] += v;
-    __syncthreads();
-  }
-  if (t <= kMaxTiers) c->tier_base[t] = t == 0 ? 0 : scan[(t <= plan.n_tiers ? t : plan.n_tiers) * kLenBuckets - 1];
-  if (t < kMaxTiers) c->queue_head[t] = 0;
-  if (t < 2) c->fallback_range[t] = 0;
-  if (t == 2) c->fallback_queue = 0;
-  for (int s = t; s < batch; s += 1024) {
-    const int64_t len = offsets[s + 1] - offsets[s];
-    const int key = (len < 0 || len > 0x7FFFFFFF) ? -1 : bin_key((int)len, plan);
-    if (key < 0) continue;
-    const uint32_t pos = (scan[key] - hist[key]) + atomicAdd(&cursor[key], 1u);
-    list[pos] = s;
-    desc[pos] = ItemDesc{offsets[s], (int32_t)len | 1 << kGroupShift, s};
-  }
-}
-
 // The work list of a batch whose strings are not split and that has more of them than are resident at once: groups of
 // neighbouring strings, longest length bucket first.  (Such a batch has one tier.)  An item costs its wave some ten
 // microseconds of round trips whatever its length, so short strings go together: 20,011 strings of up to 400 bytes

@@ -579,13 +579,15 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   // A batch that one variant's resident grid covers needs no work list: workgroup i encodes string i.
   const Variant* lanes = g_lanes_variants[cover ? 1 : 0];
   const bool direct = !w.split && plan.n_tiers == 1 && batch <= lanes[kDirect].max_grid * lanes[kDirect].waves;
-  const bool singles = !w.split && !direct && batch <= kSinglesMax;    // one item a string; above, groups of strings
   // The work list's items.  As long as every string or piece gets a wave of its own, that is what it is; beyond,
   // neighbours within `room` bytes are one item: all that the kernel takes, but so little in small batches that half of the
   // resident waves get an item before any gets two (a group stays half a member below its room on average; 20,011 strings of
-  // up to 400 bytes: 45.0 us, with three quarters 46.2, with all but one sixteenth, where some get two, 55.7).
+  // up to 400 bytes: 45.0 us, with three quarters 46.2, with all but one sixteenth, where some get two, 55.7; with a third
+  // or a quarter, 100,000 of up to 60 bytes take 65 instead of 57).  Batches that need no groups are listed by the same two
+  // kernels: binned by one workgroup and packed by one a string, 4,096 of 60, 250 and 1,000 bytes took 40.5, 43.8 and 55.5 us,
+  // so 36.2, 39.5 and 50.2.
   const int64_t small_waves = (int64_t)lanes[kSmall].max_grid * lanes[kSmall].waves;
-  const bool small_items = singles || w.max_slots <= small_waves;
+  const bool small_items = w.max_slots <= small_waves;
   const Variant& listed = lanes[small_items ? kSmall : kLarge];
   const int room = small_items ? -1
                                : (int)std::min<int64_t>(total_bytes / std::max(1, listed.max_grid * listed.waves / 2) +
@@ -595,9 +597,6 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const uint32_t* cuts = (const uint32_t*)table->d_words;
   if (direct) {
     list = nullptr;
-  } else if (singles) {
-    hipLaunchKernelGGL(bin_kernel, dim3(1), dim3(1024), 0, stream, offsets, batch, plan, ctrl, list,
-                       (ItemDesc*)(ws + w.list_desc), counts);
   } else if (!w.split) {
     // (the stretches' histograms, 256 bytes per 1,024 strings at most, borrow the fallback list, 4 bytes a string,
     // which is written only once the work list is made)
@@ -696,7 +695,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
   if (alone) {
     // (nothing to place or to copy: a launch less, one prompt of 300 bytes 15.4 -> 13.8 us)
-  } else if (direct || singles) {                        // (groups' ids do not lie string by string)
+  } else if (direct) {                                   // (groups' ids do not lie string by string)
     hipLaunchKernelGGL(scan_pack_kernel, dim3(batch), dim3(256), 0, stream, tmp_ids, offsets, counts, batch,
                        out_offsets, out_ids, table->d_id_map);
   } else if (!w.split) {

@@ -25,10 +25,10 @@
 //
 // words to emit run over as many segments at a time as the arena and the lists hold: in text, all of the item's.
 //
-// What bounds it is instruction issue: some 1,700 vector and 900 scalar instructions per KiB of text, of which the merge
+// What bounds it is instruction issue: some 2,080 vector and 550 scalar instructions per KiB of text, of which the merge
 // loop is two fifths, on four waves a SIMD.  With every segment going through the merges, one item of 1 KiB a wave
 // (14.9 trips of the loop per KiB instead of 6.3), the 65,536 documents of the throughput workload took 1,480 us in this
-// kernel; they take 920.
+// kernel; they take 985, and the whole call 1,075 instead of 1,659.
 #pragma once
 #include "encode_segmented.h"
 
@@ -36,8 +36,8 @@ namespace bpe {
 
 constexpr int kLaneSegmentMax = 32;             // positions a lane's liveness mask covers
 constexpr int kLaneBatches = 3;                 // batches of 64 segments whose look-ups are in flight together
-constexpr uint32_t kLaneChunk = 4;              // work items a wave claims at a time (1: 3.4 ms on the
-                                                // 270,000 pieces of the throughput workload, 2: 2.2, 4: 2.1, 8: 2.1);
+constexpr uint32_t kLaneChunk = 4;              // work items a wave claims at a time (1: 3.4 ms on 270,000 pieces of
+                                                // 1 KiB, 2: 2.2, 4: 2.1, 8: 2.1, when all their segments were merged);
                                                 // twice as many when the list holds 32 or more items per wave
 
 // What the lanes keep of a segment is one word for each of its positions.  It is the value of the pair that begins there,
@@ -197,8 +197,8 @@ __device__ inline uint4 load_16_bytes(const uint8_t* src, int at, int64_t before
 // in those bytes: a string's first byte starts a segment, and each string gets its own count.  The result has a
 // bit for every string with a segment that fits no lane; the others are encoded all the same, and if there is such a
 // string, each one's ids lie at its own place in tmp_ids instead of one after the other.  (100,000 rows of up to 60 bytes,
-// one in twenty with such a segment: 183 us.  With the whole group given away, five rows in six went to the
-// wave-per-item encoder: 1,029 us; with each row an item of its own 728.)
+// one in twenty with such a segment: 153 us.  With the whole group given away, five rows in six went to the wave-per-item
+// encoder: 1,029 us; with each row an item of its own 728; both when all segments were merged and this took 183.)
 template <class L, bool SPECIAL, bool GROUPS, bool ALONE>
 __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int s, int64_t begin, int n, int members,
                                                       uint32_t* lds, const uint32_t* shared) {

@@ -651,8 +651,8 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.tmp_ids = tmp_ids;
   p.counts = counts;
   const bool alone = direct && batch == 1;               // the encode kernel writes the output itself
-  p.out_ids = alone ? out_ids : nullptr;
-  p.out_offsets = out_offsets;
+  p.out_ids = out_ids;
+  p.out_offsets = alone ? out_offsets : nullptr;         // (out_ids may be null: one empty string)
   p.id_map = table->d_id_map;
   p.direct_count = small_split ? (uint32_t)w.max_slots : (uint32_t)batch;
   p.slot_kind = small_split ? (int32_t*)(ws + w.item_len) : nullptr;

@@ -62,9 +62,9 @@ struct EncodeParams {
   uint32_t* queue_head;       // [tiers] next unclaimed item of each tier
   int32_t* tmp_ids;           // ids of an item are written at tmp_ids[first byte of the item ...]
   int32_t* counts;            // token count of each item
-  int32_t* out_ids;           // a batch of one short string: the output, which this kernel writes itself, else null;
-  int64_t* out_offsets;       // ... and the vocabulary's id of every token, or null
-  const int32_t* id_map;
+  int64_t* out_offsets;       // a batch of one short string, whose output the encode kernel writes itself: the offsets, else null;
+  int32_t* out_ids;           // ... its ids (which only a string without bytes may have as null) ...
+  const int32_t* id_map;      // ... and the vocabulary's id of every token, or null
   const int64_t* member_begin;// lane-per-segment kernel: first byte of each string or piece; an item is several in a row
   int32_t* group_ids;         // pieces: how many ids the packing kernel copies from a piece's first byte on: those of all its
                               //   item, none for the item's other pieces, -1: its own

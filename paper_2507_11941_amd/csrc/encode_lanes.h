@@ -333,7 +333,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
   const uint32_t my_count = (uint32_t)__builtin_popcount(my_starts);
   const uint32_t starts_upto = wave_scan<OpAdd>(my_count, 0u);
 
-  int32_t* const dst = ALONE && p.out_ids ? p.out_ids : p.tmp_ids + begin;
+  int32_t* const dst = ALONE && p.out_offsets ? p.out_ids : p.tmp_ids + begin;
   // Single bytes all (blank lines, padding that no row joins): their ids are the bytes.  (64 strings of 64 KiB of spaces: 16 us,
   // as segments 48.)
   if ((int)__builtin_amdgcn_readlane((int)starts_upto, 63) == n && !any_marked) {        // uniform
@@ -838,7 +838,7 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
       }
       if constexpr (INLINE) {
         // The only string of its batch: this wave finishes the output, for which there is no other launch.
-        if (p.out_ids) {                               // uniform
+        if (p.out_offsets) {                           // uniform
           __threadfence();                             // (it reads what it has just written)
           const int k = __hip_atomic_load(p.counts + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           const int32_t* const ids = left ? p.tmp_ids + begin : p.out_ids;

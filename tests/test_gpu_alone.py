@@ -50,3 +50,27 @@ def test_one_string(length, text, ids):
         torch.cuda.synchronize()
         got_off = off.cpu().numpy()
         assert_same_encoding(out.cpu().numpy()[:got_off[1]], got_off, want_ids, want_off, "static")
+
+
+@pytest.mark.parametrize("ids", ["own", "vocab"])
+@pytest.mark.parametrize("batch", [1, 2, 3073])
+@pytest.mark.parametrize("max_len", [0, 300, 1024, 1025])
+def test_empty_strings_without_an_ids_buffer(max_len, batch, ids):
+    """A tensor without elements has a null pointer, which is a valid out_ids where there are no bytes."""
+    import torch
+
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2507_11941_amd as bpe
+
+    merges = workloads.load_merges("1k")
+    names = np.random.default_rng(1).permutation(256 + len(merges)).astype(np.int32)
+    table = bpe.build_table(merges) if ids == "own" else bpe.build_table_vocab(names[:256], names[merges], names[256:])
+    dev = torch.device("cuda:0")
+    data, out = torch.empty(0, dtype=torch.uint8, device=dev), torch.empty(0, dtype=torch.int32, device=dev)
+    assert out.data_ptr() == 0
+    offsets = torch.zeros(batch + 1, dtype=torch.int64, device=dev)
+    for encode in (bpe.encode_batch, bpe.encode_batch_static):
+        off = torch.full((batch + 1,), -1, dtype=torch.int64, device=dev)
+        encode(table, data, offsets, max_len, out, off)
+        torch.cuda.synchronize()
+        assert not off.any().item(), encode.__name__

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "piece_slots.h"
 #include "string_groups.h"
 #include "table_format.h"
 
@@ -251,82 +252,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const int32_t* tmp_ids, const
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Splitting long strings into pieces.
-//
-// No merge can cross a cut (a byte bigram that occurs at no merge junction, see table_format.h), so the two
-// sides of a cut are encoded independently and their ids concatenated.  Strings longer than the piece target
-// P are therefore cut near every multiple of P: the string gets ceil(len / P) "slots"; slot 0 starts at the
-// string's first byte, slot i at the last cut within kCutWindow bytes before byte i*P, or is void if there is
-// none (then the piece before it simply runs on).  Pieces, not strings, are what the encode kernels work on;
-// their ids land in tmp_ids at the piece's own byte offset, so a string's ids are the concatenation of its
-// slots' runs.
-
-constexpr int kCutWindow = 128;
-
-__device__ inline uint32_t slots_of_length(int64_t len, int piece_target, int max_string) {
-  // (a 32-bit division: a valid length fits, and the 64-bit one is a long software routine)
-  return (len <= 0 || len > max_string) ? 1u : ((uint32_t)len + (uint32_t)piece_target - 1u) / (uint32_t)piece_target;
-}
-
-// Orders a wave's own LDS traffic (which the hardware executes in order) for the compiler.
-__device__ inline void wave_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// Slots are numbered without a scan: string s's first slot is s + offsets[s] / P, and a string of ceil(len / P) slots never
-// reaches the next one's.  Numbers in between that no string uses (one for every other string) are void slots too.
-__device__ inline uint32_t slot_base(int64_t offset, int s, int piece_target) {
-  return (uint32_t)s + (uint32_t)(offset >> 7) / ((uint32_t)piece_target >> 7);        // (the target is a multiple of 128)
-}
-
-// Which of the sixteen candidates q = p - 15 ... p have a cut before byte q, a bit each?  v, last: the seventeen bytes
-// p - 16 ... p; m, last_m: their marks; cuts: the bit set of the cuts.
-__device__ inline uint32_t cut_candidates(const uint4& v, uint32_t last, const uint4& m, uint32_t last_m, bool marked,
-                                          const uint32_t* cuts) {
-  const uint32_t w[5] = {v.x, v.y, v.z, v.w, last};
-  uint32_t found = 0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const uint32_t pair = (i & 3) == 3 ? __builtin_amdgcn_alignbit(w[(i >> 2) + 1], w[i >> 2], 24u) : w[i >> 2] >> (8 * (i & 3));
-    found |= ((cuts[(pair >> 5) & 2047u] >> (pair & 31u)) & 1u) << i;
-  }
-  if (marked) {                                        // special tokens: their ends are cuts, their inside is not
-    const uint32_t mark[5] = {m.x, m.y, m.z, m.w, last_m};
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t two = ((i & 3) == 3 ? __builtin_amdgcn_alignbit(mark[(i >> 2) + 1], mark[i >> 2], 24u)
-                                         : mark[i >> 2] >> (8 * (i & 3))) & 0xFFFFu;
-      if (two) found |= 1u << i;
-      if (two >> 8 == kCoverRest) found &= ~(1u << i);
-    }
-  }
-  return found;
-}
-// The last cut within the kCutWindow positions up to t, or -1: a thread's own search, sixteen candidates a round; in text
-// the first round nearly always finds one.  Whole waves take part, with `searching` unset where there is nothing to find.
-__device__ inline int64_t last_cut(const uint8_t* bytes, const uint8_t* cover, const uint32_t* cuts, int64_t t, bool searching) {
-  int64_t at = -1;
-  for (int round = 0; round < kCutWindow / 16; ++round) {
-    if (!__ballot(searching)) break;                   // uniform
-    if (searching) {
-      const int64_t p = t - 16 * round;
-      uint4 v, m = make_uint4(0, 0, 0, 0);
-      uint32_t last_m = 0;
-      __builtin_memcpy(&v, bytes + p - 16, 16);
-      if (cover) {
-        __builtin_memcpy(&m, cover + p - 16, 16);
-        last_m = cover[p];
-      }
-      const uint32_t found = cut_candidates(v, bytes[p], m, last_m, cover != nullptr, cuts);
-      if (found) {
-        at = p - 15 + (31 - __builtin_clz(found));
-        searching = false;
-      }
-    }
-  }
-  return at;
-}
+// Listing the pieces of long strings (piece_slots.h), packing their ids.
 
 // The pieces of a batch's strings and the histogram of their items' keys.  A wave takes 63 slots at a time and looks at one
 // more, where its last piece may end; its 64 lanes hold the strings they can belong to.  Pieces that one wave can take
@@ -340,7 +266,6 @@ __device__ inline int64_t last_cut(const uint8_t* bytes, const uint8_t* cover, c
 // ten dependent reads.  8,192 strings of 4 KiB: 11 and 6 us, where numbering the slots, finding the cuts, the histogram, its
 // scan and the list were five kernels and 42 us.
 constexpr int kListGrid = 256;
-constexpr int kListSlots = 63;                         // of a wave's step
 __global__ __launch_bounds__(1024) void piece_list_kernel(const uint8_t* bytes, const int64_t* offsets, int batch,
                                                           const uint32_t* cut_bits, const uint8_t* cover, int piece_target,
                                                           int max_string, TierPlan plan, int room, uint32_t n_slots,
@@ -359,93 +284,21 @@ __global__ __launch_bounds__(1024) void piece_list_kernel(const uint8_t* bytes, 
   for (uint32_t step = 0; step < steps_each; ++step) { // uniform
     const uint32_t g0 = (first_step + step) * kListSlots;
     if (g0 >= n_slots) break;                          // uniform
-    if (step == 0) {                                   // the last string with its base <= g0: 64 asked at a time
-      int n = batch;
-      while (n > 1) {                                  // uniform; n shrinks every round
-        const int stride = (n + 63) >> 6;
-        const int64_t i = (int64_t)s0 + (int64_t)(lane + 1) * stride;
-        const bool upto = i < (int64_t)s0 + n && slot_base(offsets[i], (int)i, piece_target) <= g0;
-        const int64_t skipped = (int64_t)__builtin_popcountll(__ballot(upto)) * stride;
-        s0 += (int)skipped;
-        n = (int)min((int64_t)stride, (int64_t)n - skipped);
-      }
-    }
-    // my string, one of the 64 from s0 on, and the string of my slot
-    const int mine = min(s0 + lane, batch - 1);
-    const int64_t my_begin = offsets[mine], my_end = offsets[mine + 1];
-    const uint32_t my_base = s0 + lane < batch ? slot_base(my_begin, mine, piece_target) : 0xFFFFFFFFu;
-    string_at[wave][lane] = 0;
-    wave_order();
-    if (lane > 0 && my_base - g0 < 64u) string_at[wave][my_base - g0] = lane;
-    wave_order();
-    int owner = string_at[wave][lane];
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(owner, d, 64);
-      if (lane >= d) owner = max(owner, o);
-    }
-    wave_order();
-    const int64_t begin = __shfl(my_begin, owner, 64), end = __shfl(my_end, owner, 64);
-    const uint32_t base = (uint32_t)__shfl((int)my_base, owner, 64);
+    if (step == 0) s0 = wave_last_string(batch, [&](int i) { return slot_base(offsets[i], i, piece_target) <= g0; });
+    const StepSlot slot = step_slots(bytes, offsets, batch, cover, cuts, piece_target, max_string, n_slots, g0, s0,
+                                     string_at[wave], slot_string, piece_begin, piece_len);
     const uint32_t g = g0 + (uint32_t)lane;
-    const int i = (int)(g - base);
-    const uint32_t end_slot = base + slots_of_length(end - begin, piece_target, max_string);
-    const bool used = g < n_slots && g < end_slot && end >= begin && end - begin <= max_string;
-    int64_t start = last_cut(bytes, cover, cuts, begin + (int64_t)i * piece_target, used && i > 0);
-    if (used && i == 0) start = begin;
-    // ---- where my piece ends: at the next one of its string, or at the string's end ----
-    const uint64_t pieces = __ballot(start >= 0);
-    const uint64_t later = lane < 63 ? pieces & (~0ull << (lane + 1)) : 0ull;
-    const int next = later ? (int)__builtin_ctzll(later) : 64;
-    int64_t piece_end = __shfl(start, next & 63, 64);
-    const bool beyond = start >= 0 && lane < kListSlots && (next == 64 || g0 + (uint32_t)next >= end_slot);
-    if (beyond) piece_end = end;
-    // (one piece at most runs on past the slots of this step)
-    uint64_t runs_on = __ballot(beyond && next == 64 && end_slot > g0 + 64u);
-    if (runs_on) {                                     // uniform
-      const int from = (int)__builtin_ctzll(runs_on);
-      const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)end_slot, from);
-      const uint32_t its_base = (uint32_t)__builtin_amdgcn_readlane((int)base, from);
-      const int64_t its_begin = __shfl(begin, from, 64);
-      for (uint32_t h0 = g0 + 64u; h0 < last; h0 += 64u) {               // uniform
-        const uint32_t h = h0 + (uint32_t)lane;
-        const int64_t at = last_cut(bytes, cover, cuts, its_begin + (int64_t)(h - its_base) * piece_target, h < last);
-        const uint64_t found = __ballot(at >= 0);
-        const uint32_t stop = found ? h0 + (uint32_t)__builtin_ctzll(found) : last;
-        if (h < stop) piece_len[h] = (int32_t)(g0 + (uint32_t)from) - (int32_t)h;
-        if (found) {
-          const int64_t its_end = __shfl(at, (int)__builtin_ctzll(found), 64);
-          if (lane == from) piece_end = its_end;
-          break;                                       // uniform
-        }
-      }
-    }
-    const int32_t len = start >= 0 ? (int32_t)(piece_end - start) : 0;
-    // ---- what there is to say of the slot ----
-    const int key = start >= 0 && lane < kListSlots ? bin_key(len, plan) : -1;
+    const int key = slot.start >= 0 && lane < kListSlots ? bin_key(slot.len, plan) : -1;
     const bool single = key >= 0 && key < kLenBuckets;
-    const StringGroup group = group_members(start, start + len, !single, (int)min(n_slots - g0, (uint32_t)kListSlots), room);
+    const StringGroup group = group_members(slot.start, slot.start + slot.len, !single, (int)min(n_slots - g0, (uint32_t)kListSlots), room);
     const int item_key = !single ? key : group.members ? group_key(group.len) : -1;
     if (item_key >= 0) atomicAdd(&hist[item_key], 1u);
-    const uint64_t before = pieces & ((1ull << lane) - 1ull);
-    const int piece = before ? 63 - (int)__builtin_clzll(before) : -1;   // the piece before my slot, if it is of my string
-    const bool of_my_string = piece >= 0 && g0 + (uint32_t)max(piece, 0) >= base;
-    if (g < n_slots) {
-      if (lane < kListSlots) {
-        piece_begin[g] = start;
-        slot_string[g] = i == 0 ? s0 + owner : -1;
-        group_ids[g] = -1;
-        item_len[g] = item_key < 0 ? 0 : single ? group.len | (group.members << kGroupShift) : -len;
-        if (key < 0) counts[g] = 0;                    // void slot, or too long for the launched variants
-      }
-      if (start >= 0) {
-        if (lane < kListSlots) piece_len[g] = len;
-      } else if (used && of_my_string) {               // (of earlier steps' pieces: theirs to say)
-        piece_len[g] = piece - lane;
-      } else if (!used && lane < kListSlots) {
-        piece_len[g] = 0;
-      }
+    if (g < n_slots && lane < kListSlots) {
+      group_ids[g] = -1;
+      item_len[g] = item_key < 0 ? 0 : single ? group.len | (group.members << kGroupShift) : -slot.len;
+      if (key < 0) counts[g] = 0;                      // void slot, or too long for the launched variants
     }
-    s0 += __builtin_amdgcn_readlane(owner, 63);
+    s0 = slot.next_s0;
   }
   __syncthreads();
   if (t < kBinKeys) part[blockIdx.x * kBinKeys + t] = hist[t];
@@ -503,72 +356,6 @@ __global__ __launch_bounds__(1024) void piece_scatter_kernel(TierPlan plan, uint
 // slot and finds its piece itself (slot_piece).  It leaves what is to be done with the piece, for the kernels that come after.
 constexpr int kSmallSlots = 4096;
 enum { kSlotDone, kSlotPassed, kSlotTier1, kSlotTier2, kSlotTier3 };   // (tier t is kSlotDone + 1 + t)
-struct SlotPiece {
-  int64_t begin;
-  int32_t len;                                         // -1: no piece starts in the slot
-};
-// The last cut within the kCutWindow positions up to t, or -1, by a whole wave: 64 candidates at a time.
-__device__ inline int64_t wave_last_cut(const uint8_t* bytes, const uint8_t* cover, const uint32_t* cuts, int64_t t) {
-  const int lane = threadIdx.x & 63;
-  for (int round = 0; round < kCutWindow / 64; ++round) {
-    const int64_t q = t - 64 * round - lane;
-    const uint32_t pair = bytes[q - 1] | (uint32_t)bytes[q] << 8;
-    bool cut = (cuts[pair >> 5] >> (pair & 31u)) & 1u;
-    if (cover) {                                       // special tokens: their ends are cuts, their inside is not
-      const uint32_t before = cover[q - 1], here = cover[q];
-      cut = (cut || before != 0 || here != 0) && here != kCoverRest;
-    }
-    const uint64_t found = __ballot(cut);
-    if (found) return t - 64 * round - (int)__builtin_ctzll(found);
-  }
-  return -1;
-}
-// The piece that starts in slot g, and what the packing kernel wants to know of the slots it covers.  A wave's work; all
-// arguments are uniform.
-__device__ inline SlotPiece slot_piece(const uint8_t* bytes, const int64_t* offsets, int batch, const uint8_t* cover,
-                                       const uint32_t* cuts, int piece_target, int max_string, uint32_t g,
-                                       int32_t* slot_string, int64_t* piece_begin, int32_t* piece_len) {
-  const int lane = threadIdx.x & 63;
-  int s = 0, n = batch;                                // the last string with its base <= g: 64 asked at a time
-  while (n > 1) {                                      // uniform; n shrinks every round
-    const int stride = (n + 63) >> 6;
-    const int64_t i = (int64_t)s + (int64_t)(lane + 1) * stride;
-    const bool upto = i < (int64_t)s + n && slot_base(offsets[i], (int)i, piece_target) <= g;
-    const int64_t skipped = (int64_t)__builtin_popcountll(__ballot(upto)) * stride;
-    s += (int)skipped;
-    n = (int)min((int64_t)stride, (int64_t)n - skipped);
-  }
-  const int64_t begin = offsets[s], end = offsets[s + 1];
-  const uint32_t base = slot_base(begin, s, piece_target);
-  const uint32_t end_slot = base + slots_of_length(end - begin, piece_target, max_string);
-  const bool used = g < end_slot && end >= begin && end - begin <= max_string;
-  const int64_t t = begin + (int64_t)(g - base) * piece_target;
-  SlotPiece piece{-1, -1};
-  if (used) piece.begin = g == base ? begin : wave_last_cut(bytes, cover, cuts, t);
-  if (lane == 0) {
-    slot_string[g] = g == base ? s : -1;
-    piece_begin[g] = piece.begin;
-    if (!used) piece_len[g] = 0;                       // (of a void slot that a piece runs over: the piece's wave)
-  }
-  if (piece.begin < 0) return piece;
-  int64_t piece_end = end;
-  if (g + 1u < end_slot) {
-    int64_t next = wave_last_cut(bytes, cover, cuts, t + piece_target);
-    for (uint32_t h0 = g + 1u; next < 0 && h0 < end_slot; h0 += 64u) {   // a slot a lane
-      const uint32_t h = h0 + (uint32_t)lane;
-      const int64_t at = last_cut(bytes, cover, cuts, begin + (int64_t)(h - base) * piece_target, h < end_slot);
-      const uint64_t found = __ballot(at >= 0);
-      const uint32_t stop = found ? h0 + (uint32_t)__builtin_ctzll(found) : end_slot;
-      if (h < stop) piece_len[h] = (int32_t)g - (int32_t)h;
-      if (found) next = __shfl(at, (int)__builtin_ctzll(found), 64);
-    }
-    if (next >= 0) piece_end = next;
-  }
-  piece.len = (int32_t)(piece_end - piece.begin);
-  if (lane == 0) piece_len[g] = piece.len;
-  return piece;
-}
-
 // Token offsets of the slots: per-tile sums, then the scan inside each tile.
 constexpr int kScanTile = 4096;
 
@@ -646,24 +433,6 @@ struct SpecialSet {
   uint8_t text[kMaxSpecials][kMaxSpecialBytes];
 };
 
-// The last string with offsets[s] <= at (for at below the first offset: string 0), found by a whole wave: every
-// round asks 64 strings at once, so 65,536 strings take three round trips instead of sixteen.  All lanes take part
-// and get the result; `at` is uniform.
-__device__ inline int wave_string_at(const int64_t* offsets, int batch, int64_t at) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, n = batch;                               // the answer is one of [lo, lo + n)
-  while (n > 1) {                                      // uniform; n shrinks every round
-    const int step = (n + 63) >> 6;
-    const int64_t i = (int64_t)lo + (int64_t)(lane + 1) * step;
-    const bool upto = i < (int64_t)lo + n && offsets[i] <= at;
-    const int k = (int)__builtin_popcountll(__ballot(upto));
-    const int64_t skipped = (int64_t)k * step;
-    lo += (int)skipped;
-    n = (int)min((int64_t)step, (int64_t)n - skipped);
-  }
-  return lo;
-}
-
 // A workgroup writes the marks of kMarkBlock consecutive bytes, each once and 16 bytes a lane: it collects them in LDS,
 // for which it also looks at the kMaxSpecialBytes positions before its stretch, where an occurrence that reaches into
 // it can start.  What bounds it is the text and the marks themselves, as long as a byte that starts a special, or looks
@@ -715,10 +484,10 @@ __global__ __launch_bounds__(256) void special_mark_kernel(const uint8_t* bytes,
   if (tid == 0) text[kMarkWords] = 0;
   if (tid < kMarkBlock / 16) *(uint4*)&marks[4 * tid] = make_uint4(0, 0, 0, 0);
   if (tid >= 128 && tid < 192) {
-    const int s = wave_string_at(offsets, batch, max(start, (int64_t)0));
+    const int s = wave_last_string(batch, [&](int i) { return offsets[i] <= max(start, (int64_t)0); });
     if (tid == 128) first_string = s;
   } else if (tid >= 192) {
-    const int s = wave_string_at(offsets, batch, end - 1);
+    const int s = wave_last_string(batch, [&](int i) { return offsets[i] <= end - 1; });
     if (tid == 192) last_string = s;
   }
   __syncthreads();

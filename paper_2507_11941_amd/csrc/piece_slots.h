@@ -29,7 +29,8 @@ __device__ inline void wave_order() {
 }
 
 // Slots are numbered without a scan: string s's first slot is s + offsets[s] / P, and a string of ceil(len / P) slots never
-// reaches the next one's.  Numbers in between that no string uses (one for every other string) are void slots too.
+// reaches the next one's.  Numbers in between that no string uses (one for every other string) are void slots too, and so are
+// those before string 0's, if the offsets are a window of a longer array and do not begin with 0.
 __device__ inline uint32_t slot_base(int64_t offset, int s, int piece_target) {
   return (uint32_t)s + (uint32_t)(offset >> 7) / ((uint32_t)piece_target >> 7);        // (the target is a multiple of 128)
 }
@@ -133,7 +134,7 @@ __device__ inline StepSlot step_slots(const uint8_t* bytes, const int64_t* offse
   const uint32_t g = g0 + (uint32_t)lane;
   const int i = (int)(g - base);
   const uint32_t end_slot = base + slots_of_length(end - begin, piece_target, max_string);
-  const bool used = g < n_slots && g < end_slot && end >= begin && end - begin <= max_string;
+  const bool used = g < n_slots && g >= base && g < end_slot && end >= begin && end - begin <= max_string;
   int64_t start = last_cut(bytes, cover, cuts, begin + (int64_t)i * piece_target, used && i > 0);
   if (used && i == 0) start = begin;
   // ---- where my piece ends: at the next one of its string, or at the string's end ----
@@ -213,7 +214,7 @@ __device__ inline SlotPiece slot_piece(const uint8_t* bytes, const int64_t* offs
   const int64_t begin = offsets[s], end = offsets[s + 1];
   const uint32_t base = slot_base(begin, s, piece_target);
   const uint32_t end_slot = base + slots_of_length(end - begin, piece_target, max_string);
-  const bool used = g < end_slot && end >= begin && end - begin <= max_string;
+  const bool used = g >= base && g < end_slot && end >= begin && end - begin <= max_string;
   const int64_t t = begin + (int64_t)(g - base) * piece_target;
   SlotPiece piece{-1, -1};
   if (used) piece.begin = g == base ? begin : wave_last_cut(bytes, cover, cuts, t);

@@ -104,3 +104,15 @@ def test_slots(lib, lens, runs, specials, steps_each):
     got = slots(lib, data, offsets, cover, CUT, steps_each)
     for what, g, e in zip(("string", "begin", "length"), got, expected(data, offsets, cover, CUT)):
         assert np.array_equal(g, e), (what, np.flatnonzero(g != e)[:5], g[g != e][:5], e[g != e][:5])
+
+
+@pytest.mark.parametrize("steps_each", [0, 1, 3])
+@pytest.mark.parametrize("skipped", [100, 2000, 130 * TARGET + 17])
+def test_offsets_that_begin_later(lib, skipped, steps_each):
+    """A window of a longer offsets array: the slots below the first string's are void, and nothing is read for them."""
+    rng = np.random.default_rng(skipped)
+    offsets = skipped + np.concatenate([[0], np.cumsum([700, 5000, 0, 66000, 30, 2000])]).astype(np.int64)
+    data = text(rng, int(offsets[-1]), 4)
+    got = slots(lib, data, offsets, None, CUT, steps_each)
+    for what, g, e in zip(("string", "begin", "length"), got, expected(data, offsets, None, CUT)):
+        assert np.array_equal(g, e), (what, np.flatnonzero(g != e)[:5], g[g != e][:5], e[g != e][:5])

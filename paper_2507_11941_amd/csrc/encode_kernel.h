@@ -71,7 +71,7 @@ struct EncodeParams {
   const void* list_desc;      // ItemDesc of every entry of `list` (begin, length, item), in the same order
   uint32_t* staged;           // HBM staging for the strings that exceed LDS (a slab per workgroup; else null)
   uint32_t prefetch_lines;    // 128-byte lines of table memory to pull into L2 at kernel start (0 = none)
-  uint32_t direct_count;      // when `list` is null: items are the strings 0..direct_count-1, one per workgroup
+  uint32_t direct_count;      // when `list` is null: items are the strings, or a small split batch's slots, 0..direct_count-1, a wave each
   int n_tiers;
   // when the items are the slots of a small split batch (no list):
   int32_t* slot_kind;         // kSlot... of every slot, else null

@@ -10,25 +10,32 @@
 // longer segments first, so the lanes stay busy whatever the mix of segment lengths.
 //
 //   cuts     lane t holds bytes 16 t ... 16 t + 15 of the item (one wide load), asks a bit set of all byte bigrams in LDS
-//            where they are cut, and leaves the segments' first positions as a bitmap, then as a list.
-//   words    segment-parallel, 64 at a time and four such batches in flight: the segment's bytes are its key; two
+//            where they are cut, and leaves the segments' first positions as a bitmap.  Segments of one byte are a token as
+//            they are; the others become a list.
+//   words    segment-parallel, 64 at a time and three such batches in flight: the segment's bytes are its key; two
 //            dependent table reads say which token it is, if it is one.
-//   list     the other segments, sorted by length, longest first: a counting sort with one LDS counter per length.
-//            Handing the long segments out first is what keeps the lanes level at the end.  Only these segments get a
-//            place in the arrays of tokens and pair values (the "arena"), in the list's order.
+//   list     the other segments, the "jobs", sorted by length, longest first: a counting sort with one LDS counter per
+//            length.  Handing the long segments out first is what keeps the lanes level at the end.  Only they get a
+//            place in the array of tokens and pair values (the "arena").
 //   merge    segment-parallel, as above; a lane keeps its segment's liveness as a 32-bit mask, so a segment
 //            may have at most 32 bytes.  A string with a longer segment is not encoded here: the kernel hands
 //            it to the wave-per-item encoder of encode_segmented.h, which has no such limit.  (An item is one
 //            string, a piece of one, or a group of short ones; of a group only such strings are handed on.)
-//   emit     segment-parallel: a prefix sum of the segments' token counts gives every one its place in the output
-//            (section 4.3's compaction).
+//   emit     a bitmap of the item says where tokens start; the bits before one are its place in the output (section 4.3's
+//            compaction).  Words and jobs segment-parallel, single bytes position-parallel.
 //
-// words to emit run over as many segments at a time as the arena and the lists hold: in text, all of the item's.
+// list to emit run over as many jobs at a time as the arena and the list hold: in words, all of the item's.
 //
-// What bounds it is instruction issue: some 2,080 vector and 550 scalar instructions per KiB of text, of which the merge
+// What bounds it is instruction issue: some 2,080 vector and 600 scalar instructions per KiB of text, of which the merge
 // loop is two fifths, on four waves a SIMD.  With every segment going through the merges, one item of 1 KiB a wave
-// (14.9 trips of the loop per KiB instead of 6.3), the 65,536 documents of the throughput workload took 1,480 us in this
-// kernel; they take 985, and the whole call 1,075 instead of 1,659.
+// (14.9 trips of the loop per KiB instead of 6.8), the 65,536 documents of the throughput workload took 1,480 us in this
+// kernel; they take 975, and the whole call 1,066 instead of 1,659.
+//
+// Of text that is not words most look-ups find nothing and cost what they cost, and its jobs do not fit the arena at once.
+// 32 MiB in strings of 4 KiB, whole call, all segments merged / single bytes listed and looked up like the others, the arena
+// filled to the brim and the rest in a part of its own / now: bytes at random, 100k rows 281 / 453 / 241 us; digits and
+// letters of a hexadecimal dump, 32k rows 303 / 405 / 332; text of a larger table's words under 1k rows 254 / 396 / 305;
+// words of no table, 100k rows 314 / 367 / 371; words, 100k rows 312 / 241 / 239.
 #pragma once
 #include "encode_segmented.h"
 
@@ -61,64 +68,58 @@ __device__ inline uint32_t lane_merged_word(uint32_t lv) {
 // (a byte that no row can use costs a look-up that finds nothing; asking for its bits costs another LDS round trip)
 __device__ inline uint32_t lane_byte_word(uint32_t byte) { return byte | kLaneCanLeft | kLaneCanRight; }
 
-// What becomes of a segment: its token's number, or one of these.
-constexpr uint32_t kRecJob = 1u << 30;          // | its place among the jobs in the text's order
-constexpr uint32_t kRecNone = 1u << 31;         // no token
+constexpr uint32_t kRecNone = 1u << 31;         // what becomes of a segment: its token's number, or this: it is not one token
 
 // LDS of a workgroup, in 32-bit words: read-only, shared by its waves.
 struct LaneShared {
   static constexpr int kCuts = 0;                                       // bit a + 256 b: bytes a, b have a cut between them
-  static constexpr int kByteWord = kCuts + 2048;                        // token word of every byte
-  static constexpr int kMasks = kByteWord + 256;                        // [16][4] first l bytes of a key
-  static constexpr int kWords = kMasks + 64;
+  static constexpr int kMasks = kCuts + 2048;                           // [16][4] first l bytes of a key
+  static constexpr int kByteWord = kMasks + 64;                         // token word of every byte, for the one-wave encoder
+  static constexpr int kWords = kByteWord;                              // (INLINE: and those 256)
 };
 // Shape of a workgroup, and the LDS of one of its waves.  WAVES: they take items of their own; BYTES: an item's capacity;
-// LIST: segments listed at a time; JOBS: those of them that need merges; ARENA: the bytes of those, in fours.  What bounds
+// LIST: segments listed at a time; JOBS: those that go through the merges at a time; ARENA: the bytes of those, in fours.  What bounds
 // the number of waves is LDS, and what bounds the kernel is how many waves there are to wait at once: 65,536 documents take
 // 1,554 us with 8 waves a CU, 1,379 with 10, 1,232 with 12 (that was with the tokens in a second array beside V) and 1,107
 // with the 16 that one array leaves room for.  Twice as long an item takes less than half as many trips of the merge loop
-// for each of its bytes (5.4 instead of 12.2 per KiB: the longest chain of merges is 10 long in either): the same batch in
-// items of 1 KiB took 1,443 instead of 1,232.  A small batch wants each piece of text to have a wave.
+// for each of its bytes (the longest chain of merges is 10 long in either): the same batch in items of 1 KiB took 1,443
+// instead of 1,232.  A small batch wants each piece of text to have a wave; its items of 1 KiB fit the arena whatever they
+// hold (1,024 strings of 1 KiB of words of no table: 35 us in two parts, 28 in one).
 template <int BYTES, int WAVES, int LIST, int JOBS, int ARENA, int AT_LEAST>
 struct LaneShape {
   static constexpr int kBytes = BYTES, kWaves = WAVES, kListed = LIST, kMostJobs = JOBS, kArena = ARENA;
   static constexpr int kText = 0;                                       // the item's bytes; a key's words reach beyond them
   static constexpr int kStrings = kText + BYTES / 4 + 8;                // (groups) bit p: a string starts at p
-  static constexpr int kList = kStrings + BYTES / 32;                   // uint16 first position of a segment
-  static constexpr int kJobs = kList + LIST / 2 + 2;                    // the jobs sorted: first position | (length - 1) << 11 |
-                                                                        //   place << 16, then arena position / 4 << 16 instead
-  static constexpr int kPlaces = kJobs + JOBS;                          // uint16 arena position of the jobs in the text's order
-  static constexpr int kHist = kPlaces + JOBS / 2;                      // jobs of each length, then list bases
+  static constexpr int kTokens = kStrings + BYTES / 32;                 // bit p: a token starts at p
+  static constexpr int kRanks = kTokens + BYTES / 32;                   // uint16 tokens before each word of kTokens
+  static constexpr int kHeads = kRanks + BYTES / 64;                    // uint16 last start in the words before each of kStrings
+  static constexpr int kList = kHeads + BYTES / 64;                     // uint16 segments: first position | (length - 1) << 11
+  static constexpr int kJobs = kList + LIST / 2;                        // the jobs sorted: the same, and the arena's places up to it << 16
+  static constexpr int kHist = kJobs + JOBS;                            // jobs of each length, then list bases
   static constexpr int kV = (kHist + 32 + 3) / 4 * 4;                   // a word for every arena position
   static constexpr int kIdle = kV + ARENA;                              // what a lane without a segment reads and writes
   static constexpr int kEnd = kIdle + 4;
   // before the arena is used:
   static constexpr int kStarts = kV;                                    // bit p: a segment starts at p, or the item ends
-  static constexpr int kFirstJobs = kV;                                 // the jobs in the text's order
-  static constexpr int kFound = kV + JOBS;                              // what becomes of a segment
+  static constexpr int kFound = kV;                                     // what becomes of a segment
   static constexpr int kWords = ((kEnd > AT_LEAST ? kEnd : AT_LEAST) + 3) / 4 * 4;
-  static constexpr size_t kLdsBytes = lds_blocks(sizeof(uint32_t) * (LaneShared::kWords + WAVES * kWords));
-  static_assert(kText % 4 == 0 && ARENA % 4 == 0, "wide loads and stores");
-  static_assert(ARENA <= 2048 && BYTES <= 2048 && BYTES % 1024 == 0 && LIST % 64 == 0 && LIST <= 512 && JOBS % 64 == 0,
+  static constexpr int kSharedWords = LaneShared::kWords + (AT_LEAST ? 256 : 0);
+  static constexpr size_t kLdsBytes = lds_blocks(sizeof(uint32_t) * (kSharedWords + WAVES * kWords));
+  static_assert(kText % 4 == 0 && ARENA % 4 == 0 && kSharedWords % 4 == 0, "wide loads and stores");
+  static_assert(ARENA <= 2048 && BYTES <= 2048 && BYTES % 1024 == 0 && LIST % 64 == 0 && LIST <= 1024 && JOBS % 64 == 0,
                 "fields of the packed words; a lane per word of the bitmap");
-  static_assert(JOBS + LIST <= ARENA && BYTES / 32 + 4 <= ARENA, "what shares a place fits it");
+  static_assert(LIST <= ARENA && BYTES / 32 + 4 <= ARENA, "what shares a place fits it");
   static_assert(kLdsBytes <= 160 * 1024, "one workgroup a CU");
 };
-using LargeItems = LaneShape<kGroupBytes, 16, 448, 256, 1152, 0>;
-using SmallItems = LaneShape<kMemberBytes, 16, 256, 128, 704, 0>;
+using LargeItems = LaneShape<kGroupBytes, 16, 448, 256, 1168, 0>;
+using SmallItems = LaneShape<kMemberBytes, 16, 256, 256, 1536, 0>;
 // (the arrays of the one-wave encoder that takes a string over)
 constexpr int kOtherWords = encode_array_words<1, 16, false, true>() + encode_exchange_words<1>();
-using InlineItems = LaneShape<kMemberBytes, 12, 256, 128, 704, kOtherWords>;
+using InlineItems = LaneShape<kMemberBytes, 12, 256, 256, 1536, kOtherWords>;
 
 __device__ inline uint32_t mbcnt64(uint64_t mask) {                     // set bits of mask below my lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
-// Where a segment that is done keeps its place in the output, its tokens being the mask in its first word: at its second
-// token, whose pair no longer counts, or behind the one token's word (a segment has four words at least).
-__device__ inline uint32_t lane_spare(uint32_t tokens) {
-  return tokens & (tokens - 1u) ? (uint32_t)__builtin_ctz(tokens & (tokens - 1u)) : 2u;
-}
-
 // A look-up in the merge table on its way: two start at the end of every trip of the merge loop.
 struct LaneProbe {
   uint4 q;                                             // the home bucket: two slots of {value, tag}
@@ -207,9 +208,11 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
   uint32_t* const text = lds + L::kText;
   uint32_t* const starts = lds + L::kStarts;
   uint32_t* const strings = lds + L::kStrings;
+  uint32_t* const tokens = lds + L::kTokens;
+  uint16_t* const ranks = (uint16_t*)(lds + L::kRanks);
+  uint16_t* const heads = (uint16_t*)(lds + L::kHeads);
   uint16_t* const list = (uint16_t*)(lds + L::kList);
   uint32_t* const jobs = lds + L::kJobs;
-  uint16_t* const places = (uint16_t*)(lds + L::kPlaces);
   uint32_t* const hist = lds + L::kHist;
   uint32_t* const V = lds + L::kV;
 
@@ -276,14 +279,19 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
           // an occurrence of a special token is one token on its first byte and nothing on the others: every marked
           // byte is a segment of its own
           const uint4 m = marks[pass];
-          uint32_t marked = 0;
+          uint32_t marked = 0, inside = 0;             // (inside: no token)
           if (__ballot((m.x | m.y | m.z | m.w) != 0)) {
             any_marked = true;
             const uint32_t mw[4] = {m.x, m.y, m.z, m.w};
 #pragma unroll
-            for (int j = 0; j < 16; ++j) marked |= (((mw[j >> 2] >> (8 * (j & 3))) & 0xFFu) ? 1u : 0u) << j;
+            for (int j = 0; j < 16; ++j) {
+              const uint32_t mark = (mw[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+              marked |= (mark ? 1u : 0u) << j;
+              inside |= (mark == kCoverRest ? 1u : 0u) << j;
+            }
             if (at < n && n - at < 16) marked &= (1u << (n - at)) - 1u;      // (the next string's, or none)
           }
+          ((uint16_t*)tokens)[64 * pass + lane] = (uint16_t)~inside;
           const uint32_t mine_before = wave_shift_up(marked, 0u);
           begins |= marked | (marked << 1) | (lane == 0 ? marked_before : mine_before >> 15);
           marked_before = (uint32_t)__builtin_amdgcn_readlane((int)marked, 63) >> 15;
@@ -305,9 +313,11 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
   // ---- segments that no lane can take: more than 32 positions from a start to the next (nothing has left LDS) ----
   const int n_words = (n + 31) >> 5;                   // words of the bitmap, a lane each (uniform)
   uint64_t left = 0;                                   // strings that are not encoded here (uniform)
-  uint32_t my_starts = lane < n_words ? starts[lane] : 0u;
+  const uint32_t my_starts = lane < n_words ? starts[lane] : 0u;         // (the item's end among them)
+  const uint32_t next = lane < n_words ? starts[lane + 1] : 0u;
+  uint32_t segments = my_starts;                       // first positions of the segments that are encoded here
+  if (32 * lane + 31 >= n && lane < n_words && (n & 31)) segments &= (1u << (n & 31)) - 1u;
   {
-    const uint32_t next = lane < n_words ? starts[lane + 1] : 0u;
     const int top = 32 * lane + 31 - (int)__builtin_clz(my_starts | 1u);   // the word's last start
     const bool empty = lane < n_words && my_starts == 0;
     const bool gap = my_starts != 0 && next != 0 && top < n &&
@@ -315,28 +325,27 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     uint64_t too_long = __ballot(empty || gap);
     if (too_long) {                                    // uniform
       if constexpr (!GROUPS) return 1;
-      // The strings that hold one: lane m asks for string m.  Of their segments only the first start is kept; so long a
-      // one gets no token below.
+      // The strings that hold one: lane m asks for string m.  They get no tokens below.
       const int inside = empty ? 32 * lane : top;
       for (; too_long; too_long &= too_long - 1ull) {  // uniform
         const int at = __builtin_amdgcn_readlane(inside, (int)__builtin_ctzll(too_long));
         left |= __ballot(from <= at && at < to);
       }
       for (uint64_t m = left; m; m &= m - 1ull) {      // uniform
-        const int lo = max(__builtin_amdgcn_readlane(from, (int)__builtin_ctzll(m)) + 1 - 32 * lane, 0);
+        const int lo = max(__builtin_amdgcn_readlane(from, (int)__builtin_ctzll(m)) - 32 * lane, 0);
         const int hi = min(__builtin_amdgcn_readlane(to, (int)__builtin_ctzll(m)) - 32 * lane, 32);
-        if (lo < hi) my_starts &= ~((hi >= 32 ? 0xFFFFFFFFu : (1u << hi) - 1u) & (0xFFFFFFFFu << lo));
+        if (lo < hi) segments &= ~((hi >= 32 ? 0xFFFFFFFFu : (1u << hi) - 1u) & (0xFFFFFFFFu << lo));
       }
     }
   }
-  if (32 * lane + 31 >= n && lane < n_words && (n & 31)) my_starts &= (1u << (n & 31)) - 1u;   // the end is no start
-  const uint32_t my_count = (uint32_t)__builtin_popcount(my_starts);
-  const uint32_t starts_upto = wave_scan<OpAdd>(my_count, 0u);
+  const uint32_t follows = __builtin_amdgcn_alignbit(next, my_starts, 1u);   // bit p: a segment, or nothing, starts at p + 1
+  const uint32_t multi = segments & ~follows;          // segments of two bytes or more; the others are a token each as they are
+  const uint64_t any_multi = __ballot(multi != 0);
 
   int32_t* const dst = ALONE && p.out_offsets ? p.out_ids : p.tmp_ids + begin;
   // Single bytes all (blank lines, padding that no row joins): their ids are the bytes.  (64 strings of 64 KiB of spaces: 16 us,
   // as segments 48.)
-  if ((int)__builtin_amdgcn_readlane((int)starts_upto, 63) == n && !any_marked) {        // uniform
+  if (!any_multi && !any_marked && !left) {            // uniform
     for (int o = lane; o < n; o += 64) dst[o] = (int32_t)((text[o >> 2] >> (8 * (o & 3))) & 0xFFu);
     if constexpr (GROUPS) {
       if (lane < members) {
@@ -349,139 +358,204 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     wave_order();
     return 0;
   }
-  uint32_t total = 0;                                  // tokens of the segments done (uniform)
-  uint32_t tokens_before = 0;                          // (groups) of string `lane`
-  uint32_t lack = 0;                                   // (apart) what the place of a token lacks to its string's own
-  uint32_t listed_before = 0;                          // segments of earlier lists (uniform)
-  uint32_t my_segment = 0xFFFFFFFFu;                   // (groups) the one that string `lane` starts with
-  if constexpr (GROUPS) {
-    const int word = min(from >> 5, 63);
-    const uint32_t before = lane_read(starts_upto - my_count, word);
-    const uint32_t bits = lane_read(my_starts, word);
-    if (from < n) my_segment = before + (uint32_t)__builtin_popcount(bits & ((1u << (from & 31)) - 1u));
+  // ---- where tokens start: at the segments' first bytes, and wherever the merges leave one ----
+  uint32_t singles = segments & follows;
+  {
+    uint32_t first_tokens = segments;
+    if constexpr (SPECIAL) {
+      const uint32_t not_inside = lane < n_words ? tokens[lane] : 0u;
+      singles &= not_inside;
+      first_tokens &= not_inside;
+    }
+    if (lane < L::kBytes / 32) tokens[lane] = first_tokens;
   }
-  for (int word0 = 0; word0 < n_words;) {              // (a list of the whole item, unless it has very many segments)
-    // ---- list of the segments that start in words word0 ... word1 - 1 ----
-    const uint64_t in_list = __ballot(lane >= word0 && lane < n_words && starts_upto - listed_before <= (uint32_t)L::kListed);
-    const int word1 = word0 + (int)__builtin_popcountll(in_list);          // (at least one more: a word has 32 starts)
-    const uint32_t listed_upto = (uint32_t)__builtin_amdgcn_readlane((int)starts_upto, word1 - 1);
+  if constexpr (GROUPS) {
+    if (left) {                                        // uniform: strings at their own places
+      const uint32_t my_heads = lane < L::kBytes / 32 ? strings[lane] : 0u;
+      const uint32_t upto = wave_scan<OpMax>(my_heads ? 32u * (uint32_t)lane + 31u - (uint32_t)__builtin_clz(my_heads) : 0u, 0u);
+      const uint32_t before = wave_shift_up(upto, 0u);
+      if (lane < L::kBytes / 32) heads[lane] = (uint16_t)before;
+    }
+  }
+  wave_order();
+  uint32_t my_tokens = 0, my_rank = 0, total = 0;      // word `lane` of the bitmap, the tokens before it, all (uniform)
+  auto count_tokens = [&]() {
+    wave_order();
+    my_tokens = lane < L::kBytes / 32 ? tokens[lane] : 0u;
+    const uint32_t upto = wave_scan<OpAdd>((uint32_t)__builtin_popcount(my_tokens), 0u);
+    my_rank = upto - (uint32_t)__builtin_popcount(my_tokens);
+    total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    if (lane < L::kBytes / 32) ranks[lane] = (uint16_t)my_rank;
+    wave_order();
+  };
+  // tokens before position `at`, which is in the item
+  auto rank_of = [&](uint32_t at) {
+    return (uint32_t)ranks[at >> 5] + (uint32_t)__builtin_popcount(tokens[at >> 5] & ((1u << (at & 31u)) - 1u));
+  };
+  // (strings at their own places) what the place of a token of the string that holds position `at` lacks to it
+  auto lack_of = [&](uint32_t at) {
+    const uint32_t here = strings[at >> 5] & ((2u << (at & 31u)) - 1u);
+    const uint32_t head = here ? (at | 31u) - (uint32_t)__builtin_clz(here) : heads[at >> 5];
+    return head - rank_of(head);
+  };
+  const uint32_t my_multis = (uint32_t)__builtin_popcount(multi);
+  const uint32_t multis_upto = wave_scan<OpAdd>(my_multis, 0u);
+  uint32_t listed_before = 0;                          // segments of earlier lists (uniform)
+  if (!any_multi) count_tokens();                      // uniform
+  for (int word0 = any_multi ? 0 : n_words; word0 < n_words;) {          // (one list, unless there are very many segments)
+    // ---- list of the segments of two bytes or more that start in words word0 ... word1 - 1 ----
+    const uint64_t in_list = __ballot(lane >= word0 && lane < n_words && multis_upto - listed_before <= (uint32_t)L::kListed);
+    const int word1 = word0 + (int)__builtin_popcountll(in_list);          // (at least one more: a word has 16 at most)
+    const uint32_t listed_upto = (uint32_t)__builtin_amdgcn_readlane((int)multis_upto, word1 - 1);
     const int n_listed = (int)(listed_upto - listed_before);
     {
-      const uint64_t later = __ballot(lane >= word1 && my_starts != 0);
-      const int first = 32 * lane + (int)__builtin_ctz(my_starts | 0x80000000u);
-      const int end = later ? __builtin_amdgcn_readlane(first, (int)__builtin_ctzll(later)) : n;
-      uint32_t at = starts_upto - my_count - listed_before;
-      uint32_t m = lane >= word0 && lane < word1 ? my_starts : 0u;
+      uint32_t at = multis_upto - my_multis - listed_before;
+      uint32_t m = lane >= word0 && lane < word1 ? multi : 0u;
       while (__ballot(m != 0)) {
-        if (m) list[at++] = (uint16_t)(32 * lane + (int)__builtin_ctz(m));
+        if (m) {
+          const uint32_t bit = (uint32_t)__builtin_ctz(m);
+          const uint32_t window = __builtin_amdgcn_alignbit(next >> 1, follows, bit);    // (its next start is among these)
+          list[at++] = (uint16_t)((32u * (uint32_t)lane + bit) | ((uint32_t)__builtin_ctz(window | 0x80000000u) << 11));
+        }
         m &= m - 1u;
       }
-      if (lane == 0) list[n_listed] = (uint16_t)end;
     }
     wave_order();
     word0 = word1;
-    const uint32_t list_first = listed_before;
     listed_before = listed_upto;
 
-    for (int i0 = 0; i0 < n_listed;) {                 // uniform
-      // ---- words: which segments are one token ----
-      int i1 = i0;                                     // segments from i0 to here are done in this round
-      uint32_t n_jobs = 0, used = 0;                   // those that need merges, and their places in the arena (uniform)
-      const int round_end = min(n_listed, i0 + L::kListed);
-      bool full = false;                               // uniform
-      while (i1 < round_end && !full) {                // uniform
-        uint32_t k[kLaneBatches][4], first[kLaneBatches], len[kLaneBatches], mark[kLaneBatches], tag[kLaneBatches];
-        uint4 bucket[kLaneBatches], key[kLaneBatches];
-        const int base = i1;
+    // ---- words: which segments are one token ----
+#pragma unroll 1
+    for (int base = 0; base < n_listed; base += 64 * kLaneBatches) {     // uniform
+      uint32_t k[kLaneBatches][4], len[kLaneBatches], tag[kLaneBatches];
+      uint4 bucket[kLaneBatches], key[kLaneBatches];
 #pragma unroll
-        for (int r = 0; r < kLaneBatches; ++r) {
-          const int i = min(base + 64 * r + lane, n_listed - 1);
-          first[r] = list[i];
-          len[r] = (uint32_t)list[i + 1] - first[r];
-        }
+      for (int r = 0; r < kLaneBatches; ++r) {
+        const uint32_t e = list[min(base + 64 * r + lane, n_listed - 1)];
+        len[r] = (e >> 11) + 1u;
+        const uint32_t* const word = text + ((e & 2047u) >> 2);
+        const uint32_t shift = 8u * (e & 3u);
+        const uint4 mask = *(const uint4*)(shared + LaneShared::kMasks + 4 * min(len[r], (uint32_t)kWordBytes));
+        k[r][0] = __builtin_amdgcn_alignbit(word[1], word[0], shift) & mask.x;
+        k[r][1] = __builtin_amdgcn_alignbit(word[2], word[1], shift) & mask.y;
+        k[r][2] = __builtin_amdgcn_alignbit(word[3], word[2], shift) & mask.z;
+        k[r][3] = (__builtin_amdgcn_alignbit(word[4], word[3], shift) & mask.w) | (len[r] << 24);
+      }
 #pragma unroll
-        for (int r = 0; r < kLaneBatches; ++r) {
-          if (base + 64 * r + lane >= n_listed) len[r] = 0;
-          const uint32_t* const word = text + (first[r] >> 2);
-          const uint32_t shift = 8u * (first[r] & 3u);
-          const uint4 mask = *(const uint4*)(shared + LaneShared::kMasks + 4 * min(len[r], (uint32_t)kWordBytes));
-          k[r][0] = __builtin_amdgcn_alignbit(word[1], word[0], shift) & mask.x;
-          k[r][1] = __builtin_amdgcn_alignbit(word[2], word[1], shift) & mask.y;
-          k[r][2] = __builtin_amdgcn_alignbit(word[3], word[2], shift) & mask.z;
-          k[r][3] = (__builtin_amdgcn_alignbit(word[4], word[3], shift) & mask.w) | (len[r] << 24);
-        }
-#pragma unroll
-        for (int r = 0; r < kLaneBatches; ++r) {
-          tag[r] = mark[r] = 0;
-          bucket[r] = make_uint4(kWordNone, kWordNone, kWordNone, kWordNone);
-          if (__ballot(len[r] > 1u)) {                 // uniform: else single bytes all, or nothing
-            const uint32_t hash = word_hash(k[r][0], k[r][1], k[r][2], k[r][3]);
-            tag[r] = word_tag(hash);
-            if (len[r] - 2u <= (uint32_t)kWordBytes - 2u)
-              bucket[r] = tab.word_buckets[word_bucket(hash, tab.log2_word_buckets)];
-          }
-          if constexpr (SPECIAL)
-            if (len[r] == 1u) mark[r] = p.cover[begin + first[r]];
-        }
-#pragma unroll
-        for (int r = 0; r < kLaneBatches; ++r) {
-          // (at most one slot of a bucket has the tag; an empty one leaves all ones in the id's bits at best)
-          tag[r] = min(min(bucket[r].x ^ tag[r], bucket[r].y ^ tag[r]), min(bucket[r].z ^ tag[r], bucket[r].w ^ tag[r]));
-          key[r] = make_uint4(0, 0, 0, 0);
-          if (tag[r] < (1u << kWordIdBits) - 1u) key[r] = tab.word_keys[tag[r]];
-        }
-#pragma unroll
-        for (int r = 0; r < kLaneBatches; ++r) {
-          if (base + 64 * r < round_end && !full) {    // uniform
-            const bool same = len[r] - 2u <= (uint32_t)kWordBytes - 2u &&          // (then no key of zeros is its own)
-                              ((key[r].x ^ k[r][0]) | (key[r].y ^ k[r][1]) | (key[r].z ^ k[r][2]) | (key[r].w ^ k[r][3])) == 0;
-            uint32_t what = same ? tag[r] : kRecNone;
-            const bool job = !same && len[r] - 2u <= (uint32_t)kLaneSegmentMax - 2u;
-            if (len[r] == 1u) {
-              what = k[r][0];
-              if constexpr (SPECIAL)
-                if (mark[r]) what = (mark[r] & kCoverFirst) ? p.special_base + (mark[r] & kCoverIndex) : kRecNone;
-            }
-            int taken = 64;
-            const uint64_t job_lanes = __ballot(job);
-            if (job_lanes) {                           // uniform
-              const uint32_t upto = used + wave_scan<OpAdd>(job ? (len[r] + 3u) & ~3u : 0u, 0u);
-              const uint32_t place = n_jobs + mbcnt64(job_lanes);
-              const uint64_t misfit = __ballot(job && (upto > (uint32_t)L::kArena || place >= (uint32_t)L::kMostJobs));
-              if (misfit) {                            // uniform: the round ends before this segment
-                taken = (int)__builtin_ctzll(misfit);
-                full = true;
-              }
-              if (job && lane < taken) {
-                lds[L::kFirstJobs + place] = first[r] | ((len[r] - 1u) << 11) | (place << 16);
-                what = kRecJob | place;
-              }
-              n_jobs += (uint32_t)__builtin_popcountll(taken < 64 ? job_lanes & ((1ull << taken) - 1ull) : job_lanes);
-              if (taken > 0) used = (uint32_t)__builtin_amdgcn_readlane((int)upto, taken - 1);
-            }
-            lds[L::kFound + base - i0 + 64 * r + lane] = what;     // (of what is not taken, looked up again)
-            i1 = min(base + 64 * r + taken, round_end);
-          }
+      for (int r = 0; r < kLaneBatches; ++r) {
+        tag[r] = 0;
+        bucket[r] = make_uint4(kWordNone, kWordNone, kWordNone, kWordNone);
+        if (base + 64 * r < n_listed) {                // uniform
+          const uint32_t hash = word_hash(k[r][0], k[r][1], k[r][2], k[r][3]);
+          tag[r] = word_tag(hash);
+          if (len[r] <= (uint32_t)kWordBytes) bucket[r] = tab.word_buckets[word_bucket(hash, tab.log2_word_buckets)];
         }
       }
+#pragma unroll
+      for (int r = 0; r < kLaneBatches; ++r) {
+        // (at most one slot of a bucket has the tag; an empty one leaves all ones in the id's bits at best)
+        tag[r] = min(min(bucket[r].x ^ tag[r], bucket[r].y ^ tag[r]), min(bucket[r].z ^ tag[r], bucket[r].w ^ tag[r]));
+        key[r] = make_uint4(0, 0, 0, 0);               // (no key: a key has a length)
+        if (tag[r] < (1u << kWordIdBits) - 1u) key[r] = tab.word_keys[tag[r]];
+      }
+#pragma unroll
+      for (int r = 0; r < kLaneBatches; ++r) {
+        if (base + 64 * r < n_listed) {                // uniform
+          const bool same = ((key[r].x ^ k[r][0]) | (key[r].y ^ k[r][1]) | (key[r].z ^ k[r][2]) | (key[r].w ^ k[r][3])) == 0;
+          lds[L::kFound + base + 64 * r + lane] = same ? tag[r] : kRecNone;
+        }
+      }
+    }
+    wave_order();
+    // ---- the others ("jobs") need merges, and a place in the arena: four words or more, whole fours ----
+    constexpr int kBatches = L::kListed / 64;
+    // found: what becomes of segment 64 r + lane.  job: list entry of the r-th segment that the lane has, and the places up to
+    // it << 16; 0 if it is no job.
+    const int each = (n_listed + 63) >> 6;             // uniform
+    uint32_t found[kBatches], job[kBatches];
+#pragma unroll
+    for (int r = 0; r < kBatches; ++r) found[r] = job[r] = 0;
+    uint32_t all_places = 0, part = 0, n_jobs = 0;     // uniform
+    for (int by_lane = 1, by_r = 64;;) {               // uniform
+#pragma unroll
+      for (int r = 0; r < kBatches; ++r) {             // (all reads go out before the first is waited for)
+        if (r >= each) break;                          // uniform
+        const int i = by_lane * lane + by_r * r;
+        const uint32_t what = lds[L::kFound + i], e = list[i];
+        found[r] = by_lane == 1 ? what : found[r];
+        const uint32_t is_job = (uint32_t)((int)what >> 31);             // (kRecNone or a token's number)
+        job[r] = i < n_listed ? e & is_job : 0u;                         // (a segment has a length)
+      }
+      uint32_t mine = 0;                               // places | jobs << 16
+#pragma unroll
+      for (int r = 0; r < kBatches; ++r) {
+        if (r >= each) break;                          // uniform
+        if (job[r]) {
+          mine += (((job[r] >> 11) + 4u) & ~3u) + 0x10000u;
+          job[r] |= mine << 16;
+        }
+      }
+      const uint32_t upto = wave_scan<OpAdd>(mine, 0u);
+#pragma unroll
+      for (int r = 0; r < kBatches; ++r) {
+        if (r >= each) break;                          // uniform
+        if (job[r]) job[r] += (upto - mine) << 16;
+      }
+      const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+      part = all_places = all & 0xFFFFu;
+      n_jobs = all >> 16;
+      // As many as the arena and the jobs' list hold at a time: all of the item's, in text.  Else in parts of about the
+      // same size, for each part ends with some lanes idle, a small one as much as a large one; and parts of the text, so
+      // that what lies before a part is known when it is written: the lanes' segments are neighbours then.
+      if (all_places <= (uint32_t)L::kArena && n_jobs <= (uint32_t)L::kMostJobs) break;
+      const uint32_t most = min(n_jobs > (uint32_t)L::kMostJobs ? 4u * (uint32_t)L::kMostJobs : ~0u, (uint32_t)L::kArena);
+      const uint32_t parts = (all_places + most - 1u) / most;
+      part = min(all_places / parts + (uint32_t)kLaneSegmentMax, most);
+      if (by_r == 1 || each == 1) break;
+      by_lane = each;
+      by_r = 1;
+    }
+    auto write_words = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int r = 0; r < kBatches; ++r) {
+        if (r >= each) break;                            // uniform
+        if (64 * r + lane < n_listed && found[r] != kRecNone) {
+          const uint32_t at = list[64 * r + lane] & 2047u;
+          uint32_t o = rank_of(at);
+          if constexpr (GROUPS)
+            if (left) o += lack_of(at);
+          dst[o] = (int32_t)found[r];
+        }
+      }
+    };
+    if (!all_places) {                                 // uniform
+      count_tokens();
+      write_words();
+    }
+    for (uint32_t done = 0; done < all_places;) {      // uniform: places of the parts before
+      wave_order();
       if (lane < 32) hist[lane] = 0;
       wave_order();
-      uint32_t found[L::kListed / 64];                  // what becomes of segment i0 + 64 r + lane
+      uint32_t upto_part = all_places;                 // uniform
+      // where a job begins in the arena: whole fours
+      auto place_of = [&](uint32_t e) { return (e >> 16) - done - ((((e >> 11) & 31u) + 4u) & ~3u); };
+      {
+        // ---- list: longest first (counting sort over the 31 possible lengths) ----
+        uint32_t place[kBatches], mine = 0, last = done;
 #pragma unroll
-      for (int r = 0; r < L::kListed / 64; ++r) found[r] = lds[L::kFound + 64 * r + lane];
-      wave_order();
-
-      if (n_jobs) {                                    // uniform
-        // ---- list: the segments that need merges, longest first (counting sort over the 31 possible lengths) ----
-        constexpr int kRounds = L::kMostJobs / 64;
-        uint32_t entry[kRounds], place[kRounds];       // (entry: as in kJobs)
+        for (int r = 0; r < kBatches; ++r) place[r] = 0;
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-          entry[r] = place[r] = 0;
-          if (64u * r + (uint32_t)lane < n_jobs) {
-            entry[r] = lds[L::kFirstJobs + 64 * r + lane];
-            place[r] = atomicAdd(&hist[31u - ((entry[r] >> 11) & 31u)], 1u);   // my place among those of my length
+        for (int r = 0; r < kBatches; ++r) {
+          if (r >= each) break;                        // uniform
+          if ((job[r] >> 16) - done - 1u < part) {
+            place[r] = atomicAdd(&hist[31u - ((job[r] >> 11) & 31u)], 1u);                       // among those of its length
+            ++mine;
+            last = job[r] >> 16;
           }
+        }
+        if (part < all_places) {                       // uniform
+          n_jobs = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<OpAdd>(mine, 0u), 63);
+          upto_part = wave_reduce<OpMax>(last);
         }
         wave_order();
         {
@@ -492,26 +566,22 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         }
         wave_order();
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r)
-          if (64u * r + (uint32_t)lane < n_jobs) jobs[hist[31u - ((entry[r] >> 11) & 31u)] + place[r]] = entry[r];
+        for (int r = 0; r < kBatches; ++r) {
+          if (r >= each) break;                        // uniform
+          if ((job[r] >> 16) - done - 1u < part)
+            jobs[hist[31u - ((job[r] >> 11) & 31u)] + place[r]] = job[r];
+        }
         wave_order();
-        // ---- their places in the arena: byte-level pre-tokenisation (section 4.1) and the initial pair values ----
-        uint32_t arena = 0;                            // uniform
+      }
+      {
+        // ---- in the arena: byte-level pre-tokenisation (section 4.1) and the initial pair values ----
 #pragma unroll 1
         for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) { // uniform
           const uint32_t j = j0 + (uint32_t)lane;
           const uint32_t e = jobs[min(j, n_jobs - 1u)];
           const uint32_t at = e & 2047u;
           const uint32_t len = j < n_jobs ? ((e >> 11) & 31u) + 1u : 0u;
-          const uint32_t room = (len + 3u) & ~3u;
-          const uint32_t upto = arena + wave_scan<OpAdd>(room, 0u);
-          const uint32_t base = upto - room;
-          arena = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-          wave_order();                                 // (all lanes have read their entries)
-          if (len) {
-            jobs[j] = (e & 0xFFFFu) | (base << 14);
-            places[e >> 16] = (uint16_t)base;
-          }
+          const uint32_t base = place_of(e);
           const uint32_t* word = text + (at >> 2);
           const uint32_t shift = 8u * (at & 3u);
           uint32_t w0 = word[0], w1 = word[1];
@@ -546,7 +616,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         }
         wave_order();
       }
-      if (n_jobs) {                                    // uniform
+      {
         // ---- merge: Algorithm 1 on one segment per lane ----
         // The look-ups of the two pairs a merge creates stay in flight over the loop's edge: the next trip first scans
         // the pair values that did not change and only then takes the two new ones.
@@ -580,7 +650,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
               const uint32_t top = (e >> 11) & 31u;
               alive = (2u << top) - 1u;
               joined = 0;
-              v0 = V + 4u * (e >> 16);
+              v0 = V + place_of(e);
               b0 = (const uint8_t*)text + (e & 2047u);
               last = top & ~3u;
             }
@@ -589,7 +659,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         take_segments();
         // Every trip ends a segment or removes a token in each lane that has a segment, so so many trips cannot be needed;
         // the bound only guarantees that the loop ends whatever the memory contents.
-        const int most_trips = 2 * (int)used + 64;
+        const int most_trips = 2 * (int)(upto_part - done) + 64;
         for (int trip = 0; trip < most_trips; ++trip) {
           if (!__ballot(alive != 0)) break;            // every segment is done
 
@@ -660,72 +730,88 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         wave_order();
       }
 
-      // ---- emit: a prefix sum of the segments' token counts gives every one its place ----
-      // First the segments that are one token, in the text's order; then the others, in the jobs' order: neighbours there
-      // have about as many tokens.  (In the text's order too, a store instruction per token of the longest of 64 segments,
-      // few lanes in each, was a fifth of the kernel.)
-#pragma unroll
-      for (int r = 0; r < L::kListed / 64; ++r) {
-        const int b = i0 + 64 * r;
-        if (b >= i1) continue;                         // uniform
-        const int i = b + lane;
-        const uint32_t what = i < i1 ? found[r] : kRecNone;
-        uint32_t count = what < kRecJob ? 1u : 0u;
-        uint32_t at = 0, tokens = 0;
-        if (what & kRecJob) {
-          at = places[what & (uint32_t)(L::kMostJobs - 1)];
-          tokens = V[at];
-          count = (uint32_t)__builtin_popcount(tokens);
-        }
-        const uint32_t upto = total + wave_scan<OpAdd>(count, 0u);
-        uint32_t o = upto - count;
-        if constexpr (GROUPS) {                        // my string's first segment is one of these: its tokens begin there
-          const uint32_t which = my_segment - (list_first + (uint32_t)b);
-          const uint32_t its = lane_read(o, (int)(which & 63u));
-          if (which < 64u && b + (int)which < i1) tokens_before = its;
-          if (left) {                                  // uniform: strings at their own places
-            const uint32_t pos = i < i1 ? list[i] : 0u;
-            const uint64_t heads = __ballot(i < i1 && ((strings[pos >> 5] >> (pos & 31u)) & 1u));
-            const uint64_t upto_me = heads & (~0ull >> (63 - lane));
-            const uint32_t mine = pos - o;             // (of a string's first segment)
-            const uint32_t its_lack = lane_read(mine, upto_me ? 63 - (int)__builtin_clzll(upto_me) : lane);
-            o += upto_me ? its_lack : lack;
-            if (heads) lack = (uint32_t)__builtin_amdgcn_readlane((int)mine, 63 - (int)__builtin_clzll(heads));
-          }
-        }
-        if (what < kRecJob) dst[o] = (int32_t)what;
-        if (what & kRecJob) V[at + lane_spare(tokens)] = o;
-        total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-      }
-      wave_order();
+      // ---- emit: the tokens before a position are its place in the output ----
 #pragma unroll 1
       for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) {   // uniform
-        uint32_t tokens = 0, o = 0, made = 0;
+        if (j0 + (uint32_t)lane < n_jobs) {
+          const uint32_t e = jobs[j0 + (uint32_t)lane];
+          const uint32_t at = e & 2047u;
+          const uint64_t its_tokens = (uint64_t)V[place_of(e)] << (at & 31u);
+          atomicOr(&tokens[at >> 5], (uint32_t)its_tokens);
+          if (its_tokens >> 32) atomicOr(&tokens[(at >> 5) + 1u], (uint32_t)(its_tokens >> 32));
+        }
+      }
+      count_tokens();                                  // (of what comes after this part: not yet all)
+      if (upto_part == all_places) write_words();      // uniform
+      // In the jobs' order, in which neighbours have about as many tokens.  (In the text's order, a store instruction per
+      // token of the longest of 64 segments, few lanes in each, was a fifth of the kernel.)
+#pragma unroll 1
+      for (uint32_t j0 = 0; j0 < n_jobs; j0 += 64) {   // uniform
+        uint32_t mine = 0, o = 0, made = 0;
         const uint32_t* v = V;
         const uint8_t* bytes = (const uint8_t*)text;
         if (j0 + (uint32_t)lane < n_jobs) {
           const uint32_t e = jobs[j0 + (uint32_t)lane];
-          v = V + 4u * (e >> 16);
+          v = V + place_of(e);
           bytes += e & 2047u;
-          tokens = v[0];
-          o = v[lane_spare(tokens)];
-          made = (~tokens >> 1) & ((1u << ((e >> 11) & 31u)) - 1u);      // (the position after is of the segment, and dead)
+          mine = v[0];
+          o = rank_of(e & 2047u);
+          if constexpr (GROUPS)
+            if (left) o += lack_of(e & 2047u);         // (left: uniform)
+          made = (~mine >> 1) & ((1u << ((e >> 11) & 31u)) - 1u);        // (the position after is of the segment, and dead)
         }
-        while (__ballot(tokens != 0)) {
-          if (tokens) {
-            const uint32_t q = (uint32_t)__builtin_ctz(tokens);
+        while (__ballot(mine != 0)) {
+          if (mine) {
+            const uint32_t q = (uint32_t)__builtin_ctz(mine);
             const uint32_t word = v[q + 1u], byte = bytes[q];
             dst[o++] = (int32_t)((made >> q) & 1u ? word & kTokIdMask : byte);
           }
-          tokens &= tokens - 1u;
+          mine &= mine - 1u;
         }
       }
-      wave_order();                                     // the round's LDS is used again
-      i0 = i1;
+      done = upto_part;
+    }
+    wave_order();                                      // the list's LDS is used again
+  }
+  // ---- the single bytes ----
+  auto write_single = [&](uint32_t at, uint32_t o) __attribute__((always_inline)) {
+    uint32_t id = ((const uint8_t*)text)[at];
+    if constexpr (SPECIAL) {
+      if (any_marked) {                                // uniform
+        const uint32_t mark = p.cover[begin + at];
+        if (mark) id = p.special_base + (mark & kCoverIndex);
+      }
+    }
+    if constexpr (GROUPS)
+      if (left) o += lack_of(at);
+    dst[o] = (int32_t)id;
+  };
+  if (!__ballot(__builtin_popcount(singles) > 4)) {    // uniform: few, each lane its word's
+    while (__ballot(singles != 0)) {
+      if (singles) {
+        const uint32_t bit = (uint32_t)__builtin_ctz(singles);
+        write_single(32u * (uint32_t)lane + bit, my_rank + (uint32_t)__builtin_popcount(my_tokens & ((1u << bit) - 1u)));
+      }
+      singles &= singles - 1u;
     }
   }
+#pragma unroll 1
+  for (uint64_t words = __ballot(singles != 0); words;) {                // uniform: a row of 64 positions at a time
+    const int row = (int)__builtin_ctzll(words) >> 1;
+    words &= ~(3ull << (2 * row));
+    auto row_of = [&](uint32_t word) {
+      return (uint32_t)__builtin_amdgcn_readlane((int)word, 2 * row) |
+             (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)word, 2 * row + 1) << 32;
+    };
+    const uint64_t row_tokens = row_of(my_tokens);
+    const uint32_t o = __builtin_amdgcn_mbcnt_hi((uint32_t)(row_tokens >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)row_tokens,
+                                                                           (uint32_t)__builtin_amdgcn_readlane((int)my_rank, 2 * row)));
+    if (__builtin_amdgcn_inverse_ballot_w64(row_of(singles))) write_single(64u * (uint32_t)row + (uint32_t)lane, o);
+  }
   if constexpr (GROUPS) {
-    if (from >= n) tokens_before = total;              // (empty strings at the end, and lanes without one)
+    // (empty strings at the end, and lanes without one: nothing after them)
+    const uint32_t tokens_before = from < n ? rank_of((uint32_t)from) : total;
     const uint32_t after = lane_read(tokens_before, min(lane + 1, 63));
     if (lane < members) {
       p.counts[s + lane] = (int32_t)((lane + 1 < members ? after : total) - tokens_before);
@@ -734,6 +820,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
   } else {
     if (lane == 63) p.counts[s] = (int32_t)total;
   }
+  wave_order();
   return left;
 }
 
@@ -765,38 +852,12 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t b = wave * gridDim.x + blockIdx.x;
   if (blockIdx.x >= g || (uint64_t)blockIdx.x * per_claim >= count) return;   // uniform: nothing for this workgroup
-  for (int i = (int)threadIdx.x; i < 2048 / 4; i += 64 * L::kWaves)
-    ((uint4*)(smem + LaneShared::kCuts))[i] = ((const uint4*)p.table.cuts)[i];
-  for (int i = (int)threadIdx.x; i < 256; i += 64 * L::kWaves) smem[LaneShared::kByteWord + i] = p.table.byte_word[i];
-  if (threadIdx.x < 64) {                              // word w of the first l bytes
-    const int bytes = (int)(threadIdx.x >> 2) - 4 * (int)(threadIdx.x & 3u);
-    smem[LaneShared::kMasks + threadIdx.x] = bytes >= 4 ? 0xFFFFFFFFu : bytes > 0 ? (1u << (8 * bytes)) - 1u : 0u;
-  }
-  __syncthreads();
-  if (b >= g || (uint64_t)b * per_claim >= count) return;   // uniform in the wave; no barrier follows
-  uint32_t* const arrays = smem + LaneShared::kWords + wave * L::kWords;
-
   // Items are claimed kLaneChunk at a time: the first chunk of a wave is its own index, later ones come from
   // the tier's queue head (which starts at zero).  One claim per item would make every wave wait for a round trip
   // to the one contended address after each item.  Lane i fetches the descriptor of the chunk's i-th item, so a
   // chunk costs one round trip for its claim and one for its descriptors.  (Claiming ahead does not pay: loads
   // return in order, so whatever is loaded after the claim waits for it.)
   const int lane = (int)threadIdx.x & 63;
-  if constexpr (SLOTS) {                               // (the grid covers the slots)
-    const SlotPiece piece = slot_piece(p.bytes, p.offsets, p.batch, p.cover, smem + LaneShared::kCuts, p.piece_target,
-                                       p.max_string, b, p.slot_string, p.slot_begin, p.slot_len);
-    int kind = kSlotDone;
-    const int tier = piece.len <= kMemberBytes ? 0 : piece.len <= 4096 ? 1 : piece.len <= 16384 ? 2 : 3;
-    if (piece.len < 0 || tier >= p.n_tiers) {          // void, or longer than the host said: nobody encodes it
-      if (lane == 0) p.counts[b] = 0;
-    } else if (tier > 0) {
-      kind = kSlotDone + 1 + tier;
-    } else if (encode_item_lanes<L, SPECIAL, false, false>(p, (int)b, piece.begin, piece.len, 1, arrays, smem)) {
-      kind = kSlotPassed;
-    }
-    if (lane == 0) p.slot_kind[b] = kind;
-    return;
-  }
   const ItemDesc* const descs = (const ItemDesc*)p.list_desc;
   auto load_chunk = [&](uint64_t first_item, uint32_t n_items, ItemDesc& d) {
     d.begin = 0;
@@ -813,6 +874,41 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
       }
     }
   };
+  // A wave's own first chunk: per_claim items, and when the list is long zero to three more, by its number,
+  // so that the waves do not all come back for their first claim at the same moment (claims on one address
+  // are served one after the other, some ten nanoseconds each).
+  const uint32_t spread = per_claim >= kLaneChunk ? 1u : 0u;
+  constexpr uint32_t kBefore[4] = {0, 0, 1, 3};        // extra items of the waves before b within its group of four
+  uint64_t first_item = (uint64_t)b * per_claim + spread * ((b >> 2) * 6u + kBefore[b & 3u]);
+  const uint64_t own_items = (uint64_t)g * per_claim + spread * ((g >> 2) * 6u + kBefore[g & 3u]);
+  uint32_t here = (uint32_t)min((uint64_t)(per_claim + spread * (b & 3u)), count - min(first_item, (uint64_t)count));
+  ItemDesc cur;
+  if (!SLOTS && b < g) load_chunk(first_item, here, cur);   // (on its way while the workgroup's LDS is filled)
+  for (int i = (int)threadIdx.x; i < 2048 / 4; i += 64 * L::kWaves)
+    ((uint4*)(smem + LaneShared::kCuts))[i] = ((const uint4*)p.table.cuts)[i];
+  if (threadIdx.x < 64) {                              // word w of the first l bytes
+    const int bytes = (int)(threadIdx.x >> 2) - 4 * (int)(threadIdx.x & 3u);
+    smem[LaneShared::kMasks + threadIdx.x] = bytes >= 4 ? 0xFFFFFFFFu : bytes > 0 ? (1u << (8 * bytes)) - 1u : 0u;
+  }
+  __syncthreads();
+  if (b >= g || first_item >= count) return;           // uniform in the wave; no barrier follows
+  uint32_t* const arrays = smem + L::kSharedWords + wave * L::kWords;
+
+  if constexpr (SLOTS) {                               // (the grid covers the slots)
+    const SlotPiece piece = slot_piece(p.bytes, p.offsets, p.batch, p.cover, smem + LaneShared::kCuts, p.piece_target,
+                                       p.max_string, b, p.slot_string, p.slot_begin, p.slot_len);
+    int kind = kSlotDone;
+    const int tier = piece.len <= kMemberBytes ? 0 : piece.len <= 4096 ? 1 : piece.len <= 16384 ? 2 : 3;
+    if (piece.len < 0 || tier >= p.n_tiers) {          // void, or longer than the host said: nobody encodes it
+      if (lane == 0) p.counts[b] = 0;
+    } else if (tier > 0) {
+      kind = kSlotDone + 1 + tier;
+    } else if (encode_item_lanes<L, SPECIAL, false, false>(p, (int)b, piece.begin, piece.len, 1, arrays, smem)) {
+      kind = kSlotPassed;
+    }
+    if (lane == 0) p.slot_kind[b] = kind;
+    return;
+  }
   auto encode_chunk = [&](uint64_t at, uint32_t here, const ItemDesc& cur) __attribute__((always_inline)) {
     for (uint32_t i = 0; i < here; ++i) {
       const int s = __builtin_amdgcn_readlane(cur.item, (int)i);
@@ -825,7 +921,9 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
       if (left) {                                      // uniform
         if constexpr (INLINE) {
           wave_order();
-          // (the other encoder's arrays take the place of this one's)
+          // (the other encoder's arrays take the place of this one's; every wave that needs the bytes' words writes them)
+          for (int o = lane; o < 256; o += 64) smem[LaneShared::kByteWord + o] = p.table.byte_word[o];
+          wave_order();
           const BlockShared<1> sh = block_shared<1>(arrays + 3 * 1024, smem + LaneShared::kByteWord);
           encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2 * 1024, sh);
           wave_order();
@@ -852,17 +950,6 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
       }
     }
   };
-  // A wave's own first chunk: per_claim items, and when the list is long zero to three more, by its number,
-  // so that the waves do not all come back for their first claim at the same moment (claims on one address
-  // are served one after the other, some ten nanoseconds each).
-  const uint32_t spread = per_claim >= kLaneChunk ? 1u : 0u;
-  constexpr uint32_t kBefore[4] = {0, 0, 1, 3};        // extra items of the waves before b within its group of four
-  uint64_t first_item = (uint64_t)b * per_claim + spread * ((b >> 2) * 6u + kBefore[b & 3u]);
-  const uint64_t own_items = (uint64_t)g * per_claim + spread * ((g >> 2) * 6u + kBefore[g & 3u]);
-  if (first_item >= count) return;                     // uniform
-  uint32_t here = (uint32_t)min((uint64_t)(per_claim + spread * (b & 3u)), count - first_item);
-  ItemDesc cur;
-  load_chunk(first_item, here, cur);
   for (;;) {
     encode_chunk(first_item, here, cur);
     if (own_items >= count) break;                     // uniform: the grid's own chunks cover the list

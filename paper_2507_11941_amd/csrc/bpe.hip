@@ -309,26 +309,13 @@ int build_image(const int32_t* merges, int32_t n_merges, std::vector<uint32_t>& 
   return BPE_OK;
 }
 
-// Row of the pair (a, b) in a finished image, or a value above all rows.
-uint32_t image_rank(const std::vector<uint32_t>& host, int log2_buckets, uint32_t a, uint32_t b) {
-  const Placement pl = place_pair(a, b, log2_buckets);
-  const uint32_t* const home = host.data() + (size_t)pl.bucket * kSlotsPerBucket * 2;
-  const uint32_t reach = home[3] == 0xFFFFFFFFu ? 0u : bucket_reach(home[0], home[2]);
-  for (uint32_t d = 0; d <= reach; ++d) {
-    const uint32_t* const bucket = host.data() + (size_t)(pl.bucket ^ d) * kSlotsPerBucket * 2;
-    for (int k = 0; k < kSlotsPerBucket; ++k)
-      if (bucket[2 * k + 1] == slot_tag(pl.fingerprint, d)) return bucket[2 * k] >> kRankShift;
-  }
-  return kNoRank;
-}
-
 // The bit set of the cuts and the word table, as they lie in device memory: [cuts: 2048][buckets][keys].
 int build_word_memory(const int32_t* merges, int32_t n_merges, const std::vector<uint32_t>& host, int log2_buckets,
                       std::vector<uint32_t>& memory, int& log2_word_buckets) {
   try {
     WordImage words;
     build_words(merges, n_merges,
-                [&](uint32_t a, uint32_t b) { return image_rank(host, log2_buckets, a, b); }, words);
+                [&](uint32_t a, uint32_t b) { return image_rank(host.data(), log2_buckets, a, b); }, words);
     memory.assign(2048, 0);
     memory.reserve(2048 + words.buckets.size() + words.keys.size());
     const uint32_t* const byte_pair = host.data() + host.size() - 65536;

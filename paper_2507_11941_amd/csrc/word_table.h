@@ -40,6 +40,19 @@ BPE_HD uint32_t word_hash(uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) {
 BPE_HD uint32_t word_bucket(uint32_t hash, int log2_buckets) { return hash >> (32 - log2_buckets); }
 BPE_HD uint32_t word_tag(uint32_t hash) { return hash << kWordIdBits; }        // the hash's low 12 bits, in a slot's place
 
+// Row of the pair (a, b) in a table image (see table_format.h; its buckets come first), or a value above all rows.
+inline uint32_t image_rank(const uint32_t* image, int log2_buckets, uint32_t a, uint32_t b) {
+  const Placement pl = place_pair(a, b, log2_buckets);
+  const uint32_t* const home = image + (size_t)pl.bucket * kSlotsPerBucket * 2;
+  const uint32_t reach = home[3] == 0xFFFFFFFFu ? 0u : bucket_reach(home[0], home[2]);
+  for (uint32_t d = 0; d <= reach; ++d) {
+    const uint32_t* const bucket = image + (size_t)(pl.bucket ^ d) * kSlotsPerBucket * 2;
+    for (int k = 0; k < kSlotsPerBucket; ++k)
+      if (bucket[2 * k + 1] == slot_tag(pl.fingerprint, d)) return bucket[2 * k] >> kRankShift;
+  }
+  return kNoRank;
+}
+
 // Does Algorithm 1 turn the bytes of row t's token into that token?  known[x]: the answer for every older token.
 // It does if it does so for both operands and no merge joins a token of the left one's bytes with a token of the right
 // one's before both are whole.  What stands at the boundary meanwhile are the tokens down the left operand's right edge

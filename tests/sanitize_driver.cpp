@@ -1,10 +1,14 @@
-// Exercises every entry point of the CPU oracle and of the workload generators in one process, for a build with
-// AddressSanitizer and UndefinedBehaviorSanitizer (tests/test_sanitizers.py compiles this file together with
-// oracle/bpe_oracle.cpp and workloads/gen.cpp and runs it).  Prints a checksum; any sanitizer report aborts.
+// Exercises every entry point of the CPU oracle and of the workload generators, and the builder of the word table
+// (csrc/word_table.h), in one process, for a build with AddressSanitizer and UndefinedBehaviorSanitizer
+// (tests/test_sanitizers.py compiles this file together with oracle/bpe_oracle.cpp and workloads/gen.cpp and runs it).  Prints a checksum; any sanitizer report aborts.
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <map>
+#include <utility>
 #include <vector>
+
+#include "word_table.h"
 
 extern "C" {
 void* orc_table_new(const int32_t* merges, int32_t n_merges);
@@ -89,6 +93,28 @@ int main() {
     if (k != 2 || ids[0] != 3 || ids[1] != 5) return 6;
     if (orc_decode(vocab, ids.data(), k, back.data(), 4096) != 5 || std::memcmp(back.data(), t, 5)) return 6;
     orc_table_free(vocab);
+  }
+  // the word table: the trained rows, rows whose tokens are all of one byte (the longest edges), no rows
+  {
+    std::vector<int32_t> chain;
+    for (int32_t r = 0; r < 40; ++r) {                     // aa, aaa, aaaa, ... one longer each
+      chain.push_back(r == 0 ? 'a' : 255 + r);
+      chain.push_back('a');
+    }
+    const std::vector<int32_t> trained(rows.begin(), rows.begin() + 2 * n_rows);
+    for (const std::vector<int32_t>& list : {trained, chain, std::vector<int32_t>()}) {
+      std::map<std::pair<uint32_t, uint32_t>, uint32_t> rank;
+      for (size_t r = 0; r < list.size() / 2; ++r) rank[{(uint32_t)list[2 * r], (uint32_t)list[2 * r + 1]}] = (uint32_t)r;
+      bpe::WordImage image;
+      bpe::build_words(list.data(), (int32_t)(list.size() / 2),
+                       [&](uint32_t a, uint32_t b) {
+                         const auto it = rank.find({a, b});
+                         return it == rank.end() ? bpe::kNoRank : it->second;
+                       },
+                       image);
+      if (image.keys.size() != 4 * (256 + list.size() / 2)) return 7;
+      for (uint32_t w : image.buckets) sum = sum * 31 + w;
+    }
   }
   orc_table_free(table);
   std::printf("sanitize_driver ok %llu\n", (unsigned long long)sum);

@@ -1,4 +1,4 @@
-"""Split batches around the size up to which one workgroup lists them (4,096 slots: strings + bytes // 896) and beyond: the most strings,
+"""Split batches around the size up to which they are not listed (4,096 slots: strings + bytes // 896) and beyond: the most strings,
 the most slots of one string each, stretches without a cut over many slots, special tokens on the nominal cut positions."""
 import random
 

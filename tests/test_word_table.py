@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 import oracle
+import paper_2507_11941_amd as bpe
 import workloads
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -45,10 +46,16 @@ def chained_table(rng, n_rows, alphabet):
 def check(lib, merges, rng, others):
     merges = np.ascontiguousarray(merges, dtype=np.int32).reshape(-1, 2)
     n = len(merges)
-    known, keys = np.zeros(256 + n, np.uint8), np.zeros((256 + n) * 4, np.uint32)
-    buckets = np.zeros(1 << 20, np.uint32)
-    log2 = lib.build_words(ptr(merges), n, ptr(known), ptr(buckets), ctypes.c_int64(len(buckets)), ptr(keys))
-    assert log2 >= 0
+    image, log2_image = bpe.table_image(merges)
+    built = []
+    for words_image in (None, image):                    # ranks from a map, and from the table as the library has them
+        known, keys = np.zeros(256 + n, np.uint8), np.zeros((256 + n) * 4, np.uint32)
+        buckets = np.zeros(1 << 20, np.uint32)
+        log2 = lib.build_words(ptr(merges), n, None if words_image is None else ptr(words_image), log2_image, ptr(known),
+                               ptr(buckets), ctypes.c_int64(len(buckets)), ptr(keys))
+        assert log2 >= 0
+        built.append((log2, known, buckets, keys))
+    assert all(np.array_equal(a, b) for a, b in zip(*built))
     expansion = [bytes([b]) for b in range(256)]
     for a, b in merges.tolist():
         expansion.append((expansion[a] + expansion[b])[:WORD_BYTES + 1])      # (a long one stays long)
@@ -93,9 +100,28 @@ def test_random_tables(lib, seed):
         assert missing <= 3 + known // 20
 
 
-@pytest.mark.parametrize("table,style", [("1k", 1), ("32k", 2)])
+@pytest.mark.parametrize("table,style", [("1k", 1), ("32k", 2), ("100k", 3)])
 def test_trained_tables(lib, table, style):
     text = workloads.text(style, 77, 40000).tobytes()
     others = [text[i:i + 2 + i % (WORD_BYTES - 1)] for i in range(0, 30000, 17)]
     missing, known = check(lib, workloads.load_merges(table), random.Random(1), others)
     assert known > 0 and missing <= known // 30            # full buckets: one word in sixty
+
+
+@pytest.mark.parametrize("table", ["1k", "32k", "100k"])
+def test_ranks_in_a_table_image(lib, table):
+    """Every row is found at its rank, those outside their home bucket too, and no other pair is found."""
+    lib.rank_in_image.restype = ctypes.c_int64
+    merges = workloads.load_merges(table)
+    image, log2 = bpe.table_image(merges)
+    tags = image[:4 << log2][1::2]
+    if table != "1k":
+        assert ((tags != 0xFFFFFFFF) & (tags >> 28 != 0)).any()        # displaced rows
+    for r, (a, b) in enumerate(merges.tolist()):
+        assert lib.rank_in_image(ptr(image), log2, a, b) == r
+    rows = set(map(tuple, merges.tolist()))
+    rng, lefts = random.Random(len(rows)), merges[:, 0].tolist()
+    for _ in range(50000):
+        a, b = lefts[rng.randrange(len(lefts))], rng.randrange(256 + len(merges))
+        if (a, b) not in rows:
+            assert lib.rank_in_image(ptr(image), log2, a, b) == -1

@@ -5,13 +5,20 @@
 
 #include "word_table.h"
 
-// Builds the word table of a merge list.  known[t]: the table holds token t.
-// buckets: capacity words; returns log2 of the number of buckets, or -1 if they do not fit.
-extern "C" int build_words(const int32_t* merges, int32_t n, uint8_t* known, uint32_t* buckets, int64_t capacity,
-                           uint32_t* keys) {
+// Rank of a pair in a table image, as the library asks for it; -1: it is no row.
+extern "C" int64_t rank_in_image(const uint32_t* image, int log2_buckets, uint32_t a, uint32_t b) {
+  const uint32_t rank = bpe::image_rank(image, log2_buckets, a, b);
+  return rank == bpe::kNoRank ? -1 : (int64_t)rank;
+}
+
+// Builds the word table of a merge list, with ranks from its table image (as the library does) or, without one, from a map.
+// known[t]: the table holds token t.  buckets: capacity words; returns log2 of the number of buckets, or -1 if they do not fit.
+extern "C" int build_words(const int32_t* merges, int32_t n, const uint32_t* table_image, int log2_buckets, uint8_t* known,
+                           uint32_t* buckets, int64_t capacity, uint32_t* keys) {
   std::map<std::pair<uint32_t, uint32_t>, uint32_t> rank;
   for (int32_t r = 0; r < n; ++r) rank[{(uint32_t)merges[2 * r], (uint32_t)merges[2 * r + 1]}] = (uint32_t)r;
   const auto rank_of = [&](uint32_t a, uint32_t b) {
+    if (table_image) return bpe::image_rank(table_image, log2_buckets, a, b);
     const auto it = rank.find({a, b});
     return it == rank.end() ? bpe::kNoRank : it->second;
   };

@@ -155,8 +155,8 @@ struct WorkspaceLayout {
   bool split;                        // strings are cut into pieces
   int64_t max_slots;                 // upper bound on the number of work items (strings or piece slots)
   int n_tiles;                       // scan tiles over the slots
-  size_t control, list, list_desc, fallback, counts, tmp_ids, cover, staged;
-  size_t slot_string, piece_begin, piece_len, item_len, group_ids, slot_out, tile_sum, part;   // split only
+  size_t control, list_desc, fallback, counts, tmp_ids, cover, staged;
+  size_t list, slot_string, piece_begin, piece_len, item_len, group_ids, slot_out, tile_sum, part;   // split only
   size_t total;
 };
 
@@ -167,14 +167,14 @@ WorkspaceLayout layout_for(int32_t batch, int64_t total_bytes, int32_t max_len) 
   w.n_tiles = (int)((w.max_slots + kScanTile - 1) / kScanTile);
   size_t at = 0;
   w.control = at; at += align_up(sizeof(Control));
-  w.list = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
   w.list_desc = at; at += align_up((size_t)w.max_slots * sizeof(ItemDesc));
   w.fallback = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
   w.counts = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
   w.tmp_ids = at; at += align_up((size_t)total_bytes * sizeof(int32_t));
   w.cover = at; at += align_up((size_t)total_bytes + 4);      // special-token marks, one per byte, whole chunks of 16
-  w.slot_string = w.piece_begin = w.piece_len = w.item_len = w.group_ids = w.slot_out = w.tile_sum = w.part = 0;
+  w.list = w.slot_string = w.piece_begin = w.piece_len = w.item_len = w.group_ids = w.slot_out = w.tile_sum = w.part = 0;
   if (w.split) {
+    w.list = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
     w.slot_string = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
     w.piece_begin = at; at += align_up((size_t)w.max_slots * sizeof(int64_t));
     w.piece_len = at; at += align_up((size_t)w.max_slots * sizeof(int32_t));
@@ -538,7 +538,6 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   hipStream_t stream = (hipStream_t)stream_ptr;
   char* ws = (char*)workspace;
   Control* ctrl = (Control*)(ws + w.control);
-  int32_t* list = (int32_t*)(ws + w.list);
   int32_t* counts = (int32_t*)(ws + w.counts);
   int32_t* tmp_ids = (int32_t*)(ws + w.tmp_ids);
 
@@ -582,9 +581,10 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const bool small_split = w.split && w.max_slots <= kSmallSlots &&
                            w.max_slots <= (int64_t)lanes[kSlots].max_grid * lanes[kSlots].waves;
   const uint32_t* cuts = (const uint32_t*)table->d_words;
-  if (direct) {
-    list = nullptr;
-  } else if (!w.split) {
+  ItemDesc* desc = nullptr;                              // the work list, if there is one
+  int32_t* list = nullptr;                               // ... and, of pieces, their slots
+  if (!direct && !small_split) desc = (ItemDesc*)(ws + w.list_desc);
+  if (!direct && !w.split) {
     // (the stretches' histograms, 256 bytes per 1,024 strings at most, borrow the fallback list, 4 bytes a string,
     // which is written only once the work list is made)
     uint32_t* part = (uint32_t*)(ws + w.fallback);
@@ -592,13 +592,13 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
     const int64_t stretch = (tiles + kBinGrid - 1) / kBinGrid * 1024;
     const int grid = (int)(((int64_t)batch + stretch - 1) / stretch);
     hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, part);
-    hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, ctrl, part, (ItemDesc*)(ws + w.list_desc));
-  } else {
+    hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(1024), 0, stream, offsets, batch, stretch, room, ctrl, part, desc);
+  } else if (w.split) {
     int32_t* ss = (int32_t*)(ws + w.slot_string);
-    if (small_split) list = nullptr;
     int64_t* pb = (int64_t*)(ws + w.piece_begin);
     int32_t* pl = (int32_t*)(ws + w.piece_len);
     if (!small_split) {
+      list = (int32_t*)(ws + w.list);
       uint32_t* part = (uint32_t*)(ws + w.part);
       int32_t* il = (int32_t*)(ws + w.item_len);
       group_ids = (int32_t*)(ws + w.group_ids);
@@ -609,7 +609,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
       hipLaunchKernelGGL(piece_list_kernel, dim3(grid), dim3(1024), 0, stream, bytes, offsets, batch, cuts, cover, kPieceTarget,
                          BPE_MAX_STRING_BYTES, plan, room, n_slots, steps_each, ss, pb, pl, il, counts, group_ids, part);
       hipLaunchKernelGGL(piece_scatter_kernel, dim3(grid), dim3(1024), 0, stream, plan, n_slots, 16 * steps_each * kListSlots,
-                         ctrl, part, pb, il, list, (ItemDesc*)(ws + w.list_desc));
+                         ctrl, part, pb, il, list, desc);
     }
     piece_begin = pb;
     piece_len = pl;
@@ -630,7 +630,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.piece_begin = piece_begin;
   p.piece_len = piece_len;
   p.list = list;
-  p.list_desc = list ? (const void*)(ws + w.list_desc) : nullptr;
+  p.list_desc = desc;
   p.member_begin = w.split ? piece_begin : offsets;
   p.group_ids = group_ids;
   p.tier_base = ctrl->tier_base;
@@ -692,7 +692,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
                        stream, counts, batch, (int)(tiles_each * 1024), out_offsets);
     const int grid = (int)std::min<int64_t>(((int64_t)batch + 3) / 4, 8192);        // (there are fewer groups than strings)
     hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, stream, tmp_ids, offsets, out_offsets, ctrl,
-                       (const ItemDesc*)(ws + w.list_desc), out_ids, table->d_id_map);
+                       desc, out_ids, table->d_id_map);
   } else if (small_split) {
     hipLaunchKernelGGL(small_pack_kernel, dim3((unsigned)((w.max_slots + 3) / 4)), dim3(256), 0, stream, tmp_ids, (int)w.max_slots, slot_string,
                        piece_begin, piece_len, counts, out_offsets, batch, out_ids, table->d_id_map);

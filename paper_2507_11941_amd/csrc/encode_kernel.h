@@ -57,7 +57,7 @@ struct EncodeParams {
   const int64_t* offsets;
   const int64_t* piece_begin; // when strings are split: first byte of each piece (absolute), else null
   const int32_t* piece_len;   //                         and its length
-  const int32_t* list;        // work items (strings or pieces) of all tiers, tier-major, longest first inside a tier
+  const int32_t* list;        // work items that are pieces, of all tiers, tier-major, longest first inside a tier
   const uint32_t* tier_base;  // [tiers+1] start of each tier's slice of `list`
   uint32_t* queue_head;       // [tiers] next unclaimed item of each tier
   int32_t* tmp_ids;           // ids of an item are written at tmp_ids[first byte of the item ...]
@@ -68,10 +68,10 @@ struct EncodeParams {
   const int64_t* member_begin;// lane-per-segment kernel: first byte of each string or piece; an item is several in a row
   int32_t* group_ids;         // pieces: how many ids the packing kernel copies from a piece's first byte on: those of all its
                               //   item, none for the item's other pieces, -1: its own
-  const void* list_desc;      // ItemDesc of every entry of `list` (begin, length, item), in the same order
+  const void* list_desc;      // ItemDesc of every work item (begin, length, item), in the same order; null: no work list
   uint32_t* staged;           // HBM staging for the strings that exceed LDS (a slab per workgroup; else null)
   uint32_t prefetch_lines;    // 128-byte lines of table memory to pull into L2 at kernel start (0 = none)
-  uint32_t direct_count;      // when `list` is null: items are the strings, or a small split batch's slots, 0..direct_count-1, a wave each
+  uint32_t direct_count;      // when there is no work list: items are the strings, or a small split batch's slots, 0..direct_count-1, a wave each
   int n_tiers;
   // when the items are the slots of a small split batch (no list):
   int32_t* slot_kind;         // kSlot... of every slot, else null

@@ -833,8 +833,8 @@ template <class L, bool SPECIAL, bool INLINE, bool SLOTS>
 __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodeParams p) {
   constexpr bool GROUPS = !INLINE && !SLOTS;
   extern __shared__ __align__(16) uint32_t smem[];
-  const uint32_t first = p.list ? p.tier_base[0] : 0u;
-  const uint32_t count = p.list ? p.tier_base[1] - first : p.direct_count;
+  const uint32_t first = p.list_desc ? p.tier_base[0] : 0u;
+  const uint32_t count = p.list_desc ? p.tier_base[1] - first : p.direct_count;
   // The waves that take part: as many as make the rounds even.  5,120 items on 4,096 resident waves
   // are two rounds of 2,560 -- the same two item times, with fewer waves sharing each SIMD.
   const uint32_t n_waves = gridDim.x * L::kWaves;

@@ -10,13 +10,14 @@
 // longer segments first, so the lanes stay busy whatever the mix of segment lengths.
 //
 //   cuts     lane t holds bytes 16 t ... 16 t + 15 of the item (one wide load), asks a bit set of all byte bigrams in LDS
-//            where they are cut, and leaves the segments' first positions as a bitmap.  Segments of one byte are a token as
-//            they are; the others become a list.
+//            where they are cut, and leaves the segments' first positions as a bitmap, then as a list -- without the
+//            segments of one byte, which are a token as they are, where those are many.
 //   words    segment-parallel, 64 at a time and three such batches in flight: the segment's bytes are its key; two
 //            dependent table reads say which token it is, if it is one.
 //   list     the other segments, the "jobs", sorted by length, longest first: a counting sort with one LDS counter per
-//            length.  Handing the long segments out first is what keeps the lanes level at the end.  Only they get a
-//            place in the array of tokens and pair values (the "arena").
+//            length.  Handing the long segments out first is what keeps the lanes level at the end; up to 64 jobs are
+//            not sorted, every lane has one at once (64 strings of 4 KiB: 0.4 us).  Only they get a place in the array of
+//            tokens and pair values (the "arena").
 //   merge    segment-parallel, as above; a lane keeps its segment's liveness as a 32-bit mask, so a segment
 //            may have at most 32 bytes.  A string with a longer segment is not encoded here: the kernel hands
 //            it to the wave-per-item encoder of encode_segmented.h, which has no such limit.  (An item is one
@@ -398,19 +399,25 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     const uint32_t head = here ? (at | 31u) - (uint32_t)__builtin_clz(here) : heads[at >> 5];
     return head - rank_of(head);
   };
-  const uint32_t my_multis = (uint32_t)__builtin_popcount(multi);
-  const uint32_t multis_upto = wave_scan<OpAdd>(my_multis, 0u);
+  // Few single bytes (one or two in a word here and there) are listed with the others: a look-up batch has room for them, and
+  // a pass of their own costs a wave that is alone half a microsecond.
+  const bool few = !__ballot(__builtin_popcount(singles) > 2);           // uniform
+  const uint32_t listed = few ? multi | singles : multi;
+  if (few) singles = 0;
+  const uint32_t my_listed = (uint32_t)__builtin_popcount(listed);
+  const uint32_t all_upto = wave_scan<OpAdd>(my_listed, 0u);
   uint32_t listed_before = 0;                          // segments of earlier lists (uniform)
-  if (!any_multi) count_tokens();                      // uniform
-  for (int word0 = any_multi ? 0 : n_words; word0 < n_words;) {          // (one list, unless there are very many segments)
-    // ---- list of the segments of two bytes or more that start in words word0 ... word1 - 1 ----
-    const uint64_t in_list = __ballot(lane >= word0 && lane < n_words && multis_upto - listed_before <= (uint32_t)L::kListed);
-    const int word1 = word0 + (int)__builtin_popcountll(in_list);          // (at least one more: a word has 16 at most)
-    const uint32_t listed_upto = (uint32_t)__builtin_amdgcn_readlane((int)multis_upto, word1 - 1);
+  const bool any_listed = __ballot(listed != 0) != 0;  // uniform
+  if (!any_listed) count_tokens();
+  for (int word0 = any_listed ? 0 : n_words; word0 < n_words;) {         // (one list, unless there are very many segments)
+    // ---- list of the segments that start in words word0 ... word1 - 1 ----
+    const uint64_t in_list = __ballot(lane >= word0 && lane < n_words && all_upto - listed_before <= (uint32_t)L::kListed);
+    const int word1 = word0 + (int)__builtin_popcountll(in_list);          // (at least one more: a word has 18 at most)
+    const uint32_t listed_upto = (uint32_t)__builtin_amdgcn_readlane((int)all_upto, word1 - 1);
     const int n_listed = (int)(listed_upto - listed_before);
     {
-      uint32_t at = multis_upto - my_multis - listed_before;
-      uint32_t m = lane >= word0 && lane < word1 ? multi : 0u;
+      uint32_t at = all_upto - my_listed - listed_before;
+      uint32_t m = lane >= word0 && lane < word1 ? listed : 0u;
       while (__ballot(m != 0)) {
         if (m) {
           const uint32_t bit = (uint32_t)__builtin_ctz(m);
@@ -427,11 +434,12 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     // ---- words: which segments are one token ----
 #pragma unroll 1
     for (int base = 0; base < n_listed; base += 64 * kLaneBatches) {     // uniform
-      uint32_t k[kLaneBatches][4], len[kLaneBatches], tag[kLaneBatches];
+      uint32_t k[kLaneBatches][4], len[kLaneBatches], tag[kLaneBatches], at[kLaneBatches], mark[kLaneBatches];
       uint4 bucket[kLaneBatches], key[kLaneBatches];
 #pragma unroll
       for (int r = 0; r < kLaneBatches; ++r) {
         const uint32_t e = list[min(base + 64 * r + lane, n_listed - 1)];
+        if constexpr (SPECIAL) at[r] = e & 2047u;
         len[r] = (e >> 11) + 1u;
         const uint32_t* const word = text + ((e & 2047u) >> 2);
         const uint32_t shift = 8u * (e & 3u);
@@ -448,7 +456,12 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
         if (base + 64 * r < n_listed) {                // uniform
           const uint32_t hash = word_hash(k[r][0], k[r][1], k[r][2], k[r][3]);
           tag[r] = word_tag(hash);
-          if (len[r] <= (uint32_t)kWordBytes) bucket[r] = tab.word_buckets[word_bucket(hash, tab.log2_word_buckets)];
+          if (len[r] - 2u <= (uint32_t)kWordBytes - 2u)
+            bucket[r] = tab.word_buckets[word_bucket(hash, tab.log2_word_buckets)];
+        }
+        if constexpr (SPECIAL) {
+          mark[r] = 0;
+          if (any_marked && len[r] == 1u) mark[r] = p.cover[begin + at[r]];
         }
       }
 #pragma unroll
@@ -462,7 +475,13 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
       for (int r = 0; r < kLaneBatches; ++r) {
         if (base + 64 * r < n_listed) {                // uniform
           const bool same = ((key[r].x ^ k[r][0]) | (key[r].y ^ k[r][1]) | (key[r].z ^ k[r][2]) | (key[r].w ^ k[r][3])) == 0;
-          lds[L::kFound + base + 64 * r + lane] = same ? tag[r] : kRecNone;
+          uint32_t what = same ? tag[r] : kRecNone;
+          if (len[r] == 1u) {
+            what = k[r][0];
+            if constexpr (SPECIAL)
+              if (mark[r]) what = p.special_base + (mark[r] & kCoverIndex);
+          }
+          lds[L::kFound + base + 64 * r + lane] = what;
         }
       }
     }
@@ -534,13 +553,23 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     }
     for (uint32_t done = 0; done < all_places;) {      // uniform: places of the parts before
       wave_order();
-      if (lane < 32) hist[lane] = 0;
-      wave_order();
       uint32_t upto_part = all_places;                 // uniform
       // where a job begins in the arena: whole fours
       auto place_of = [&](uint32_t e) { return (e >> 16) - done - ((((e >> 11) & 31u) + 4u) & ~3u); };
-      {
+      if (n_jobs <= 64u && part == all_places) {       // uniform: a lane for each at once, in whatever order
+        uint32_t before = 0;
+#pragma unroll
+        for (int r = 0; r < kBatches; ++r) {
+          if (r >= each) break;                        // uniform
+          const uint64_t mine = __ballot(job[r] != 0);
+          if (job[r]) jobs[before + mbcnt64(mine)] = job[r];
+          before += (uint32_t)__builtin_popcountll(mine);
+        }
+        wave_order();
+      } else {
         // ---- list: longest first (counting sort over the 31 possible lengths) ----
+        if (lane < 32) hist[lane] = 0;
+        wave_order();
         uint32_t place[kBatches], mine = 0, last = done;
 #pragma unroll
         for (int r = 0; r < kBatches; ++r) place[r] = 0;
@@ -773,28 +802,7 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
     }
     wave_order();                                      // the list's LDS is used again
   }
-  // ---- the single bytes ----
-  auto write_single = [&](uint32_t at, uint32_t o) __attribute__((always_inline)) {
-    uint32_t id = ((const uint8_t*)text)[at];
-    if constexpr (SPECIAL) {
-      if (any_marked) {                                // uniform
-        const uint32_t mark = p.cover[begin + at];
-        if (mark) id = p.special_base + (mark & kCoverIndex);
-      }
-    }
-    if constexpr (GROUPS)
-      if (left) o += lack_of(at);
-    dst[o] = (int32_t)id;
-  };
-  if (!__ballot(__builtin_popcount(singles) > 4)) {    // uniform: few, each lane its word's
-    while (__ballot(singles != 0)) {
-      if (singles) {
-        const uint32_t bit = (uint32_t)__builtin_ctz(singles);
-        write_single(32u * (uint32_t)lane + bit, my_rank + (uint32_t)__builtin_popcount(my_tokens & ((1u << bit) - 1u)));
-      }
-      singles &= singles - 1u;
-    }
-  }
+  // ---- the single bytes, where they are many ----
 #pragma unroll 1
   for (uint64_t words = __ballot(singles != 0); words;) {                // uniform: a row of 64 positions at a time
     const int row = (int)__builtin_ctzll(words) >> 1;
@@ -804,10 +812,22 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
              (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)word, 2 * row + 1) << 32;
     };
     const uint64_t row_tokens = row_of(my_tokens);
-    const uint32_t o = __builtin_amdgcn_mbcnt_hi((uint32_t)(row_tokens >> 32),
-                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)row_tokens,
-                                                                           (uint32_t)__builtin_amdgcn_readlane((int)my_rank, 2 * row)));
-    if (__builtin_amdgcn_inverse_ballot_w64(row_of(singles))) write_single(64u * (uint32_t)row + (uint32_t)lane, o);
+    uint32_t o = __builtin_amdgcn_mbcnt_hi((uint32_t)(row_tokens >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)row_tokens,
+                                                                     (uint32_t)__builtin_amdgcn_readlane((int)my_rank, 2 * row)));
+    if (__builtin_amdgcn_inverse_ballot_w64(row_of(singles))) {
+      const uint32_t at = 64u * (uint32_t)row + (uint32_t)lane;
+      uint32_t id = ((const uint8_t*)text)[at];
+      if constexpr (SPECIAL) {
+        if (any_marked) {                              // uniform
+          const uint32_t mark = p.cover[begin + at];
+          if (mark) id = p.special_base + (mark & kCoverIndex);
+        }
+      }
+      if constexpr (GROUPS)
+        if (left) o += lack_of(at);
+      dst[o] = (int32_t)id;
+    }
   }
   if constexpr (GROUPS) {
     // (empty strings at the end, and lanes without one: nothing after them)
@@ -883,7 +903,13 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   const uint64_t own_items = (uint64_t)g * per_claim + spread * ((g >> 2) * 6u + kBefore[g & 3u]);
   uint32_t here = (uint32_t)min((uint64_t)(per_claim + spread * (b & 3u)), count - min(first_item, (uint64_t)count));
   ItemDesc cur;
-  if (!SLOTS && b < g) load_chunk(first_item, here, cur);   // (on its way while the workgroup's LDS is filled)
+  // (on their way while the workgroup's LDS is filled)
+  SlotString string{0, 0, 0};
+  if constexpr (SLOTS) {
+    if (b < g) string = slot_string_of(p.offsets, p.batch, p.piece_target, b);
+  } else {
+    if (b < g) load_chunk(first_item, here, cur);
+  }
   for (int i = (int)threadIdx.x; i < 2048 / 4; i += 64 * L::kWaves)
     ((uint4*)(smem + LaneShared::kCuts))[i] = ((const uint4*)p.table.cuts)[i];
   if (threadIdx.x < 64) {                              // word w of the first l bytes
@@ -895,8 +921,8 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   uint32_t* const arrays = smem + L::kSharedWords + wave * L::kWords;
 
   if constexpr (SLOTS) {                               // (the grid covers the slots)
-    const SlotPiece piece = slot_piece(p.bytes, p.offsets, p.batch, p.cover, smem + LaneShared::kCuts, p.piece_target,
-                                       p.max_string, b, p.slot_string, p.slot_begin, p.slot_len);
+    const SlotPiece piece = slot_piece(p.bytes, string, p.cover, smem + LaneShared::kCuts, p.piece_target, p.max_string, b,
+                                       p.slot_string, p.slot_begin, p.slot_len);
     int kind = kSlotDone;
     const int tier = piece.len <= kMemberBytes ? 0 : piece.len <= 4096 ? 1 : piece.len <= 16384 ? 2 : 3;
     if (piece.len < 0 || tier >= p.n_tiers) {          // void, or longer than the host said: nobody encodes it

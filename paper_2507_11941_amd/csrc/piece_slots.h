@@ -204,14 +204,23 @@ __device__ inline int64_t wave_last_cut(const uint8_t* bytes, const uint8_t* cov
   }
   return -1;
 }
+// The string that slot g may belong to, a wave's work: no cuts are needed for it.
+struct SlotString {
+  int s;
+  int64_t begin, end;
+};
+__device__ inline SlotString slot_string_of(const int64_t* offsets, int batch, int piece_target, uint32_t g) {
+  const int s = wave_last_string(batch, [&](int i) { return slot_base(offsets[i], i, piece_target) <= g; });
+  return SlotString{s, offsets[s], offsets[s + 1]};
+}
 // The piece that starts in slot g, and what the packing kernel wants to know of the slots it covers.  A wave's work; all
 // arguments are uniform.
-__device__ inline SlotPiece slot_piece(const uint8_t* bytes, const int64_t* offsets, int batch, const uint8_t* cover,
+__device__ inline SlotPiece slot_piece(const uint8_t* bytes, const SlotString& string, const uint8_t* cover,
                                        const uint32_t* cuts, int piece_target, int max_string, uint32_t g,
                                        int32_t* slot_string, int64_t* piece_begin, int32_t* piece_len) {
   const int lane = threadIdx.x & 63;
-  const int s = wave_last_string(batch, [&](int i) { return slot_base(offsets[i], i, piece_target) <= g; });
-  const int64_t begin = offsets[s], end = offsets[s + 1];
+  const int s = string.s;
+  const int64_t begin = string.begin, end = string.end;
   const uint32_t base = slot_base(begin, s, piece_target);
   const uint32_t end_slot = base + slots_of_length(end - begin, piece_target, max_string);
   const bool used = g >= base && g < end_slot && end >= begin && end - begin <= max_string;

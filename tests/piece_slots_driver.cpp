@@ -12,7 +12,8 @@ extern "C" void piece_slots(const uint8_t* bytes, const int64_t* offsets, int ba
   run_wave([&](int) {
     if (steps_each == 0) {
       for (uint32_t g = 0; g < n_slots; ++g)
-        bpe::slot_piece(bytes, offsets, batch, cover, cuts, piece_target, max_string, g, slot_string, piece_begin, piece_len);
+        bpe::slot_piece(bytes, bpe::slot_string_of(offsets, batch, piece_target, g), cover, cuts, piece_target, max_string, g,
+                        slot_string, piece_begin, piece_len);
       return;
     }
     int s0 = 0;

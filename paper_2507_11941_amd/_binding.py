@@ -222,6 +222,9 @@ def encode_batch_static(table: Table, data, offsets, max_len: int, out_ids, out_
     return out_ids, out_offsets
 
 
+GUESS_BYTES = 1 << 19                            # of text, up to which encode_strings guesses how many ids it becomes
+
+
 def encode_strings(table: Table, strings, device=None):
     """Convenience for callers that start from host strings: ``strings`` is a sequence of ``bytes`` (or ``str``,
     encoded as UTF-8); returns one int32 numpy array of token ids per string.  Marshalling only: the bytes are
@@ -237,17 +240,21 @@ def encode_strings(table: Table, strings, device=None):
         raise ValueError(f"a string has {max_len} bytes; the encoder takes at most {MAX_STRING_BYTES}")
     dev = torch.device(device if device is not None else "cuda:0")
     # A copy between host and device costs some 15 us, whatever its size below 100 KB: offsets and bytes go up in one, and
-    # offsets and ids come down in one -- as many ids as text usually has (of 64 strings of up to 4 KiB 144 -> 117 us).
+    # offsets and ids come down in one -- as many ids as text usually has (of 64 strings of up to 4 KiB 144 -> 117 us).  Of
+    # more text the ids are fetched once their number is known, for a guess fetches too many or has to be put together with
+    # the rest: 0.4 MB of words 285 us with a guess, 317 without; 0.6 MB 162 and 170, of bytes at random 345 and 282; 1.2 MB
+    # of those 618 and 487; 6.5 MB 2,970 and 2,300.
     total, head = int(offsets[-1]), offsets.nbytes + (-offsets.nbytes) % 16
     up = torch.frombuffer(bytearray(b"".join((offsets.tobytes(), bytes(head - offsets.nbytes), *raw))), dtype=torch.uint8).to(dev)
     down = torch.empty(2 * len(offsets) + max(total, 1), dtype=torch.int32, device=dev)
     out_off, ids = down[:2 * len(offsets)].view(torch.int64), down[2 * len(offsets):]
     with torch.cuda.device(dev):
         encode_batch(table, up[head:], up[:offsets.nbytes].view(torch.int64), max_len, ids, out_off)
-    got = down[:2 * len(offsets) + total // 3 + 64].cpu().numpy()
+    got = down[:2 * len(offsets) + (total // 3 + 64 if total <= GUESS_BYTES else 0)].cpu().numpy()
     out_off, ids = got[:2 * len(offsets)].view(np.int64).tolist(), got[2 * len(offsets):]
     if out_off[-1] > len(ids):
-        ids = np.concatenate((ids, down[len(got):2 * len(offsets) + out_off[-1]].cpu().numpy()))
+        rest = down[len(got):2 * len(offsets) + out_off[-1]].cpu().numpy()
+        ids = np.concatenate((ids, rest)) if len(ids) else rest
     return [ids[out_off[i]:out_off[i + 1]] for i in range(len(raw))]
 
 

@@ -27,16 +27,17 @@
 //
 // list to emit run over as many jobs at a time as the arena and the list hold: in words, all of the item's.
 //
-// What bounds it is instruction issue: some 2,080 vector and 600 scalar instructions per KiB of text, of which the merge
+// What bounds it is instruction issue: some 2,100 vector and 550 scalar instructions per KiB of text, of which the merge
 // loop is two fifths, on four waves a SIMD.  With every segment going through the merges, one item of 1 KiB a wave
 // (14.9 trips of the loop per KiB instead of 6.8), the 65,536 documents of the throughput workload took 1,480 us in this
-// kernel; they take 975, and the whole call 1,066 instead of 1,659.
+// kernel; they take 977, and the whole call 1,066 instead of 1,659.
 //
 // Of text that is not words most look-ups find nothing and cost what they cost, and its jobs do not fit the arena at once.
 // 32 MiB in strings of 4 KiB, whole call, all segments merged / single bytes listed and looked up like the others, the arena
 // filled to the brim and the rest in a part of its own / now: bytes at random, 100k rows 281 / 453 / 241 us; digits and
 // letters of a hexadecimal dump, 32k rows 303 / 405 / 332; text of a larger table's words under 1k rows 254 / 396 / 305;
-// words of no table, 100k rows 314 / 367 / 371; words, 100k rows 312 / 241 / 239.
+// words of no table, 100k rows 314 / 367 / 371; words, 100k rows 312 / 241 / 239.  (Single bytes four positions a lane instead
+// of a row at a time: 3 to 4 % off the third, but 128 registers, and 0.4 % more for words and 1.8 % for runs and motifs.)
 #pragma once
 #include "encode_segmented.h"
 

@@ -704,10 +704,11 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
             best = min(best, min(min(min(c.x, c.y), min(c.z, c.w)), min(min(d.x, d.y), min(d.z, d.w))));
           }
           if (__ballot(last >= 16u)) {                 // uniform
-            for (uint32_t o = 16; o < 32; o += 4) {
-              const uint4 a = *(const uint4*)(v0 + min(o, last));
-              best = min(best, min(min(a.x, a.y), min(a.z, a.w)));
-            }
+            const uint4 a = *(const uint4*)(v0 + min(16u, last)), b = *(const uint4*)(v0 + min(20u, last)),
+                        c = *(const uint4*)(v0 + min(24u, last)), d = *(const uint4*)(v0 + min(28u, last));
+            __builtin_amdgcn_sched_barrier(0);         // (likewise)
+            best = min(best, min(min(min(a.x, a.y), min(a.z, a.w)), min(min(b.x, b.y), min(b.z, b.w))));
+            best = min(best, min(min(min(c.x, c.y), min(c.z, c.w)), min(min(d.x, d.y), min(d.z, d.w))));
           }
           // From here to the issue of the new look-ups a wave is on its way to its next memory round trip: it goes
           // before the waves that are scanning or loading (measured: 1 % on the large workloads).
@@ -911,6 +912,11 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   } else {
     if (b < g) load_chunk(first_item, here, cur);
   }
+  if constexpr (INLINE) {                              // (for the wave-per-item encoder)
+    static_assert(!INLINE || 64 * L::kWaves >= 2048 / 4 + 256, "waves that copy no cuts");
+    const int i = (int)threadIdx.x - (64 * L::kWaves - 256);
+    if (i >= 0) smem[LaneShared::kByteWord + i] = p.table.byte_word[i];
+  }
   for (int i = (int)threadIdx.x; i < 2048 / 4; i += 64 * L::kWaves)
     ((uint4*)(smem + LaneShared::kCuts))[i] = ((const uint4*)p.table.cuts)[i];
   if (threadIdx.x < 64) {                              // word w of the first l bytes
@@ -948,9 +954,7 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
       if (left) {                                      // uniform
         if constexpr (INLINE) {
           wave_order();
-          // (the other encoder's arrays take the place of this one's; every wave that needs the bytes' words writes them)
-          for (int o = lane; o < 256; o += 64) smem[LaneShared::kByteWord + o] = p.table.byte_word[o];
-          wave_order();
+          // (the other encoder's arrays take the place of this one's)
           const BlockShared<1> sh = block_shared<1>(arrays + 3 * 1024, smem + LaneShared::kByteWord);
           encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2 * 1024, sh);
           wave_order();

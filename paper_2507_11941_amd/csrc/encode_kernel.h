@@ -266,7 +266,7 @@ struct BlockShared {
   uint32_t* first_tok;   // [2][NW] first live token of each wave after the pass's merges
   uint32_t* part;        // [2][NW] scan partials, double buffered by pass parity
   uint32_t* item;        // [1] work item broadcast
-  const uint32_t* byte_word;  // [256] LDS copy of the byte token words
+  const uint32_t* byte_word;  // [256] the byte token words: an LDS copy, or the table's own
 };
 
 template <int NW>

@@ -76,8 +76,7 @@ constexpr uint32_t kRecNone = 1u << 31;         // what becomes of a segment: it
 struct LaneShared {
   static constexpr int kCuts = 0;                                       // bit a + 256 b: bytes a, b have a cut between them
   static constexpr int kMasks = kCuts + 2048;                           // [16][4] first l bytes of a key
-  static constexpr int kByteWord = kMasks + 64;                         // token word of every byte, for the one-wave encoder
-  static constexpr int kWords = kByteWord;                              // (INLINE: and those 256)
+  static constexpr int kWords = kMasks + 64;
 };
 // Shape of a workgroup, and the LDS of one of its waves.  WAVES: they take items of their own; BYTES: an item's capacity;
 // LIST: segments listed at a time; JOBS: those that go through the merges at a time; ARENA: the bytes of those, in fours.  What bounds
@@ -105,9 +104,8 @@ struct LaneShape {
   static constexpr int kStarts = kV;                                    // bit p: a segment starts at p, or the item ends
   static constexpr int kFound = kV;                                     // what becomes of a segment
   static constexpr int kWords = ((kEnd > AT_LEAST ? kEnd : AT_LEAST) + 3) / 4 * 4;
-  static constexpr int kSharedWords = LaneShared::kWords + (AT_LEAST ? 256 : 0);
-  static constexpr size_t kLdsBytes = lds_blocks(sizeof(uint32_t) * (kSharedWords + WAVES * kWords));
-  static_assert(kText % 4 == 0 && ARENA % 4 == 0 && kSharedWords % 4 == 0, "wide loads and stores");
+  static constexpr size_t kLdsBytes = lds_blocks(sizeof(uint32_t) * (LaneShared::kWords + WAVES * kWords));
+  static_assert(kText % 4 == 0 && ARENA % 4 == 0 && LaneShared::kWords % 4 == 0, "wide loads and stores");
   static_assert(ARENA <= 2048 && BYTES <= 2048 && BYTES % 1024 == 0 && LIST % 64 == 0 && LIST <= 1024 && JOBS % 64 == 0,
                 "fields of the packed words; a lane per word of the bitmap");
   static_assert(LIST <= ARENA && BYTES / 32 + 4 <= ARENA, "what shares a place fits it");
@@ -912,11 +910,6 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   } else {
     if (b < g) load_chunk(first_item, here, cur);
   }
-  if constexpr (INLINE) {                              // (for the wave-per-item encoder)
-    static_assert(!INLINE || 64 * L::kWaves >= 2048 / 4 + 256, "waves that copy no cuts");
-    const int i = (int)threadIdx.x - (64 * L::kWaves - 256);
-    if (i >= 0) smem[LaneShared::kByteWord + i] = p.table.byte_word[i];
-  }
   for (int i = (int)threadIdx.x; i < 2048 / 4; i += 64 * L::kWaves)
     ((uint4*)(smem + LaneShared::kCuts))[i] = ((const uint4*)p.table.cuts)[i];
   if (threadIdx.x < 64) {                              // word w of the first l bytes
@@ -925,7 +918,7 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   }
   __syncthreads();
   if (b >= g || first_item >= count) return;           // uniform in the wave; no barrier follows
-  uint32_t* const arrays = smem + L::kSharedWords + wave * L::kWords;
+  uint32_t* const arrays = smem + LaneShared::kWords + wave * L::kWords;
 
   if constexpr (SLOTS) {                               // (the grid covers the slots)
     const SlotPiece piece = slot_piece(p.bytes, string, p.cover, smem + LaneShared::kCuts, p.piece_target, p.max_string, b,
@@ -954,8 +947,8 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
       if (left) {                                      // uniform
         if constexpr (INLINE) {
           wave_order();
-          // (the other encoder's arrays take the place of this one's)
-          const BlockShared<1> sh = block_shared<1>(arrays + 3 * 1024, smem + LaneShared::kByteWord);
+          // (the other encoder's arrays take the place of this one's; the bytes' words come from memory, beside their pairs)
+          const BlockShared<1> sh = block_shared<1>(arrays + 3 * 1024, p.table.byte_word);
           encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2 * 1024, sh);
           wave_order();
         } else {

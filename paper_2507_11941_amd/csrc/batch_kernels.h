@@ -27,7 +27,7 @@ struct Control {
   uint32_t tier_base[kMaxTiers + 1];                 // start of each tier's slice of the list
   uint32_t queue_head[kMaxTiers];                    // work-queue heads of the encode kernels
   uint32_t fallback_range[2];                        // {0, items the lane-per-segment kernel passed on}
-  uint32_t fallback_queue;                           // work-queue head of the kernel that takes those
+  uint32_t unfolded_count[kMaxTiers];                // items of each tier that are left to the kernel of the longest ones
 };
 
 __device__ inline int bin_key(int len, const TierPlan& plan) {
@@ -115,7 +115,6 @@ __global__ __launch_bounds__(1024) void bin_scatter_kernel(const int64_t* offset
       if (lane <= kMaxTiers) c->tier_base[lane] = lane == 0 ? 0u : total;
       if (lane < kMaxTiers) c->queue_head[lane] = 0;
       if (lane < 2) c->fallback_range[lane] = 0;
-      if (lane == 2) c->fallback_queue = 0;
     }
   }
   __syncthreads();
@@ -337,9 +336,8 @@ __global__ __launch_bounds__(1024) void piece_scatter_kernel(TierPlan plan, uint
   if (t < kBinKeys) cursor[t] = scan[t] - total + sum_before[0][t] + sum_before[1][t] + sum_before[2][t] + sum_before[3][t];
   if (blockIdx.x == 0) {
     if (t <= kMaxTiers) c->tier_base[t] = t == 0 ? 0 : scan[(t <= plan.n_tiers ? t : plan.n_tiers) * kLenBuckets - 1];
-    if (t < kMaxTiers) c->queue_head[t] = 0;
+    if (t < kMaxTiers) c->queue_head[t] = c->unfolded_count[t] = 0;
     if (t < 2) c->fallback_range[t] = 0;
-    if (t == 2) c->fallback_queue = 0;
   }
   __syncthreads();
   const uint32_t first = blockIdx.x * slots_each, last = min(first + slots_each, n_slots);

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -144,6 +145,7 @@ int n_tiers_for(int32_t max_len) {
 
 // Resident workgroups of the long variant each own one staging slab (768 KiB), where there is a tier that needs them.
 constexpr int kMaxLongGrid = 256;
+static_assert(offsetof(Control, unfolded_count) - offsetof(Control, queue_head) == kTierCounts * sizeof(uint32_t), "its place");
 
 constexpr size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -644,7 +646,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.out_offsets = alone ? out_offsets : nullptr;         // (out_ids may be null: one empty string)
   p.id_map = table->d_id_map;
   p.direct_count = small_split ? (uint32_t)w.max_slots : (uint32_t)batch;
-  p.slot_kind = small_split ? (int32_t*)(ws + w.item_len) : nullptr;
+  p.slot_kind = w.split ? (int32_t*)(ws + w.item_len) : nullptr;        // (whose use for a list ends when it is made)
   p.slot_string = (int32_t*)(ws + w.slot_string);
   p.slot_begin = (int64_t*)(ws + w.piece_begin);
   p.slot_len = (int32_t*)(ws + w.piece_len);
@@ -656,7 +658,6 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   p.total_bytes = total_bytes;
   p.fallback_count = &ctrl->fallback_range[1];
   p.fallback_list = (int32_t*)(ws + w.fallback);
-  p.fallback_queue = &ctrl->fallback_queue;
   p.n_tiers = plan.n_tiers;
   p.staged = (uint32_t*)(ws + w.staged);
   // Warming L2 pays once the batch probes the table more often than it has lines: ~1 probe per input byte.

@@ -51,6 +51,7 @@ struct DeviceTable {
   int log2_word_buckets;
 };
 
+constexpr int kTierCounts = 6;
 struct EncodeParams {
   DeviceTable table;
   const uint8_t* bytes;
@@ -59,7 +60,8 @@ struct EncodeParams {
   const int32_t* piece_len;   //                         and its length
   const int32_t* list;        // work items that are pieces, of all tiers, tier-major, longest first inside a tier
   const uint32_t* tier_base;  // [tiers+1] start of each tier's slice of `list`
-  uint32_t* queue_head;       // [tiers] next unclaimed item of each tier
+  uint32_t* queue_head;       // [tiers] next unclaimed item of each tier; kTierCounts words further on
+                              //   [tiers] the longer tiers' items that do not fold, 64 for each
   int32_t* tmp_ids;           // ids of an item are written at tmp_ids[first byte of the item ...]
   int32_t* counts;            // token count of each item
   int64_t* out_offsets;       // a batch of one short string, whose output the encode kernel writes itself: the offsets, else null;
@@ -74,7 +76,8 @@ struct EncodeParams {
   uint32_t direct_count;      // when there is no work list: items are the strings, or a small split batch's slots, 0..direct_count-1, a wave each
   int n_tiers;
   // when the items are the slots of a small split batch (no list):
-  int32_t* slot_kind;         // kSlot... of every slot, else null
+  int32_t* slot_kind;         // kSlot... of every slot (of listed pieces: those of the longer tiers that do not fold, in the
+                              //   places of `list`; one field for both: two more of them cost a small call 0.2 us)
   int32_t* slot_string;
   int64_t* slot_begin;        // (piece_begin and piece_len)
   int32_t* slot_len;
@@ -83,8 +86,7 @@ struct EncodeParams {
   uint32_t special_base;      // token number of special 0 (256 + rows)
   int64_t total_bytes;        // size of `bytes`: wide loads must not run past it
   uint32_t* fallback_count;   // lane-per-segment kernel: items it cannot take are counted here ...
-  int32_t* fallback_list;     // ... and listed here, for the wave-per-item kernel that runs after it ...
-  uint32_t* fallback_queue;   // ... and claims from here
+  int32_t* fallback_list;     // ... and listed here, for the wave-per-item kernel that runs after it
 };
 
 // What the load phases make of them: "byte codes" above the byte values.  Any code >= 0x100 is no byte, so
@@ -101,6 +103,12 @@ __device__ inline uint32_t cover_code(uint32_t byte, uint32_t mark) {
 // wave64 primitives
 
 __device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
+// Sums that waves add to: a lane that adds alone, by a condition on its number or with zeros from the others, makes the
+// compiler go over all 64 lanes one by one (some 640 scalar instructions, 1.3 us) or, where it cannot tell that the address is
+// the same in all, sends the memory all 64.  Where every lane adds the same it sends one addition, of 64 times that; so
+// these sums count 64 for each.  All lanes take part; returns the sum before, divided by 64.
+__device__ inline uint32_t wave_add(uint32_t* sum, uint32_t each) { return uniform(atomicAdd(sum, each) >> 6); }
 
 template <int CTRL>
 __device__ inline uint32_t dpp(uint32_t v) {
@@ -210,6 +218,38 @@ __device__ inline uint32_t wave_parity_exclusive(uint32_t elem, int lane, uint32
 // The value the lane before mine holds (lane 0 receives `identity`).
 __device__ inline uint32_t wave_shift_up(uint32_t v, uint32_t identity) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, 0x138, 0xF, 0xF, false);  // wave_shr:1
+}
+
+// Bytes at ... at + 15 of the `room` bytes from src on, whatever their alignment; 0 <= at < room, and what lies beyond
+// them reads as anything.  `before`: bytes that may be read before src as well.
+__device__ inline uint4 load_16_bytes(const uint8_t* src, int at, int64_t before, int64_t room) {
+  uint4 v = make_uint4(0, 0, 0, 0);
+  const int last = (int)min(room, (int64_t)1 << 30) - 16;                // (uniform)
+  if (before + last < 0) {                             // uniform: fewer than 16 bytes in all
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll 1
+    for (int j = 0; j < (int)room; ++j) {
+      const uint32_t b = src[j];
+      const int to = j - at;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (to >> 2 == i) w[i] |= b << (8 * (to & 3));
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  const int from = min(at, last);
+  __builtin_memcpy(&v, src + (int64_t)from, 16);
+  const uint32_t skip = (uint32_t)(at - from);         // 0 but at the end
+  if (__ballot(skip != 0)) {
+    if (skip & 8u) { v.x = v.z; v.y = v.w; }
+    if (skip & 4u) { v.x = v.y; v.y = v.z; v.z = v.w; }
+    const uint32_t bits = 8u * (skip & 3u);
+    v.x = __builtin_amdgcn_alignbit(v.y, v.x, bits);
+    v.y = __builtin_amdgcn_alignbit(v.z, v.y, bits);
+    v.z = __builtin_amdgcn_alignbit(v.w, v.z, bits);
+    v.w >>= bits;
+  }
+  return v;
 }
 
 // ---------------------------------------------------------------------------------------------------

@@ -160,38 +160,6 @@ __device__ inline void lane_probe_finish(const DeviceTable& t, const LaneProbe& 
   }
 }
 
-// Bytes at ... at + 15 of the `room` bytes from src on, whatever their alignment; 0 <= at < room, and what lies beyond
-// them reads as anything.  `before`: bytes that may be read before src as well.
-__device__ inline uint4 load_16_bytes(const uint8_t* src, int at, int64_t before, int64_t room) {
-  uint4 v = make_uint4(0, 0, 0, 0);
-  const int last = (int)min(room, (int64_t)1 << 30) - 16;                // (uniform)
-  if (before + last < 0) {                             // uniform: fewer than 16 bytes in all
-    uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll 1
-    for (int j = 0; j < (int)room; ++j) {
-      const uint32_t b = src[j];
-      const int to = j - at;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (to >> 2 == i) w[i] |= b << (8 * (to & 3));
-    }
-    return make_uint4(w[0], w[1], w[2], w[3]);
-  }
-  const int from = min(at, last);
-  __builtin_memcpy(&v, src + (int64_t)from, 16);
-  const uint32_t skip = (uint32_t)(at - from);         // 0 but at the end
-  if (__ballot(skip != 0)) {
-    if (skip & 8u) { v.x = v.z; v.y = v.w; }
-    if (skip & 4u) { v.x = v.y; v.y = v.z; v.z = v.w; }
-    const uint32_t bits = 8u * (skip & 3u);
-    v.x = __builtin_amdgcn_alignbit(v.y, v.x, bits);
-    v.y = __builtin_amdgcn_alignbit(v.z, v.y, bits);
-    v.z = __builtin_amdgcn_alignbit(v.w, v.z, bits);
-    v.w >>= bits;
-  }
-  return v;
-}
-
 // Encodes item s -- n bytes from `begin` on (both uniform) -- if all its segments fit a lane; returns 1 (and
 // has written nothing to global memory) if one does not, else 0.  lds: this wave's words of the shape L; shared: the
 // workgroup's LaneShared.  GROUPS: the item is the `members` strings from s on, at most 64, which lie one after the other
@@ -949,7 +917,11 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
           wave_order();
           // (the other encoder's arrays take the place of this one's; the bytes' words come from memory, beside their pairs)
           const BlockShared<1> sh = block_shared<1>(arrays + 3 * 1024, p.table.byte_word);
-          encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2 * 1024, sh);
+          int64_t its_begin;                           // (read again: kept, they cost registers where few strings come here)
+          int its_n;
+          item_of(p, s, its_begin, its_n);
+          encode_string_segmented<1, 16, true, SPECIAL, false>(p, s, its_begin, its_n, arrays, arrays + 1024, arrays + 2 * 1024,
+                                                               sh, Fold{}, nullptr);
           wave_order();
         } else {
           const uint32_t slot = uniform(

@@ -21,6 +21,7 @@
 // horizon to get the candidate mask.  The rest of the pass is the same as in encode_string().
 #pragma once
 #include "encode_kernel.h"
+#include "fold.h"
 
 namespace bpe {
 
@@ -60,11 +61,122 @@ struct SegRecord {
   uint32_t pad0, pad1;
 };
 
-template <int NW, int D, bool LIMITS, bool SPECIAL>
-__device__ void encode_string_segmented(const EncodeParams& p, int s, uint32_t* __restrict__ T,
+// LDS that a folded text's emission needs, in words.  Bit p of the first ones: a token starts at p, or the text ends; then, for
+// each stretch, the place behind which its copies go | how many ids they are << 12.  (Three workgroups of four such waves
+// fit a CU with not a block to spare: with the ranks of the words here too it was two, and runs and motifs took 90 us more.)
+constexpr int kFoldStarts = kFoldBytes / 32 + 3;       // (the end, and two more that are read)
+constexpr int kFoldWords = kFoldStarts + kFoldStretches;
+
+// The ids of a folded text (fold.h): those of its tokens, and each stretch's block as often as it was left out.  A wave's work;
+// live, T, d: as encode_string_segmented() leaves them; out0: tokens before my positions; *total: all of them, to which the
+// copies' ids are added.  Returns false, and has written nothing, if a stretch has no block that is there twice in a row.
+__device__ __forceinline__ bool emit_folded(const Fold& f, uint32_t live, const uint32_t* T, uint32_t* starts, int d,
+                                            uint32_t out0, int32_t* dst, uint32_t* total) {
+  static_assert(kFoldStarts <= 64 && kFoldBytes < 4096, "a lane per word; fields of `copies`");
+  const int lane = (int)threadIdx.x & 63;
+  const uint32_t base = (uint32_t)(lane * d), n = (uint32_t)f.bytes;
+  uint32_t* const copies = starts + kFoldStarts;
+  wave_order();
+  if (lane < kFoldStarts) starts[lane] = 0;
+  wave_order();
+  if (live) {
+    const uint64_t mine = (uint64_t)live << (base & 31u);
+    atomicOr(&starts[base >> 5], (uint32_t)mine);
+    if (mine >> 32) atomicOr(&starts[(base >> 5) + 1u], (uint32_t)(mine >> 32));
+  }
+  if (lane == 0) atomicOr(&starts[n >> 5], 1u << (n & 31u));
+  wave_order();
+  const uint32_t word = lane < kFoldStarts ? starts[lane] : 0u;
+  const uint32_t rank = wave_scan<OpAdd>((uint32_t)__builtin_popcount(word), 0u) - (uint32_t)__builtin_popcount(word);
+  // ---- my stretch's block ----
+  const uint32_t end_before = wave_shift_up(f.end, 0u);
+  const bool mine = lane < f.stretches && f.out != 0;
+  FoldBlock b{0, 0};
+  uint64_t w = 0;
+  if (mine) {
+    const uint32_t i = f.first >> 5, shift = f.first & 31u;
+    w = (uint64_t)__builtin_amdgcn_alignbit(starts[i + 2], starts[i + 1], shift) << 32 |
+        __builtin_amdgcn_alignbit(starts[i + 1], starts[i], shift);
+    b = fold_block(w, f.end - f.first, f.q, end_before > f.first ? end_before - f.first : 0u);
+  }
+  if (__ballot(mine && b.bytes == 0)) return false;    // uniform
+  const uint32_t block = mine ? (uint32_t)(w >> (b.at + b.bytes)) & ((1u << b.bytes) - 1u) : 0u;    // the second one's tokens
+  const uint32_t size = (uint32_t)__builtin_popcount(block);
+  const uint32_t ids = mine ? f.out / b.bytes * size : 0u;
+  const uint32_t behind = mine ? f.first + b.at + 2u * b.bytes : lane < f.stretches ? f.x : 0u;    // (ascending)
+  const uint32_t upto = wave_scan<OpAdd>(ids, 0u);
+  const uint32_t place = lane_read(rank, (int)(behind >> 5)) +
+                         (uint32_t)__builtin_popcount(lane_read(word, (int)(behind >> 5)) & ((1u << (behind & 31u)) - 1u)) +
+                         (upto - ids);
+  *total += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+  copies[lane] = behind | ids << 12;                   // (ids: at most 65,536)
+  wave_order();
+  // ---- the tokens ----
+  {
+    uint32_t o = out0;
+    int j = 0;                                         // stretches whose copies lie before my token
+    for (int i = 0; i < f.stretches; ++i) {            // uniform
+      const bool before = (uint32_t)__builtin_amdgcn_readlane((int)behind, i) <= base;
+      o += before ? (uint32_t)__builtin_amdgcn_readlane((int)ids, i) : 0u;
+      j += before ? 1 : 0;
+    }
+    for (uint32_t m = live; m; m &= m - 1u) {
+      const uint32_t k = (uint32_t)__builtin_ctz(m);
+      for (; j < f.stretches && (copies[j] & 0xFFFu) <= base + k; ++j) o += copies[j] >> 12;
+      dst[o++] = (int32_t)(T[k * 64u + (uint32_t)lane] & kTokIdMask);
+    }
+  }
+  // ---- the copies ----
+  const uint32_t per_d = 65536u / (uint32_t)d + 1u;    // (positions are below 1,041, d at most 16: the quotient is exact)
+  for (int i = 0; i < f.stretches; ++i) {              // uniform
+    const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)ids, i);
+    if (count == 0) continue;
+    const uint32_t tokens = (uint32_t)__builtin_amdgcn_readlane((int)size, i);
+    uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)block, i);
+    const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)(behind - b.bytes), i);
+    int32_t* const to = dst + (uint32_t)__builtin_amdgcn_readlane((int)place, i);
+    for (uint32_t c = 1; c < tokens; ++c) m = (uint32_t)lane >= c ? m & (m - 1u) : m;      // lane c: from the block's token c on
+    const uint32_t at = from + (uint32_t)__builtin_ctz(m | 1u << 16);
+    const uint32_t column = at * per_d >> 16;
+    const uint32_t id = T[(at - column * (uint32_t)d) * 64u + min(column, 63u)] & kTokIdMask;
+    uint32_t done = 0;
+    if (count >= 1024u) {                              // four ids a lane and store
+      uint32_t r = 4u * (uint32_t)lane % tokens;
+      const uint32_t step = 256u % tokens;
+      for (; done + 256u <= count; done += 256u) {
+        int32_t v[4];
+        uint32_t c = r;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          v[u] = (int32_t)lane_read(id, (int)c);
+          c = c + 1u == tokens ? 0u : c + 1u;
+        }
+        __builtin_memcpy(to + done + 4u * (uint32_t)lane, v, 16);
+        r += step;
+        r -= r >= tokens ? tokens : 0u;
+      }
+    }
+    uint32_t r = (done + (uint32_t)lane) % tokens;
+    const uint32_t step = 64u % tokens;
+    for (; done < count; done += 64u) {
+      const int32_t v = (int32_t)lane_read(id, (int)r);
+      if (done + (uint32_t)lane < count) to[done + (uint32_t)lane] = v;
+      r += step;
+      r -= r >= tokens ? tokens : 0u;
+    }
+  }
+  return true;
+}
+
+// Encodes work item s, a whole string or a piece of one between two cuts: the n bytes from `begin` on (uniform).  FOLD: f says
+// what of them is left out, if anything is, and n what stays; returns false, and has written nothing, if that can't be put back
+// in.  Otherwise true.
+template <int NW, int D, bool LIMITS, bool SPECIAL, bool FOLD>
+__device__ bool encode_string_segmented(const EncodeParams& p, int s, int64_t begin, int n, uint32_t* __restrict__ T,
                                         uint32_t* __restrict__ V, uint32_t* __restrict__ L,
-                                        const BlockShared<NW>& sh) {
+                                        const BlockShared<NW>& sh, const Fold& f, uint32_t* fold_lds) {
   static_assert(D % kGroup == 0 && D <= 16, "the per-position registers of the sweep are sized for 16");
+  static_assert(!FOLD || (NW == 1 && kFoldBytes <= 64 * D && D + 2 <= (int)kFoldApart), "a wave's work, and room for what stays");
   using mask_t = uint32_t;
   constexpr int W = NW * 64;
   const int tid = (int)threadIdx.x & (W - 1);          // (one wave: of a workgroup that may have others)
@@ -73,12 +185,9 @@ __device__ void encode_string_segmented(const EncodeParams& p, int s, uint32_t* 
   const DeviceTable& tab = p.table;
   SegRecord* const rec_base = (SegRecord*)sh.rec;
 
-  // a work item is a whole string, or a piece of one between two cuts
-  const int64_t begin = p.piece_begin ? p.piece_begin[s] : p.offsets[s];
-  const int n = (int)uniform((uint32_t)(p.piece_len ? p.piece_len[s] : (int32_t)(p.offsets[s + 1] - begin)));
   if (n <= 0 || n > W * D) {                           // uniform branch; too long only if max_len was wrong
     if (tid == W - 1) p.counts[s] = 0;
-    return;
+    return true;
   }
   const uint8_t* src = p.bytes + begin;
   const int d = (n + W - 1) / W;                       // bytes per lane, 1 <= d <= D (uniform)
@@ -96,18 +205,28 @@ __device__ void encode_string_segmented(const EncodeParams& p, int s, uint32_t* 
   //      lookup per adjacent byte pair in the direct 256 x 256 table; and the cuts ----
   {
     const int base = tid * d;
+    // (folded) bytes left out before mine, and where among them some are: once, since places lie 16 or more apart
+    int skip = 0, gap_at = n, gap = 0;
+    if constexpr (FOLD) {
+      for (int j = 0; j < f.stretches; ++j) {          // uniform
+        const int x = __builtin_amdgcn_readlane((int)f.x, j), out = __builtin_amdgcn_readlane((int)f.out, j);
+        if (x <= base - 1) skip += out;
+        else if (x <= base + d) { gap_at = x; gap = out; }
+      }
+    }
+    auto place_of = [&](int i) { return FOLD ? i + skip + (i >= gap_at ? gap : 0) : i; };
     uint32_t b[D + 2];                                 // b[j] = byte (base - 1 + j) of the string, 0x100 = none
 #pragma unroll
     for (int j = 0; j < D + 2; ++j) {
       const int i = base - 1 + j;
-      b[j] = (j <= c0 + 1 && c0 > 0 && i >= 0 && i < n) ? src[i] : 0x100u;
+      b[j] = (j <= c0 + 1 && c0 > 0 && i >= 0 && i < n) ? src[place_of(i)] : 0x100u;
     }
     if constexpr (SPECIAL) {                           // special tokens are configured: their marks
       const uint8_t* mark = p.cover + begin;
 #pragma unroll
       for (int j = 0; j < D + 2; ++j) {
         const int i = base - 1 + j;
-        if (j <= c0 + 1 && c0 > 0 && i >= 0 && i < n) b[j] = cover_code(b[j], mark[i]);
+        if (j <= c0 + 1 && c0 > 0 && i >= 0 && i < n) b[j] = cover_code(b[j], mark[place_of(i)]);
       }
     }
     uint32_t raw[D + 1];                               // raw[j]: table entry of the pair (b[j], b[j+1])
@@ -471,10 +590,18 @@ __device__ void encode_string_segmented(const EncodeParams& p, int s, uint32_t* 
   // ---- emit: prefix sum of live counts gives each lane's write index (section 4.3's compaction) ----
   uint32_t total;
   const uint32_t out0 = block_prefix_sum<NW>((uint32_t)pop_bits<mask_t>(live), sh, lane, wave, &total);
-  int32_t* dst = p.tmp_ids + begin + out0;
-  for (mask_t m = live; m; m &= m - 1) *dst++ = (int32_t)(T[ctz_bits<mask_t>(m) * W + tid] & kTokIdMask);
+  bool folded = false;
+  if constexpr (FOLD) {
+    folded = f.stretches > 0;
+    if (folded && !emit_folded(f, live, T, fold_lds, d, out0, p.tmp_ids + begin, &total)) return false;
+  }
+  if (!folded) {
+    int32_t* dst = p.tmp_ids + begin + out0;
+    for (mask_t m = live; m; m &= m - 1) *dst++ = (int32_t)(T[ctz_bits<mask_t>(m) * W + tid] & kTokIdMask);
+  }
   if (tid == W - 1) p.counts[s] = (int32_t)total;
   block_sync<NW>();                                    // the LDS exchange arrays are reused by the next string
+  return true;
 }
 
 // LDS of a workgroup of the wave-per-item variants, in 32-bit words: the per-position arrays, then what its waves exchange.
@@ -510,6 +637,10 @@ __device__ inline void warm_table(const EncodeParams& p, uint32_t* scratch) {
   if (sink == 0x9E3779B9u && p.prefetch_lines == 0xFFFFFFFFu) *scratch = sink;   // keeps the loads alive
 }
 
+__device__ inline void item_of(const EncodeParams& p, int s, int64_t& begin, int& n) {
+  begin = p.piece_begin ? p.piece_begin[s] : p.offsets[s];
+  n = (int)uniform((uint32_t)(p.piece_len ? p.piece_len[s] : (int32_t)(p.offsets[s + 1] - begin)));
+}
 // A persistent workgroup's share of a tier: its first item is its own index, later ones come from the tier's atomic counter
 // (which starts at zero and is offset by the grid size) until the tier's list is exhausted.  When the grid covers the whole
 // list no atomic is needed.  SEGMENTED selects encode_string_segmented() (LDS variants with at most 16 positions per
@@ -523,12 +654,22 @@ __device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uin
   uint32_t* const T = arrays;
   uint32_t* const V = T + W * D;
   uint32_t* const L = LIMITS ? V + W * D : V;
-  const int32_t* const list = OWN ? nullptr : p.list + p.tier_base[tier];
+  const int32_t* const list = OWN ? nullptr : p.slot_kind + p.tier_base[tier];
   uint32_t item = OWN ? 0u : blockIdx.x;
   while (item < count) {
     const int s = (int)uniform(OWN ? (uint32_t)own[item] : (uint32_t)list[item]);
-    if constexpr (SEGMENTED) encode_string_segmented<NW, D, LIMITS, SPECIAL>(p, s, T, V, L, sh);
-    else encode_string<NW, D, STAGED, LIMITS, SPECIAL>(p, s, T, V, L, sh);
+    if (OWN && p.fallback_list[s] != 0) {              // uniform: done folded
+      ++item;
+      continue;
+    }
+    if constexpr (SEGMENTED) {
+      int64_t begin;
+      int n;
+      item_of(p, s, begin, n);
+      encode_string_segmented<NW, D, LIMITS, SPECIAL, false>(p, s, begin, n, T, V, L, sh, Fold{}, nullptr);
+    } else {
+      encode_string<NW, D, STAGED, LIMITS, SPECIAL>(p, s, T, V, L, sh);
+    }
     if constexpr (OWN) {
       ++item;
       continue;
@@ -547,32 +688,47 @@ __device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uin
     item = gridDim.x + uniform(claimed);               // lane 0's value, as a scalar
   }
 }
-// The same for the strings and pieces that the lane-per-segment kernel has passed on: each wave takes items of its own.
-template <bool SPECIAL, bool OWN>
-__device__ __forceinline__ void encode_passed(const EncodeParams& p, uint32_t count, int n_waves, const uint16_t* own,
-                                              uint32_t* arrays, const BlockShared<1>& sh) {
-  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint32_t grid = OWN ? (uint32_t)n_waves : gridDim.x * (uint32_t)n_waves;
-  uint32_t item = OWN ? wave : wave * gridDim.x + blockIdx.x;            // (few items are spread over the workgroups)
-  while (item < count) {
-    const int s = (int)uniform(OWN ? (uint32_t)own[item] : (uint32_t)p.fallback_list[item]);
-    encode_string_segmented<1, 16, true, SPECIAL>(p, s, arrays, arrays + 1024, arrays + 2048, sh);
-    if constexpr (OWN) {
-      item += grid;
-      continue;
-    }
-    if (grid >= count) break;                          // uniform
-    // (all lanes take part, as above)
-    item = grid + uniform(atomicAdd(p.fallback_queue, (threadIdx.x & 63) == 0 ? 1u : 0u));
+// An item on one wave: folded, if it has stretches enough, else, up to 1 KiB, as it is.  False: neither.
+template <bool SPECIAL>
+__device__ __forceinline__ bool encode_item_wave(const EncodeParams& p, int s, uint32_t* arrays, const BlockShared<1>& sh,
+                                                 uint32_t* fold_lds) {
+  int64_t begin;
+  int n;
+  item_of(p, s, begin, n);
+  Fold f{};
+  if (n >= kFoldLeast) {                               // uniform
+    const int64_t room = p.total_bytes - begin;
+    auto load = [&](int at) { return load_16_bytes(p.bytes + begin, at, begin, room); };
+    auto marked = [&](int at) {
+      uint32_t mask = 0;
+      if constexpr (SPECIAL) {
+        const uint4 m = load_16_bytes(p.cover + begin, at, begin, room);
+        const uint32_t w[4] = {m.x, m.y, m.z, m.w};
+        if (m.x | m.y | m.z | m.w) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) mask |= ((w[j >> 2] >> (8 * (j & 3))) & 0xFFu ? 1u : 0u) << j;
+        }
+      }
+      return mask;
+    };
+    if (!fold_text(n, kFoldBytes, arrays, load, marked, f)) f.stretches = 0;
+  }
+  for (;;) {                                           // uniform; twice at most
+    if (f.stretches == 0 && n > 1024) return false;
+    if (encode_string_segmented<1, 16, true, SPECIAL, true>(p, s, begin, f.stretches ? f.bytes : n, arrays, arrays + 1024,
+                                                            arrays + 2048, sh, f, fold_lds))
+      return true;
+    f.stretches = 0;
+    wave_order();
   }
 }
 
-// The items of a small split batch that are of one kind and this workgroup's: every gridDim.x-th one.  Returns how many
+// The items of a small split batch that are of the kinds from `first` to `last` and this workgroup's: every gridDim.x-th one.  Returns how many
 // there are; own: room for kOwnItems of them (a grid has a workgroup for each slot, or one at least for every sixteen).
 // What bounds it is reading the kinds of all slots, 16 KiB at most, in every workgroup: some 1.5 us, less than a launch.
 constexpr int kOwnItems = 17;
 template <int THREADS>
-__device__ inline uint32_t own_items(const EncodeParams& p, int kind, uint16_t* own, uint32_t* wave_sum) {
+__device__ inline uint32_t own_items(const EncodeParams& p, int first, int last, uint16_t* own, uint32_t* wave_sum) {
   constexpr int kPer = 4096 / THREADS;
   const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
   const uint32_t n = p.direct_count;
@@ -582,7 +738,8 @@ __device__ inline uint32_t own_items(const EncodeParams& p, int kind, uint16_t* 
     const uint32_t g = (uint32_t)(kPer * t + i);
     if (g < n) {
       const int4 k = *(const int4*)(p.slot_kind + g);
-      mine |= (uint32_t)((k.x == kind) | (k.y == kind) << 1 | (k.z == kind) << 2 | (k.w == kind) << 3) << i;
+      auto is = [&](int kind) { return kind >= first && kind <= last ? 1u : 0u; };
+      mine |= (is(k.x) | is(k.y) << 1 | is(k.z) << 2 | is(k.w) << 3) << i;
     }
   }
   if ((uint32_t)(kPer * t) < n && n - (uint32_t)(kPer * t) < (uint32_t)kPer) mine &= (1u << (n - (uint32_t)(kPer * t))) - 1u;
@@ -603,42 +760,101 @@ __device__ inline uint32_t own_items(const EncodeParams& p, int kind, uint16_t* 
   return all > blockIdx.x ? min((all - 1u - blockIdx.x) / gridDim.x + 1u, (uint32_t)kOwnItems) : 0u;
 }
 
-// What four waves or one encode: tier 1, up to 4 KiB, if it is there, then the items passed on, up to 1 KiB.  One launch for
-// both: mostly there is nothing to do, and a launch costs some 2 us (one document of 60,001 bytes: 46 us with a launch for
-// each of four variants, 43 with two); where there is, the long items come first and the waves that find no more of them go
-// on to the short ones, each by itself (2,048 x 16 KiB of runs and motifs: 936 us with the short ones
-// first, whose end then waited for the last long item; 896 this way round).
+// What single waves encode, and four together.  Each wave takes items on its own: first those of the tiers, the longest tier
+// first, of which it can do those that fold (fold.h) to 1 KiB or less, then the ones passed on, up to 1 KiB.  A wave that finds
+// an item of tier 1, up to 4 KiB, that does not fold stops there, and once all four have stopped the workgroup encodes
+// what they found; items of the longer tiers that do not fold are left to the next kernel.  One launch for all: mostly
+// there is nothing to do, and a launch costs some 2 us.
+// What bounds it is latency: some 25 dependent round trips an item, of twelve waves a CU (with eight, runs and motifs took 90 us
+// more).  2,048 x 16 KiB of runs and motifs: 176 us and 5 in the next kernel, 417 and 303 when every position of an item had an
+// element; 256 x 64 KiB of one byte: 43 instead of 225 in the next kernel.  Items are dealt to the workgroups by number: when
+// each wave claimed its items from one address (15,700 claims), the kernel took 578 us instead of 336, since a CU's loads
+// return in order and so waited for them too.  Text that does not fold costs the attempt: 500 strings of 16,000 bytes
+// without a cut 252 us instead of 239, 256 of 64 KiB 813 instead of 802; runs under a table whose tokens are longer than what
+// stays of a stretch are encoded for nothing first, 725 us instead of 653.
+constexpr int kMaxTierLists = 3;
 constexpr int kShortArrayWords = encode_array_words<4, 16, false, true>();
-constexpr int kShortWords = kShortArrayWords + 4 * encode_exchange_words<1>() + encode_exchange_words<4>() + 256;
+constexpr int kShortWords = kShortArrayWords + 4 * (encode_exchange_words<1>() + kFoldWords) + encode_exchange_words<4>() + 256;
 // SLOTS: for a small split batch, whose items are found by their kind.
 template <bool SPECIAL, bool SLOTS>
-__global__ __launch_bounds__(256) void encode_short_kernel(EncodeParams p) {
+__global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
   static_assert(4 * encode_array_words<1, 16, false, true>() <= kShortArrayWords, "four one-wave items in the space of one");
   extern __shared__ __align__(16) uint32_t smem[];
-  __shared__ uint16_t own[2][kOwnItems];
-  uint32_t passed, count;                              // in all; of a small split batch, this workgroup's
+  __shared__ uint16_t own[kOwnItems];
+  __shared__ int32_t whole[4];                         // what each wave leaves to the workgroup, -1: nothing
+  __shared__ uint32_t claims;                          // the workgroup's items that are taken
+  uint32_t count;                                      // items, in all; of a small split batch, this workgroup's
+  uint32_t tier[kMaxTierLists] = {0, 0, 0};            // (a list) items of tier 3, of 3 and 2, of 3 to 1
   if constexpr (SLOTS) {
-    passed = own_items<256>(p, kSlotPassed, own[0], smem);
-    count = own_items<256>(p, kSlotTier1, own[1], smem);
-    if (!passed && !count) return;
+    count = own_items<256>(p, kSlotPassed, kSlotTier3, own, smem);
+    if (!count) return;
   } else {
-    passed = *p.fallback_count;
-    count = p.n_tiers > 1 ? p.tier_base[2] - p.tier_base[1] : 0u;
-    if (blockIdx.x >= passed && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
+    if (p.n_tiers > 1) {
+      for (int t = 0; t < kMaxTierLists; ++t) tier[t] = p.tier_base[4] - p.tier_base[3 - t];
+    }
+    count = tier[2] + *p.fallback_count;
+    if (blockIdx.x >= count) return;                   // uniform: nothing for this workgroup
   }
   uint32_t* const byte_word = smem + kShortWords - 256;
   byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
-  if (p.prefetch_lines > 0 && !SLOTS && blockIdx.x < count) warm_table(p, byte_word);
+  if (threadIdx.x == 0) claims = 4 * 64;
+  if (p.prefetch_lines > 0 && !SLOTS && blockIdx.x < tier[2]) warm_table(p, byte_word);
   __syncthreads();
-  const int wave = (int)threadIdx.x >> 6;
+  const int lane = (int)threadIdx.x & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint32_t* const exchange = smem + kShortArrayWords;
-  if (SLOTS ? count > 0 : blockIdx.x < count) {        // uniform
-    encode_tier<4, 16, false, true, true, SPECIAL, SLOTS>(p, 1, count, own[1], smem,
-                                                          block_shared<4>(exchange + 4 * encode_exchange_words<1>(), byte_word));
-    __syncthreads();                                   // the arrays are used again
+  uint32_t* const fold_lds = exchange + 4 * encode_exchange_words<1>() + encode_exchange_words<4>();
+  uint32_t* const arrays = smem + wave * encode_array_words<1, 16, false, true>();
+  const BlockShared<1> alone = block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word);
+  const BlockShared<4> together = block_shared<4>(exchange + 4 * encode_exchange_words<1>(), byte_word);
+  // Of a list, every gridDim.x-th item is the workgroup's (few are spread over all workgroups, and of a long list, sorted by
+  // length, all get the same); which of its waves takes one is settled in LDS.
+  uint32_t item = SLOTS ? wave : wave * gridDim.x + blockIdx.x;
+  for (;;) {                                           // uniform in the workgroup
+    int stopped_at = -1;
+    while (item < count && stopped_at < 0) {           // uniform in the wave
+      int s, its_tier = 0;
+      if constexpr (SLOTS) {
+        s = (int)uniform((uint32_t)own[item]);
+        its_tier = (int)uniform((uint32_t)p.slot_kind[s]) - (kSlotDone + 1);
+      } else if (item >= tier[2]) {
+        s = (int)uniform((uint32_t)p.fallback_list[item - tier[2]]);
+      } else {
+        its_tier = (int)uniform(item < tier[0] ? 3u : item < tier[1] ? 2u : 1u);
+        s = (int)uniform((uint32_t)p.list[p.tier_base[its_tier] + item - (its_tier == 3 ? 0u : tier[2 - its_tier])]);
+      }
+      // (uniform, which the compiler is told: an address that it took for the lanes' own got 64 additions)
+      const bool done = uniform(encode_item_wave<SPECIAL>(p, s, arrays, alone, fold_lds + wave * kFoldWords) ? 1u : 0u) != 0;
+      its_tier = (int)uniform((uint32_t)its_tier);
+      if (its_tier == 1 && !done) stopped_at = s;
+      if (its_tier > 1) {                              // uniform
+        if constexpr (SLOTS) {
+          if (lane == 0) p.fallback_list[s] = done ? 1 : 0;              // (which such a batch has no other use for)
+        } else if (!done) {
+          const uint32_t at = wave_add(p.queue_head + kTierCounts + its_tier, 1u);
+          p.slot_kind[p.tier_base[its_tier] + at] = s;
+        }
+      }
+      const uint32_t claimed = wave_add(&claims, 1u);
+      item = SLOTS ? claimed : claimed * gridDim.x + blockIdx.x;
+    }
+    if (p.n_tiers <= 1) break;                         // uniform: no item is left to the workgroup
+    if (lane == 0) whole[wave] = stopped_at;
+    __syncthreads();
+    bool any = false;
+    for (int w = 0; w < 4; ++w) {
+      const int s = (int)uniform((uint32_t)whole[w]);
+      if (s >= 0) {                                    // uniform
+        any = true;
+        int64_t begin;
+        int n;
+        item_of(p, s, begin, n);
+        encode_string_segmented<4, 16, true, SPECIAL, false>(p, s, begin, n, smem, smem + 4096, smem + 8192, together, Fold{}, nullptr);
+      }
+    }
+    __syncthreads();                                   // (the arrays, and what the waves left, are used again)
+    if (!any) break;                                   // all four have run out of items
   }
-  encode_passed<SPECIAL, SLOTS>(p, passed, 4, own[0], smem + wave * encode_array_words<1, 16, false, true>(),
-                                block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word));
 }
 
 // What sixteen waves encode: tier 2, up to 16 KiB, in LDS (two arrays: three of 16 Ki words would not fit), and tier 3, up to
@@ -652,12 +868,12 @@ __global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
   __shared__ uint16_t own[2][kOwnItems];
   uint32_t longest, count;                             // in all; of a small split batch, this workgroup's
   if constexpr (SLOTS) {
-    longest = own_items<1024>(p, kSlotTier3, own[0], smem);
-    count = own_items<1024>(p, kSlotTier2, own[1], smem);
+    longest = own_items<1024>(p, kSlotTier3, kSlotTier3, own[0], smem);
+    count = own_items<1024>(p, kSlotTier2, kSlotTier2, own[1], smem);
     if (!longest && !count) return;
   } else {
-    longest = p.n_tiers > 3 ? p.tier_base[4] - p.tier_base[3] : 0u;
-    count = p.tier_base[3] - p.tier_base[2];
+    longest = p.queue_head[kTierCounts + 3] >> 6;
+    count = p.queue_head[kTierCounts + 2] >> 6;
     if (blockIdx.x >= longest && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
   }
   uint32_t* const byte_word = smem + kLongWords - 256;

@@ -60,7 +60,7 @@ struct EncodeParams {
   const int32_t* piece_len;   //                         and its length
   const int32_t* list;        // work items that are pieces, of all tiers, tier-major, longest first inside a tier
   const uint32_t* tier_base;  // [tiers+1] start of each tier's slice of `list`
-  uint32_t* queue_head;       // [tiers] next unclaimed item of each tier; kTierCounts words further on
+  uint32_t* queue_head;       // [tiers] next unclaimed item of each tier, 64 for each in tier 0; kTierCounts words further on
                               //   [tiers] the longer tiers' items that do not fold, 64 for each
   int32_t* tmp_ids;           // ids of an item are written at tmp_ids[first byte of the item ...]
   int32_t* counts;            // token count of each item

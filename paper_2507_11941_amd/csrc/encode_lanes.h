@@ -949,9 +949,8 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   for (;;) {
     encode_chunk(first_item, here, cur);
     if (own_items >= count) break;                     // uniform: the grid's own chunks cover the list
-    // (lane 0 adds 1; every lane takes part, so that no lane-dependent branch sits at the loop's edge)
-    const uint32_t claimed = atomicAdd(p.queue_head, lane == 0 ? 1u : 0u);
-    first_item = own_items + (uint64_t)uniform(claimed) * per_claim;
+    // (every lane takes part, so that no lane-dependent branch sits at the loop's edge)
+    first_item = own_items + (uint64_t)wave_add(p.queue_head, 1u) * per_claim;
     if (first_item >= count) break;                    // uniform
     here = (uint32_t)min((uint64_t)per_claim, count - first_item);
     load_chunk(first_item, here, cur);

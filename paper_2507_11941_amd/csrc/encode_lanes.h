@@ -250,13 +250,17 @@ __device__ __forceinline__ uint64_t encode_item_lanes(const EncodeParams& p, int
           uint32_t marked = 0, inside = 0;             // (inside: no token)
           if (__ballot((m.x | m.y | m.z | m.w) != 0)) {
             any_marked = true;
+            // (a mark's top bit, or the one below it, says which kind it is, four marks at a time: one by one the kernel took 340
+            // us on 54 MB of separated documents instead of 329)
+            static_assert(kCoverFirst == 0x80u && kCoverRest == 0x40u && kCoverIndex == 0x3Fu, "bits of a mark");
             const uint32_t mw[4] = {m.x, m.y, m.z, m.w};
+            uint32_t firsts = 0;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-              const uint32_t mark = (mw[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-              marked |= (mark ? 1u : 0u) << j;
-              inside |= (mark == kCoverRest ? 1u : 0u) << j;
+            for (int j = 3; j >= 0; --j) {
+              firsts = firsts << 4 | __builtin_amdgcn_udot4((mw[j] >> 7) & 0x01010101u, 0x08040201u, 0u, false);
+              inside = inside << 4 | __builtin_amdgcn_udot4((mw[j] >> 6) & 0x01010101u, 0x08040201u, 0u, false);
             }
+            marked = firsts | inside;
             if (at < n && n - at < 16) marked &= (1u << (n - at)) - 1u;      // (the next string's, or none)
           }
           ((uint16_t*)tokens)[64 * pass + lane] = (uint16_t)~inside;

@@ -353,7 +353,7 @@ __global__ __launch_bounds__(1024) void piece_scatter_kernel(TierPlan plan, uint
 // A batch of at most kSmallSlots slots, which are all resident at once, is not listed: each wave of the encode kernel takes a
 // slot and finds its piece itself (slot_piece).  It leaves what is to be done with the piece, for the kernels that come after.
 constexpr int kSmallSlots = 4096;
-enum { kSlotDone, kSlotPassed, kSlotTier1, kSlotTier2, kSlotTier3 };   // (tier t is kSlotDone + 1 + t)
+enum { kSlotDone, kSlotLeft };
 // Token offsets of the slots: per-tile sums, then the scan inside each tile.
 constexpr int kScanTile = 4096;
 

@@ -61,27 +61,33 @@ struct Variant {
 
 // Items of tier t have up to kTierBytes[t] bytes: one wave, four, sixteen in LDS, sixteen with their arrays in HBM.
 constexpr int kTierBytes[kMaxTiers] = {kMemberBytes, 4096, 16384, 65536};
-template <bool SPC, bool SLT>
+template <bool SPC>
 void launch_short(const EncodeParams& p, int grid, hipStream_t stream) {
-  encode_short_kernel<SPC, SLT><<<dim3(grid), dim3(256), lds_blocks(4 * kShortWords), stream>>>(p);
+  encode_short_kernel<SPC><<<dim3(grid), dim3(256), lds_blocks(4 * kShortWords), stream>>>(p);
 }
-template <bool SPC, bool SLT>
+template <bool SPC>
 void launch_long(const EncodeParams& p, int grid, hipStream_t stream) {
-  encode_long_kernel<SPC, SLT><<<dim3(grid), dim3(1024), lds_blocks(4 * kLongWords), stream>>>(p);
+  encode_long_kernel<SPC><<<dim3(grid), dim3(1024), lds_blocks(4 * kLongWords), stream>>>(p);
 }
-template <bool SPC, bool SLT>
+template <bool SPC>
+void launch_rest(const EncodeParams& p, int grid, hipStream_t stream) {
+  encode_rest_kernel<SPC><<<dim3(grid), dim3(1024), lds_blocks(4 * kRestWords), stream>>>(p);
+}
+template <bool SPC>
 Variant make_short_variant() {
-  return {4, lds_blocks(4 * kShortWords), (const void*)&encode_short_kernel<SPC, SLT>, &launch_short<SPC, SLT>};
+  return {4, lds_blocks(4 * kShortWords), (const void*)&encode_short_kernel<SPC>, &launch_short<SPC>};
 }
-template <bool SPC, bool SLT>
+template <bool SPC>
 Variant make_long_variant() {
-  return {16, lds_blocks(4 * kLongWords), (const void*)&encode_long_kernel<SPC, SLT>, &launch_long<SPC, SLT>};
+  return {16, lds_blocks(4 * kLongWords), (const void*)&encode_long_kernel<SPC>, &launch_long<SPC>};
 }
-// [family][the batch is split, and small enough not to be listed]
-Variant g_short_variants[2][2] = {{make_short_variant<false, false>(), make_short_variant<false, true>()},
-                                  {make_short_variant<true, false>(), make_short_variant<true, true>()}};
-Variant g_long_variants[2][2] = {{make_long_variant<false, false>(), make_long_variant<false, true>()},
-                                 {make_long_variant<true, false>(), make_long_variant<true, true>()}};
+template <bool SPC>
+Variant make_rest_variant() {
+  return {16, lds_blocks(4 * kRestWords), (const void*)&encode_rest_kernel<SPC>, &launch_rest<SPC>};
+}
+Variant g_short_variants[2] = {make_short_variant<false>(), make_short_variant<true>()};       // [family]
+Variant g_long_variants[2] = {make_long_variant<false>(), make_long_variant<true>()};
+Variant g_rest_variants[2] = {make_rest_variant<false>(), make_rest_variant<true>()};          // split batches that are not listed
 
 // Items of tier 0 go to the lane-per-segment kernel; it passes those strings and pieces on that have a segment of more than
 // 32 bytes.  [family][shape]: with kDirect item i is string i, and the kernel encodes those itself (the launch without a
@@ -115,8 +121,9 @@ void init_variants() {
   }
   g_num_cus = prop.multiProcessorCount;
   std::vector<Variant*> all;
-  for (auto& family : g_short_variants) for (auto& v : family) all.push_back(&v);
-  for (auto& family : g_long_variants) for (auto& v : family) all.push_back(&v);
+  for (auto& v : g_short_variants) all.push_back(&v);
+  for (auto& v : g_long_variants) all.push_back(&v);
+  for (auto& v : g_rest_variants) all.push_back(&v);
   for (auto& family : g_lanes_variants) for (auto& v : family) all.push_back(&v);
   for (Variant* vp : all) {
     Variant& v = *vp;
@@ -674,13 +681,17 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   }
   const Variant& lv = direct ? lanes[kDirect] : small_split ? lanes[kSlots] : listed;
   lv.launch(p, std::min(lv.max_grid, n_items_max), stream);
-  if (!direct) {
-    const Variant& rest = g_short_variants[cover ? 1 : 0][small_split ? 1 : 0];
+  const int family = cover ? 1 : 0;
+  if (small_split) {
+    const Variant& rest = g_rest_variants[family];
+    rest.launch(p, std::min(std::min(rest.max_grid, kMaxLongGrid), n_items_max), stream);
+  } else if (!direct) {
+    const Variant& rest = g_short_variants[family];
     rest.launch(p, std::min(rest.max_grid, n_items_max), stream);
-  }
-  if (plan.n_tiers > 2) {
-    const Variant& longest = g_long_variants[cover ? 1 : 0][small_split ? 1 : 0];
-    longest.launch(p, std::min(std::min(longest.max_grid, kMaxLongGrid), n_items_max), stream);
+    if (plan.n_tiers > 2) {
+      const Variant& longest = g_long_variants[family];
+      longest.launch(p, std::min(std::min(longest.max_grid, kMaxLongGrid), n_items_max), stream);
+    }
   }
   if (prof_slot >= 0 && hipEventRecord(g_prof.end[prof_slot], stream) != hipSuccess) return BPE_EHIP;
   if (alone) {

@@ -390,7 +390,7 @@ template <class M> __device__ inline M bits_below(int k) { return ((M)1 << k) - 
 template <class M> __device__ inline M bits_above(int k) { return ~((((M)2) << k) - 1); }        // k < width
 
 template <int NW, int D, bool STAGED, bool LIMITS, bool SPECIAL>
-__device__ void encode_string(const EncodeParams& p, int s, uint32_t* __restrict__ T, uint32_t* __restrict__ V,
+__device__ __forceinline__ void encode_string(const EncodeParams& p, int s, uint32_t* __restrict__ T, uint32_t* __restrict__ V,
                               uint32_t* __restrict__ L, const BlockShared<NW>& sh) {
   static_assert(D % kGroup == 0 && D <= 64, "groups must tile the column; positions are a 64-bit mask at most");
   using mask_t = typename std::conditional<(D <= 32), uint32_t, uint64_t>::type;

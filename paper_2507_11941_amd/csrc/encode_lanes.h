@@ -900,9 +900,9 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
     if (piece.len < 0 || tier >= p.n_tiers) {          // void, or longer than the host said: nobody encodes it
       if (lane == 0) p.counts[b] = 0;
     } else if (tier > 0) {
-      kind = kSlotDone + 1 + tier;
+      kind = kSlotLeft;
     } else if (encode_item_lanes<L, SPECIAL, false, false>(p, (int)b, piece.begin, piece.len, 1, arrays, smem)) {
-      kind = kSlotPassed;
+      kind = kSlotLeft;
     }
     if (lane == 0) p.slot_kind[b] = kind;
     return;

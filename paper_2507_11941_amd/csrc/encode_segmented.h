@@ -172,7 +172,7 @@ __device__ __forceinline__ bool emit_folded(const Fold& f, uint32_t live, const 
 // what of them is left out, if anything is, and n what stays; returns false, and has written nothing, if that can't be put back
 // in.  Otherwise true.
 template <int NW, int D, bool LIMITS, bool SPECIAL, bool FOLD>
-__device__ bool encode_string_segmented(const EncodeParams& p, int s, int64_t begin, int n, uint32_t* __restrict__ T,
+__device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, int s, int64_t begin, int n, uint32_t* __restrict__ T,
                                         uint32_t* __restrict__ V, uint32_t* __restrict__ L,
                                         const BlockShared<NW>& sh, const Fold& f, uint32_t* fold_lds) {
   static_assert(D % kGroup == 0 && D <= 16, "the per-position registers of the sweep are sized for 16");
@@ -645,23 +645,18 @@ __device__ inline void item_of(const EncodeParams& p, int s, int64_t& begin, int
 // (which starts at zero and is offset by the grid size) until the tier's list is exhausted.  When the grid covers the whole
 // list no atomic is needed.  SEGMENTED selects encode_string_segmented() (LDS variants with at most 16 positions per
 // lane); SPECIAL compiles in the reading of the special-token marks (EncodeParams::cover must then be set).
-// OWN: the items are not the tier's list, but those that this workgroup has found for itself.
-template <int NW, int D, bool STAGED, bool LIMITS, bool SEGMENTED, bool SPECIAL, bool OWN>
-__device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uint32_t count, const uint16_t* own,
-                                            uint32_t* arrays, const BlockShared<NW>& sh) {
+template <int NW, int D, bool STAGED, bool LIMITS, bool SEGMENTED, bool SPECIAL>
+__device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uint32_t count, uint32_t* arrays,
+                                            const BlockShared<NW>& sh) {
   static_assert(!(SEGMENTED && STAGED), "the segmented encoder keeps its arrays in LDS");
   constexpr int W = NW * 64;
   uint32_t* const T = arrays;
   uint32_t* const V = T + W * D;
   uint32_t* const L = LIMITS ? V + W * D : V;
-  const int32_t* const list = OWN ? nullptr : p.slot_kind + p.tier_base[tier];
-  uint32_t item = OWN ? 0u : blockIdx.x;
+  const int32_t* const list = p.slot_kind + p.tier_base[tier];
+  uint32_t item = blockIdx.x;
   while (item < count) {
-    const int s = (int)uniform(OWN ? (uint32_t)own[item] : (uint32_t)list[item]);
-    if (OWN && p.fallback_list[s] != 0) {              // uniform: done folded
-      ++item;
-      continue;
-    }
+    const int s = (int)uniform((uint32_t)list[item]);
     if constexpr (SEGMENTED) {
       int64_t begin;
       int n;
@@ -669,10 +664,6 @@ __device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uin
       encode_string_segmented<NW, D, LIMITS, SPECIAL, false>(p, s, begin, n, T, V, L, sh, Fold{}, nullptr);
     } else {
       encode_string<NW, D, STAGED, LIMITS, SPECIAL>(p, s, T, V, L, sh);
-    }
-    if constexpr (OWN) {
-      ++item;
-      continue;
     }
     if (gridDim.x >= count) break;                     // uniform: one item per workgroup at most
     // Claim the next item.  Every lane of the first wave takes part in the atomic (lane 0 adds 1, the
@@ -689,7 +680,7 @@ __device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uin
   }
 }
 // An item on one wave: folded, if it has stretches enough, else, up to 1 KiB, as it is.  False: neither.
-template <bool SPECIAL>
+template <bool LIMITS, bool SPECIAL>
 __device__ __forceinline__ bool encode_item_wave(const EncodeParams& p, int s, uint32_t* arrays, const BlockShared<1>& sh,
                                                  uint32_t* fold_lds) {
   int64_t begin;
@@ -715,49 +706,12 @@ __device__ __forceinline__ bool encode_item_wave(const EncodeParams& p, int s, u
   }
   for (;;) {                                           // uniform; twice at most
     if (f.stretches == 0 && n > 1024) return false;
-    if (encode_string_segmented<1, 16, true, SPECIAL, true>(p, s, begin, f.stretches ? f.bytes : n, arrays, arrays + 1024,
-                                                            arrays + 2048, sh, f, fold_lds))
+    if (encode_string_segmented<1, 16, LIMITS, SPECIAL, true>(p, s, begin, f.stretches ? f.bytes : n, arrays, arrays + 1024,
+                                                              arrays + (LIMITS ? 2048 : 1024), sh, f, fold_lds))
       return true;
     f.stretches = 0;
     wave_order();
   }
-}
-
-// The items of a small split batch that are of the kinds from `first` to `last` and this workgroup's: every gridDim.x-th one.  Returns how many
-// there are; own: room for kOwnItems of them (a grid has a workgroup for each slot, or one at least for every sixteen).
-// What bounds it is reading the kinds of all slots, 16 KiB at most, in every workgroup: some 1.5 us, less than a launch.
-constexpr int kOwnItems = 17;
-template <int THREADS>
-__device__ inline uint32_t own_items(const EncodeParams& p, int first, int last, uint16_t* own, uint32_t* wave_sum) {
-  constexpr int kPer = 4096 / THREADS;
-  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
-  const uint32_t n = p.direct_count;
-  uint32_t mine = 0;                                   // bit i: my slot i is of the kind
-#pragma unroll
-  for (int i = 0; i < kPer; i += 4) {
-    const uint32_t g = (uint32_t)(kPer * t + i);
-    if (g < n) {
-      const int4 k = *(const int4*)(p.slot_kind + g);
-      auto is = [&](int kind) { return kind >= first && kind <= last ? 1u : 0u; };
-      mine |= (is(k.x) | is(k.y) << 1 | is(k.z) << 2 | is(k.w) << 3) << i;
-    }
-  }
-  if ((uint32_t)(kPer * t) < n && n - (uint32_t)(kPer * t) < (uint32_t)kPer) mine &= (1u << (n - (uint32_t)(kPer * t))) - 1u;
-  const uint32_t count = (uint32_t)__builtin_popcount(mine);
-  const uint32_t upto = wave_scan<OpAdd>(count, 0u);
-  __syncthreads();                                     // (wave_sum may still be read)
-  if (lane == 63) wave_sum[wave] = upto;
-  __syncthreads();
-  uint32_t at = upto - count, all = 0;
-  for (int w = 0; w < THREADS / 64; ++w) {
-    if (w < wave) at += wave_sum[w];
-    all += wave_sum[w];
-  }
-  for (uint32_t m = mine; m; m &= m - 1u, ++at)
-    if (at % gridDim.x == blockIdx.x && at / gridDim.x < (uint32_t)kOwnItems)
-      own[at / gridDim.x] = (uint16_t)(kPer * t + __builtin_ctz(m));
-  __syncthreads();
-  return all > blockIdx.x ? min((all - 1u - blockIdx.x) / gridDim.x + 1u, (uint32_t)kOwnItems) : 0u;
 }
 
 // What single waves encode, and four together.  Each wave takes items on its own: first those of the tiers, the longest tier
@@ -775,30 +729,22 @@ __device__ inline uint32_t own_items(const EncodeParams& p, int first, int last,
 constexpr int kMaxTierLists = 3;
 constexpr int kShortArrayWords = encode_array_words<4, 16, false, true>();
 constexpr int kShortWords = kShortArrayWords + 4 * (encode_exchange_words<1>() + kFoldWords) + encode_exchange_words<4>() + 256;
-// SLOTS: for a small split batch, whose items are found by their kind.
-template <bool SPECIAL, bool SLOTS>
+template <bool SPECIAL>
 __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
   static_assert(4 * encode_array_words<1, 16, false, true>() <= kShortArrayWords, "four one-wave items in the space of one");
   extern __shared__ __align__(16) uint32_t smem[];
-  __shared__ uint16_t own[kOwnItems];
   __shared__ int32_t whole[4];                         // what each wave leaves to the workgroup, -1: nothing
   __shared__ uint32_t claims;                          // the workgroup's items that are taken
-  uint32_t count;                                      // items, in all; of a small split batch, this workgroup's
-  uint32_t tier[kMaxTierLists] = {0, 0, 0};            // (a list) items of tier 3, of 3 and 2, of 3 to 1
-  if constexpr (SLOTS) {
-    count = own_items<256>(p, kSlotPassed, kSlotTier3, own, smem);
-    if (!count) return;
-  } else {
-    if (p.n_tiers > 1) {
-      for (int t = 0; t < kMaxTierLists; ++t) tier[t] = p.tier_base[4] - p.tier_base[3 - t];
-    }
-    count = tier[2] + *p.fallback_count;
-    if (blockIdx.x >= count) return;                   // uniform: nothing for this workgroup
+  uint32_t tier[kMaxTierLists] = {0, 0, 0};            // items of tier 3, of 3 and 2, of 3 to 1
+  if (p.n_tiers > 1) {
+    for (int t = 0; t < kMaxTierLists; ++t) tier[t] = p.tier_base[4] - p.tier_base[3 - t];
   }
+  const uint32_t count = tier[2] + *p.fallback_count;
+  if (blockIdx.x >= count) return;                     // uniform: nothing for this workgroup
   uint32_t* const byte_word = smem + kShortWords - 256;
   byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
   if (threadIdx.x == 0) claims = 4 * 64;
-  if (p.prefetch_lines > 0 && !SLOTS && blockIdx.x < tier[2]) warm_table(p, byte_word);
+  if (p.prefetch_lines > 0 && blockIdx.x < tier[2]) warm_table(p, byte_word);
   __syncthreads();
   const int lane = (int)threadIdx.x & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -807,36 +753,28 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
   uint32_t* const arrays = smem + wave * encode_array_words<1, 16, false, true>();
   const BlockShared<1> alone = block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word);
   const BlockShared<4> together = block_shared<4>(exchange + 4 * encode_exchange_words<1>(), byte_word);
-  // Of a list, every gridDim.x-th item is the workgroup's (few are spread over all workgroups, and of a long list, sorted by
+  // Every gridDim.x-th item is the workgroup's (few are spread over all workgroups, and of a long list, sorted by
   // length, all get the same); which of its waves takes one is settled in LDS.
-  uint32_t item = SLOTS ? wave : wave * gridDim.x + blockIdx.x;
+  uint32_t item = wave * gridDim.x + blockIdx.x;
   for (;;) {                                           // uniform in the workgroup
     int stopped_at = -1;
     while (item < count && stopped_at < 0) {           // uniform in the wave
       int s, its_tier = 0;
-      if constexpr (SLOTS) {
-        s = (int)uniform((uint32_t)own[item]);
-        its_tier = (int)uniform((uint32_t)p.slot_kind[s]) - (kSlotDone + 1);
-      } else if (item >= tier[2]) {
+      if (item >= tier[2]) {
         s = (int)uniform((uint32_t)p.fallback_list[item - tier[2]]);
       } else {
         its_tier = (int)uniform(item < tier[0] ? 3u : item < tier[1] ? 2u : 1u);
         s = (int)uniform((uint32_t)p.list[p.tier_base[its_tier] + item - (its_tier == 3 ? 0u : tier[2 - its_tier])]);
       }
       // (uniform, which the compiler is told: an address that it took for the lanes' own got 64 additions)
-      const bool done = uniform(encode_item_wave<SPECIAL>(p, s, arrays, alone, fold_lds + wave * kFoldWords) ? 1u : 0u) != 0;
+      const bool done = uniform(encode_item_wave<true, SPECIAL>(p, s, arrays, alone, fold_lds + wave * kFoldWords) ? 1u : 0u) != 0;
       its_tier = (int)uniform((uint32_t)its_tier);
       if (its_tier == 1 && !done) stopped_at = s;
-      if (its_tier > 1) {                              // uniform
-        if constexpr (SLOTS) {
-          if (lane == 0) p.fallback_list[s] = done ? 1 : 0;              // (which such a batch has no other use for)
-        } else if (!done) {
-          const uint32_t at = wave_add(p.queue_head + kTierCounts + its_tier, 1u);
-          p.slot_kind[p.tier_base[its_tier] + at] = s;
-        }
+      if (its_tier > 1 && !done) {                     // uniform
+        const uint32_t at = wave_add(p.queue_head + kTierCounts + its_tier, 1u);
+        p.slot_kind[p.tier_base[its_tier] + at] = s;
       }
-      const uint32_t claimed = wave_add(&claims, 1u);
-      item = SLOTS ? claimed : claimed * gridDim.x + blockIdx.x;
+      item = wave_add(&claims, 1u) * gridDim.x + blockIdx.x;
     }
     if (p.n_tiers <= 1) break;                         // uniform: no item is left to the workgroup
     if (lane == 0) whole[wave] = stopped_at;
@@ -862,30 +800,116 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
 constexpr int kLongArrayWords = encode_array_words<16, 16, false, false>();
 constexpr int kLongWords = kLongArrayWords + encode_exchange_words<16>() + 256;
 constexpr int kStagedWords = 3 * 16 * 64 * 64;         // of a slab
-template <bool SPECIAL, bool SLOTS>
+template <bool SPECIAL>
 __global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
   extern __shared__ __align__(16) uint32_t smem[];
-  __shared__ uint16_t own[2][kOwnItems];
-  uint32_t longest, count;                             // in all; of a small split batch, this workgroup's
-  if constexpr (SLOTS) {
-    longest = own_items<1024>(p, kSlotTier3, kSlotTier3, own[0], smem);
-    count = own_items<1024>(p, kSlotTier2, kSlotTier2, own[1], smem);
-    if (!longest && !count) return;
-  } else {
-    longest = p.queue_head[kTierCounts + 3] >> 6;
-    count = p.queue_head[kTierCounts + 2] >> 6;
-    if (blockIdx.x >= longest && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
-  }
+  const uint32_t longest = p.queue_head[kTierCounts + 3] >> 6, count = p.queue_head[kTierCounts + 2] >> 6;
+  if (blockIdx.x >= longest && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
   uint32_t* const byte_word = smem + kLongWords - 256;
   if (threadIdx.x < 256) byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
-  if (p.prefetch_lines > 0 && !SLOTS) warm_table(p, byte_word);
+  if (p.prefetch_lines > 0) warm_table(p, byte_word);
   __syncthreads();
   const BlockShared<16> sh = block_shared<16>(smem + kLongArrayWords, byte_word);
-  if (SLOTS ? longest > 0 : blockIdx.x < longest) {    // uniform
-    encode_tier<16, 64, true, true, false, SPECIAL, SLOTS>(p, 3, longest, own[0], p.staged + (size_t)blockIdx.x * kStagedWords, sh);
+  if (blockIdx.x < longest) {                          // uniform
+    encode_tier<16, 64, true, true, false, SPECIAL>(p, 3, longest, p.staged + (size_t)blockIdx.x * kStagedWords, sh);
     __syncthreads();
   }
-  encode_tier<16, 16, false, false, true, SPECIAL, SLOTS>(p, 2, count, own[1], smem, sh);
+  encode_tier<16, 16, false, false, true, SPECIAL>(p, 2, count, smem, sh);
+}
+
+// The items of a small split batch that something is left to do for and that are this workgroup's: every gridDim.x-th one.  Returns how many
+// there are; own: room for kOwnItems of them (a grid has a workgroup for each slot, or one at least for every sixteen).
+// What bounds it is reading the kinds of all slots, 16 KiB at most, in every workgroup: some 1.5 us, less than a launch.
+constexpr int kOwnItems = 17;
+template <int THREADS>
+__device__ inline uint32_t own_items(const EncodeParams& p, uint16_t* own, uint32_t* wave_sum) {
+  constexpr int kPer = 4096 / THREADS;
+  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint32_t n = p.direct_count;
+  uint32_t mine = 0;                                   // bit i: my slot i is of the kind
+#pragma unroll
+  for (int i = 0; i < kPer; i += 4) {
+    const uint32_t g = (uint32_t)(kPer * t + i);
+    if (g < n) {
+      const int4 k = *(const int4*)(p.slot_kind + g);
+      mine |= (uint32_t)((k.x != kSlotDone) | (k.y != kSlotDone) << 1 | (k.z != kSlotDone) << 2 | (k.w != kSlotDone) << 3) << i;
+    }
+  }
+  if ((uint32_t)(kPer * t) < n && n - (uint32_t)(kPer * t) < (uint32_t)kPer) mine &= (1u << (n - (uint32_t)(kPer * t))) - 1u;
+  const uint32_t count = (uint32_t)__builtin_popcount(mine);
+  const uint32_t upto = wave_scan<OpAdd>(count, 0u);
+  __syncthreads();                                     // (wave_sum may still be read)
+  if (lane == 63) wave_sum[wave] = upto;
+  __syncthreads();
+  uint32_t at = upto - count, all = 0;
+  for (int w = 0; w < THREADS / 64; ++w) {
+    if (w < wave) at += wave_sum[w];
+    all += wave_sum[w];
+  }
+  for (uint32_t m = mine; m; m &= m - 1u, ++at)
+    if (at % gridDim.x == blockIdx.x && at / gridDim.x < (uint32_t)kOwnItems)
+      own[at / gridDim.x] = (uint16_t)(kPer * t + __builtin_ctz(m));
+  __syncthreads();
+  return all > blockIdx.x ? min((all - 1u - blockIdx.x) / gridDim.x + 1u, (uint32_t)kOwnItems) : 0u;
+}
+
+// What is left of a small split batch, in one launch: mostly nothing, and a launch that looks for items and finds none costs 2 to
+// 4 us (with two such kernels, like those above, one document of 60,001 bytes took 26.7 us instead of 24.3, 1,003
+// conversations 51.9 instead of 48.3).  Sixteen waves: each takes items on its own, and what a wave cannot do all of
+// them then encode.  (The limits are not kept in LDS: there is room for sixteen such items only without.)  Text in which
+// nothing repeats and nothing can be cut pays for that: 40 strings of 4,000 such bytes 77 us instead of 58.
+constexpr int kRestWave = encode_array_words<1, 16, false, false>();
+constexpr int kRestWords = 16 * (kRestWave + encode_exchange_words<1>() + kFoldWords) + encode_exchange_words<16>() + 256;
+template <bool SPECIAL>
+__global__ __launch_bounds__(1024) void encode_rest_kernel(EncodeParams p) {
+  static_assert(kLongArrayWords <= 16 * kRestWave, "an item of all waves in the space of sixteen");
+  extern __shared__ __align__(16) uint32_t smem[];
+  __shared__ uint16_t own[kOwnItems];
+  __shared__ int32_t whole[16];                        // what each wave leaves to the workgroup, -1: nothing
+  __shared__ uint32_t claims;                          // items that are taken, 64 for each
+  const uint32_t count = own_items<1024>(p, own, smem);
+  if (!count) return;                                  // uniform
+  uint32_t* const byte_word = smem + kRestWords - 256;
+  if (threadIdx.x < 256) byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
+  if (threadIdx.x == 0) claims = 16 * 64;
+  __syncthreads();
+  const int lane = (int)threadIdx.x & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  uint32_t* const exchange = smem + 16 * kRestWave;
+  uint32_t* const fold_lds = exchange + 16 * encode_exchange_words<1>() + encode_exchange_words<16>() + wave * kFoldWords;
+  const BlockShared<1> alone = block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word);
+  const BlockShared<16> together = block_shared<16>(exchange + 16 * encode_exchange_words<1>(), byte_word);
+  uint32_t item = wave;
+  for (;;) {                                           // uniform in the workgroup
+    int stopped_at = -1;
+    while (item < count && stopped_at < 0) {           // uniform in the wave
+      const int s = (int)uniform((uint32_t)own[item]);
+      if (!uniform(encode_item_wave<false, SPECIAL>(p, s, smem + wave * kRestWave, alone, fold_lds) ? 1u : 0u)) stopped_at = s;
+      item = wave_add(&claims, 1u);
+    }
+    if (lane == 0) whole[wave] = stopped_at;
+    __syncthreads();
+    bool any = false;
+    for (int w = 0; w < 16; ++w) {
+      const int s = (int)uniform((uint32_t)whole[w]);
+      if (s >= 0) {                                    // uniform
+        any = true;
+        int64_t begin;
+        int n;
+        item_of(p, s, begin, n);
+        if (n > 16 * 1024) {                           // uniform
+          uint32_t* const slab = p.staged + (size_t)blockIdx.x * kStagedWords;
+          encode_string<16, 64, true, true, SPECIAL>(p, s, slab, slab + 65536, slab + 2 * 65536, together);
+        } else {
+          encode_string_segmented<16, 16, false, SPECIAL, false>(p, s, begin, n, smem, smem + 16384, smem + 16384, together, Fold{},
+                                                                 nullptr);
+        }
+        __syncthreads();
+      }
+    }
+    __syncthreads();                                   // (the arrays, and what the waves left, are used again)
+    if (!any) break;                                   // all have run out of items
+  }
 }
 
 // LDS is handed out in blocks, and the occupancy the runtime reports is for the bytes asked for: for 9,552 bytes it

@@ -59,7 +59,8 @@ struct Variant {
   int max_grid = 0;               // resident workgroups on the whole device (filled on first use)
 };
 
-// Items of tier t have up to kTierBytes[t] bytes: one wave, four, sixteen in LDS, sixteen with their arrays in HBM.
+// Items of tier t have up to kTierBytes[t] bytes.  Those that do not fold (fold.h) are encoded by one wave, four, sixteen in LDS,
+// sixteen with their arrays in HBM.
 constexpr int kTierBytes[kMaxTiers] = {kMemberBytes, 4096, 16384, 65536};
 template <bool SPC>
 void launch_short(const EncodeParams& p, int grid, hipStream_t stream) {

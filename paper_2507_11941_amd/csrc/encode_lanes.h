@@ -30,7 +30,7 @@
 // What bounds it is instruction issue: some 2,100 vector and 550 scalar instructions per KiB of text, of which the merge
 // loop is two fifths, on four waves a SIMD.  With every segment going through the merges, one item of 1 KiB a wave
 // (14.9 trips of the loop per KiB instead of 6.8), the 65,536 documents of the throughput workload took 1,480 us in this
-// kernel; they take 977, and the whole call 1,066 instead of 1,659.
+// kernel; they take 977, and the whole call 1,066 instead of 1,659 (1,053 since claims add alike in all lanes, see wave_add).
 //
 // Of text that is not words most look-ups find nothing and cost what they cost, and its jobs do not fit the arena at once.
 // 32 MiB in strings of 4 KiB, whole call, all segments merged / single bytes listed and looked up like the others, the arena

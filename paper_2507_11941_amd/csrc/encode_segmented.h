@@ -817,8 +817,8 @@ __global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
   encode_tier<16, 16, false, false, true, SPECIAL>(p, 2, count, smem, sh);
 }
 
-// The items of a small split batch that something is left to do for and that are this workgroup's: every gridDim.x-th one.  Returns how many
-// there are; own: room for kOwnItems of them (a grid has a workgroup for each slot, or one at least for every sixteen).
+// The items of a small split batch that something is left to do for and that are this workgroup's: every gridDim.x-th one.
+// Returns how many there are; own: room for kOwnItems of them (a grid has a workgroup for each slot, or one at least for every sixteen).
 // What bounds it is reading the kinds of all slots, 16 KiB at most, in every workgroup: some 1.5 us, less than a launch.
 constexpr int kOwnItems = 17;
 template <int THREADS>

@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "table_format.h"
+#include "wave_claim.h"
 #include "word_table.h"
 
 namespace bpe {
@@ -60,8 +61,8 @@ struct EncodeParams {
   const int32_t* piece_len;   //                         and its length
   const int32_t* list;        // work items that are pieces, of all tiers, tier-major, longest first inside a tier
   const uint32_t* tier_base;  // [tiers+1] start of each tier's slice of `list`
-  uint32_t* queue_head;       // [tiers] next unclaimed item of each tier, 64 for each in tier 0; kTierCounts words further on
-                              //   [tiers] the longer tiers' items that do not fold, 64 for each
+  uint32_t* queue_head;       // [tiers] next unclaimed item of each tier; kTierCounts words further on [tiers] how many of the
+                              //   longer tiers' items do not fold
   int32_t* tmp_ids;           // ids of an item are written at tmp_ids[first byte of the item ...]
   int32_t* counts;            // token count of each item
   int64_t* out_offsets;       // a batch of one short string, whose output the encode kernel writes itself: the offsets, else null;
@@ -103,12 +104,6 @@ __device__ inline uint32_t cover_code(uint32_t byte, uint32_t mark) {
 // wave64 primitives
 
 __device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-
-// Sums that waves add to: a lane that adds alone, by a condition on its number or with zeros from the others, makes the
-// compiler go over all 64 lanes one by one (some 640 scalar instructions, 1.3 us) or, where it cannot tell that the address is
-// the same in all, sends the memory all 64.  Where every lane adds the same it sends one addition, of 64 times that; so
-// these sums count 64 for each.  All lanes take part; returns the sum before, divided by 64.
-__device__ inline uint32_t wave_add(uint32_t* sum, uint32_t each) { return uniform(atomicAdd(sum, each) >> 6); }
 
 template <int CTRL>
 __device__ inline uint32_t dpp(uint32_t v) {

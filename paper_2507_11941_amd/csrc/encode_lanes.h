@@ -30,7 +30,7 @@
 // What bounds it is instruction issue: some 2,100 vector and 550 scalar instructions per KiB of text, of which the merge
 // loop is two fifths, on four waves a SIMD.  With every segment going through the merges, one item of 1 KiB a wave
 // (14.9 trips of the loop per KiB instead of 6.8), the 65,536 documents of the throughput workload took 1,480 us in this
-// kernel; they take 977, and the whole call 1,066 instead of 1,659 (1,053 since claims add alike in all lanes, see wave_add).
+// kernel; they take 977, and the whole call 1,066 instead of 1,659 (1,053 since no claim makes a loop over the lanes, see wave_claim).
 //
 // Of text that is not words most look-ups find nothing and cost what they cost, and its jobs do not fit the arena at once.
 // 32 MiB in strings of 4 KiB, whole call, all segments merged / single bytes listed and looked up like the others, the arena
@@ -953,8 +953,7 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   for (;;) {
     encode_chunk(first_item, here, cur);
     if (own_items >= count) break;                     // uniform: the grid's own chunks cover the list
-    // (every lane takes part, so that no lane-dependent branch sits at the loop's edge)
-    first_item = own_items + (uint64_t)wave_add(p.queue_head, 1u) * per_claim;
+    first_item = own_items + (uint64_t)wave_claim(p.queue_head) * per_claim;
     if (first_item >= count) break;                    // uniform
     here = (uint32_t)min((uint64_t)per_claim, count - first_item);
     load_chunk(first_item, here, cur);

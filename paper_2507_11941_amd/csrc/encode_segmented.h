@@ -666,17 +666,14 @@ __device__ __forceinline__ void encode_tier(const EncodeParams& p, int tier, uin
       encode_string<NW, D, STAGED, LIMITS, SPECIAL>(p, s, T, V, L, sh);
     }
     if (gridDim.x >= count) break;                     // uniform: one item per workgroup at most
-    // Claim the next item.  Every lane of the first wave takes part in the atomic (lane 0 adds 1, the
-    // others 0) so that no lane-dependent branch sits at the loop boundary: a branch on "thread 0" here,
-    // next to a single-lane store that ends the previous string, lets the compiler send the other lanes
-    // round the loop on their own, past the lane-0 broadcast below.
-    uint32_t claimed = 0;
-    if (threadIdx.x < 64) claimed = atomicAdd(p.queue_head + tier, threadIdx.x == 0 ? 1u : 0u);
-    if (threadIdx.x == 0) *sh.item = claimed;
+    // Claim the next item: the first wave does, for all.
+    if (threadIdx.x < 64) {
+      const uint32_t claimed = wave_claim(p.queue_head + tier);
+      *sh.item = claimed;                              // (every lane the same)
+    }
     __syncthreads();
-    claimed = *sh.item;
+    item = gridDim.x + uniform(*sh.item);
     __syncthreads();
-    item = gridDim.x + uniform(claimed);               // lane 0's value, as a scalar
   }
 }
 // An item on one wave: folded, if it has stretches enough, else, up to 1 KiB, as it is.  False: neither.
@@ -743,7 +740,7 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
   if (blockIdx.x >= count) return;                     // uniform: nothing for this workgroup
   uint32_t* const byte_word = smem + kShortWords - 256;
   byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
-  if (threadIdx.x == 0) claims = 4 * 64;
+  if (threadIdx.x == 0) claims = 4;
   if (p.prefetch_lines > 0 && blockIdx.x < tier[2]) warm_table(p, byte_word);
   __syncthreads();
   const int lane = (int)threadIdx.x & 63;
@@ -771,10 +768,10 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
       its_tier = (int)uniform((uint32_t)its_tier);
       if (its_tier == 1 && !done) stopped_at = s;
       if (its_tier > 1 && !done) {                     // uniform
-        const uint32_t at = wave_add(p.queue_head + kTierCounts + its_tier, 1u);
+        const uint32_t at = wave_claim(p.queue_head + kTierCounts + its_tier);
         p.slot_kind[p.tier_base[its_tier] + at] = s;
       }
-      item = wave_add(&claims, 1u) * gridDim.x + blockIdx.x;
+      item = wave_claim(&claims) * gridDim.x + blockIdx.x;
     }
     if (p.n_tiers <= 1) break;                         // uniform: no item is left to the workgroup
     if (lane == 0) whole[wave] = stopped_at;
@@ -803,7 +800,7 @@ constexpr int kStagedWords = 3 * 16 * 64 * 64;         // of a slab
 template <bool SPECIAL>
 __global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
   extern __shared__ __align__(16) uint32_t smem[];
-  const uint32_t longest = p.queue_head[kTierCounts + 3] >> 6, count = p.queue_head[kTierCounts + 2] >> 6;
+  const uint32_t longest = p.queue_head[kTierCounts + 3], count = p.queue_head[kTierCounts + 2];
   if (blockIdx.x >= longest && blockIdx.x >= count) return;   // uniform: nothing for this workgroup
   uint32_t* const byte_word = smem + kLongWords - 256;
   if (threadIdx.x < 256) byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
@@ -866,12 +863,12 @@ __global__ __launch_bounds__(1024) void encode_rest_kernel(EncodeParams p) {
   extern __shared__ __align__(16) uint32_t smem[];
   __shared__ uint16_t own[kOwnItems];
   __shared__ int32_t whole[16];                        // what each wave leaves to the workgroup, -1: nothing
-  __shared__ uint32_t claims;                          // items that are taken, 64 for each
+  __shared__ uint32_t claims;                          // items that are taken
   const uint32_t count = own_items<1024>(p, own, smem);
   if (!count) return;                                  // uniform
   uint32_t* const byte_word = smem + kRestWords - 256;
   if (threadIdx.x < 256) byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
-  if (threadIdx.x == 0) claims = 16 * 64;
+  if (threadIdx.x == 0) claims = 16;
   __syncthreads();
   const int lane = (int)threadIdx.x & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -885,7 +882,7 @@ __global__ __launch_bounds__(1024) void encode_rest_kernel(EncodeParams p) {
     while (item < count && stopped_at < 0) {           // uniform in the wave
       const int s = (int)uniform((uint32_t)own[item]);
       if (!uniform(encode_item_wave<false, SPECIAL>(p, s, smem + wave * kRestWave, alone, fold_lds) ? 1u : 0u)) stopped_at = s;
-      item = wave_add(&claims, 1u);
+      item = wave_claim(&claims);
     }
     if (lane == 0) whole[wave] = stopped_at;
     __syncthreads();

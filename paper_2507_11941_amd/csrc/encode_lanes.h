@@ -952,6 +952,7 @@ __global__ __launch_bounds__(64 * L::kWaves) void encode_lanes_kernel(EncodePara
   };
   for (;;) {
     encode_chunk(first_item, here, cur);
+    if constexpr (INLINE) break;                       // (the grid covers the strings, a wave each)
     if (own_items >= count) break;                     // uniform: the grid's own chunks cover the list
     first_item = own_items + (uint64_t)wave_claim(p.queue_head) * per_claim;
     if (first_item >= count) break;                    // uniform

@@ -1,4 +1,4 @@
-"""Folding (csrc/fold.h), compiled for the CPU with a wave of 64 threads: what is left out repeats what stays, and the encoding
+"""Folding (csrc/fold.h), compiled for the CPU with a wave of 64 lanes: what is left out repeats what stays, and the encoding
 of what stays (by the oracle), with each stretch's block put back in as often as it was left out, is the encoding of the
 whole text -- for text of runs and motifs over random tables, in which tokens join in every way, and over a trained one."""
 import ctypes
@@ -18,7 +18,7 @@ HISTORY, MOST = 24, 1024
 @pytest.fixture(scope="module")
 def lib(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("fold") / "fold.so")
-    subprocess.check_call(["g++", "-O1", "-std=c++20", "-shared", "-fPIC", "-pthread", "-o", out,
+    subprocess.check_call(["g++", "-O1", "-std=c++20", "-shared", "-fPIC", "-o", out,
                            "-I", os.path.join(ROOT, "paper_2507_11941_amd", "csrc"),
                            os.path.join(ROOT, "tests", "fold_driver.cpp")])
     return ctypes.CDLL(out)

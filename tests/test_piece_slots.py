@@ -1,5 +1,5 @@
 """The slots of a split batch and the pieces that begin in them (csrc/piece_slots.h), compiled for the CPU with a wave of 64
-threads and compared with the rules said plainly: string s has the slots from s + offsets[s] // 896 on, one for each 896
+lanes and compared with the rules said plainly: string s has the slots from s + offsets[s] // 896 on, one for each 896
 bytes begun and one at least; a piece begins at its string's first byte and at the last cut within the 128 bytes up to
 every 896th, a slot without one is void, and the piece before it runs on.  Both ways of finding them: listed, and a wave a slot."""
 import ctypes
@@ -18,7 +18,7 @@ UNSET = -(1 << 20)
 @pytest.fixture(scope="module")
 def lib(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("slots") / "slots.so")
-    subprocess.check_call(["g++", "-O1", "-std=c++20", "-shared", "-fPIC", "-pthread", "-o", out,
+    subprocess.check_call(["g++", "-O1", "-std=c++20", "-shared", "-fPIC", "-o", out,
                            "-I", os.path.join(ROOT, "paper_2507_11941_amd", "csrc"),
                            os.path.join(ROOT, "tests", "piece_slots_driver.cpp")])
     return ctypes.CDLL(out)

@@ -1,5 +1,5 @@
 """The division of neighbouring strings into work items (csrc/string_groups.h), compiled for the CPU with a wave of 64
-threads and compared with the rule said plainly: a group takes strings until the next one would end more than `room`
+lanes and compared with the rule said plainly: a group takes strings until the next one would end more than `room`
 bytes after its beginning; one that ends 2^28 bytes or more after the first of its 64 is alone.  Offsets only, so
 strings of any length cost nothing: a string longer than max_len may not take its neighbours' lengths away, wherever in
 64 bits the text after it lies."""
@@ -17,7 +17,7 @@ NOT_ENCODABLE = 0xFFF
 @pytest.fixture(scope="module")
 def lib(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("groups") / "groups.so")
-    subprocess.check_call(["g++", "-O1", "-std=c++20", "-shared", "-fPIC", "-pthread", "-o", out,
+    subprocess.check_call(["g++", "-O1", "-std=c++20", "-shared", "-fPIC", "-o", out,
                            "-I", os.path.join(ROOT, "paper_2507_11941_amd", "csrc"),
                            os.path.join(ROOT, "tests", "string_groups_driver.cpp")])
     return ctypes.CDLL(out)

@@ -1,4 +1,4 @@
-"""Numbers that waves claim from one counter (csrc/wave_claim.h), compiled for the CPU with two waves of 64 threads whose atomic
+"""Numbers that waves claim from one counter (csrc/wave_claim.h), compiled for the CPU with two waves of 64 lanes whose atomic
 operations come one by one, in any order: each number goes to one wave, whose lanes all get it, and none is left out."""
 import ctypes
 import os
@@ -12,7 +12,7 @@ WAVES, TIMES = 2, 300
 
 def test_each_number_once(tmp_path):
     out = str(tmp_path / "claims.so")
-    subprocess.check_call(["g++", "-O1", "-std=c++20", "-shared", "-fPIC", "-pthread", "-o", out,
+    subprocess.check_call(["g++", "-O1", "-std=c++20", "-shared", "-fPIC", "-o", out,
                            "-I", os.path.join(ROOT, "paper_2507_11941_amd", "csrc"),
                            os.path.join(ROOT, "tests", "wave_claim_driver.cpp")])
     taken = np.zeros((WAVES, 64, TIMES), np.uint32)

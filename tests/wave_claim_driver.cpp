@@ -1,19 +1,18 @@
 // csrc/wave_claim.h on the CPU: two waves that claim from one counter.  Built as a shared library by tests/test_wave_claim.py.
-#include <atomic>
-
 #include "wave_on_cpu.h"
 
 // As the memory serves them: one lane's after the other, in any order among the lanes of both waves.
 static uint32_t atomicInc(uint32_t* at, uint32_t last) {
-  std::this_thread::yield();
-  std::atomic_ref<uint32_t> value(*at);
-  uint32_t before = value.load();
-  while (!value.compare_exchange_weak(before, before >= last ? 0u : before + 1u)) {}
+  let_others_run();
+  const uint32_t before = *at;
+  *at = before >= last ? 0u : before + 1u;
   return before;
 }
 [[maybe_unused]] static uint32_t atomicAdd(uint32_t* at, uint32_t each) {
-  std::this_thread::yield();
-  return std::atomic_ref<uint32_t>(*at).fetch_add(each);
+  let_others_run();
+  const uint32_t before = *at;
+  *at += each;
+  return before;
 }
 static int __builtin_amdgcn_readfirstlane(int mine) { return __builtin_amdgcn_readlane(mine, 0); }
 

@@ -350,9 +350,8 @@ __global__ __launch_bounds__(1024) void piece_scatter_kernel(TierPlan plan, uint
   }
 }
 
-// A batch of at most kSmallSlots slots, which are all resident at once, is not listed: each wave of the encode kernel takes a
-// slot and finds its piece itself (slot_piece).  It leaves what is to be done with the piece, for the kernels that come after.
-constexpr int kSmallSlots = 4096;
+// A small batch (small_batch_fits) is not listed: each wave of the encode kernel takes a slot and finds its piece itself
+// (slot_piece).  It leaves what is to be done with the piece, for the kernel that comes after.
 enum { kSlotDone, kSlotLeft };
 // Token offsets of the slots: per-tile sums, then the scan inside each tile.
 constexpr int kScanTile = 4096;

@@ -588,8 +588,8 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   const int room = small_items ? -1
                                : (int)std::min<int64_t>(total_bytes / std::max(1, listed.max_grid * listed.waves / 2) +
                                                             total_bytes / w.max_slots / 2, kGroupBytes);
-  const bool small_split = w.split && w.max_slots <= kSmallSlots &&
-                           w.max_slots <= (int64_t)lanes[kSlots].max_grid * lanes[kSlots].waves;
+  const int rest_grid = std::min(g_rest_variants[cover ? 1 : 0].max_grid, kMaxLongGrid);
+  const bool small_split = w.split && small_batch_fits(w.max_slots, (int64_t)lanes[kSlots].max_grid * lanes[kSlots].waves, rest_grid);
   const uint32_t* cuts = (const uint32_t*)table->d_words;
   ItemDesc* desc = nullptr;                              // the work list, if there is one
   int32_t* list = nullptr;                               // ... and, of pieces, their slots
@@ -684,8 +684,7 @@ static int encode_enqueue(const bpe_table* table, const uint8_t* bytes, const in
   lv.launch(p, std::min(lv.max_grid, n_items_max), stream);
   const int family = cover ? 1 : 0;
   if (small_split) {
-    const Variant& rest = g_rest_variants[family];
-    rest.launch(p, std::min(std::min(rest.max_grid, kMaxLongGrid), n_items_max), stream);
+    g_rest_variants[family].launch(p, std::min(rest_grid, n_items_max), stream);
   } else if (!direct) {
     const Variant& rest = g_short_variants[family];
     rest.launch(p, std::min(rest.max_grid, n_items_max), stream);

@@ -17,6 +17,14 @@ namespace bpe {
 
 constexpr int kCutWindow = 128;
 
+// A batch whose slots are all resident at once, a wave each, needs no list.  `resident`: waves of the kernel that encodes the
+// pieces; rest_grid: workgroups of the one that comes after it, each of which can take kRestItems of what is left, every
+// rest_grid-th item.
+constexpr int kSmallSlots = 4096, kRestItems = 16;
+constexpr bool small_batch_fits(int64_t slots, int64_t resident, int64_t rest_grid) {
+  return slots <= kSmallSlots && slots <= resident && slots <= kRestItems * rest_grid;
+}
+
 __device__ inline uint32_t slots_of_length(int64_t len, int piece_target, int max_string) {
   // (a 32-bit division: a valid length fits, and the 64-bit one is a long software routine)
   return (len <= 0 || len > max_string) ? 1u : ((uint32_t)len + (uint32_t)piece_target - 1u) / (uint32_t)piece_target;

@@ -25,3 +25,5 @@ extern "C" void piece_slots(const uint8_t* bytes, const int64_t* offsets, int ba
     }
   });
 }
+
+extern "C" bool small_batch(int64_t slots, int64_t resident, int64_t rest_grid) { return bpe::small_batch_fits(slots, resident, rest_grid); }

@@ -116,3 +116,15 @@ def test_offsets_that_begin_later(lib, skipped, steps_each):
     got = slots(lib, data, offsets, None, CUT, steps_each)
     for what, g, e in zip(("string", "begin", "length"), got, expected(data, offsets, None, CUT)):
         assert np.array_equal(g, e), (what, np.flatnonzero(g != e)[:5], g[g != e][:5], e[g != e][:5])
+
+
+def test_small_batches_leave_no_item_out(lib):
+    """Batches without a list: every slot has a wave, and no workgroup of the kernel that does the rest, which takes every
+    grid-th of what is left, gets more than the sixteen it has room for -- however few fit the device."""
+    lib.small_batch.argtypes = [ctypes.c_int64] * 3
+    lib.small_batch.restype = ctypes.c_bool
+    for resident in (512, 4096, 8192):
+        for rest_grid in (1, 31, 32, 255, 256, 768):
+            fits = [slots for slots in range(1, 5000) if lib.small_batch(slots, resident, rest_grid)]
+            assert fits == list(range(1, min(resident, 16 * rest_grid, 4096) + 1))
+            assert max(-(-slots // min(rest_grid, slots)) for slots in fits) <= 16

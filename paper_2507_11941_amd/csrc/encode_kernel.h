@@ -105,6 +105,14 @@ __device__ inline uint32_t cover_code(uint32_t byte, uint32_t mark) {
 
 __device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
+// threadIdx.x, as the compiler knows nothing about: what an item's work makes of it is not kept in registers from item to item,
+// where sixteen waves have 128 each and would spill it (rest kernel: 46 without, 16 so).
+__device__ inline uint32_t own_thread() {
+  uint32_t t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 template <int CTRL>
 __device__ inline uint32_t dpp(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
@@ -390,7 +398,7 @@ __device__ __forceinline__ void encode_string(const EncodeParams& p, int s, uint
   static_assert(D % kGroup == 0 && D <= 64, "groups must tile the column; positions are a 64-bit mask at most");
   using mask_t = typename std::conditional<(D <= 32), uint32_t, uint64_t>::type;
   constexpr int W = NW * 64;
-  const int tid = (int)threadIdx.x;
+  const int tid = (int)own_thread();
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const DeviceTable& tab = p.table;

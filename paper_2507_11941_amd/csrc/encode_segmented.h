@@ -61,6 +61,10 @@ struct SegRecord {
   uint32_t pad0, pad1;
 };
 
+// Words of LDS through which the waves of an item tell each other things (BlockShared).
+template <int NW>
+constexpr int encode_exchange_words() { return 20 * NW + 4; }
+
 // LDS that a folded text's emission needs, in words.  Bit p of the first ones: a token starts at p, or the text ends; then, for
 // each stretch, the place behind which its copies go | how many ids they are << 12.  (Three workgroups of four such waves
 // fit a CU with not a block to spare: with the ranks of the words here too it was two, and runs and motifs took 90 us more.)
@@ -170,8 +174,9 @@ __device__ __forceinline__ bool emit_folded(const Fold& f, uint32_t live, const 
 
 // Encodes work item s, a whole string or a piece of one between two cuts: the n bytes from `begin` on (uniform).  FOLD: f says
 // what of them is left out, if anything is, and n what stays; returns false, and has written nothing, if that can't be put back
-// in.  Otherwise true.
-template <int NW, int D, bool LIMITS, bool SPECIAL, bool FOLD>
+// in.  Otherwise true.  TEAMS: as many teams of NW waves in the workgroup do an item each at the same time, or none with n = 0, with
+// sh their own; they meet at the same barriers, so that all go on until the last has no pair left.
+template <int NW, int D, bool LIMITS, bool SPECIAL, bool FOLD, int TEAMS = 1>
 __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, int s, int64_t begin, int n, uint32_t* __restrict__ T,
                                         uint32_t* __restrict__ V, uint32_t* __restrict__ L,
                                         const BlockShared<NW>& sh, const Fold& f, uint32_t* fold_lds) {
@@ -179,13 +184,14 @@ __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, i
   static_assert(!FOLD || (NW == 1 && kFoldBytes <= 64 * D && D + 2 <= (int)kFoldApart), "a wave's work, and room for what stays");
   using mask_t = uint32_t;
   constexpr int W = NW * 64;
-  const int tid = (int)threadIdx.x & (W - 1);          // (one wave: of a workgroup that may have others)
+  // (one wave, or a team: of a workgroup that has others)
+  const int tid = (int)(NW == 16 || TEAMS > 1 ? own_thread() : threadIdx.x) & (W - 1);
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const DeviceTable& tab = p.table;
   SegRecord* const rec_base = (SegRecord*)sh.rec;
 
-  if (n <= 0 || n > W * D) {                           // uniform branch; too long only if max_len was wrong
+  if (TEAMS == 1 && (n <= 0 || n > W * D)) {           // uniform branch; too long only if max_len was wrong
     if (tid == W - 1) p.counts[s] = 0;
     return true;
   }
@@ -289,7 +295,7 @@ __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, i
   // Every pass removes at least one token, so n passes can never be needed; the bound only guarantees
   // that the loop ends whatever the memory contents.
   int buf = 0;                                         // which half of the double-buffered exchange is current
-  for (int pass = 0; pass < n; ++pass) {
+  for (int pass = 0; pass < (TEAMS > 1 ? W * D : n); ++pass) {
     // -- sweep: values and limits of my positions; minima inside my segments --
     // Per-position conditions are taken as 0 / all-ones words with bit-field extracts so that the running
     // minima are three or four vector instructions per position and no lane mask has to stay live.
@@ -386,8 +392,15 @@ __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, i
       __syncthreads();                                 // records of all waves are in place
       const SegRecord* rec = rec_base + buf * NW;
       uint32_t anyp = 0, pre = kInf31, suf = kInf31;
+      if constexpr (TEAMS > 1) {                       // (the teams' exchange areas lie one after the other)
+        const uint32_t its = (uint32_t)lane / NW, before = its * (uint32_t)encode_exchange_words<NW>();
+        const uint32_t* const first = (const uint32_t*)rec_base - (threadIdx.x / W) * encode_exchange_words<NW>();
+        anyp = lane < NW * TEAMS ? ((const SegRecord*)(first + before) + buf * NW + lane % NW)->any_pair : 0u;
+        anyp = __ballot(anyp != 0) != 0 ? 1u : 0u;
+      } else {
 #pragma unroll
-      for (int w = 0; w < NW; ++w) anyp |= rec[w].any_pair;
+        for (int w = 0; w < NW; ++w) anyp |= rec[w].any_pair;
+      }
       for (int w = 0; w < wave; ++w) pre = OpSegMin::apply(pre, rec[w].fwd);          // left to right
       for (int w = NW - 1; w > wave; --w) suf = OpSegMin::apply(suf, rec[w].bwd);      // right to left
       in_fwd = OpSegMin::apply(pre, in_fwd);
@@ -599,7 +612,7 @@ __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, i
     int32_t* dst = p.tmp_ids + begin + out0;
     for (mask_t m = live; m; m &= m - 1) *dst++ = (int32_t)(T[ctz_bits<mask_t>(m) * W + tid] & kTokIdMask);
   }
-  if (tid == W - 1) p.counts[s] = (int32_t)total;
+  if (tid == W - 1 && (TEAMS == 1 || n > 0)) p.counts[s] = (int32_t)total;
   block_sync<NW>();                                    // the LDS exchange arrays are reused by the next string
   return true;
 }
@@ -607,8 +620,6 @@ __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, i
 // LDS of a workgroup of the wave-per-item variants, in 32-bit words: the per-position arrays, then what its waves exchange.
 template <int NW, int D, bool STAGED, bool LIMITS>
 constexpr int encode_array_words() { return STAGED ? 0 : (LIMITS ? 3 : 2) * NW * 64 * D; }
-template <int NW>
-constexpr int encode_exchange_words() { return 20 * NW + 4; }
 template <int NW>
 __device__ inline BlockShared<NW> block_shared(uint32_t* cur, const uint32_t* byte_word) {
   BlockShared<NW> sh;
@@ -815,97 +826,104 @@ __global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
 }
 
 // The items of a small split batch that something is left to do for and that are this workgroup's: every gridDim.x-th one.
-// Returns how many there are; own: room for kOwnItems of them (a grid has a workgroup for each slot, or one at least for every sixteen).
+// Returns how many there are; own: room for kRestItems of them, which the host sees to (small_batch_fits).
 // What bounds it is reading the kinds of all slots, 16 KiB at most, in every workgroup: some 1.5 us, less than a launch.
-constexpr int kOwnItems = 17;
-template <int THREADS>
 __device__ inline uint32_t own_items(const EncodeParams& p, uint16_t* own, uint32_t* wave_sum) {
-  constexpr int kPer = 4096 / THREADS;
+  constexpr int kPer = kSmallSlots / 1024;
+  static_assert(kPer == 4, "a thread's kinds are one load");
   const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
-  const uint32_t n = p.direct_count;
-  uint32_t mine = 0;                                   // bit i: my slot i is of the kind
-#pragma unroll
-  for (int i = 0; i < kPer; i += 4) {
-    const uint32_t g = (uint32_t)(kPer * t + i);
-    if (g < n) {
-      const int4 k = *(const int4*)(p.slot_kind + g);
-      mine |= (uint32_t)((k.x != kSlotDone) | (k.y != kSlotDone) << 1 | (k.z != kSlotDone) << 2 | (k.w != kSlotDone) << 3) << i;
-    }
+  const uint32_t n = p.direct_count, g = (uint32_t)(kPer * t);
+  uint32_t mine = 0;                                   // bit i: there is something to do for my slot i
+  if (g < n) {
+    const int4 k = *(const int4*)(p.slot_kind + g);
+    mine = (uint32_t)((k.x != kSlotDone) | (k.y != kSlotDone) << 1 | (k.z != kSlotDone) << 2 | (k.w != kSlotDone) << 3);
+    if (n - g < (uint32_t)kPer) mine &= (1u << (n - g)) - 1u;
   }
-  if ((uint32_t)(kPer * t) < n && n - (uint32_t)(kPer * t) < (uint32_t)kPer) mine &= (1u << (n - (uint32_t)(kPer * t))) - 1u;
   const uint32_t count = (uint32_t)__builtin_popcount(mine);
   const uint32_t upto = wave_scan<OpAdd>(count, 0u);
-  __syncthreads();                                     // (wave_sum may still be read)
   if (lane == 63) wave_sum[wave] = upto;
   __syncthreads();
   uint32_t at = upto - count, all = 0;
-  for (int w = 0; w < THREADS / 64; ++w) {
+  for (int w = 0; w < 16; ++w) {
     if (w < wave) at += wave_sum[w];
     all += wave_sum[w];
   }
   for (uint32_t m = mine; m; m &= m - 1u, ++at)
-    if (at % gridDim.x == blockIdx.x && at / gridDim.x < (uint32_t)kOwnItems)
-      own[at / gridDim.x] = (uint16_t)(kPer * t + __builtin_ctz(m));
+    if (at % gridDim.x == blockIdx.x && at / gridDim.x < (uint32_t)kRestItems) own[at / gridDim.x] = (uint16_t)(g + __builtin_ctz(m));
   __syncthreads();
-  return all > blockIdx.x ? min((all - 1u - blockIdx.x) / gridDim.x + 1u, (uint32_t)kOwnItems) : 0u;
+  return all > blockIdx.x ? (all - 1u - blockIdx.x) / gridDim.x + 1u : 0u;
 }
 
 // What is left of a small split batch, in one launch: mostly nothing, and a launch that looks for items and finds none costs 2 to
 // 4 us (with two such kernels, like those above, one document of 60,001 bytes took 26.7 us instead of 24.3, 1,003
-// conversations 51.9 instead of 48.3).  Sixteen waves: each takes items on its own, and what a wave cannot do all of
-// them then encode.  (The limits are not kept in LDS: there is room for sixteen such items only without.)  Text in which
-// nothing repeats and nothing can be cut pays for that: 40 strings of 4,000 such bytes 77 us instead of 58.
+// conversations 51.9 instead of 48.3).  Each wave takes one item on its own; of what does not fold, four waves encode an item of up
+// to 4 KiB, four items at a time, and all sixteen one of more.  (The limits are not kept in LDS: there is room for sixteen
+// such items only without.)
 constexpr int kRestWave = encode_array_words<1, 16, false, false>();
-constexpr int kRestWords = 16 * (kRestWave + encode_exchange_words<1>() + kFoldWords) + encode_exchange_words<16>() + 256;
+constexpr int kRestTeam = encode_array_words<4, 16, false, false>();
+constexpr int kRestTogether = 4 * encode_exchange_words<4>() > encode_exchange_words<16>() ? 4 * encode_exchange_words<4>()
+                                                                                           : encode_exchange_words<16>();
+constexpr int kRestWords = 16 * (kRestWave + encode_exchange_words<1>() + kFoldWords) + kRestTogether + 256;
 template <bool SPECIAL>
 __global__ __launch_bounds__(1024) void encode_rest_kernel(EncodeParams p) {
-  static_assert(kLongArrayWords <= 16 * kRestWave, "an item of all waves in the space of sixteen");
+  static_assert(kRestItems == 16, "a wave each");
+  static_assert(kLongArrayWords <= 16 * kRestWave && 4 * kRestTeam <= 16 * kRestWave, "in the space of sixteen");
   extern __shared__ __align__(16) uint32_t smem[];
-  __shared__ uint16_t own[kOwnItems];
-  __shared__ int32_t whole[16];                        // what each wave leaves to the workgroup, -1: nothing
-  __shared__ uint32_t claims;                          // items that are taken
-  const uint32_t count = own_items<1024>(p, own, smem);
+  __shared__ uint16_t own[kRestItems];
+  __shared__ int32_t whole[kRestItems];                // bytes of the items that their waves could not do, else 0
+  const uint32_t count = own_items(p, own, smem);
   if (!count) return;                                  // uniform
   uint32_t* const byte_word = smem + kRestWords - 256;
   if (threadIdx.x < 256) byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
-  if (threadIdx.x == 0) claims = 16;
   __syncthreads();
   const int lane = (int)threadIdx.x & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint32_t* const exchange = smem + 16 * kRestWave;
-  uint32_t* const fold_lds = exchange + 16 * encode_exchange_words<1>() + encode_exchange_words<16>() + wave * kFoldWords;
-  const BlockShared<1> alone = block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word);
-  const BlockShared<16> together = block_shared<16>(exchange + 16 * encode_exchange_words<1>(), byte_word);
-  uint32_t item = wave;
-  for (;;) {                                           // uniform in the workgroup
-    int stopped_at = -1;
-    while (item < count && stopped_at < 0) {           // uniform in the wave
-      const int s = (int)uniform((uint32_t)own[item]);
-      if (!uniform(encode_item_wave<false, SPECIAL>(p, s, smem + wave * kRestWave, alone, fold_lds) ? 1u : 0u)) stopped_at = s;
-      item = wave_claim(&claims);
+  uint32_t* const together = exchange + 16 * encode_exchange_words<1>();
+  int stays = 0;
+  if (wave < count) {                                  // uniform in the wave
+    const int s = (int)uniform((uint32_t)own[wave]);
+    if (!encode_item_wave<false, SPECIAL>(p, s, smem + wave * kRestWave,
+                                          block_shared<1>(exchange + wave * encode_exchange_words<1>(), byte_word),
+                                          together + kRestTogether + wave * kFoldWords)) {
+      int64_t begin;
+      item_of(p, s, begin, stays);
     }
-    if (lane == 0) whole[wave] = stopped_at;
+  }
+  if (lane == 0) whole[wave] = stays;
+  __syncthreads();
+  const int32_t bytes = lane < kRestItems ? whole[lane] : 0;
+  uint32_t some = (uint32_t)__ballot(bytes > 0 && bytes <= 4096), long_ones = (uint32_t)__ballot(bytes > 4096);
+  while (some) {                                       // uniform in the workgroup
+    uint32_t mine = some;                              // without the items of the teams before mine
+    for (uint32_t team = 0; team < 4; ++team) {
+      if (team < wave >> 2) mine &= mine - 1u;
+      some &= some - 1u;
+    }
+    int64_t begin = 0;
+    int s = 0, n = 0;
+    if (mine) {                                        // uniform in the wave
+      s = (int)uniform((uint32_t)own[__builtin_ctz(mine)]);
+      item_of(p, s, begin, n);
+    }
+    uint32_t* const arrays = smem + (wave >> 2) * kRestTeam;
+    encode_string_segmented<4, 16, false, SPECIAL, false, 4>(p, s, begin, n, arrays, arrays + 4096, arrays + 4096,
+                                                             block_shared<4>(together + (wave >> 2) * encode_exchange_words<4>(), byte_word),
+                                                             Fold{}, nullptr);
+  }
+  const BlockShared<16> sh = block_shared<16>(together, byte_word);
+  for (; long_ones; long_ones &= long_ones - 1u) {     // uniform in the workgroup
+    const int s = (int)uniform((uint32_t)own[__builtin_ctz(long_ones)]);
+    int64_t begin;
+    int n;
+    item_of(p, s, begin, n);
+    if (n > 16 * 1024) {                               // uniform
+      uint32_t* const slab = p.staged + (size_t)blockIdx.x * kStagedWords;
+      encode_string<16, 64, true, true, SPECIAL>(p, s, slab, slab + 65536, slab + 2 * 65536, sh);
+    } else {
+      encode_string_segmented<16, 16, false, SPECIAL, false>(p, s, begin, n, smem, smem + 16384, smem + 16384, sh, Fold{}, nullptr);
+    }
     __syncthreads();
-    bool any = false;
-    for (int w = 0; w < 16; ++w) {
-      const int s = (int)uniform((uint32_t)whole[w]);
-      if (s >= 0) {                                    // uniform
-        any = true;
-        int64_t begin;
-        int n;
-        item_of(p, s, begin, n);
-        if (n > 16 * 1024) {                           // uniform
-          uint32_t* const slab = p.staged + (size_t)blockIdx.x * kStagedWords;
-          encode_string<16, 64, true, true, SPECIAL>(p, s, slab, slab + 65536, slab + 2 * 65536, together);
-        } else {
-          encode_string_segmented<16, 16, false, SPECIAL, false>(p, s, begin, n, smem, smem + 16384, smem + 16384, together, Fold{},
-                                                                 nullptr);
-        }
-        __syncthreads();
-      }
-    }
-    __syncthreads();                                   // (the arrays, and what the waves left, are used again)
-    if (!any) break;                                   // all have run out of items
   }
 }
 

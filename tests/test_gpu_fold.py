@@ -114,3 +114,41 @@ def test_special_tokens(listed):
     reference.set_specials(specials)
     got = gpu_encode(table, data, offsets)
     assert_same_encoding(*got, *reference.encode_batch(data, offsets, tier=oracle.HEAP), "specials")
+
+
+NO_CUTS = [(a, b) for a in b"ab" for b in b"ab"] + [(256, 257), (258, 256), (257, 97), (256, 256)]
+
+
+def check(batch, what):
+    rows = np.array(NO_CUTS, np.int32)
+    data, offsets = to_batch(batch)
+    got = gpu_encode(bpe.build_table(rows), data, offsets)
+    assert_same_encoding(*got, *oracle.Table(rows).encode_batch(data, offsets, tier=oracle.HEAP), what)
+    return len(batch) + int(offsets[-1]) // 896          # slots
+
+
+@pytest.mark.parametrize("longest", [4096, 4097, 16384, 16385, 40000])
+def test_workgroups_with_many_items_left(longest):
+    """Batches without a list whose workgroups have several items that do not fold beside ones that do: of up to 4 KiB, to which
+    four waves go, and longer ones, in LDS or not, among them."""
+    rng = random.Random(longest)
+    batch = [strings(rng, rng.choice(["random", "runs", "periods"]), b"ab", rng.randint(1025, 2200)) for _ in range(1200)]
+    batch += [strings(rng, "random", b"ab", n) for n in (1024, 1025, 4095, 4096)]
+    batch += [strings(rng, "random", b"ab", longest) for _ in range(3 if longest > 4096 else 1)]
+    rng.shuffle(batch)
+    assert 3000 < check(batch, "many left") <= 4096
+
+
+def test_workgroup_with_items_of_all_lengths():
+    """All slots of 16 neighbours in one workgroup at a time: too few for more, of every length that is treated in its own way."""
+    rng = random.Random(7)
+    batch = [strings(rng, "random", b"ab", n) for n in (1025, 1500, 4096, 4097, 16384, 16385, 20000, 2000, 3000, 65536)]
+    assert check(batch, "all lengths") <= 256
+
+
+@pytest.mark.parametrize("length, count", [(4200, 1100), (16385, 300)])
+def test_long_items_that_do_not_fold(length, count):
+    """More of them than there are workgroups of sixteen waves: some take a second one, by a claim (and their slab again)."""
+    rng = random.Random(length)
+    batch = [strings(rng, "random", b"ab", length + rng.randint(0, 700)) for _ in range(count)]
+    assert check(batch, "long items") > 4096

@@ -222,10 +222,18 @@ __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, i
     }
     auto place_of = [&](int i) { return FOLD ? i + skip + (i >= gap_at ? gap : 0) : i; };
     uint32_t b[D + 2];                                 // b[j] = byte (base - 1 + j) of the string, 0x100 = none
+    if (FOLD && f.stretches > 0) {                     // uniform
 #pragma unroll
-    for (int j = 0; j < D + 2; ++j) {
-      const int i = base - 1 + j;
-      b[j] = (j <= c0 + 1 && c0 > 0 && i >= 0 && i < n) ? src[place_of(i)] : 0x100u;
+      for (int j = 0; j < D + 2; ++j) {
+        const int i = base - 1 + j;
+        b[j] = (j <= c0 + 1 && c0 > 0 && i >= 0 && i < n) ? src[place_of(i)] : 0x100u;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < D + 2; ++j) {
+        const int i = base - 1 + j;
+        b[j] = (j <= c0 + 1 && c0 > 0 && i >= 0 && i < n) ? src[i] : 0x100u;
+      }
     }
     if constexpr (SPECIAL) {                           // special tokens are configured: their marks
       const uint8_t* mark = p.cover + begin;

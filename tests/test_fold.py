@@ -156,6 +156,20 @@ def test_one_stretch(lib, q):
                 assert folded[1] == n
 
 
+@pytest.mark.parametrize("q", range(1, 9))
+def test_least_stretches(lib, q):
+    """A stretch that is just long enough is found wherever it lies, in text that is short, of two rows, and beyond them."""
+    rng = np.random.default_rng(10 + q)
+    unit = 8 if q <= 2 else 2 * q
+    for n in (128, 1024, 1040, 2048, 2100):
+        for at in (*range(8, 25), n - 16 - q - HISTORY - unit, *(int(v) for v in rng.integers(8, n - 60, 4))):
+            data = rng.permutation(np.resize(np.arange(100, 256), n)).astype(np.uint8)
+            size = q + HISTORY - 1 + unit
+            data[at:at + size] = np.resize(np.arange(1, q + 1), size)
+            stretches, stay = fold(lib, data, most=100000)
+            assert len(stretches) == 1 and stay == n - unit and stretches[0][0] == at + q + HISTORY - 1
+
+
 def test_marks(lib):
     rng = np.random.default_rng(3)
     for _ in range(40):

@@ -28,7 +28,10 @@ struct Control {
   uint32_t queue_head[kMaxTiers];                    // work-queue heads of the encode kernels
   uint32_t fallback_range[2];                        // {0, items the lane-per-segment kernel passed on}
   uint32_t unfolded_count[kMaxTiers];                // items of each tier that are left to the kernel of the longest ones
+  uint32_t unused;
+  uint32_t share_head[8][4];                         // items passed on that are claimed; the first word of each
 };
+static_assert(sizeof(Control) <= 256, "the smallest part of a workspace");
 
 __device__ inline int bin_key(int len, const TierPlan& plan) {
   int lo = 0;
@@ -115,6 +118,7 @@ __global__ __launch_bounds__(1024) void bin_scatter_kernel(const int64_t* offset
       if (lane <= kMaxTiers) c->tier_base[lane] = lane == 0 ? 0u : total;
       if (lane < kMaxTiers) c->queue_head[lane] = 0;
       if (lane < 2) c->fallback_range[lane] = 0;
+      if (lane < 8) c->share_head[lane][0] = 0;
     }
   }
   __syncthreads();
@@ -338,6 +342,7 @@ __global__ __launch_bounds__(1024) void piece_scatter_kernel(TierPlan plan, uint
     if (t <= kMaxTiers) c->tier_base[t] = t == 0 ? 0 : scan[(t <= plan.n_tiers ? t : plan.n_tiers) * kLenBuckets - 1];
     if (t < kMaxTiers) c->queue_head[t] = c->unfolded_count[t] = 0;
     if (t < 2) c->fallback_range[t] = 0;
+    if (t < 8) c->share_head[t][0] = 0;
   }
   __syncthreads();
   const uint32_t first = blockIdx.x * slots_each, last = min(first + slots_each, n_slots);

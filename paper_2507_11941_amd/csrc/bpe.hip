@@ -154,6 +154,8 @@ int n_tiers_for(int32_t max_len) {
 // Resident workgroups of the long variant each own one staging slab (768 KiB), where there is a tier that needs them.
 constexpr int kMaxLongGrid = 256;
 static_assert(offsetof(Control, unfolded_count) - offsetof(Control, queue_head) == kTierCounts * sizeof(uint32_t), "its place");
+static_assert(offsetof(Control, share_head) - offsetof(Control, queue_head) == kShareHeads * sizeof(uint32_t) &&
+                  sizeof(Control::share_head) == kClaimShares * kShareStride * sizeof(uint32_t), "their places");
 
 constexpr size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 

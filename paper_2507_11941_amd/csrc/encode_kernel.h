@@ -52,7 +52,8 @@ struct DeviceTable {
   int log2_word_buckets;
 };
 
-constexpr int kTierCounts = 6;
+// Words of the control block from queue_head on.
+constexpr uint32_t kTierCounts = 6, kShareHeads = 11, kShareStride = 4, kClaimShares = 8;
 struct EncodeParams {
   DeviceTable table;
   const uint8_t* bytes;
@@ -62,7 +63,8 @@ struct EncodeParams {
   const int32_t* list;        // work items that are pieces, of all tiers, tier-major, longest first inside a tier
   const uint32_t* tier_base;  // [tiers+1] start of each tier's slice of `list`
   uint32_t* queue_head;       // [tiers] next unclaimed item of each tier; kTierCounts words further on [tiers] how many of the
-                              //   longer tiers' items do not fold
+                              //   longer tiers' items do not fold, kShareHeads words further on the next unclaimed one of each
+                              //   share of the last items passed on
   int32_t* tmp_ids;           // ids of an item are written at tmp_ids[first byte of the item ...]
   int32_t* counts;            // token count of each item
   int64_t* out_offsets;       // a batch of one short string, whose output the encode kernel writes itself: the offsets, else null;

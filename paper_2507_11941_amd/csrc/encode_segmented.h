@@ -185,7 +185,7 @@ __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, i
   using mask_t = uint32_t;
   constexpr int W = NW * 64;
   // (one wave, or a team: of a workgroup that has others)
-  const int tid = (int)(NW == 16 || TEAMS > 1 ? own_thread() : threadIdx.x) & (W - 1);
+  const int tid = (int)(NW > 1 ? own_thread() : threadIdx.x) & (W - 1);
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const DeviceTable& tab = p.table;
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
   uint32_t* const byte_word = smem + kShortWords - 256;
   byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
   if (threadIdx.x == 0) claims = 4;
-  if (p.prefetch_lines > 0 && blockIdx.x < tier[2]) warm_table(p, byte_word);
+  if (p.prefetch_lines > 0 && blockIdx.x < tier[2] - tier[1]) warm_table(p, byte_word);
   __syncthreads();
   const int lane = (int)threadIdx.x & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));

@@ -730,11 +730,45 @@ __device__ __forceinline__ bool encode_item_wave(const EncodeParams& p, int s, u
   }
 }
 
+// The items of a small split batch that something is left to do for and that are this workgroup's: every gridDim.x-th one.
+// Returns how many there are; own: room for kRestItems of them, which the host sees to (small_batch_fits).
+// What bounds it is reading the kinds of all slots, 16 KiB at most, in every workgroup: some 1.5 us, less than a launch.
+template <int THREADS>
+__device__ inline uint32_t own_items(const EncodeParams& p, uint16_t* own, uint32_t* wave_sum) {
+  constexpr int kPer = kSmallSlots / THREADS;          // slots of a thread
+  static_assert(kPer % 4 == 0 && kPer < 32, "four kinds a load, a bit each");
+  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint32_t n = p.direct_count, g = (uint32_t)(kPer * t);
+  uint32_t mine = 0;                                   // bit i: there is something to do for my slot i
+#pragma unroll
+  for (int i = 0; i < kPer; i += 4) {
+    if (g + (uint32_t)i < n) {
+      const int4 k = *(const int4*)(p.slot_kind + g + i);
+      mine |= (uint32_t)((k.x != kSlotDone) | (k.y != kSlotDone) << 1 | (k.z != kSlotDone) << 2 | (k.w != kSlotDone) << 3) << i;
+    }
+  }
+  if (g < n && n - g < (uint32_t)kPer) mine &= (1u << (n - g)) - 1u;
+  const uint32_t count = (uint32_t)__builtin_popcount(mine);
+  const uint32_t upto = wave_scan<OpAdd>(count, 0u);
+  if (lane == 63) wave_sum[wave] = upto;
+  __syncthreads();
+  uint32_t at = upto - count, all = 0;
+  for (int w = 0; w < THREADS / 64; ++w) {
+    if (w < wave) at += wave_sum[w];
+    all += wave_sum[w];
+  }
+  for (uint32_t m = mine; m; m &= m - 1u, ++at)
+    if (at % gridDim.x == blockIdx.x && at / gridDim.x < (uint32_t)kRestItems) own[at / gridDim.x] = (uint16_t)(g + __builtin_ctz(m));
+  __syncthreads();
+  return all > blockIdx.x ? (all - 1u - blockIdx.x) / gridDim.x + 1u : 0u;
+}
+
 // What single waves encode, and four together.  Each wave takes items on its own: first those of the tiers, the longest tier
 // first, of which it can do those that fold (fold.h) to 1 KiB or less, then the ones passed on, up to 1 KiB.  A wave that finds
 // an item of tier 1, up to 4 KiB, that does not fold stops there, and once all four have stopped the workgroup encodes
 // what they found; items of the longer tiers that do not fold are left to the next kernel.  One launch for all: mostly
-// there is nothing to do, and a launch costs some 2 us.
+// there is nothing to do, and a launch costs some 2 us.  SLOTS: the items are what is left of a small split batch of strings of up to
+// 4 KiB, so that none are of the longer tiers.
 // What bounds it is latency: some 25 dependent round trips an item, of twelve waves a CU (with eight, runs and motifs took 90 us
 // more).  2,048 x 16 KiB of runs and motifs: 176 us and 5 in the next kernel, 417 and 303 when every position of an item had an
 // element; 256 x 64 KiB of one byte: 43 instead of 225 in the next kernel.  Items are dealt to the workgroups by number: when
@@ -745,18 +779,25 @@ __device__ __forceinline__ bool encode_item_wave(const EncodeParams& p, int s, u
 constexpr int kMaxTierLists = 3;
 constexpr int kShortArrayWords = encode_array_words<4, 16, false, true>();
 constexpr int kShortWords = kShortArrayWords + 4 * (encode_exchange_words<1>() + kFoldWords) + encode_exchange_words<4>() + 256;
-template <bool SPECIAL>
+template <bool SPECIAL, bool SLOTS>
 __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
   static_assert(4 * encode_array_words<1, 16, false, true>() <= kShortArrayWords, "four one-wave items in the space of one");
   extern __shared__ __align__(16) uint32_t smem[];
   __shared__ int32_t whole[4];                         // what each wave leaves to the workgroup, -1: nothing
   __shared__ uint32_t claims;                          // the workgroup's items that are taken
+  __shared__ uint16_t own[SLOTS ? kRestItems : 1];
   uint32_t tier[kMaxTierLists] = {0, 0, 0};            // items of tier 3, of 3 and 2, of 3 to 1
-  if (p.n_tiers > 1) {
-    for (int t = 0; t < kMaxTierLists; ++t) tier[t] = p.tier_base[4] - p.tier_base[3 - t];
+  uint32_t count;                                      // in all; of a small split batch, this workgroup's
+  if constexpr (SLOTS) {
+    count = uniform(own_items<256>(p, own, smem));
+    if (!count) return;                                // uniform
+  } else {
+    if (p.n_tiers > 1) {
+      for (int t = 0; t < kMaxTierLists; ++t) tier[t] = p.tier_base[4] - p.tier_base[3 - t];
+    }
+    count = tier[2] + *p.fallback_count;
+    if (blockIdx.x >= count) return;                   // uniform: nothing for this workgroup
   }
-  const uint32_t count = tier[2] + *p.fallback_count;
-  if (blockIdx.x >= count) return;                     // uniform: nothing for this workgroup
   uint32_t* const byte_word = smem + kShortWords - 256;
   byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];
   if (threadIdx.x == 0) claims = 4;
@@ -778,7 +819,8 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
   // workgroup encodes those once all its waves have stopped.)
   const uint32_t passed = count - tier[2], share = blockIdx.x % kClaimShares;
   const uint32_t dealt = passed >= 4u * gridDim.x && gridDim.x >= kClaimShares ? count - passed / 4u : 0xFFFFFFFFu;
-  auto take = [&](uint32_t number) {                   // my item, if its number is one of those that are dealt, or a claimed one
+  auto take = [&](uint32_t number) -> uint32_t {       // my item, if its number is one of those that are dealt, or a claimed one
+    if constexpr (SLOTS) return number;
     const uint32_t item = number * gridDim.x + blockIdx.x;
     return item < dealt ? item : dealt + wave_claim(p.queue_head + kShareHeads + share * kShareStride) * kClaimShares + share;
   };
@@ -787,7 +829,10 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
     int stopped_at = -1;
     while (item < count && stopped_at < 0) {           // uniform in the wave
       int s, its_tier = 0;
-      if (item >= tier[2]) {
+      if constexpr (SLOTS) {
+        s = (int)uniform((uint32_t)own[item]);
+        its_tier = 1;                                  // (or one of up to 1 KiB, which is always done)
+      } else if (item >= tier[2]) {
         s = (int)uniform((uint32_t)p.fallback_list[item - tier[2]]);
       } else {
         its_tier = (int)uniform(item < tier[0] ? 3u : item < tier[1] ? 2u : 1u);
@@ -803,7 +848,7 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
       }
       item = take(wave_claim(&claims));
     }
-    if (p.n_tiers <= 1) break;                         // uniform: no item is left to the workgroup
+    if (!SLOTS && p.n_tiers <= 1) break;               // uniform: no item is left to the workgroup
     if (lane == 0) whole[wave] = stopped_at;
     __syncthreads();
     bool any = false;
@@ -844,40 +889,14 @@ __global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
   encode_tier<16, 16, false, false, true, SPECIAL>(p, 2, count, smem, sh);
 }
 
-// The items of a small split batch that something is left to do for and that are this workgroup's: every gridDim.x-th one.
-// Returns how many there are; own: room for kRestItems of them, which the host sees to (small_batch_fits).
-// What bounds it is reading the kinds of all slots, 16 KiB at most, in every workgroup: some 1.5 us, less than a launch.
-__device__ inline uint32_t own_items(const EncodeParams& p, uint16_t* own, uint32_t* wave_sum) {
-  constexpr int kPer = kSmallSlots / 1024;
-  static_assert(kPer == 4, "a thread's kinds are one load");
-  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
-  const uint32_t n = p.direct_count, g = (uint32_t)(kPer * t);
-  uint32_t mine = 0;                                   // bit i: there is something to do for my slot i
-  if (g < n) {
-    const int4 k = *(const int4*)(p.slot_kind + g);
-    mine = (uint32_t)((k.x != kSlotDone) | (k.y != kSlotDone) << 1 | (k.z != kSlotDone) << 2 | (k.w != kSlotDone) << 3);
-    if (n - g < (uint32_t)kPer) mine &= (1u << (n - g)) - 1u;
-  }
-  const uint32_t count = (uint32_t)__builtin_popcount(mine);
-  const uint32_t upto = wave_scan<OpAdd>(count, 0u);
-  if (lane == 63) wave_sum[wave] = upto;
-  __syncthreads();
-  uint32_t at = upto - count, all = 0;
-  for (int w = 0; w < 16; ++w) {
-    if (w < wave) at += wave_sum[w];
-    all += wave_sum[w];
-  }
-  for (uint32_t m = mine; m; m &= m - 1u, ++at)
-    if (at % gridDim.x == blockIdx.x && at / gridDim.x < (uint32_t)kRestItems) own[at / gridDim.x] = (uint16_t)(g + __builtin_ctz(m));
-  __syncthreads();
-  return all > blockIdx.x ? (all - 1u - blockIdx.x) / gridDim.x + 1u : 0u;
-}
-
-// What is left of a small split batch, in one launch: mostly nothing, and a launch that looks for items and finds none costs 2 to
-// 4 us (with two such kernels, like those above, one document of 60,001 bytes took 26.7 us instead of 24.3, 1,003
-// conversations 51.9 instead of 48.3).  Each wave takes one item on its own; of what does not fold, four waves encode an item of up
-// to 4 KiB, four items at a time, and all sixteen one of more.  (The limits are not kept in LDS: there is room for sixteen
-// such items only without.)
+// What is left of a small split batch that has strings of more than 4 KiB, in one launch: mostly nothing, and a launch that looks for
+// items and finds none costs 2 to 4 us (with two such kernels, like those above, one document of 60,001 bytes took 26.7 us instead
+// of 24.3, 1,003 conversations 51.9 instead of 48.3).  Each wave takes one item on its own; of what does not fold, four waves
+// encode an item of up to 4 KiB, four items at a time, and all sixteen one of more (one after the other, all sixteen waves each,
+// 300 x 8,000 bytes of words with 200 letters at random every 3,000 took 411 us instead of 153).  The limits are not kept in LDS: there
+// is room for sixteen such items only without.  That, the try whether it folds, and 16 registers a lane that do not fit (24 with
+// special tokens; 13 in the kernel above) are what long text without cuts pays: 60 x 60,000 bytes 446 us with this kernel, 409
+// with two; 40 x 16,000 133 with either.
 constexpr int kRestWave = encode_array_words<1, 16, false, false>();
 constexpr int kRestTeam = encode_array_words<4, 16, false, false>();
 constexpr int kRestTogether = 4 * encode_exchange_words<4>() > encode_exchange_words<16>() ? 4 * encode_exchange_words<4>()
@@ -890,7 +909,7 @@ __global__ __launch_bounds__(1024) void encode_rest_kernel(EncodeParams p) {
   extern __shared__ __align__(16) uint32_t smem[];
   __shared__ uint16_t own[kRestItems];
   __shared__ int32_t whole[kRestItems];                // bytes of the items that their waves could not do, else 0
-  const uint32_t count = own_items(p, own, smem);
+  const uint32_t count = uniform(own_items<1024>(p, own, smem));
   if (!count) return;                                  // uniform
   uint32_t* const byte_word = smem + kRestWords - 256;
   if (threadIdx.x < 256) byte_word[threadIdx.x] = p.table.byte_word[threadIdx.x];

@@ -184,8 +184,8 @@ __device__ __forceinline__ bool encode_string_segmented(const EncodeParams& p, i
   static_assert(!FOLD || (NW == 1 && kFoldBytes <= 64 * D && D + 2 <= (int)kFoldApart), "a wave's work, and room for what stays");
   using mask_t = uint32_t;
   constexpr int W = NW * 64;
-  // (one wave, or a team: of a workgroup that has others)
-  const int tid = (int)(NW > 1 ? own_thread() : threadIdx.x) & (W - 1);
+  // (one wave, or a team: of a workgroup that has others.  The kernel of waves that fold items has registers to spare.)
+  const int tid = (int)(NW > 1 || !FOLD ? own_thread() : threadIdx.x) & (W - 1);
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const DeviceTable& tab = p.table;

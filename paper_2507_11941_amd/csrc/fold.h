@@ -265,4 +265,112 @@ __device__ inline FoldBlock fold_block(uint64_t w, uint32_t size, uint32_t q, ui
   return b;
 }
 
+// LDS that a folded text's emission needs, in words.  Bit p of the first ones: a token starts at p, or the text ends; then, for
+// each stretch, the place behind which its copies go | how many ids they are << 12.  (Three workgroups of four such waves
+// fit a CU with not a block to spare: with the ranks of the words here too it was two, and runs and motifs took 90 us more.)
+constexpr int kFoldStarts = kFoldBytes / 32 + 3;       // (the end, and two more that are read)
+constexpr int kFoldWords = kFoldStarts + kFoldStretches;
+
+// The ids of a folded text: those of its tokens, and each stretch's block as often as it was left out.  A wave's work;
+// live, T, d: as encode_string_segmented() leaves them; out0: tokens before my positions; *total: all of them, to which the
+// copies' ids are added.  Returns false, and has written nothing, if a stretch has no block that is there twice in a row.
+__device__ __forceinline__ bool emit_folded(const Fold& f, uint32_t live, const uint32_t* T, uint32_t* starts, int d,
+                                            uint32_t out0, int32_t* dst, uint32_t* total) {
+  static_assert(kFoldStarts <= 64 && kFoldBytes < 4096, "a lane per word; fields of `copies`");
+  const int lane = (int)threadIdx.x & 63;
+  const uint32_t base = (uint32_t)(lane * d), n = (uint32_t)f.bytes;
+  uint32_t* const copies = starts + kFoldStarts;
+  wave_order();
+  if (lane < kFoldStarts) starts[lane] = 0;
+  wave_order();
+  if (live) {
+    const uint64_t mine = (uint64_t)live << (base & 31u);
+    atomicOr(&starts[base >> 5], (uint32_t)mine);
+    if (mine >> 32) atomicOr(&starts[(base >> 5) + 1u], (uint32_t)(mine >> 32));
+  }
+  if (lane == 0) atomicOr(&starts[n >> 5], 1u << (n & 31u));
+  wave_order();
+  const uint32_t word = lane < kFoldStarts ? starts[lane] : 0u;
+  const uint32_t rank = wave_scan<OpAdd>((uint32_t)__builtin_popcount(word), 0u) - (uint32_t)__builtin_popcount(word);
+  // ---- my stretch's block ----
+  const uint32_t end_before = wave_shift_up(f.end, 0u);
+  const bool mine = lane < f.stretches && f.out != 0;
+  FoldBlock b{0, 0};
+  uint64_t w = 0;
+  if (mine) {
+    const uint32_t i = f.first >> 5, shift = f.first & 31u;
+    w = (uint64_t)__builtin_amdgcn_alignbit(starts[i + 2], starts[i + 1], shift) << 32 |
+        __builtin_amdgcn_alignbit(starts[i + 1], starts[i], shift);
+    b = fold_block(w, f.end - f.first, f.q, end_before > f.first ? end_before - f.first : 0u);
+  }
+  if (__ballot(mine && b.bytes == 0)) return false;    // uniform
+  const uint32_t block = mine ? (uint32_t)(w >> (b.at + b.bytes)) & ((1u << b.bytes) - 1u) : 0u;    // the second one's tokens
+  const uint32_t size = (uint32_t)__builtin_popcount(block);
+  const uint32_t ids = mine ? f.out / b.bytes * size : 0u;
+  const uint32_t behind = mine ? f.first + b.at + 2u * b.bytes : lane < f.stretches ? f.x : 0u;    // (ascending)
+  const uint32_t upto = wave_scan<OpAdd>(ids, 0u);
+  const uint32_t place = lane_read(rank, (int)(behind >> 5)) +
+                         (uint32_t)__builtin_popcount(lane_read(word, (int)(behind >> 5)) & ((1u << (behind & 31u)) - 1u)) +
+                         (upto - ids);
+  *total += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+  copies[lane] = behind | ids << 12;                   // (ids: at most 65,536)
+  wave_order();
+  // ---- the tokens ----
+  {
+    uint32_t o = out0;
+    int j = 0;                                         // stretches whose copies lie before my token
+    for (int i = 0; i < f.stretches; ++i) {            // uniform
+      const uint32_t its_ids = (uint32_t)__builtin_amdgcn_readlane((int)ids, i);
+      const bool before = (uint32_t)__builtin_amdgcn_readlane((int)behind, i) <= base;
+      o += before ? its_ids : 0u;
+      j += before ? 1 : 0;
+    }
+    for (uint32_t m = live; m; m &= m - 1u) {
+      const uint32_t k = (uint32_t)__builtin_ctz(m);
+      for (; j < f.stretches && (copies[j] & 0xFFFu) <= base + k; ++j) o += copies[j] >> 12;
+      dst[o++] = (int32_t)(T[k * 64u + (uint32_t)lane] & kTokIdMask);
+    }
+  }
+  // ---- the copies ----
+  const uint32_t per_d = 65536u / (uint32_t)d + 1u;    // (positions are below 1,041, d at most 16: the quotient is exact)
+  for (int i = 0; i < f.stretches; ++i) {              // uniform
+    const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)ids, i);
+    if (count == 0) continue;
+    const uint32_t tokens = (uint32_t)__builtin_amdgcn_readlane((int)size, i);
+    uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)block, i);
+    const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)(behind - b.bytes), i);
+    int32_t* const to = dst + (uint32_t)__builtin_amdgcn_readlane((int)place, i);
+    for (uint32_t c = 1; c < tokens; ++c) m = (uint32_t)lane >= c ? m & (m - 1u) : m;      // lane c: from the block's token c on
+    const uint32_t at = from + (uint32_t)__builtin_ctz(m | 1u << 16);
+    const uint32_t column = at * per_d >> 16;
+    const uint32_t id = T[(at - column * (uint32_t)d) * 64u + min(column, 63u)] & kTokIdMask;
+    uint32_t done = 0;
+    if (count >= 1024u) {                              // four ids a lane and store
+      uint32_t r = 4u * (uint32_t)lane % tokens;
+      const uint32_t step = 256u % tokens;
+      for (; done + 256u <= count; done += 256u) {
+        int32_t v[4];
+        uint32_t c = r;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          v[u] = (int32_t)lane_read(id, (int)c);
+          c = c + 1u == tokens ? 0u : c + 1u;
+        }
+        __builtin_memcpy(to + done + 4u * (uint32_t)lane, v, 16);
+        r += step;
+        r -= r >= tokens ? tokens : 0u;
+      }
+    }
+    uint32_t r = (done + (uint32_t)lane) % tokens;
+    const uint32_t step = 64u % tokens;
+    for (; done < count; done += 64u) {
+      const int32_t v = (int32_t)lane_read(id, (int)r);
+      if (done + (uint32_t)lane < count) to[done + (uint32_t)lane] = v;
+      r += step;
+      r -= r >= tokens ? tokens : 0u;
+    }
+  }
+  return true;
+}
+
 }  // namespace bpe

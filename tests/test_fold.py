@@ -170,6 +170,58 @@ def test_least_stretches(lib, q):
             assert len(stretches) == 1 and stay == n - unit and stretches[0][0] == at + q + HISTORY - 1
 
 
+def emission_texts():
+    """(name, merges, text): stretches of few and many copies, of ids that fill whole stores or not, at all places of the lanes' columns."""
+    rng = np.random.default_rng(6)
+    trained = workloads.load_merges("100k")
+    for seed, n in enumerate((128, 500, 1024, 1500, 4000, 16384, 65536)):
+        yield "trained", trained, workloads.adversarial(200 + seed, 1, n)
+    for _ in range(120):
+        alphabet = np.arange(97, 97 + rng.integers(1, 5))
+        yield "random", random_table(rng, alphabet, int(rng.integers(1, 40))), stretch_text(rng, alphabet, int(rng.integers(128, 9000)))
+    pairs = np.array([(97, 98), (256, 97)], np.int32)
+    for q in range(1, 9):                                # copies of 1,000 to 1,100 ids, and of 65,000
+        motif = np.arange(97, 97 + q)
+        for n in (1000 + 24 + 2 * q, 1024 + 24 + q, 1100, 1300, 65536):
+            yield "one stretch", pairs, np.concatenate([np.arange(q) + 160, np.resize(motif, n)])[:65536].astype(np.uint8)
+    for size in range(16, 1009, 31):                     # what stays: one byte a lane to sixteen
+        words = rng.permutation(np.resize(np.arange(100, 256), size))
+        yield "what stays", pairs, np.concatenate([words, np.resize([97, 98, 97], 400)]).astype(np.uint8)
+
+
+def test_emission(lib, tmp_path):
+    """The ids that emit_folded() writes, from the oracle's tokens of what stays, in buffers of just the size they must have, with the
+    address and undefined-behaviour sanitizers looking on."""
+    exe = str(tmp_path / "fold")
+    subprocess.check_call(["g++", "-O1", "-g", "-std=c++20", "-DFOLD_PROGRAM", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                           "-static-libasan", "-o", exe, "-I", os.path.join(ROOT, "paper_2507_11941_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "fold_driver.cpp")])
+    records, want = [], []
+    for name, merges, data in emission_texts():
+        table, sizes = oracle.Table(merges), token_sizes(merges)
+        folded = fold(lib, data)
+        if folded is None or len(folded[0]) == 0:
+            continue
+        ids = encode(table, data[kept(data, folded[0])])
+        whole = encode(table, data)
+        want.append((name, whole, encode_folded(lib, table, sizes, data)))
+        records.append(np.array([len(data), len(ids), len(whole)], np.int32).tobytes() + data.tobytes() +
+                       sizes[ids].astype(np.int32).tobytes() + ids.astype(np.int32).tobytes())
+    run = subprocess.run([exe], input=b"".join(records), capture_output=True, timeout=120,
+                         env=dict(os.environ, ASAN_OPTIONS="verify_asan_link_order=0:detect_stack_use_after_return=0"))
+    assert run.returncode == 0, run.stderr[-2000:].decode()
+    got, done = np.frombuffer(run.stdout, np.int32), 0
+    for name, whole, model in want:
+        k = int(got[0])
+        if model is None:                                # a stretch without a block: nothing is written
+            assert k == -1, name
+        else:
+            done += 1
+            assert np.array_equal(got[1:1 + k], whole), name
+        got = got[1 + max(k, 0):]
+    assert done >= 100 and len(got) == 0
+
+
 def test_marks(lib):
     rng = np.random.default_rng(3)
     for _ in range(40):

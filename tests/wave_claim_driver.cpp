@@ -2,13 +2,7 @@
 #include "wave_on_cpu.h"
 
 // As the memory serves them: one lane's after the other, in any order among the lanes of both waves.
-static uint32_t atomicInc(uint32_t* at, uint32_t last) {
-  let_others_run();
-  const uint32_t before = *at;
-  *at = before >= last ? 0u : before + 1u;
-  return before;
-}
-[[maybe_unused]] static uint32_t atomicAdd(uint32_t* at, uint32_t each) {
+static uint32_t atomicAdd(uint32_t* at, uint32_t each) {
   let_others_run();
   const uint32_t before = *at;
   *at += each;

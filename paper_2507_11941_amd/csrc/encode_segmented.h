@@ -663,12 +663,13 @@ __device__ inline uint32_t own_items(const EncodeParams& p, uint16_t* own, uint3
 // there is nothing to do, and a launch costs some 2 us.  SLOTS: the items are what is left of a small split batch of strings of up to
 // 4 KiB, so that none are of the longer tiers.
 // What bounds it is latency: some 25 dependent round trips an item, of twelve waves a CU (with eight, runs and motifs took 90 us
-// more).  2,048 x 16 KiB of runs and motifs: 176 us and 5 in the next kernel, 417 and 303 when every position of an item had an
-// element; 256 x 64 KiB of one byte: 43 instead of 225 in the next kernel.  Items are dealt to the workgroups by number: when
-// each wave claimed its items from one address (15,700 claims), the kernel took 578 us instead of 336, since a CU's loads
-// return in order and so waited for them too.  Text that does not fold costs the attempt: 500 strings of 16,000 bytes
-// without a cut 252 us instead of 239, 256 of 64 KiB 813 instead of 802; runs under a table whose tokens are longer than what
-// stays of a stretch are encoded for nothing first, 725 us instead of 653.
+// more).  2,048 x 16 KiB of runs and motifs: 173 us, and 84 in the next kernel for the one or two items of which more than 1 KiB
+// stays; 417 and 303 when every position of an item had an element.  256 x 64 KiB of one byte: 43 us and 4, instead of 225 in the
+// next kernel.  Items are dealt to the workgroups by number: when each wave claimed its items from one address (15,700 claims), the
+// kernel took 578 us instead of 336, since a CU's loads return in order and so waited for them too.  Text that does not fold costs
+// the attempt: 500 strings of 16,000 bytes without a cut 297 us instead of 292, 256 of 64 KiB 886 instead of 868, 3,000 of 4,000 bytes 312
+// instead of 305; runs under a table whose tokens are longer than what stays of a stretch are encoded for nothing first, 256 x 64 KiB
+// 514 us instead of 472.
 constexpr int kMaxTierLists = 3;
 constexpr int kShortArrayWords = encode_array_words<4, 16, false, true>();
 constexpr int kShortWords = kShortArrayWords + 4 * (encode_exchange_words<1>() + kFoldWords) + encode_exchange_words<4>() + 256;
@@ -705,13 +706,16 @@ __global__ __launch_bounds__(256, 3) void encode_short_kernel(EncodeParams p) {
   const BlockShared<4> together = block_shared<4>(exchange + 4 * encode_exchange_words<1>(), byte_word);
   // Every gridDim.x-th item is the workgroup's (few are spread over all workgroups, and of a long list, sorted by
   // length, all get the same); which of its waves takes one is settled in LDS.  Items passed on come in no order of length: of
-  // four and more a workgroup, the last quarter is claimed by whoever is done, from the counter of every eighth workgroup.
+  // four and more a workgroup, the last quarter is claimed by whoever is done, from the counter of every eighth workgroup, unless the
+  // strings are so short on average that a claim takes as long as a good part of an item (100,000 rows of up to 60 bytes, one in five
+  // with a word of 44: 135 us with claims, 129 without).
   // (5,000 x 4,000 bytes of words with 40 letters at random every 600 bytes, 43 items a workgroup: 721 us with all dealt, 661 so;
   // with 200 every 3,000, 9 items: 465, 434.  From one counter, which 3,000 waves ask last and find empty, runs and motifs took 5 to
-  // 8 us more, so 2 us less.  Claiming the items of tier 1 too: 5,000 x 1,500 bytes without a cut 390 instead of 305, since a
+  // 8 us more, so 5 less.  Claiming the items of tier 1 too: 5,000 x 1,500 bytes without a cut 390 instead of 305, since a
   // workgroup encodes those once all its waves have stopped.)
   const uint32_t passed = count - tier[2], share = blockIdx.x % kClaimShares;
-  const uint32_t dealt = passed >= 4u * gridDim.x && gridDim.x >= kClaimShares ? count - passed / 4u : 0xFFFFFFFFu;
+  const bool claimed = passed >= 4u * gridDim.x && gridDim.x >= kClaimShares && p.total_bytes >= (int64_t)p.batch * kFoldLeast;
+  const uint32_t dealt = claimed ? count - passed / 4u : 0xFFFFFFFFu;
   auto take = [&](uint32_t number) -> uint32_t {       // my item, if its number is one of those that are dealt, or a claimed one
     if constexpr (SLOTS) return number;
     const uint32_t item = number * gridDim.x + blockIdx.x;
@@ -788,7 +792,7 @@ __global__ __launch_bounds__(1024) void encode_long_kernel(EncodeParams p) {
 // encode an item of up to 4 KiB, four items at a time, and all sixteen one of more (one after the other, all sixteen waves each,
 // 300 x 8,000 bytes of words with 200 letters at random every 3,000 took 411 us instead of 153).  The limits are not kept in LDS: there
 // is room for sixteen such items only without.  That, the try whether it folds, and 16 registers a lane that do not fit (24 with
-// special tokens; 13 in the kernel above) are what long text without cuts pays: 60 x 60,000 bytes 446 us with this kernel, 409
+// special tokens; 10 in the kernel above) are what long text without cuts pays: 60 x 60,000 bytes 445 us with this kernel, 409
 // with two; 40 x 16,000 133 with either.
 constexpr int kRestWave = encode_array_words<1, 16, false, false>();
 constexpr int kRestTeam = encode_array_words<4, 16, false, false>();

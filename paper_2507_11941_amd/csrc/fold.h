@@ -22,6 +22,9 @@
 
 namespace bpe {
 
+// Two words of history: a lane's sixteen bytes are compared with those up to eight earlier by shifts of six words, two periods to a
+// result word (fold_equal), and each further period would cost every text that comes here, and two more words to hand on.  Longer
+// motifs are encoded as they are: 600 strings of 16,000 bytes take 81 us with a period of 8, 197 to 208 with 9, 12 or 16.
 constexpr int kFoldPeriods = 8;
 constexpr int kFoldHistory = 24;                       // repeating bytes from which on the next ones may be left out
 constexpr int kFoldStretches = 64;                     // of a text: a lane each

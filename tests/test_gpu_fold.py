@@ -152,3 +152,18 @@ def test_long_items_that_do_not_fold(length, count):
     rng = random.Random(length)
     batch = [strings(rng, "random", b"ab", length + rng.randint(0, 700)) for _ in range(count)]
     assert check(batch, "long items") > 4096
+
+
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("longest", [150, 400])
+@pytest.mark.parametrize("count", [3071, 3072, 3073, 4099, 9001])
+def test_many_items_passed_on(count, longest, split):
+    """Around the number from which on the last ones are claimed (four for each of 768 workgroups), and well beyond; and strings that
+    are too short for that."""
+    rng = random.Random(count)
+    batch = [strings(rng, rng.choice(["random", "runs"]), b"ab", rng.randint(40, longest)) for _ in range(count)]
+    batch += [b"a" * rng.randint(0, 20) for _ in range(1500)]
+    if split:
+        batch += [strings(rng, "random", b"ab", n) for n in (1025, 3000, 5000)]
+    rng.shuffle(batch)
+    check(batch, "passed on")
